@@ -157,12 +157,7 @@ int gemm_mid_steps_ct(int N, int K);   // ... if the mid kernel serves (N, K) at
 void launch_pack_act(const bf16_t* x, op_t* out, int M, int K, hipStream_t st);  // row-major bf16 -> fragment tiles in half (rows padded to 16 with zeros)
 int gemm_bf16_splits(int M, int N, int K, int kind);  // partial tiles [splits][M][N] the launch of this shape and epilogue needs in GemmEpi::part (1: none)
 int gemm_bf16_ssq_chunks(int M, int N, int K);     // chunks per row of the sums of squares an EPI_RESID launch of this shape writes
-int gemm_bf16_counters(int max_rows, int max_n);   // ticket counters a state needs in GemmEpi::counters (zero-initialised, self-resetting)
-int gemm_tiled_counters(int max_rows, int max_n);
-int gemm_tiled_splits(int M, int N, int K);
-int gemm_tiled_ssq_chunks(int M, int N);
-int gemm_tiled_stat_parts(int M, int N);
-void gemm_tiled_set_target(int wgs);               // tuning: workgroups the K split aims at
+int gemm_bf16_counters(int max_n);                 // counters a state needs in GemmEpi::counters (zero-initialised, self-resetting)
 // rs (optional): every output row m is multiplied by rsqrt(sum_c rs.ssq[m][c] * rs.inv_d + rs.eps).
 struct RowScale {
   const float* ssq;
@@ -173,8 +168,8 @@ enum { EPI_DIRECT = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_RESID = 3, EPI_SUM = 4, 
 // What the bf16 GEMM does with a finished output tile (see gemm_bf16.hip).
 struct GemmEpi {
   int kind;
-  float* part;        // [gemm_bf16_splits][M][N] fp32 partial tiles of the tiled kernel when it splits K
-  int* counters;      // gemm_bf16_counters tickets, one per (column group, row block) of a launch that splits K
+  float* part;        // [gemm_bf16_splits][M][N] fp32 partial tiles of a launch that splits K
+  int* counters;      // gemm_bf16_counters tickets of such a launch
   RowScale rs;        // 1/rms of the GEMM's input rows (QKV, SWIGLU, DIRECT, SUM; ssq may be null)
   // EPI_QKV (weights packed with PERM_ROTARY)
   const int32_t *row_pos, *row_slot;
@@ -195,7 +190,7 @@ struct GemmEpi {
   float* out_f32;
   // EPI_STATS (the LM head of a pass that compares and retains no row; at most GEMM_STATS_MAX_ROWS rows): logits to out_bf16 as
   // EPI_DIRECT does, and per row and column group the online-softmax state of the group's logits as written (rounded to bf16,
-  // token skip_col left out) to stat_parts[m][gemm_bf16_stat_parts(N)]
+  // token skip_col left out) to stat_parts[m][gemm_bf16_stat_parts(M, N, K)]
   void* stat_parts;
   int skip_col;
   // optional second copy of W in the step-major layout (launch_pack_weight_steps) of column groups of w_steps_ct tiles
@@ -203,7 +198,7 @@ struct GemmEpi {
   int w_steps_ct;
 };
 constexpr int GEMM_STATS_MAX_ROWS = 64;
-int gemm_bf16_stat_parts(int M, int N);              // column groups per row an EPI_STATS launch of this shape writes states for
+int gemm_bf16_stat_parts(int M, int N, int K);       // column groups per row an EPI_STATS launch of this shape writes states for
 // The GEMM kernels are launched through hipExtLaunchKernelGGL, which can stamp two events with the kernel's own start and end
 // (the dispatch's timestamps: what a profiler reports, with no marker packets between dependent kernels).  A caller that
 // wants the next GEMM launch of this thread timed sets g_launch_stamp; the launch takes the events and clears it.
@@ -219,21 +214,16 @@ extern thread_local LaunchStamp g_launch_stamp;
 void launch_gemm_bf16(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);
 #define GEMM_SKINNY_MAX_ROWS 64
 void launch_gemm_skinny(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, const GemmEpi& e, hipStream_t st);  // M <= GEMM_SKINNY_MAX_ROWS
-void launch_gemm_tiled(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);
-#define GEMM_MID_MAX_ROWS 160  // 65 .. this many rows: the mid kernel (all rows in one workgroup, wavefronts split K)
-#define GEMM_MID_MAX_ROWS_NARROW 256  // ... for matrices of at most 8192 columns
 int gemm_mid_splits(int M, int N, int K);
 int gemm_mid_ssq_chunks(int M, int N, int K);
 bool gemm_mid_fills_chip(int M, int N, int K);  // its column groups are a whole number of rounds over the compute units, without a K split
+bool gemm_mid_one_round(int M, int N, int K);   // its workgroups are at most one round
 int gemm_mid_counters(int max_n);
-void gemm_mid_set_target(int wgs);  // tuning: workgroups the K split aims at
-void launch_gemm_mid(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);  // M <= GEMM_MID_MAX_ROWS(_NARROW); narrow matrices from 17 rows
-#define GEMM_MACRO_MIN_ROWS_NARROW 256  // more rows than this: the macro-tile kernel whatever the width
+void launch_gemm_mid(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);  // the row counts choose_kernel sends (gemm_bf16.hip)
 int gemm_macro_ssq_chunks(int M, int N, int K);
-int gemm_macro_splits(int M, int N, int K);
-int gemm_macro_counters(int max_rows, int max_n);
-void gemm_macro_set_target(int wgs);  // tuning: workgroups the K split aims at
-void gemm_macro_set_penalty(int tile, double p);  // tuning: relative cost per product of tile candidate 0 .. 5 (256x256, 128x256, 128x128, 192x256, 256x192, 192x192); 0 switches it off
+int gemm_macro_splits(int M, int N, int K, int kind);
+int gemm_macro_stat_parts(int M, int N, int K);
+int gemm_macro_counters();
 void launch_gemm_macro(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);
 void launch_gemm_f32(const float* x, const float* w, float* y, int M, int N, int K, RowScale rs, hipStream_t st);
 

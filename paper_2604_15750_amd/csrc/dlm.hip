@@ -261,13 +261,12 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
   size_t pe = 0;
   const int shapes[4][3] = {{qkv, c.d_model, EPI_QKV}, {c.d_model, qd, EPI_RESID}, {2 * c.d_ffn, c.d_model, EPI_SWIGLU}, {c.d_model, c.d_ffn, EPI_RESID}};
   for (auto& sh : shapes) {
-    int maxsp = 1;
+    size_t e = c.dtype == DLM_BF16 ? 0 : (size_t)max_rows * sh[0];
     if (c.dtype == DLM_BF16)
       for (int mt = 1; mt <= (max_rows + 15) / 16; ++mt) {  // the split count depends on the rows only through their 16-row tiles
-        const int sp = gemm_bf16_splits(mt * 16 < max_rows ? mt * 16 : max_rows, sh[0], sh[1], sh[2]);
-        if (sp > maxsp) maxsp = sp;
+        const int rows = mt * 16 < max_rows ? mt * 16 : max_rows, sp = gemm_bf16_splits(rows, sh[0], sh[1], sh[2]);
+        if (sp > 1 && (size_t)sp * rows * sh[0] > e) e = (size_t)sp * rows * sh[0];
       }
-    size_t e = (size_t)maxsp * max_rows * sh[0];
     if (e > pe) pe = e;
   }
   s->part_elems = pe;
@@ -289,7 +288,7 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
   if (c.dtype == DLM_BF16) {  // or one state per row and column group of the LM head, for the passes that take the statistics from its epilogue
     const int fr = max_rows < GEMM_STATS_MAX_ROWS ? max_rows : GEMM_STATS_MAX_ROWS;
     for (int mt = 1; mt <= (fr + 15) / 16; ++mt) {
-      const size_t b = (size_t)fr * gemm_bf16_stat_parts(mt * 16 < fr ? mt * 16 : fr, c.vocab) * STATS_STATE_BYTES;
+      const size_t b = (size_t)fr * gemm_bf16_stat_parts(mt * 16 < fr ? mt * 16 : fr, c.vocab, c.d_model) * STATS_STATE_BYTES;
       if (b > stats_bytes) stats_bytes = b;
     }
   }
@@ -298,7 +297,7 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
   A(s->ssq, (size_t)max_rows * ssq_chunks * 4);
   int n_counters = 1;
   if (c.dtype == DLM_BF16)
-    for (auto& sh : shapes) { int k = gemm_bf16_counters(max_rows, sh[0]); if (k > n_counters) n_counters = k; }
+    for (auto& sh : shapes) { int k = gemm_bf16_counters(sh[0]); if (k > n_counters) n_counters = k; }
   A(s->counters, (size_t)n_counters * 4);
   A(s->row_seq, (size_t)max_rows * 4); A(s->row_pos, (size_t)max_rows * 4); A(s->row_tok, (size_t)max_rows * 4); A(s->row_slot, (size_t)max_rows * 4);
   A(s->rope_cos, (size_t)max_rows * (c.head_dim / 2) * 4); A(s->rope_sin, (size_t)max_rows * (c.head_dim / 2) * 4);
@@ -449,9 +448,11 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   // every layer GEMM of this pass must fit the partial-tile workspace the state was created with
   {
     const int shapes[4][3] = {{qd + 2 * nkv * hd, dm, EPI_QKV}, {dm, qd, EPI_RESID}, {2 * ffn, dm, EPI_SWIGLU}, {dm, ffn, EPI_RESID}};
-    for (auto& sh : shapes)
-      if ((size_t)gemm_bf16_splits(rows, sh[0], sh[1], sh[2]) * rows * sh[0] > s->part_elems)
+    for (auto& sh : shapes) {
+      const int sp = gemm_bf16_splits(rows, sh[0], sh[1], sh[2]);
+      if (sp > 1 && (size_t)sp * rows * sh[0] > s->part_elems)
         return dlm_fail(DLM_ECAPACITY, "dlm_step: split-K workspace too small for %d rows x %d columns", rows, sh[0]);
+    }
   }
   auto gemm = [&](int cls, const op_t* a, const void* w, int N, int K, const GemmEpi& e) {
     ProfScope ps(pf, st, cls);
@@ -464,6 +465,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   }
   // chunks of the row sums of squares the next consumer reads: the embedding's, then those of the GEMM that produced them
   int nch = norm_chunks(dm);
+  const int nch_o = gemm_bf16_ssq_chunks(rows, dm, qd), nch_down = gemm_bf16_ssq_chunks(rows, dm, ffn);
   for (int l = 0; l < c.n_layers; ++l) {
     f16_t* kc = (f16_t*)s->kcache.p + s->layer_stride * l;
     f16_t* vc = (f16_t*)s->vcache.p + s->layer_stride * l;
@@ -485,7 +487,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
       e.h = h; e.gain = (const float*)m->norm2[l].p; e.x = x; e.ssq_out = ssq;
       if (m->steps_ct[1]) { e.w_steps = (const op_t*)m->w_steps[1][l].p; e.w_steps_ct = m->steps_ct[1]; }
       gemm(PC_O, x2, m->wo[l].p, dm, qd, e);
-      nch = gemm_bf16_ssq_chunks(rows, dm, qd);
+      nch = nch_o;
     }
     {
       GemmEpi e = base;
@@ -502,7 +504,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
       e.x = x; e.ssq_out = ssq;
       if (m->steps_ct[3]) { e.w_steps = (const op_t*)m->w_steps[3][l].p; e.w_steps_ct = m->steps_ct[3]; }
       gemm(PC_DOWN, act, m->w_down[l].p, dm, ffn, e);
-      nch = gemm_bf16_ssq_chunks(rows, dm, ffn);
+      nch = nch_down;
     }
   }
   // A pass that compares no row with a retained distribution and retains none (every in-block pass) needs no second trip over
@@ -522,7 +524,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   }
   {
     ProfScope ps(pf, st, PC_STATS);
-    if (fused) launch_stats_merge(s->stats_ws.p, rows, gemm_bf16_stat_parts(rows, c.vocab), c.vocab, sr, so, st);
+    if (fused) launch_stats_merge(s->stats_ws.p, rows, gemm_bf16_stat_parts(rows, c.vocab, dm), c.vocab, sr, so, st);
     else launch_vocab_stats<T>((const T*)d->logits, rows, c.vocab, c.mask_id, sr, so, s->stats_ws.p, st);
   }
   return DLM_OK;
@@ -704,7 +706,7 @@ extern "C" int dlm_gemm_nt(const void* x, const void* w, void* y, int M, int N, 
   if (dtype == DLM_F32) { launch_gemm_f32((const float*)x, (const float*)w, (float*)y, M, N, K, RowScale{nullptr, 0, 0.f, 0.f}, st); return DLM_OK; }
   REQUIRE(N % 32 == 0 && K % 32 == 0, DLM_ESHAPE, "dlm_gemm_nt: bf16 needs N and K to be multiples of 32");
   const size_t mp = (size_t)(M + 15) / 16 * 16;
-  const int n_counters = gemm_bf16_counters(M, N);
+  const int n_counters = gemm_bf16_counters(N);
   const size_t tiled_bytes = ((mp * K + (size_t)N * K) * 2 + 15) / 16 * 16;
   const size_t part_bytes = (size_t)gemm_bf16_splits(M, N, K, EPI_SUM) * M * N * 4;
   void* ws = nullptr;
@@ -719,7 +721,7 @@ extern "C" int dlm_gemm_nt(const void* x, const void* w, void* y, int M, int N, 
   memset(&ge, 0, sizeof ge);
   ge.out_bf16 = (bf16_t*)y;
   hipError_t e = hipSuccess;
-  // partial tiles and ticket counters (used when the tiled kernel splits K) follow the tiled operands in the scratch
+  // partial tiles and ticket counters (used when a launch splits K) follow the tiled operands in the scratch
   ge.kind = EPI_SUM;
   ge.part = part;
   ge.counters = (int*)(part + (size_t)splits * M * N);

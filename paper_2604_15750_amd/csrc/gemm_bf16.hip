@@ -2,17 +2,15 @@
 // operand tiling and the choice of kernel.
 //
 // At decode shapes (M = 8 .. 384 rows against 15 GB of weights per pass) the GEMMs are bound by
-// streaming W from HBM, so both kernels are weight streamers that happen to multiply:
+// streaming W from HBM, so the kernels are weight streamers that happen to multiply:
 //   * W is re-tiled once, when the model is created, into 1 KiB fragments (16 rows x 32 k) that are
 //     exactly the A operand of v_mfma_f32_16x16x32_f16: a wavefront fetches a fragment as 64
 //     consecutive 16-byte loads and walks a contiguous run of HBM along K; W goes HBM -> registers;
 //   * activations live in the same fragment tiling (B operand), written that way by their producer;
 //   * the product is computed transposed (W fragment = A operand), so a lane ends up with four
 //     consecutive output columns of one row.
-// gemm_skinny.hip serves M <= 64 (except the LM head), gemm_mid.hip a block with its look-ahead window (65 .. 160 rows, all
-// of them in one workgroup), gemm_macro.hip (both operands through LDS, large output tiles: bound by the matrix cores, not
-// by W) wide passes, gemm_tiled.hip what is left (choose_kernel below); the layer's row-wise glue runs in their epilogues
-// (gemm_epilogue.h):
+// gemm_skinny.hip and gemm_mid.hip (all rows of a column group in one workgroup) serve narrow passes, gemm_macro*.hip (both
+// operands through LDS, output tiles of 32 .. 256 rows) everything wider and the LM head (choose_kernel below); the layer's row-wise glue runs in their epilogues (gemm_epilogue.h):
 //   QKV     1/rms of the input row, rotary embedding, Q row-major, K and V into the tiled KV cache
 //   SWIGLU  1/rms, silu(gate) * up into the fragment tiling of the down projection
 //   RESID   residual add, x = h * gain of the next RMSNorm into fragment tiling, and the share of
@@ -78,35 +76,34 @@ __global__ void pack_act_kernel(const bf16x8* __restrict__ x, op8* __restrict__ 
   }
 }
 
-// Which kernel serves a shape (measured crossovers on the layer shapes of 7 .. 8 B models):
+// Which kernel serves a shape (measured crossovers on the layer shapes of 7 .. 8 B models, microseconds):
 //   skinny  up to 64 rows: nothing crosses workgroups, every wavefront streams W;
-//   mid     65 .. 160 rows (narrow matrices to 256, O and down to 208); and below that where its wider column groups pay: from 17 rows for
-//           wide matrices (QKV, gate/up) and for narrow ones whose K is long enough for a four-way split (down) - there
-//           the skinny kernel's re-reads of X by every 16- or 32-column group cost more than W itself - and at any row
-//           count when its 96-column groups are exactly one per compute unit (gate/up of an 8B model), or when the skinny
-//           kernel would need a second round for a few column tiles (QKV of a 7B model with grouped-query heads);
-//   macro   more rows than that when the matrix has enough 128 x 256 tiles of its own (wide from 161 rows, narrow from 257);
-//   tiled   the rest, and the LM head up to 64 rows (no workspace: no K split), with or without the statistics epilogue.
-enum { KERNEL_SKINNY, KERNEL_MID, KERNEL_MACRO, KERNEL_TILED };
+//   mid     up to 64 rows where its wider column groups pay: from 17 rows for narrow matrices whose K is long enough for a
+//           four-way split (down), at any row count for wide ones whose groups are one round over the compute units (QKV and
+//           gate/up of an 8B model), and up to 16 rows when the skinny kernel would need a second round for a few column tiles
+//           (QKV of a 7B model with grouped-query heads).  Beyond 64 rows only where it is still ahead of the macro kernel:
+//           the 48-column groups of an 8B model's QKV to 96 rows (33.3 against 34.2; at 112 36.8 against 35.7), O to 208
+//           (28.2 / 29.8; at 240 44.9 / 29.7), down to 128 (40.4 / 43.3; at 136 49.3 / 47.6);
+//   macro   everything else from 17 rows on: wide matrices whose groups are more than one round (gate/up of a 7B model, 395
+//           groups: 73.6 against 51.1 at 40 rows, 110 against 61 at 152), and all wider passes (gate/up of an 8B model 43.5
+//           against 41.9 at 80 rows, 55.6 / 50.4 at 136);
+//           The LM head is its at any row count, with or without the statistics epilogue (no workspace: no K split).
+enum { KERNEL_SKINNY, KERNEL_MID, KERNEL_MACRO };
 int choose_kernel(int M, int N, int K, int kind) {
-  if (kind == EPI_STATS) return KERNEL_TILED;  // only the tiled kernel has that epilogue (the caller keeps to GEMM_STATS_MAX_ROWS rows)
-  const int pr = weight_pack_rows(N);
-  const bool whole_groups = N % (16 * pr) == 0;
-  if (M <= GEMM_SKINNY_MAX_ROWS && kind != EPI_DIRECT && whole_groups) {
-    if (pr == 2 && (M > 16 || gemm_mid_fills_chip(M, N, K))) return KERNEL_MID;
-    if (pr == 1 && M > 16 && K >= 8192) return KERNEL_MID;
+  const bool wide = weight_pack_rows(N) == 2;
+  if (kind == EPI_STATS || kind == EPI_DIRECT) return KERNEL_MACRO;
+  if (M <= 16) {
+    if (wide) return gemm_mid_fills_chip(M, N, K) ? KERNEL_MID : KERNEL_SKINNY;
     // a narrow matrix with a few more than 256 column tiles: the skinny kernel's one-tile workgroups would run a second,
     // nearly empty round over the compute units; 32-column groups fit in one
-    if (pr == 1 && M <= 16 && (N >> 4) > 256 && (N >> 4) <= 384) return KERNEL_MID;
-    return KERNEL_SKINNY;
+    return (N >> 4) > 256 && (N >> 4) <= 384 ? KERNEL_MID : KERNEL_SKINNY;
   }
-  // narrow matrices: to 256 rows, except that the residual projections, which have the macro kernel to go to, leave the mid
-  // kernel where it starts to lose to it (measured: O and down both from 224 rows)
-  const int mid_rows = pr == 2 ? GEMM_MID_MAX_ROWS : kind != EPI_RESID ? GEMM_MID_MAX_ROWS_NARROW : 208;
-  if (M > GEMM_SKINNY_MAX_ROWS && M <= mid_rows && whole_groups) return KERNEL_MID;
-  // EPI_RESID has no instantiation of the tiled kernel: what the mid kernel does not take goes to the macro kernel
-  if (M > GEMM_MACRO_MIN_ROWS_NARROW || (M > GEMM_SKINNY_MAX_ROWS && N > 8192) || kind == EPI_RESID) return KERNEL_MACRO;
-  return KERNEL_TILED;
+  if (M <= GEMM_SKINNY_MAX_ROWS) {
+    if (wide) return gemm_mid_one_round(M, N, K) ? KERNEL_MID : KERNEL_MACRO;
+    return K >= 8192 ? KERNEL_MID : KERNEL_SKINNY;
+  }
+  const int mid_rows = wide ? (gemm_mid_fills_chip(16, N, K) && N <= 12288 ? 96 : 0) : K >= 8192 ? 128 : 208;
+  return M <= mid_rows && gemm_mid_one_round(M, N, K) ? KERNEL_MID : KERNEL_MACRO;
 }
 
 }  // namespace
@@ -134,8 +131,7 @@ void launch_pack_act(const bf16_t* x, op_t* out, int M, int K, hipStream_t st) {
 int gemm_bf16_splits(int M, int N, int K, int kind) {
   switch (choose_kernel(M, N, K, kind)) {
     case KERNEL_MID: return gemm_mid_splits(M, N, K);
-    case KERNEL_MACRO: return gemm_macro_splits(M, N, K);
-    case KERNEL_TILED: return gemm_tiled_splits(M, N, K);
+    case KERNEL_MACRO: return gemm_macro_splits(M, N, K, kind);
     default: return 1;
   }
 }
@@ -143,21 +139,19 @@ int gemm_bf16_ssq_chunks(int M, int N, int K) {
   switch (choose_kernel(M, N, K, EPI_RESID)) {
     case KERNEL_SKINNY: return N >> 4;
     case KERNEL_MID: return gemm_mid_ssq_chunks(M, N, K);
-    case KERNEL_MACRO: return gemm_macro_ssq_chunks(M, N, K);
-    default: return gemm_tiled_ssq_chunks(M, N);
+    default: return gemm_macro_ssq_chunks(M, N, K);
   }
 }
-int gemm_bf16_stat_parts(int M, int N) { return gemm_tiled_stat_parts(M, N); }
-int gemm_bf16_counters(int max_rows, int max_n) {
-  const int a = gemm_tiled_counters(max_rows, max_n), b = gemm_mid_counters(max_n), c = gemm_macro_counters(max_rows, max_n);
-  return a > b ? (a > c ? a : c) : (b > c ? b : c);
+int gemm_bf16_stat_parts(int M, int N, int K) { return gemm_macro_stat_parts(M, N, K); }
+int gemm_bf16_counters(int max_n) {
+  const int a = gemm_mid_counters(max_n), b = gemm_macro_counters();
+  return a > b ? a : b;
 }
 
 void launch_gemm_bf16(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st) {
   switch (choose_kernel(M, N, K, e.kind)) {
     case KERNEL_SKINNY: launch_gemm_skinny(xt, wt, weight_pack_rows(N), M, N, K, e, st); break;
     case KERNEL_MID: launch_gemm_mid(xt, wt, M, N, K, e, st); break;
-    case KERNEL_MACRO: launch_gemm_macro(xt, wt, M, N, K, e, st); break;
-    default: launch_gemm_tiled(xt, wt, M, N, K, e, st); break;
+    default: launch_gemm_macro(xt, wt, M, N, K, e, st); break;
   }
 }

@@ -1,0 +1,403 @@
+// Macro-tile GEMM of a bf16 model for passes of more than a block's rows (a block with its look-ahead window, batched decoding,
+// prefill): Y[M,N] = X[M,K] * W[N,K]^T, fp32 accumulation, epilogue fused.
+//
+// A workgroup of RW x CW wavefronts owns a tile of RW WM x CW WN matrix-core fragments (16 rows or columns each) and walks K:
+//   * both operands are already stored as 1 KiB matrix-core fragments (16 rows x 32 k), so a stage of the pipeline is just
+//     KB (RW WM + CW WN) fragments copied HBM/L2 -> LDS by direct-to-LDS loads (no registers, no LDS writes); S stages of KB
+//     k-tiles rotate through up to 152 KiB of LDS;
+//   * a wavefront owns WM x WN fragments of the output (fp32 accumulators) and reads its WM + WN operand fragments of the NEXT
+//     k-tile from LDS into a second register set while the matrix cores work on the current one;
+//   * one barrier per stage, in front of its last k-tile: by then every wavefront has the stage's last fragments in registers,
+//     so the copies of stage s + S may overwrite it at once (S - 1 stages stay in flight), and they go out spread over the
+//     KB k-tiles that follow;
+//   * the waits on the direct-to-LDS loads are counted by hand (every stage is the same number of loads per wavefront; indices
+//     past the end are clamped, so the count never varies), and so are the waits on the LDS reads (once per k-tile, behind the
+//     products: the compiler counts the copies to LDS as possibly out of order on that counter and could only wait for all);
+//   * the accumulators reach the epilogue through LDS, half of a wavefront's column tiles at a time.
+// What bounds it: with operands of random values the chip's power limit and the L2 -> LDS fetch rate (16 .. 18 TB/s over the
+// chip in this access pattern, loads alone) meet at about half of the published matrix-core rate for every tile from 128 x 128
+// up (macro_tiles has the measured time per k-tile of each); below that, the fixed cost of a step.  So a larger tile is no
+// faster per product than a 192 x 128 one, and what decides is how evenly the tiles divide the shape over 256 compute units:
+// hence many tiles and a planner (gemm_macro.hip) instead of few large ones.  Two k-tiles per stage against one: 192 x 192
+// 80 -> 76 us (gate/up of an 8B model at 384 rows), 128 x 128 -10 %; where only two such stages fit (256 x 192, 256 x 256) one
+// k-tile per stage is the faster one.
+#pragma once
+#include <type_traits>
+
+#include "gemm_epilogue.h"
+#include "stats_part.h"
+
+// {WM, WN, RW, CW, KB, ns1, ns4}: tile of 16 RW WM rows x 16 CW WN columns; nanoseconds per k-tile on a chip full of such
+// workgroups when each streams a W of its own (one row block) and when four or more row blocks share it (operands of random
+// values; fitted to 3500 launches of the layer and head matrices of an 8B and a 7B grouped-query model at 24 .. 2822 rows).
+#define MACRO_TILES(X)                                                                                            \
+  X(2, 2, 1, 8, 2, 683, 399) X(1, 5, 2, 4, 2, 822, 487)                                                           \
+  X(2, 1, 2, 4, 2, 174, 130) X(1, 3, 4, 2, 2, 262, 195) X(1, 5, 4, 2, 2, 429, 236) X(2, 4, 2, 4, 2, 696, 330)     \
+  X(3, 2, 2, 4, 2, 348, 244) X(3, 4, 2, 4, 2, 706, 395)                                                           \
+  X(2, 2, 4, 2, 2, 252, 193) X(2, 3, 4, 2, 2, 301, 232) X(4, 2, 2, 4, 2, 361, 278)                                \
+  X(2, 5, 4, 2, 2, 481, 343) X(4, 3, 2, 4, 2, 536, 386) X(4, 4, 2, 4, 2, 714, 466)                                \
+  X(5, 2, 2, 4, 2, 432, 338) X(5, 3, 2, 4, 2, 571, 443)                                                           \
+  X(3, 3, 4, 2, 2, 389, 322) X(3, 5, 4, 2, 2, 532, 433) X(3, 6, 4, 2, 2, 615, 513)                                \
+  X(4, 6, 4, 2, 1, 746, 695) X(4, 8, 4, 2, 1, 922, 831)
+// rows:  32 (x 256, 320 columns), 64 (x 64, 96, 160, 256), 96 (x 128, 256), 128 (x 64, 96, 128, 160, 192, 256), 160 (x 128, 192),
+//        192 (x 96, 160, 192), 256 (x 192, 256)
+
+struct MacroTile {
+  int wm, wn, rw, cw, kb;
+  float ns1, ns4;
+};
+struct MacroPlan {
+  int tile;  // index into MACRO_TILES
+  int nblocks, mblocks, splits, kps;
+};
+// K is split only where a wavefront has at most this many output fragments: the last arriver holds two tiles of them
+constexpr int MACRO_SPLIT_FRAGS = 16;
+
+// gemm_macro_<epilogue>.hip: the launches of one epilogue's instantiations
+template <int EPI>
+void launch_macro_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const MacroPlan& p, const GemmEpi& e, hipStream_t st);
+
+#ifdef GEMM_MACRO_INSTANTIATE
+namespace {
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int SC1 = 16;  // cache-policy bit of the raw-buffer builtins: device scope
+__device__ inline __amdgpu_buffer_rsrc_t part_rsrc(const float* base) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00020000);
+}
+
+#define GLOBAL_PTR(p) ((const void __attribute__((address_space(1)))*)(p))
+#define LDS_PTR(p) ((void __attribute__((address_space(3)))*)(p))
+
+template <int WM, int WN, int RW, int CW, int KB>
+struct MacroShape {
+  static constexpr int NW = RW * CW, TPB = NW * 64;
+  static constexpr int AT = RW * WM, BF = CW * WN;  // X (row) and W (column) fragments of a k-tile
+  static constexpr int NFR = AT + BF;
+  static constexpr int LPT = (NFR + NW - 1) / NW;   // direct-to-LDS loads per wavefront and k-tile (surplus ones repeat the last fragment)
+  static constexpr int LPS = KB * LPT;              // ... and stage
+  static constexpr int STAGE = KB * NFR * 1024;
+  static constexpr int S_FIT = (152 * 1024) / STAGE, S_CNT = 63 / LPS + 1;  // what LDS holds, and what the memory counter counts
+  static constexpr int S_ = S_FIT < S_CNT ? S_FIT : S_CNT;
+  static constexpr int S = S_ > 6 ? 6 : S_;
+  static constexpr int HJ = (WN + 1) / 2;           // column tiles of a wavefront that leave through LDS together
+  static constexpr int BODY = S * STAGE > NW * HJ * WM * 1024 ? S * STAGE : NW * HJ * WM * 1024;
+  static constexpr int LDS_BYTES = BODY + AT * 16 * 4 * (1 + BF);  // + 1/rms of the rows, sums of squares per row and column tile
+  static_assert(S >= 2 && LDS_BYTES <= 160 * 1024, "pipeline shape");
+};
+
+// prs: 1 if the weights are packed in interleaved pairs of column tiles, 0 for single runs (weight_pack_rows - 1)
+template <int WM, int WN, int RW, int CW, int KB, int EPI>
+__global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
+                                                                               int prs, int nblocks, int mblocks, int splits, int kt_per_split, GemmEpi e) {
+  typedef MacroShape<WM, WN, RW, CW, KB> SH;
+  constexpr int NW = SH::NW, TPB = SH::TPB, AT = SH::AT, BF = SH::BF, NFR = SH::NFR, LPT = SH::LPT, LPS = SH::LPS, STAGE = SH::STAGE, S = SH::S, HJ = SH::HJ;
+  extern __shared__ __align__(16) unsigned char lds[];
+  float* s_rinv = (float*)(lds + SH::BODY);  // [AT * 16]
+  float* s_ssq = s_rinv + AT * 16;           // [BF][AT * 16]
+  __shared__ int s_ticket;
+
+  // Workgroup id -> (column block, K split, row block), row blocks fastest.  Ids congruent mod 8 share an XCD: each XCD takes one
+  // contiguous eighth of the tiles, so the row blocks of a column block (which stream the same W) meet in one L2 and no XCD has
+  // more than its share.
+  const int total = nblocks * mblocks * splits, lin = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (lin >= total) return;
+  const int rb = lin % mblocks, cs = lin / mblocks, split = cs % splits, cb = cs / splits;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / CW, wn = wave % CW;
+  const int KT = K >> 5, MTILES = (M + 15) >> 4, NT = N >> 4;
+  const int mt0 = rb * AT, nt0 = cb * BF, m_lo = mt0 * 16;
+  // the workgroup's k-tiles kb .. kb + nkt - 1; stage s holds k-tiles s KB .. s KB + KB - 1 of them
+  const int kb = split * kt_per_split, nkt = min(KT, kb + kt_per_split) - kb, nstages = nkt / KB;
+
+  // Copies lo .. hi - 1 (of this wavefront's LPS) of stage s -> buffer buf: fragment f of a k-tile (f < AT: X row tile mt0 + f, else
+  // W column tile nt0 + f - AT) is moved by wavefront f % NW; a wavefront without a fragment of its own in the last round moves
+  // the last one again.  The fragments' addresses at the first k-tile are kept, so that a copy costs one scalar shift and one add
+  // (recomputing them from the tile indices each time took 3 .. 5 % of a wide launch).
+  const unsigned lane16 = lane * 16;
+  const char* fbase[LPT];
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) {
+    const int f = i * NW + wave, nt = min(nt0 + min(max(f - AT, 0), BF - 1), NT - 1);
+    fbase[i] = f < AT ? (const char*)xt + ((size_t)min(mt0 + f, MTILES - 1) * KT + kb) * 1024
+                      : (const char*)wt + ((((size_t)(nt >> prs) * KT + kb) << prs) + (nt & prs)) * 1024;
+  }
+  auto issue = [&](int s, int buf, int lo, int hi) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = lo; c < hi; ++c) {
+      const int sub = c / LPT, i = c % LPT, f = i * NW + wave;
+      const unsigned t = min(s * KB + sub, nkt - 1);
+      const bool is_x = AT % NW == 0 ? i < AT / NW : f < AT;  // (uniform in the wavefront)
+      const char* src = fbase[i] + (is_x ? t << 10 : t << (10 + prs));
+      unsigned char* dst = lds + buf * STAGE + (sub * NFR + min(f, NFR - 1)) * 1024;
+      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src + lane16), LDS_PTR(dst), 16, 0, 0);
+    }
+  };
+
+  f32x4 acc[WN][WM];
+#pragma unroll
+  for (int j = 0; j < WN; ++j)
+#pragma unroll
+    for (int i = 0; i < WM; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  op8 xf[2][WM], wf[2][WN];
+  auto read_frags = [&](int set, int buf, int sub) __attribute__((always_inline)) {
+    const op8* st = (const op8*)(lds + buf * STAGE + sub * NFR * 1024) + lane;
+#pragma unroll
+    for (int i = 0; i < WM; ++i) xf[set][i] = st[(wm * WM + i) * 64];
+#pragma unroll
+    for (int j = 0; j < WN; ++j) wf[set][j] = st[(AT + wn * WN + j) * 64];
+  };
+  auto multiply = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int i = 0; i < WM; ++i) acc[j][i] = mfma_op(wf[set][j], xf[set][i], acc[j][i]);
+  };
+
+  // 1/rms of the workgroup's input rows, needed only by the epilogue: fetched before the pipeline starts (its loads are counted
+  // by the compiler, the pipeline's by hand: the two must not be in flight together), all of a thread's loads in one trip;
+  // published to the other wavefronts by the loop's barriers
+  if (EPI != EPI_RESID) block_rinv_batched<TPB, AT * 16>(e.rs, m_lo, max(0, min(M, m_lo + AT * 16) - m_lo), s_rinv);
+
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s) issue(s, s, 0, LPS);
+  issue(S - 1, S - 1, 0, LPS / KB);  // (the rest of it goes out during stage 0, as for every later stage)
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * LPS + LPS / KB) : "memory");  // stage 0 has landed (this wavefront's share)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read_frags(0, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): as at the end of every k-tile below
+  // K-tile SUB of stage s (in LDS buffer buf), whose operands are in register set `set`; stages up to s + S - 1 have been issued
+  auto ktile = [&](auto SUBc, int set, int s, int buf, int nbuf) __attribute__((always_inline)) {
+    constexpr int SUB = decltype(SUBc)::value;
+    constexpr bool LAST = SUB == KB - 1;
+    constexpr int LO = LAST ? 0 : LPS * (SUB + 1) / KB, HI = LAST ? LPS / KB : LPS * (SUB + 2) / KB;
+    if (LAST) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * LPS) : "memory");  // stage s + 1 has landed
+      __builtin_amdgcn_s_barrier();  // ... for every wavefront, and every wavefront has read the last of stage s
+      asm volatile("" ::: "memory");
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (LAST) issue(s + S, buf, LO, HI);
+    else issue(s + S - 1, buf == 0 ? S - 1 : buf - 1, LO, HI);
+    if (LAST) read_frags(set ^ 1, nbuf, 0);
+    else read_frags(set ^ 1, buf, SUB + 1);
+    multiply(set);
+    // Issue order, fixed by hand: the products (which depend on registers only) start right away, and the copies and the LDS
+    // reads of the next k-tile go out between them.  Left alone, the scheduler puts the reads next to their uses, and all
+    // wavefronts of a SIMD, which leave the barrier together, would issue their loads while its matrix core idles.
+    constexpr int NM = WN * WM, RF = WM + WN, LI = HI - LO;
+    constexpr int OPS = 2 * (LI + RF) <= NM ? 1 : LI + RF <= NM ? 2 : 4;  // copies / reads per product: out by the middle of the products where they are many enough
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+#pragma unroll
+    for (int i = 0; i < LI; i += OPS) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // one product
+      __builtin_amdgcn_sched_group_barrier(0x010, OPS, 0);  // copies to LDS
+    }
+#pragma unroll
+    for (int i = 0; i < RF; i += OPS) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, OPS, 0);  // LDS reads
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, NM, 0);  // what is left of the products
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the reads have had the products' time to complete
+  };
+  // two k-tiles per trip, unconditionally: a fragment read that is used only behind a branch would be moved behind it, next to
+  // its use, and the matrix cores would wait for LDS
+  static_assert(KB == 1 || KB == 2, "k-tiles per stage");
+  int buf = 0;
+  auto next = [&](int b) { return b + 1 == S ? 0 : b + 1; };
+  if constexpr (KB == 2) {
+    for (int s = 0; s < nstages; ++s, buf = next(buf)) {
+      ktile(std::integral_constant<int, 0>{}, 0, s, buf, next(buf));
+      ktile(std::integral_constant<int, 1>{}, 1, s, buf, next(buf));
+    }
+    if (nkt & 1) multiply(0);  // the odd last k-tile: its operands were read with the stage before it
+  } else {
+    int s = 0;
+    for (; s + 1 < nstages; s += 2) {
+      ktile(std::integral_constant<int, 0>{}, 0, s, buf, next(buf));
+      buf = next(buf);
+      ktile(std::integral_constant<int, 0>{}, 1, s + 1, buf, next(buf));
+      buf = next(buf);
+    }
+    if (s < nstages) ktile(std::integral_constant<int, 0>{}, 0, s, buf, next(buf));
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the surplus loads of the last stages: LDS must be quiet before it is reused
+
+  const int g = lane >> 4, ml = lane & 15;
+  if constexpr (WM * WN <= MACRO_SPLIT_FRAGS) if (splits > 1) {
+    // K split (shapes whose tiles cover less than the chip).  Every workgroup of a tile takes a ticket; all but the last to arrive
+    // write their partial tile to the fp32 workspace, in the accumulator layout and through to device scope, and then raise the
+    // tile's count of finished partials.  The last one keeps its own in registers, waits for that count (every workgroup it
+    // waits for has taken its ticket, so it is running and finishes without waiting for anyone), adds the partial tiles in
+    // split order, its own in its place (deterministic whoever is last), and runs the epilogue.
+    const size_t stride = (size_t)M * N;
+    auto offset = [&](int j, int i) { return ((unsigned)((wm * WM + i) * 16 + ml) * N + (nt0 + wn * WN + j) * 16 + 4 * g) * 4u; };
+    auto exists = [&](int j, int i) { return nt0 + wn * WN + j < NT && m_lo + (wm * WM + i) * 16 + ml < M; };
+    int* ticket = e.counters + 2 * (cb * mblocks + rb);
+    if (tid == 0) s_ticket = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_ticket != splits - 1) {
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+          if (exists(j, i))
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j][i]), part_rsrc(e.part + split * stride + (size_t)m_lo * N), offset(j, i), 0, SC1);
+      // hand-off across workgroups (possibly across XCDs, whose L2s are separate): every wavefront waits until its own stores,
+      // written through to device scope, have been acknowledged; then the count is raised with release order at device scope
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0) (void)__hip_atomic_fetch_add(ticket + 1, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    if (tid == 0) {
+      while (__hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != splits - 1) __builtin_amdgcn_s_sleep(1);
+      __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
+      __hip_atomic_store(ticket + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    f32x4 sum[WN][WM];
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int i = 0; i < WM; ++i) sum[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < splits; ++s0) {
+      if (s0 == split) {
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+          for (int i = 0; i < WM; ++i) sum[j][i] += acc[j][i];
+        continue;
+      }
+      u32x4 t[WN][WM];
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+          t[j][i] = __builtin_amdgcn_raw_buffer_load_b128(part_rsrc(e.part + s0 * stride + (size_t)m_lo * N), exists(j, i) ? offset(j, i) : 0u, 0, SC1);
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int i = 0; i < WM; ++i) sum[j][i] += __builtin_bit_cast(f32x4, t[j][i]);
+    }
+#pragma unroll
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int i = 0; i < WM; ++i) acc[j][i] = sum[j][i];
+  }
+
+  // ---- epilogue
+  __syncthreads();
+  // The accumulators leave the registers through LDS (each wavefront its own region, half of its column tiles at a time), so
+  // that the epilogue runs as a loop over fragments instead of WM WN unrolled copies with every accumulator live.
+  f32x4* mine = (f32x4*)lds + wave * (HJ * WM * 64) + lane;
+  LiteState state[WM];  // EPI_STATS
+#pragma unroll
+  for (int i = 0; i < WM; ++i) state[i] = lite_init();
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    // what the fragments' epilogues read from memory (residual and gain; rotary cosines and sines) is fetched for up to twelve
+    // fragments per trip instead of one trip per fragment
+#pragma unroll
+    for (int jj = 0; jj < HJ; ++jj)
+#pragma unroll
+      for (int i = 0; i < WM; ++i)
+        if (h * HJ + jj < WN) mine[(jj * WM + i) * 64] = acc[h * HJ + jj < WN ? h * HJ + jj : 0][i];
+    constexpr int IB = WM * HJ <= 12 ? WM : WM % 2 == 0 ? WM / 2 : 1;  // row tiles per trip: at most 12 fragments' worth of registers
+#pragma unroll
+    for (int i0 = 0; i0 < WM; i0 += IB) {
+      EpiAhead ah[IB][HJ];
+#pragma unroll
+      for (int i = 0; i < IB; ++i)
+#pragma unroll
+        for (int jj = 0; jj < HJ; ++jj) {
+          const int nt = nt0 + wn * WN + h * HJ + jj;
+          ah[i][jj] = (EPI == EPI_RESID || EPI == EPI_QKV) && h * HJ + jj < WN && nt < NT
+                          ? epi_ahead<EPI>(e, M, N, m_lo + (wm * WM + i0 + i) * 16 + ml, nt * 16, g) : epi_none();
+        }
+#pragma unroll
+      for (int i = 0; i < IB; ++i) {
+        const int rl = (wm * WM + i0 + i) * 16 + ml;
+        const float rinv = EPI == EPI_RESID ? 1.f : s_rinv[rl];
+#pragma unroll
+        for (int jj = 0; jj < HJ; ++jj) {
+          const int nt = nt0 + wn * WN + h * HJ + jj;
+          if (EPI == EPI_STATS) {  // the logits, and the states of their values as written
+            const int m = m_lo + rl, n = nt * 16 + 4 * g;
+            if (h * HJ + jj < WN && nt < NT) {
+              const f32x4 v = mine[(jj * WM + i0 + i) * 64] * rinv;
+              if (m < M) *(bf16x4*)(e.out_bf16 + (size_t)m * N + n) = to_bf16x4(v);
+              state[i0 + i] = lite_merge(state[i0 + i], lite_of(v, n, e.skip_col));
+            }
+          } else if (h * HJ + jj < WN) {
+            float ss = 0.f;
+            if (nt < NT) ss = finish_frag<EPI>(e, M, N, m_lo + rl, nt * 16, g, mine[(jj * WM + i0 + i) * 64], rinv, ah[i][jj]);  // uniform in the wavefront
+            if (EPI == EPI_RESID && g == 0) s_ssq[(wn * WN + h * HJ + jj) * AT * 16 + rl] = ss;
+          }
+        }
+      }
+    }
+  }
+  if (EPI == EPI_STATS) {  // one state per row: the four lanes of a row, then the wavefronts' column ranges, each in a fixed order
+    LiteState* s_state = (LiteState*)lds;  // [CW][AT * 16]
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+      state[i] = lite_merge(state[i], lite_shfl_xor(state[i], 16));
+      state[i] = lite_merge(state[i], lite_shfl_xor(state[i], 32));
+      if (g == 0) s_state[wn * AT * 16 + (wm * WM + i) * 16 + ml] = state[i];
+    }
+    __syncthreads();
+    for (int r = tid; r < AT * 16 && m_lo + r < M; r += TPB) {
+      LiteState t = s_state[r];
+#pragma unroll
+      for (int c = 1; c < CW; ++c) t = lite_merge(t, s_state[c * AT * 16 + r]);
+      f32x4* dst = (f32x4*)((Part*)e.stat_parts + (size_t)(m_lo + r) * nblocks + cb);  // Part{m, s, t, w = 0, bv = m, bi, pm, ps = 0}
+      static_assert(sizeof(Part) == 32 && offsetof(Part, bv) == 16 && offsetof(Part, bi) == 20, "Part is written as two vectors");
+      dst[0] = f32x4{t.m, t.s, t.t, 0.f};
+      dst[1] = f32x4{t.m, __int_as_float(t.bi), NEG_BIG, 0.f};
+    }
+  }
+  if (EPI == EPI_RESID) {  // the workgroup's share of sum h^2 per row: each half of its column tiles in ascending order, then the two
+    __syncthreads();
+    for (int r = tid; r < AT * 16 && m_lo + r < M; r += TPB) {
+      float ss[2] = {0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < BF; ++j) ss[j >= BF / 2] += s_ssq[j * AT * 16 + r];
+      e.ssq_out[(size_t)(m_lo + r) * nblocks + cb] = ss[0] + ss[1];
+    }
+  }
+}
+
+template <int WM, int WN, int RW, int CW, int KB, int EPI>
+void launch_tile(const op_t* xt, const op_t* wt, int M, int N, int K, const MacroPlan& p, const GemmEpi& e, hipStream_t st) {
+  typedef MacroShape<WM, WN, RW, CW, KB> SH;
+  static bool configured = false;  // raise the dynamic LDS limit of this instantiation once
+  if (!configured) {
+    (void)hipFuncSetAttribute((const void*)gemm_macro_kernel<WM, WN, RW, CW, KB, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
+    configured = true;
+  }
+  const int grid = (p.nblocks * p.mblocks * p.splits + 7) / 8 * 8;
+  DLM_LAUNCH((gemm_macro_kernel<WM, WN, RW, CW, KB, EPI>), grid, SH::TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K, weight_pack_rows(N) - 1,
+             p.nblocks, p.mblocks, p.splits, p.kps, e);
+}
+
+}  // namespace
+
+template <int EPI>
+void launch_macro_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const MacroPlan& p, const GemmEpi& e, hipStream_t st) {
+  int i = 0;
+#define GO(WM, WN, RW, CW, KB, NS1, NS4)                                                                                       \
+  if constexpr (EPI != EPI_STATS || 16 * WM * RW <= GEMM_STATS_MAX_ROWS) {                                                     \
+    if (p.tile == i) return launch_tile<WM, WN, RW, CW, KB, EPI>(xt, wt, M, N, K, p, e, st);                                  \
+  }                                                                                                                            \
+  ++i;
+  MACRO_TILES(GO)
+#undef GO
+}
+#endif  // GEMM_MACRO_INSTANTIATE

@@ -1,5 +1,5 @@
-// Mid-size GEMM of a bf16 model (65 .. 160 rows: a block plus its look-ahead window, a few packed blocks; fewer rows where its wide
-// column groups pay, see choose_kernel in gemm_bf16.hip):
+// Mid-size GEMM of a bf16 model (a few dozen to two hundred rows, where its column groups are one round over the compute units:
+// choose_kernel in gemm_bf16.hip):
 // Y[M,N] = X[M,K] * W[N,K]^T, fp32 accumulation, epilogue fused.
 //
 // At these row counts W is still the larger operand, but every column group re-reads X, so the groups
@@ -18,7 +18,7 @@
 //     wavefront order, and each wavefront finishes every fourth output fragment.
 // When the column groups are fewer than the compute units, K is split across workgroups as well:
 // partial tiles go to an fp32 workspace written through to device scope, and the workgroup that takes
-// the last ticket adds them in split order (the protocol of gemm_tiled.hip; a wavefront fetches the
+// the last ticket adds them in split order (a wavefront fetches the
 // same split of all its output fragments in a single trip to memory).
 #include "gemm_epilogue.h"
 #include <type_traits>
@@ -272,36 +272,33 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   }
 }
 
-int g_mid_wgs = 256;  // workgroups the K split of a narrow matrix aims at
-
 struct MidPlan {
   int ct, pr, mt, groups, splits, kps;
 };
 
 // What the compute units can load through their L2s (W once, X once per column group; about 45 GB/s each, 10 .. 12 TB/s
 // together) bounds these shapes before HBM does, and a K split costs a round trip of partial tiles through memory plus a
-// serial tail.  Wide matrices: of the group widths 128 (to 112 rows), 96 and 48 columns, the one that fills the chip's 256
+// serial tail.  Wide matrices: of the group widths 128, 96 and 48 columns, the one that fills the chip's 256
 // compute units best, without a K split if it can (QKV of an 8B model: 256 groups of 48; gate/up: 256 groups of 96).
 // Narrow ones (O, down; at most 256 column tiles): 64-column groups and a four-way K split when K is long (down), 32-column
 // groups and a two-way split when it is short (O); all measured against their alternatives.
-MidPlan mid_plan(int M, int N, int K, bool may_split) {
+MidPlan mid_plan(int M, int N, int K) {
   MidPlan best;
   double best_fill = -1.;
   const int pr = weight_pack_rows(N), mt = (M + 15) >> 4, KT = K >> 5;
-  // accumulators (4 CT MT registers) + three k-tiles of W + two of X within the register file: 128-column groups up to 112 rows
-  // short K: the partial tiles of a four-way split cost more than X re-read by twice the groups; beyond 13 row tiles the
-  // 32-column variant's two k-tiles of X per step no longer fit the registers
-  const int narrow = (K >= 8192 && mt > 1) || mt > 13 ? 4 : 2;
-  const int cts[3] = {pr == 2 ? (mt <= 7 ? 8 : 6) : narrow, pr == 2 ? 6 : narrow, pr == 2 ? (mt <= 10 ? 3 : 6) : narrow};
+  // short K: the partial tiles of a four-way split cost more than X re-read by twice the groups
+  const int narrow = K >= 8192 && mt > 1 ? 4 : 2;
+  // (a wide matrix beyond four row tiles comes here only for its 48-column groups)
+  const int cts[3] = {pr == 2 ? (mt <= 4 ? 8 : 3) : narrow, pr == 2 ? (mt <= 4 ? 6 : 3) : narrow, pr == 2 ? 3 : narrow};
   for (int c = 0; c < 3; ++c) {
     MidPlan p;
     p.pr = pr; p.mt = mt; p.ct = cts[c];
     p.groups = (N + 16 * p.ct - 1) / (16 * p.ct);
-    int s = pr == 2 ? 256 / p.groups : (g_mid_wgs + p.groups / 2) / p.groups;
+    int s = pr == 2 ? 256 / p.groups : (256 + p.groups / 2) / p.groups;
     if (pr == 1 && mt == 1) s = 1;  // one row tile of a narrow matrix comes here only to avoid a second round of 16-column workgroups
     if (s > (pr == 2 ? 2 : 4)) s = pr == 2 ? 2 : 4;  // a short serial tail for the last arriver, and little traffic of partial tiles
     if (s > KT / 16) s = KT / 16;     // at least four k-tiles per wavefront
-    if (s < 1 || !may_split) s = 1;
+    if (s < 1) s = 1;
     p.kps = (KT + s - 1) / s;
     p.splits = (KT + p.kps - 1) / p.kps;  // no empty split
     // more groups of the widest kind than compute units (the LM head): several rounds anyway, the widest re-reads X least
@@ -341,13 +338,13 @@ template <int MT, int EPI>
 void launch_mt(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
   if (p.pr == 1) {
     if (p.ct == 2) { if constexpr (MT <= 13) launch_one<MT, 2, 1, EPI>(xt, wt, M, N, K, p, e, st); }
-    else if constexpr (MT >= 2) launch_one<MT, 4, 1, EPI>(xt, wt, M, N, K, p, e, st);
-  } else if (p.ct == 8) {
-    if constexpr (MT <= 7) launch_one<MT, 8, 2, EPI>(xt, wt, M, N, K, p, e, st);
+    else if constexpr (MT >= 2 && MT <= 8) launch_one<MT, 4, 1, EPI>(xt, wt, M, N, K, p, e, st);
   } else if (p.ct == 3) {
-    if constexpr (MT <= 10) launch_one<MT, 3, 2, EPI>(xt, wt, M, N, K, p, e, st);
+    if constexpr (MT <= 6) launch_one<MT, 3, 2, EPI>(xt, wt, M, N, K, p, e, st);
+  } else if (p.ct == 8) {
+    if constexpr (MT <= 4) launch_one<MT, 8, 2, EPI>(xt, wt, M, N, K, p, e, st);
   } else {
-    if constexpr (MT <= 10) launch_one<MT, 6, 2, EPI>(xt, wt, M, N, K, p, e, st);
+    if constexpr (MT <= 4) launch_one<MT, 6, 2, EPI>(xt, wt, M, N, K, p, e, st);
   }
 }
 
@@ -366,10 +363,7 @@ void launch_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPl
     case 10: launch_mt<10, EPI>(xt, wt, M, N, K, p, e, st); break;
     case 11: launch_mt<11, EPI>(xt, wt, M, N, K, p, e, st); break;
     case 12: launch_mt<12, EPI>(xt, wt, M, N, K, p, e, st); break;
-    case 13: launch_mt<13, EPI>(xt, wt, M, N, K, p, e, st); break;
-    case 14: launch_mt<14, EPI>(xt, wt, M, N, K, p, e, st); break;
-    case 15: launch_mt<15, EPI>(xt, wt, M, N, K, p, e, st); break;
-    default: launch_mt<16, EPI>(xt, wt, M, N, K, p, e, st); break;
+    default: launch_mt<13, EPI>(xt, wt, M, N, K, p, e, st); break;
   }
 }
 
@@ -377,22 +371,24 @@ void launch_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPl
 
 // one compute unit's worth of workgroups per 96-column group, no K split: the shapes the mid kernel takes even below 17 rows
 bool gemm_mid_fills_chip(int M, int N, int K) {
-  const MidPlan p = mid_plan(M, N, K, true);
+  const MidPlan p = mid_plan(M, N, K);
   return p.splits == 1 && p.groups % 256 == 0;
 }
-int gemm_mid_splits(int M, int N, int K) { return mid_plan(M, N, K, true).splits; }
-int gemm_mid_ssq_chunks(int M, int N, int K) { return mid_plan(M, N, K, true).groups; }
+bool gemm_mid_one_round(int M, int N, int K) {
+  const MidPlan p = mid_plan(M, N, K);
+  return p.groups * p.splits <= 256;
+}
+int gemm_mid_splits(int M, int N, int K) { return mid_plan(M, N, K).splits; }
+int gemm_mid_ssq_chunks(int M, int N, int K) { return mid_plan(M, N, K).groups; }
 int gemm_mid_counters(int max_n) { return (max_n + 31) / 32; }  // 32-column groups are the narrowest
-void gemm_mid_set_target(int wgs) { g_mid_wgs = wgs; }
-
 
 int gemm_mid_steps_ct(int N, int K) {
-  const MidPlan p = mid_plan(16, N, K, true);
+  const MidPlan p = mid_plan(16, N, K);
   return (p.splits == 1 && N % (16 * p.ct) == 0 && (K >> 5) % NWV == 0) ? p.ct : 0;
 }
 
 void launch_gemm_mid(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e_in, hipStream_t st) {
-  const MidPlan p = mid_plan(M, N, K, e_in.kind != EPI_DIRECT);  // EPI_DIRECT has no workspace
+  const MidPlan p = mid_plan(M, N, K);
   GemmEpi e = e_in;
   // the step-major copy serves exactly the launches it was laid out for
   if (!(e.w_steps && p.mt <= MID_STEPS_MAX_MT && e.w_steps_ct == p.ct && p.splits == 1 && N % (16 * p.ct) == 0 && (K >> 5) % NWV == 0)) e.w_steps = nullptr;

@@ -41,3 +41,41 @@ __device__ inline Part part_shfl_xor(const Part& p, int o) {
   return r;
 }
 
+// The part of a row's online-softmax state that a pass without a previous-step distribution needs (stats_part.h has the whole):
+// maximum (= the best logit), sum e^(z-m), sum e^(z-m)(z-m), lowest token id of the maximum.
+struct LiteState {
+  float m, s, t;
+  int bi;
+};
+__device__ __attribute__((always_inline)) inline LiteState lite_init() { return LiteState{NEG_BIG, 0.f, 0.f, 0x7fffffff}; }
+__device__ __attribute__((always_inline)) inline LiteState lite_merge(const LiteState a, const LiteState b) {
+  LiteState r;
+  r.m = fmaxf(a.m, b.m);
+  const float da = a.m - r.m, db = b.m - r.m;
+  const float fa = __expf(da), fb = __expf(db);
+  r.s = fa * a.s + fb * b.s;
+  r.t = fa * (a.t + da * a.s) + fb * (b.t + db * b.s);
+  r.bi = (b.m > a.m || (b.m == a.m && b.bi < a.bi)) ? b.bi : a.bi;
+  return r;
+}
+__device__ __attribute__((always_inline)) inline LiteState lite_shfl_xor(const LiteState p, int o) {
+  return LiteState{__shfl_xor(p.m, o, 64), __shfl_xor(p.s, o, 64), __shfl_xor(p.t, o, 64), __shfl_xor(p.bi, o, 64)};
+}
+// state of four consecutive logits, token ids n .. n+3, token `skip` left out
+__device__ __attribute__((always_inline)) inline LiteState lite_of(f32x4 v, int n, int skip) {
+  float z[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) z[i] = (float)(bf16_t)v[i];  // the logit as stored
+  LiteState r = lite_init();
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (n + i != skip && z[i] > r.m) { r.m = z[i]; r.bi = n + i; }  // ascending ids and strict '>' keep the lowest id
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (n + i == skip) continue;
+    const float d = z[i] - r.m, ex = __expf(d);
+    r.s += ex;
+    r.t = fmaf(ex, d, r.t);
+  }
+  return r;
+}

@@ -53,6 +53,31 @@ def test_gemm_bf16(device, M, N, K):
     assert np.abs(got - ref).mean() <= 4e-3 * np.abs(ref).mean() + 1e-6
 
 
+# One shape for every tile the macro GEMM's planner has for more than 32 rows, each with a ragged last row block, a ragged last
+# column block, an odd number of k-tiles (13: more than the pipeline has stages) and rows that are no multiple of 16; and K splits
+# of three and four ways, whose workgroups hand their partial tiles to the last arriver, run twice (the tickets reset themselves).
+# (The 32-row tiles serve the LM head: every in-block pass of the step tests.)
+@pytest.mark.parametrize("M,N,K", [(209, 96, 416), (17, 16480, 416), (17, 32864, 416), (259, 10976, 416), (17, 24768, 416), (259, 16608, 416),
+                                   (70, 12704, 416), (129, 8704, 416), (97, 24768, 416), (68, 33088, 416), (17, 40992, 416), (199, 24672, 416),
+                                   (129, 24928, 416), (291, 16448, 416), (133, 16448, 416), (164, 24896, 416), (161, 41024, 416), (387, 16640, 416),
+                                   (257, 24608, 416), (300, 160, 4128), (264, 96, 4128), (290, 4064, 8224)])
+def test_gemm_macro_tiles(device, M, N, K):
+    g = torch.Generator(device="cpu").manual_seed(M + N + K)
+    x = torch.randn(M, K, generator=g).to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g) * 0.05).to(torch.bfloat16)
+    xd, wd = x.to(device), w.to(device)
+    y = api.dlm_gemm_nt(xd, wd)
+    again = api.dlm_gemm_nt(xd, wd)
+    torch.cuda.synchronize()
+    ref = o_fwd.matmul_nt(_np(x), _np(w))
+    got = o_fwd.widen(_np(y))
+    # bf16 rounding of an fp32 sum of exact products (half converts these values exactly): 2^-9 relative, plus K roundings of
+    # 2^-24 of partial sums that grow like the result's scale
+    bound = 2.0 ** -8 * np.abs(ref) + K * 2.0 ** -24 * 0.05 * np.sqrt(K)
+    assert (np.abs(got - ref) <= bound).all(), (np.abs(got - ref) / bound).max()
+    assert torch.equal(y, again)
+
+
 @pytest.mark.parametrize("M", [8, 100, 300])
 def test_gemm_operand_conversion_at_the_ends_of_halfs_range(device, M):
     """A bf16 model's matrix-core operands are IEEE half.  Weights far below half's smallest normal number (2^-14) land on its
