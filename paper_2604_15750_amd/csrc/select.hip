@@ -1,144 +1,191 @@
 // CAP-Decoding (paper Sec. 4.3, Eq. 5-6, Alg. 1) and the token write of Eq. 2.
-// One workgroup per sequence, one lane per block row (block <= 256 rows).  The pairwise conflict
-// scores are gathered straight from the logits (two scalars per pooled pair), kept as a bit matrix
-// in LDS; the confidence order is found by counting; the greedy pass is a short sequential walk
-// over bit masks.
+// One workgroup per sequence, one lane of its first four wavefronts per block row (block <= 256 rows).  What bounds it is
+// latency: a chain of dependent steps, each a trip to memory or to LDS.  So
+//   * the pairwise conflict scores (two scalars per pair of pooled rows, gathered straight from the logits) go over all threads
+//     of the workgroup, four pairs of loads in flight per thread, over a compacted list of the pooled rows: 1024 threads for
+//     blocks of more than 32 rows, whose pairs would otherwise take several trips one after another; the conflicts are a bit
+//     matrix in LDS;
+//   * the greedy walk of phase 2 (in the order of confidence: take a row, drop its conflicts) runs in rounds: a row whose
+//     undecided conflicts all come later in that order is taken, and what conflicts with a row just taken is dropped.  That is
+//     the same set as the walk's, in as many rounds as the longest chain of conflicts instead of as many steps as rows.
+// 16 sequences x 64 rows: 34 us with one thread walking and one pair per thread and trip, 14 us now.
 #include "common.h"
 
 namespace {
 
-constexpr int TPB = 256;
-constexpr int WORDS = TPB / 32;
+constexpr int MAXL = 256;       // rows of a block
+constexpr int RW = MAXL / 64;   // wavefronts that own rows
+constexpr int WORDS = MAXL / 32;
 constexpr float INF = __builtin_inff();
 
-__device__ inline float block_min(float v, float* buf) {
-  v = -wave_max(-v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = buf[0];
-  for (int i = 1; i < TPB / 64; ++i) r = fminf(r, buf[i]);
-  return r;
-}
+union RowSet {  // one bit per row
+  unsigned long long q[RW];
+  uint32_t w[WORDS];
+  __device__ bool has(int j) const { return (w[j >> 5] >> (j & 31)) & 1u; }
+};
 
-// position of row i in the order (descending conf, ascending row) among rows with member[j] != 0
-__device__ inline int rank_among(int i, int L, const float* c, const uint8_t* member) {
-  int r = 0;
-  const float ci = c[i];
-  for (int j = 0; j < L; ++j)
-    if (member[j] && (c[j] > ci || (c[j] == ci && j < i))) ++r;
-  return r;
-}
-
-template <typename T>
+template <typename T, int TPB>
 __global__ __launch_bounds__(TPB) void select_kernel(const T* __restrict__ logits, int vocab, const float* __restrict__ lse_g,
                                                      const float* __restrict__ conf_g, const int32_t* __restrict__ argmax_g,
                                                      int32_t* __restrict__ tokens, SelectMeta meta, int mask_id, dlm_select_params p,
                                                      int apply, uint8_t* __restrict__ sel_out, int32_t* __restrict__ nsel_out,
                                                      float* __restrict__ margin_out) {
-  __shared__ float c[TPB], lse[TPB], fbuf[TPB / 64];
-  __shared__ int yh[TPB], order[TPB];
-  __shared__ uint8_t elig[TPB], pool[TPB], alive[TPB], sel[TPB];
-  __shared__ uint32_t bits[TPB][WORDS];
-  __shared__ int n_alive, n_sel, top_row, second_row;
+  __shared__ float c[MAXL], lse[MAXL], fbuf[TPB / 64];
+  __shared__ int yh[MAXL], list[MAXL];
+  __shared__ uint32_t bits[MAXL][WORDS + 1];  // conflicts of a row (padded: lanes read the same word of neighbouring rows)
+  __shared__ RowSet s_elig, s_pool, s_high, s_und, s_new, s_sel;
+  __shared__ int top_row, second_row;
 
-  const int b = blockIdx.x, i = threadIdx.x;
+  const int b = blockIdx.x, i = threadIdx.x, wave = i >> 6;
   const int row0 = meta.row_start[b], tok0 = meta.tok_start[b], L = meta.block_len[b];
-  const bool act = i < L;
+  const bool own = i < MAXL, act = i < L;  // (L <= MAXL)
   float margin = INF;
+  // publishes one bit per row: called by every thread, read after the next barrier
+  auto publish = [&](RowSet& s, bool v) {
+    const unsigned long long m = __ballot(v);
+    if (own && (i & 63) == 0) s.q[wave] = m;
+  };
 
-  c[i] = act ? conf_g[row0 + i] : -1.f;
-  lse[i] = act ? lse_g[row0 + i] : 0.f;
-  yh[i] = act ? min(max(argmax_g[row0 + i], 0), vocab - 1) : 0;  // a caller-supplied prediction outside the vocabulary is clamped into it
-  elig[i] = act && tokens[tok0 + i] == mask_id;
-  sel[i] = 0;
-  alive[i] = 0;
-  for (int w = 0; w < WORDS; ++w) bits[i][w] = 0;
-  if (i == 0) { n_alive = 0; n_sel = 0; top_row = -1; second_row = -1; }
+  float ci = -1.f;
+  bool e = false;
+  if (act) {
+    ci = conf_g[row0 + i];
+    lse[i] = lse_g[row0 + i];
+    yh[i] = min(max(argmax_g[row0 + i], 0), vocab - 1);  // a caller-supplied prediction outside the vocabulary is clamped into it
+    e = tokens[tok0 + i] == mask_id;
+  }
+  if (own) c[i] = ci;
+  publish(s_elig, e);
+  for (int k = i; k < MAXL * (WORDS + 1); k += TPB) ((uint32_t*)bits)[k] = 0;
+  if (i == 0) { top_row = -1; second_row = -1; }
+  bool pool = false, sel = false;
+  if (p.mode == 0) {
+    if (e) margin = fminf(fabsf(ci - p.tau_low), fabsf(ci - p.tau_high));
+    pool = e && ci >= p.tau_low;
+    publish(s_pool, pool);
+  } else if (p.mode == 1 && e) {
+    margin = fabsf(ci - p.tau_high);
+    sel = ci >= p.tau_high;
+  }
   __syncthreads();
 
+  // a row comes before another in the order of confidence: descending, ties by ascending row
+  auto before = [&](int j) { return c[j] > ci || (c[j] == ci && j < i); };
   // most confident eligible row and the runner-up (for the safeguard and modes 1, 2)
-  if (elig[i]) {
-    int r = rank_among(i, L, c, elig);
+  if (e) {
+    int r = 0;
+#pragma unroll 8
+    for (int j = 0; j < L; ++j) r += s_elig.has(j) && before(j);
     if (r == 0) top_row = i;
     if (r == 1) second_row = i;
   }
-  __syncthreads();
-  float top_gap = INF;
-  if (top_row >= 0 && second_row >= 0 && c[top_row] != c[second_row]) top_gap = c[top_row] - c[second_row];
 
   if (p.mode == 0) {
-    if (elig[i]) margin = fminf(fabsf(c[i] - p.tau_low), fabsf(c[i] - p.tau_high));
-    pool[i] = elig[i] && c[i] >= p.tau_low;
+    int np = 0, at = 0;  // pooled rows, in ascending order
+#pragma unroll
+    for (int w = 0; w < RW; ++w) {
+      const unsigned long long m = s_pool.q[w];
+      if (w < wave) at += __popcll(m);
+      else if (w == wave) at += __popcll(m & ((1ull << (i & 63)) - 1));
+      np += __popcll(m);
+    }
+    if (pool) list[at] = i;
     __syncthreads();
     // conflict bit matrix over pooled pairs (Eq. 6), each unordered pair once
-    for (int pr = i; pr < L * L; pr += TPB) {
-      int a = pr / L, d = pr - a * L;
-      if (a < d && pool[a] && pool[d]) {
-        float la = to_f32(logits[(size_t)(row0 + a) * vocab + yh[d]]) - lse[a];
-        float ld = to_f32(logits[(size_t)(row0 + d) * vocab + yh[a]]) - lse[d];
-        float D = la + ld;
+    constexpr int U = 4;
+    for (int k0 = i; k0 < np * np; k0 += U * TPB) {
+      int ra[U], rd[U];
+      float za[U], zd[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = k0 + u * TPB, ka = k / np, kd = k - ka * np;
+        const bool ok = k < np * np && ka < kd;
+        ra[u] = ok ? list[ka] : -1;
+        rd[u] = ok ? list[kd] : -1;
+        za[u] = zd[u] = 0.f;
+        if (ok) {
+          za[u] = to_f32(logits[(size_t)(row0 + ra[u]) * vocab + yh[rd[u]]]);
+          zd[u] = to_f32(logits[(size_t)(row0 + rd[u]) * vocab + yh[ra[u]]]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (ra[u] < 0) continue;
+        const float D = (za[u] - lse[ra[u]]) + (zd[u] - lse[rd[u]]);
         margin = fminf(margin, fabsf(D - p.gamma));
         if (D > p.gamma) {
-          atomicOr(&bits[a][d >> 5], 1u << (d & 31));
-          atomicOr(&bits[d][a >> 5], 1u << (a & 31));
+          atomicOr(&bits[ra[u]][rd[u] >> 5], 1u << (rd[u] & 31));
+          atomicOr(&bits[rd[u]][ra[u] >> 5], 1u << (ra[u] & 31));
         }
       }
     }
-    __syncthreads();
     // phase 1: every pooled row with conf >= tau_high; drop their conflicts from the pool
-    const bool high = pool[i] && c[i] >= p.tau_high;
-    if (high) sel[i] = 1;
+    const bool high = pool && ci >= p.tau_high;
+    publish(s_high, high);
     __syncthreads();
-    bool dropped = false;
-    if (pool[i] && !high)
-      for (int j = 0; j < L; ++j)
-        if (sel[j] && (bits[j][i >> 5] >> (i & 31) & 1u)) { dropped = true; break; }
-    alive[i] = pool[i] && !high && !dropped;
-    __syncthreads();
-    // phase 2 order: descending conf, ties by row
-    if (alive[i]) {
-      order[rank_among(i, L, c, alive)] = i;
-      atomicAdd(&n_alive, 1);
+    bool und = pool && !high;
+    uint32_t blk[WORDS];  // the row's conflicts; then those of them that come before it in the order
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) {
+      blk[w] = own ? bits[i][w] : 0;
+      und = und && (blk[w] & s_high.w[w]) == 0;
     }
+    publish(s_und, und);
     __syncthreads();
-    if (i + 1 < n_alive) {
-      float g = c[order[i]] - c[order[i + 1]];
-      if (g != 0.f) margin = fminf(margin, g);
-    }
-    if (i == 0) {
-      for (int r = 0; r < n_alive; ++r) {
-        int a = order[r];
-        if (!alive[a]) continue;
-        sel[a] = 1;
-        alive[a] = 0;
-        for (int j = 0; j < L; ++j)
-          if (bits[a][j >> 5] >> (j & 31) & 1u) alive[j] = 0;
+    sel = high;
+    float next = -INF;  // the next smaller confidence among the rows phase 2 starts with
+    if (und) {
+#pragma unroll
+      for (int w = 0; w < WORDS; ++w) {
+        if (32 * w >= L) break;
+        uint32_t m = 0;
+#pragma unroll 8
+        for (int j = 32 * w; j < 32 * w + 32; ++j) {
+          const bool a = s_und.has(j);
+          m |= (uint32_t)(a && before(j)) << (j & 31);
+          next = a && c[j] < ci ? fmaxf(next, c[j]) : next;
+        }
+        blk[w] &= m;
       }
+      if (next > -INF) margin = fminf(margin, ci - next);
     }
-    __syncthreads();
-  } else if (p.mode == 1) {
-    if (elig[i]) {
-      margin = fabsf(c[i] - p.tau_high);
-      sel[i] = c[i] >= p.tau_high;
+    // phase 2.  Every round decides at least the first undecided row of the order, so it ends after at most L of them.
+    while (true) {
+      if ((s_und.q[0] | s_und.q[1] | s_und.q[2] | s_und.q[3]) == 0) break;  // (uniform: read between two barriers)
+      bool take = und;
+#pragma unroll
+      for (int w = 0; w < WORDS; ++w) take = take && (blk[w] & s_und.w[w]) == 0;
+      publish(s_new, take);
+      __syncthreads();
+      if (take) { sel = true; und = false; }
+      if (und) {
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) und = und && (bits[i][w] & s_new.w[w]) == 0;
+      }
+      publish(s_und, und);
+      __syncthreads();
     }
-    __syncthreads();
   }
-  if (sel[i]) atomicAdd(&n_sel, 1);
+  publish(s_sel, sel);
   __syncthreads();
+  int n_sel = 0;
+#pragma unroll
+  for (int w = 0; w < RW; ++w) n_sel += __popcll(s_sel.q[w]);
   if (n_sel == 0 && top_row >= 0) {  // safeguard / top-1 rule: the most confident eligible row
-    margin = fminf(margin, top_gap);
-    if (i == top_row) sel[i] = 1;
+    if (second_row >= 0 && c[top_row] != c[second_row]) margin = fminf(margin, c[top_row] - c[second_row]);
+    if (i == top_row) sel = true;
   }
-  __syncthreads();
   if (act) {
-    sel_out[row0 + i] = sel[i];
-    if (apply && sel[i]) tokens[tok0 + i] = yh[i];
+    sel_out[row0 + i] = sel;
+    if (apply && sel) tokens[tok0 + i] = yh[i];
   }
-  float m = block_min(margin, fbuf);
+  margin = -wave_max(-margin);
+  if ((i & 63) == 0) fbuf[wave] = margin;
+  __syncthreads();
   if (i == 0) {
+    for (int w = 1; w < TPB / 64; ++w) margin = fminf(margin, fbuf[w]);
     nsel_out[b] = n_sel ? n_sel : (top_row >= 0 ? 1 : 0);
-    if (margin_out) margin_out[b] = m;
+    if (margin_out) margin_out[b] = margin;
   }
 }
 
@@ -148,7 +195,13 @@ template <typename T>
 void launch_select(const T* logits, int vocab, const float* lse, const float* conf, const int32_t* argmax, int32_t* tokens,
                         const SelectMeta& meta, int n_seqs, int mask_id, dlm_select_params p, int apply, uint8_t* sel,
                         int32_t* nsel, float* margin, hipStream_t st) {
-  select_kernel<T><<<n_seqs, TPB, 0, st>>>(logits, vocab, lse, conf, argmax, tokens, meta, mask_id, p, apply, sel, nsel, margin);
+  int longest = 0;
+  for (int b = 0; b < n_seqs; ++b) longest = meta.block_len[b] > longest ? meta.block_len[b] : longest;
+  // up to 32 rows: at most 1024 pairs, one trip of 256 threads; more threads would only make the barriers slower
+  if (longest <= 32 || p.mode != 0)
+    select_kernel<T, 256><<<n_seqs, 256, 0, st>>>(logits, vocab, lse, conf, argmax, tokens, meta, mask_id, p, apply, sel, nsel, margin);
+  else
+    select_kernel<T, 1024><<<n_seqs, 1024, 0, st>>>(logits, vocab, lse, conf, argmax, tokens, meta, mask_id, p, apply, sel, nsel, margin);
 }
 template void launch_select<float>(const float*, int, const float*, const float*, const int32_t*, int32_t*, const SelectMeta&, int,
                                         int, dlm_select_params, int, uint8_t*, int32_t*, float*, hipStream_t);

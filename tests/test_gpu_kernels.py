@@ -288,6 +288,34 @@ def test_select_parallel(device, dt, mode):
         assert fired["fallback"] > 0 and fired["dropped"] > 3, fired
 
 
+@pytest.mark.parametrize("L", [2, 31, 32, 33, 63, 64, 65, 255, 256])
+def test_select_parallel_chain_of_conflicts(device, L):
+    """Every row conflicts with its two neighbours and the confidences descend along the block: the greedy walk takes every other
+    row, each decision depending on the one before it - the longest chain of rounds the kernel can meet, at the row counts
+    where its bit words, wavefronts and workgroup sizes end."""
+    V, mask_id = 1024, 1023
+    z = torch.full((L, V), -10.0)
+    y = torch.arange(L)
+    z[y, y] = 30.0 - torch.arange(L) * 0.05
+    z[y[1:], y[:-1]] = 16.0
+    z[y[:-1], y[1:]] = 16.0
+    conf = (0.9 - torch.arange(L) * 0.001).to(torch.float32)
+    lse = torch.full((L,), 30.0)
+    z64 = z.double().numpy()
+    ref, margin = o_select.select_parallel(z64, lse.numpy(), conf.numpy(), y.numpy(), np.ones(L, dtype=bool), 0.5, 0.95, -30.0, 0)
+    assert ref.sum() == (L + 1) // 2 and margin > 1e-5
+    tok = torch.full((L,), mask_id, dtype=torch.int32, device=device)
+    sel = torch.zeros(L, dtype=torch.uint8, device=device)
+    nsel = torch.empty(1, dtype=torch.int32, device=device)
+    mg = torch.empty(1, dtype=torch.float32, device=device)
+    api.select_parallel(z.to(device), lse.to(device), conf.to(device), y.to(torch.int32).to(device), tok, [0], [0], [L], mask_id, 0.5, 0.95, -30.0, 0,
+                        sel, nsel, margin_out=mg)
+    torch.cuda.synchronize()
+    assert (sel.cpu().numpy().astype(bool) == ref).all() and int(nsel) == ref.sum()
+    assert abs(float(mg) - margin) <= 1e-6
+    assert (tok.cpu().numpy() == np.where(ref, y.numpy(), mask_id)).all()
+
+
 # ---- measurement helpers --------------------------------------------------------------------------
 def test_probes_report_plausible_rates(device):
     """The two probes bench.py quotes rooflines against: a plain streaming read reaches most of, and no more than, the
