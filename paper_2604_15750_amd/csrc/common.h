@@ -116,9 +116,7 @@ struct SelectMeta {
   int32_t block_len[DLM_MAX_SEQS];
 };
 struct RowTables {  // device arrays of one pass, [rows]
-  int32_t* row_seq;   // packed sequence index of the row
   int32_t* row_pos;   // absolute position
-  int32_t* row_tok;   // index of the row's token in the caller's token array
   int32_t* row_slot;  // KV-cache slot of the row's sequence
   float* rope_cos;    // [rows, hd/2]
   float* rope_sin;
@@ -225,25 +223,35 @@ int gemm_macro_splits(int M, int N, int K, int kind);
 int gemm_macro_stat_parts(int M, int N, int K);
 int gemm_macro_counters();
 void launch_gemm_macro(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);
-void launch_gemm_f32(const float* x, const float* w, float* y, int M, int N, int K, RowScale rs, hipStream_t st);
+// What the fp32 model's GEMM does with a finished output tile (gemm_f32.hip); the same kinds as GemmEpi, on row-major operands.
+struct GemmF32Epi {
+  RowScale rs;  // 1/rms of the GEMM's input rows (QKV, SWIGLU, DIRECT; ssq may be null)
+  // EPI_QKV: Q row-major, K (after the rotary embedding) and V to cache[slot][pos][n_kv * hd]
+  const int32_t *row_pos, *row_slot;
+  const float *rope_cos, *rope_sin;
+  float *q, *kcache, *vcache;
+  size_t slot_stride;
+  int n_q, n_kv, hd;
+  // EPI_SWIGLU
+  float* act;
+  int ffn;
+  // EPI_RESID: h += y; x = h * gain; ssq_out[m][gemm_f32_pairs(N, EPI_RESID)]
+  float* h;
+  const float* gain;
+  float *x, *ssq_out;
+  // EPI_DIRECT
+  float* out;
+};
+int gemm_f32_pairs(int N, int kind);
+void launch_gemm_f32(const float* x, const float* w, int M, int N, int K, int kind, const GemmF32Epi& e, hipStream_t st);
 
-void launch_prepare(const SeqMeta& meta, const StatsMeta& sm, RowTables t, int rows, int vocab, int head_dim, float theta, hipStream_t st);
-// RMSNorm in two halves: producers write x = h * gain and per-row sums of squares ssq [rows][norm_chunks(d)]; the consumer of the
-// following GEMM multiplies rsqrt(sum(ssq)/d + eps) back in (a per-row scalar commutes with the GEMM).
+// RMSNorm in two halves: producers write x = h * gain and per-row sums of squares (ssq; the embedding writes norm_chunks(d) chunks
+// per row); the consumer of the following GEMM multiplies rsqrt(sum(ssq)/d + eps) back in (a per-row scalar commutes with the GEMM).
 int norm_chunks(int d);
+// The first launch of a pass: row tables and rotary tables, h = embedding row, x = h * gain, ssq
 template <typename T>
-void launch_embed_norm(const T* embed, const int32_t* tokens, const RowTables& t, const float* gain, float* h, typename Act<T>::x_t* x, float* ssq, int rows,
-                       int d, int vocab, hipStream_t st);
-// h += sum_s part[s]; x = h * gain; ssq
-template <typename T>
-void launch_reduce_residual_norm(const float* part, int splits, float* h, const float* gain, T* x, float* ssq, int rows, int d, hipStream_t st);
-// act = silu(gate) * up from rinv * part [splits][rows][2*ffn]
-template <typename T>
-void launch_silu_mul(const float* part, int splits, const float* ssq, int d, float eps, T* act, int rows, int ffn, hipStream_t st);
-// rinv * part -> rotary embedding of Q and K; Q -> q [rows, n_q*hd] row-major; K, V -> cache[slot][pos]
-template <typename T>
-void launch_rope_kv(const float* part, int splits, const float* ssq, int d, float eps, const RowTables& t, const SeqMeta& meta, T* q,
-                    T* kcache, T* vcache, size_t slot_stride, size_t head_stride, int rows, int n_q, int n_kv, int hd, hipStream_t st);
+void launch_embed(const SeqMeta& meta, const StatsMeta& sm, const T* embed, const int32_t* tokens, const RowTables& t, const float* gain, float* h,
+                  typename Act<T>::x_t* x, float* ssq, int rows, int d, int vocab, int head_dim, float theta, hipStream_t st);
 // softmax(q k^T / sqrt(hd)) v over keys [0, n_keys) of the row's slot; q row-major, out in the activation layout [rows, n_q*hd]
 // (out_tiled) or row-major.  fp32 cache: row-major [pos][n_kv*hd] per slot (head_stride unused); bf16 cache: per (slot, kv head)
 // a region of head_stride elements in the fragment tiling below.

@@ -109,7 +109,7 @@ struct dlm_state {
   size_t layer_stride;  // elements per layer
   DevBuf kcache, vcache, prev_logits, prev_lse;
   DevBuf h, x, x2, act, q, part, stats_ws, ssq, counters;
-  DevBuf row_seq, row_pos, row_tok, row_slot, rope_cos, rope_sin, prev_row, save_row;
+  DevBuf row_pos, row_slot, rope_cos, rope_sin, prev_row, save_row;
   std::vector<int> kv_len, covered_end, prev_cur, prev_base, prev_count;  // covered_end: positions [0, covered_end) hold K and V of some pass
   size_t part_elems;
   bool fuse_stats = true;  // passes that qualify take their statistics from the LM head's epilogue (dlm_state_fuse_stats)
@@ -261,7 +261,7 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
   size_t pe = 0;
   const int shapes[4][3] = {{qkv, c.d_model, EPI_QKV}, {c.d_model, qd, EPI_RESID}, {2 * c.d_ffn, c.d_model, EPI_SWIGLU}, {c.d_model, c.d_ffn, EPI_RESID}};
   for (auto& sh : shapes) {
-    size_t e = c.dtype == DLM_BF16 ? 0 : (size_t)max_rows * sh[0];
+    size_t e = 0;
     if (c.dtype == DLM_BF16)
       for (int mt = 1; mt <= (max_rows + 15) / 16; ++mt) {  // the split count depends on the rows only through their 16-row tiles
         const int rows = mt * 16 < max_rows ? mt * 16 : max_rows, sp = gemm_bf16_splits(rows, sh[0], sh[1], sh[2]);
@@ -293,13 +293,13 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
     }
   }
   A(s->stats_ws, stats_bytes);
-  const int ssq_chunks = c.dtype == DLM_BF16 ? c.d_model / 16 : norm_chunks(c.d_model);
+  const int ssq_chunks = c.dtype == DLM_BF16 ? c.d_model / 16 : gemm_f32_pairs(c.d_model, EPI_RESID);  // (never fewer than the embedding's)
   A(s->ssq, (size_t)max_rows * ssq_chunks * 4);
   int n_counters = 1;
   if (c.dtype == DLM_BF16)
     for (auto& sh : shapes) { int k = gemm_bf16_counters(sh[0]); if (k > n_counters) n_counters = k; }
   A(s->counters, (size_t)n_counters * 4);
-  A(s->row_seq, (size_t)max_rows * 4); A(s->row_pos, (size_t)max_rows * 4); A(s->row_tok, (size_t)max_rows * 4); A(s->row_slot, (size_t)max_rows * 4);
+  A(s->row_pos, (size_t)max_rows * 4); A(s->row_slot, (size_t)max_rows * 4);
   A(s->rope_cos, (size_t)max_rows * (c.head_dim / 2) * 4); A(s->rope_sin, (size_t)max_rows * (c.head_dim / 2) * 4);
   A(s->prev_row, (size_t)max_rows * 8); A(s->save_row, (size_t)max_rows * 8);
   if (rc == DLM_OK) {
@@ -370,53 +370,66 @@ extern "C" int dlm_profile_read(dlm_state* s, int n, double* ms_out, int64_t* la
 // ---- dlm_step ------------------------------------------------------------------------------------
 namespace {
 
-// fp32 model: plain GEMMs with the row-wise glue in kernels of their own
+// fp32 model: the same five launches per layer on row-major fp32 operands
 int run_step_f32(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, const StatsMeta& sm, const AttnMeta& am, int rows, int max_seq_rows,
                  hipStream_t st) {
   typedef float T;
   const dlm_model* m = s->m;
   const dlm_config& c = m->cfg;
   const int dm = c.d_model, hd = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads, qd = nq * hd, ffn = c.d_ffn;
-  RowTables t{(int32_t*)s->row_seq.p, (int32_t*)s->row_pos.p, (int32_t*)s->row_tok.p, (int32_t*)s->row_slot.p, (float*)s->rope_cos.p, (float*)s->rope_sin.p,
-              (int64_t*)s->prev_row.p, (int64_t*)s->save_row.p};
+  RowTables t{(int32_t*)s->row_pos.p, (int32_t*)s->row_slot.p, (float*)s->rope_cos.p, (float*)s->rope_sin.p, (int64_t*)s->prev_row.p, (int64_t*)s->save_row.p};
   float* h = (float*)s->h.p;
   T *x = (T*)s->x.p, *x2 = (T*)s->x2.p, *act = (T*)s->act.p, *q = (T*)s->q.p;
-  float* part = (float*)s->part.p;
   float* ssq = (float*)s->ssq.p;
   Profile& pf = s->prof;
-  const RowScale none{nullptr, 0, 0.f, 0.f};
-  auto gemm = [&](int cls, const float* a, const void* w, int N, int K) {
+  GemmF32Epi base;
+  memset(&base, 0, sizeof base);
+  auto gemm = [&](int cls, int kind, const float* a, const void* w, int N, int K, const GemmF32Epi& e) {
     ProfScope ps(pf, st, cls);
-    launch_gemm_f32(a, (const float*)w, part, rows, N, K, none, st);
+    launch_gemm_f32(a, (const float*)w, rows, N, K, kind, e, st);
   };
   {
-    ProfScope ps(pf, st, PC_OTHER, 2);
-    launch_prepare(meta, sm, t, rows, c.vocab, hd, c.rope_theta, st);
-    launch_embed_norm<T>((const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, st);
+    ProfScope ps(pf, st, PC_OTHER);
+    launch_embed<T>(meta, sm, (const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, hd, c.rope_theta, st);
   }
+  int nch = norm_chunks(dm);  // chunks of the row sums of squares the next consumer reads: the embedding's, then those of EPI_RESID
+  auto scale = [&]() { return RowScale{ssq, nch, 1.f / (float)dm, c.rms_eps}; };
   for (int l = 0; l < c.n_layers; ++l) {
     T* kc = (T*)s->kcache.p + s->layer_stride * l;
     T* vc = (T*)s->vcache.p + s->layer_stride * l;
-    gemm(PC_QKV, x, m->wqkv[l].p, qd + 2 * nkv * hd, dm);
-    { ProfScope ps(pf, st, PC_OTHER);
-      launch_rope_kv<T>(part, 1, ssq, dm, c.rms_eps, t, meta, q, kc, vc, s->slot_stride, s->head_stride, rows, nq, nkv, hd, st); }
+    {
+      GemmF32Epi e = base;
+      e.rs = scale();
+      e.row_pos = t.row_pos; e.row_slot = t.row_slot; e.rope_cos = t.rope_cos; e.rope_sin = t.rope_sin;
+      e.q = q; e.kcache = kc; e.vcache = vc; e.slot_stride = s->slot_stride; e.n_q = nq; e.n_kv = nkv; e.hd = hd;
+      gemm(PC_QKV, EPI_QKV, x, m->wqkv[l].p, qd + 2 * nkv * hd, dm, e);
+    }
     { ProfScope ps(pf, st, PC_ATTENTION);
       launch_attention<T>(q, kc, vc, s->slot_stride, s->head_stride, am, x2, true, rows, max_seq_rows, nq, nkv, hd, st); }
-    gemm(PC_O, x2, m->wo[l].p, dm, qd);
-    { ProfScope ps(pf, st, PC_OTHER);
-      launch_reduce_residual_norm<T>(part, 1, h, (const float*)m->norm2[l].p, x, ssq, rows, dm, st); }
-    gemm(PC_GATE_UP, x, m->w_gate_up[l].p, 2 * ffn, dm);
-    { ProfScope ps(pf, st, PC_OTHER);
-      launch_silu_mul<T>(part, 1, ssq, dm, c.rms_eps, act, rows, ffn, st); }
-    gemm(PC_DOWN, act, m->w_down[l].p, dm, ffn);
-    { ProfScope ps(pf, st, PC_OTHER);
-      const float* g = l + 1 < c.n_layers ? (const float*)m->norm1[l + 1].p : (const float*)m->final_norm.p;
-      launch_reduce_residual_norm<T>(part, 1, h, g, x, ssq, rows, dm, st); }
+    {
+      GemmF32Epi e = base;
+      e.h = h; e.gain = (const float*)m->norm2[l].p; e.x = x; e.ssq_out = ssq;
+      gemm(PC_O, EPI_RESID, x2, m->wo[l].p, dm, qd, e);
+      nch = gemm_f32_pairs(dm, EPI_RESID);
+    }
+    {
+      GemmF32Epi e = base;
+      e.rs = scale();
+      e.act = act; e.ffn = ffn;
+      gemm(PC_GATE_UP, EPI_SWIGLU, x, m->w_gate_up[l].p, 2 * ffn, dm, e);
+    }
+    {
+      GemmF32Epi e = base;
+      e.h = h; e.gain = l + 1 < c.n_layers ? (const float*)m->norm1[l + 1].p : (const float*)m->final_norm.p;
+      e.x = x; e.ssq_out = ssq;
+      gemm(PC_DOWN, EPI_RESID, act, m->w_down[l].p, dm, ffn, e);
+    }
   }
   {
-    ProfScope ps(pf, st, PC_LM_HEAD);
-    const RowScale rs{ssq, norm_chunks(dm), 1.f / (float)dm, c.rms_eps};
-    launch_gemm_f32((const float*)x, (const float*)m->lm_head.p, (float*)d->logits, rows, c.vocab, dm, rs, st);
+    GemmF32Epi e = base;
+    e.rs = scale();
+    e.out = (float*)d->logits;
+    gemm(PC_LM_HEAD, EPI_DIRECT, x, m->lm_head.p, c.vocab, dm, e);
   }
   {
     ProfScope ps(pf, st, PC_STATS);
@@ -434,8 +447,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   const dlm_model* m = s->m;
   const dlm_config& c = m->cfg;
   const int dm = c.d_model, hd = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads, qd = nq * hd, ffn = c.d_ffn;
-  RowTables t{(int32_t*)s->row_seq.p, (int32_t*)s->row_pos.p, (int32_t*)s->row_tok.p, (int32_t*)s->row_slot.p, (float*)s->rope_cos.p, (float*)s->rope_sin.p,
-              (int64_t*)s->prev_row.p, (int64_t*)s->save_row.p};
+  RowTables t{(int32_t*)s->row_pos.p, (int32_t*)s->row_slot.p, (float*)s->rope_cos.p, (float*)s->rope_sin.p, (int64_t*)s->prev_row.p, (int64_t*)s->save_row.p};
   float* h = (float*)s->h.p;
   op_t *x = (op_t*)s->x.p, *x2 = (op_t*)s->x2.p, *act = (op_t*)s->act.p;  // GEMM inputs: IEEE half in fragment tiles (common.h)
   f16_t* q = (f16_t*)s->q.p;  // Q and the KV cache hold IEEE half (common.h)
@@ -459,9 +471,8 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
     launch_gemm_bf16(a, (const op_t*)w, rows, N, K, e, st);
   };
   {
-    ProfScope ps(pf, st, PC_OTHER, 2);
-    launch_prepare(meta, sm, t, rows, c.vocab, hd, c.rope_theta, st);
-    launch_embed_norm<T>((const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, st);
+    ProfScope ps(pf, st, PC_OTHER);
+    launch_embed<T>(meta, sm, (const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, hd, c.rope_theta, st);
   }
   // chunks of the row sums of squares the next consumer reads: the embedding's, then those of the GEMM that produced them
   int nch = norm_chunks(dm);
@@ -703,7 +714,13 @@ extern "C" int dlm_gemm_nt(const void* x, const void* w, void* y, int M, int N, 
   REQUIRE(dtype == DLM_F32 || dtype == DLM_BF16, DLM_EINVAL, "dlm_gemm_nt: dtype %d", dtype);
   REQUIRE(M >= 1 && N >= 1 && K >= 1, DLM_ESHAPE, "dlm_gemm_nt: non-positive dimension");
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == DLM_F32) { launch_gemm_f32((const float*)x, (const float*)w, (float*)y, M, N, K, RowScale{nullptr, 0, 0.f, 0.f}, st); return DLM_OK; }
+  if (dtype == DLM_F32) {
+    GemmF32Epi e;
+    memset(&e, 0, sizeof e);
+    e.out = (float*)y;
+    launch_gemm_f32((const float*)x, (const float*)w, M, N, K, EPI_DIRECT, e, st);
+    return DLM_OK;
+  }
   REQUIRE(N % 32 == 0 && K % 32 == 0, DLM_ESHAPE, "dlm_gemm_nt: bf16 needs N and K to be multiples of 32");
   const size_t mp = (size_t)(M + 15) / 16 * 16;
   const int n_counters = gemm_bf16_counters(N);
