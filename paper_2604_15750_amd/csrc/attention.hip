@@ -97,32 +97,33 @@ __global__ __launch_bounds__(256) void attention_kernel(const T* __restrict__ q,
 }
 
 // ---- bf16 models: on the matrix cores, half-precision operands (attention_core.h) -----------------------------
-// One workgroup per (16-query tile, head, sequence), or DS of them with a share of the head's output dims each.
-// per_unit = 0: grid (tiles * DS, heads, sequences).  per_unit > 0: a 1-D grid in which the per_unit workgroups that read the
+// One workgroup per (T 16-query tiles, head, sequence), or DS of them with a share of the head's output dims each; `groups` of T
+// tiles cover the longest span.
+// per_unit = 0: grid (groups * DS, heads, sequences).  per_unit > 0: a 1-D grid in which the per_unit workgroups that read the
 // same K and V (the query tiles, output-dim shares and query heads of one kv head of one sequence) have ids congruent mod 8:
 // they run on the same XCD, and all but the first reader find K and V in its L2 (the XCDs' L2s are separate: spread over
 // them, every tile of a block fetches its own copy from memory).
-template <int HD, int NWV, int DS>
-__global__ __launch_bounds__(NWV * 64) void attention_mfma_kernel(const f16_t* __restrict__ q, const f16_t* __restrict__ kcache,
+template <int HD, int NWV, int DS, int T>
+__global__ __launch_bounds__(NWV * 64, T > 1 ? 2 : 1) void attention_mfma_kernel(const f16_t* __restrict__ q, const f16_t* __restrict__ kcache,
                                                                   const f16_t* __restrict__ vcache, size_t slot_stride, size_t head_stride,
                                                                   AttnMeta meta, op_t* __restrict__ out_tiles, bf16_t* __restrict__ out_rows, int n_q, int n_kv,
-                                                                  int per_unit, int tiles) {
+                                                                  int per_unit, int groups) {
   __shared__ AttnLds<HD, NWV, DS> L;
   int b = blockIdx.z, head = blockIdx.y, x = blockIdx.x;
   if (per_unit > 0) {
     const int j = blockIdx.x >> 3, w = j % per_unit, unit = (j / per_unit) * 8 + (blockIdx.x & 7);
     if (unit >= n_kv * meta.n_seqs) return;
     b = unit / n_kv;
-    head = (unit - b * n_kv) * (n_q / n_kv) + w / (tiles * DS);
-    x = w % (tiles * DS);
+    head = (unit - b * n_kv) * (n_q / n_kv) + w / (groups * DS);
+    x = w % (groups * DS);
   }
-  const int tile = x / DS, dpart = x - tile * DS;
-  const int row0 = meta.row_off[b] + tile * 16;
+  const int group = x / DS, dpart = x - group * DS;
+  const int row0 = meta.row_off[b] + group * 16 * T;
   const int row_end = meta.row_off[b + 1];
   if (row0 >= row_end) return;
   const int kvh = head / (n_q / n_kv);
   const size_t region = (size_t)meta.slot[b] * slot_stride + (size_t)kvh * head_stride;
-  attention_tile<HD, NWV, DS>(q, kcache + region, vcache + region, row0, row_end, meta.n_keys[b], head, n_q, out_tiles, out_rows, L, dpart);
+  attention_tiles<HD, NWV, DS, T>(q, kcache + region, vcache + region, row0, min(row_end, row0 + 16 * T), meta.n_keys[b], head, n_q, out_tiles, out_rows, L, dpart);
 }
 
 // K [T, n_kv, hd] and V row-major bf16 -> the tiled half-precision cache layout of one slot (test helper for dlm_attention)
@@ -165,15 +166,25 @@ void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcac
   // enough (kv head, sequence) units to keep every XCD busy (four each): the workgroups of a unit share an XCD (see the kernel)
   const int units = n_kv * meta.n_seqs;
   const bool by_unit = units >= 32;
-#define GO(HD, NWV, DS)                                                                                                                          \
+#define GO(HD, NWV, DS, T)                                                                                                                       \
   do {                                                                                                                                           \
-    const int per_unit = by_unit ? tiles * DS * (n_q / n_kv) : 0;                                                                                \
-    const dim3 grid = by_unit ? dim3((units + 7) / 8 * 8 * per_unit) : dim3(tiles * DS, n_q, meta.n_seqs);                                       \
-    attention_mfma_kernel<HD, NWV, DS><<<grid, NWV * 64, 0, st>>>(q, kcache, vcache, slot_stride, head_stride, meta, out_tiles, out_rows, n_q,   \
-                                                                  n_kv, per_unit, tiles);                                                        \
+    const int groups = (tiles + T - 1) / T, per_unit = by_unit ? groups * DS * (n_q / n_kv) : 0;                                                 \
+    const dim3 grid = by_unit ? dim3((units + 7) / 8 * 8 * per_unit) : dim3(groups * DS, n_q, meta.n_seqs);                                      \
+    attention_mfma_kernel<HD, NWV, DS, T><<<grid, NWV * 64, 0, st>>>(q, kcache, vcache, slot_stride, head_stride, meta, out_tiles, out_rows, n_q, \
+                                                                     n_kv, per_unit, groups);                                                    \
   } while (0)
-  if (hd == 32) { if (wide) GO(32, 4, 1); else GO(32, 8, 1); }
-  else if (hd == 64) { if (narrow) GO(64, 8, 2); else if (wide) GO(64, 4, 1); else GO(64, 8, 1); }
-  else { if (narrow) GO(128, 8, 4); else if (wide) GO(128, 4, 1); else GO(128, 8, 1); }
+  // Query tiles per workgroup.  A wide pass takes two wherever a span has two (the K and V traffic is what bounds it); a narrow one
+  // the fewest that leave at most one workgroup per compute unit (8B shape, 24 rows x 856 keys, one tile / two: 7.7 / 9.7 us;
+  // 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that).
+  const bool pair = wide ? tiles > 1 : (size_t)tiles * n_q * meta.n_seqs * 4 > 256;
+#define BY_TILES(HD, NWV, DS)              \
+  do {                                     \
+    if (pair) GO(HD, NWV, DS, 2);          \
+    else GO(HD, NWV, DS, 1);               \
+  } while (0)
+  if (hd == 32) { if (wide) BY_TILES(32, 4, 1); else GO(32, 8, 1, 1); }
+  else if (hd == 64) { if (narrow) GO(64, 8, 2, 1); else if (wide) BY_TILES(64, 4, 1); else GO(64, 8, 1, 1); }
+  else { if (narrow) BY_TILES(128, 8, 4); else if (wide) BY_TILES(128, 4, 1); else GO(128, 8, 1, 1); }
+#undef BY_TILES
 #undef GO
 }

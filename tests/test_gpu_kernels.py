@@ -140,6 +140,24 @@ def test_attention(device, dt, A, T, nq, nkv, hd):
     assert (np.abs(got - ref) <= tol * np.maximum(np.abs(ref).max(-1, keepdims=True), 0.1)).all(), np.abs(got - ref).max()
 
 
+# Two query tiles per workgroup: narrow (split output dims) and wide, each head dim, an odd number of tiles (a workgroup whose second
+# tile does not exist), a last tile with one row, key counts at the ends of a 32-key block and fewer blocks than wavefronts.
+@pytest.mark.parametrize("A,T,nq,nkv,hd", [(49, 33, 28, 4, 128), (64, 31, 28, 4, 128), (33, 64, 30, 30, 128), (520, 97, 16, 4, 128), (513, 32, 16, 16, 128),
+                                           (520, 65, 16, 8, 64), (529, 95, 16, 16, 32), (515, 1, 16, 2, 64)])
+def test_attention_pairs_of_query_tiles(device, A, T, nq, nkv, hd):
+    g = torch.Generator(device="cpu").manual_seed(A + T + nq)
+    q = (torch.randn(A, nq, hd, generator=g) * 1.5).to(torch.bfloat16)
+    k = (torch.randn(T, nkv, hd, generator=g) * 1.5).to(torch.bfloat16)
+    v = torch.randn(T, nkv, hd, generator=g).to(torch.bfloat16)
+    out = api.dlm_attention(q.to(device), k.to(device), v.to(device))
+    torch.cuda.synchronize()
+    ref = o_fwd.attention(_np(q), _np(k), _np(v))
+    got = o_fwd.widen(_np(out))
+    # the output rounded to bf16 (2^-9), the probabilities to half (2^-12 each, weighted by them) and fp32 sums
+    bound = 2.0 ** -8 * np.abs(ref) + 2.0 ** -11 * float(v.abs().max())
+    assert (np.abs(got - ref) <= bound).all(), (np.abs(got - ref) / bound).max()
+
+
 # ---- vocabulary statistics -------------------------------------------------------------------------
 def _check_stats(got, ref, z64, zp64, mask_id):
     for key in ("max_logit", "lse", "entropy", "conf"):
