@@ -8,7 +8,6 @@
 
 namespace {
 
-constexpr int TPB = 256;
 template <typename T> struct Vec;
 template <> struct Vec<bf16_t> { static constexpr int N = 8; typedef bf16x8 type; };
 template <> struct Vec<float> { static constexpr int N = 4; typedef f32x4 type; };
@@ -122,13 +121,13 @@ __device__ inline void finalize(const Part& p, int row, bool has_prev, float pre
 // l-th vector of every stride).  Whole trips of U vectors (16 bytes each) per lane are loaded together and absorbed one after
 // the other without a bounds or mask test; the trip that holds the mask token and the ragged last one take the path with
 // per-element validity.  Loop bounds are uniform in the workgroup: the absorb steps exchange values between lanes.
-template <typename T, bool VECTOR, bool KL, bool PREV_SUMS>
+template <typename T, int TPB, bool VECTOR, bool KL, bool PREV_SUMS>
 __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const T* __restrict__ p_row, T* __restrict__ s_row, int lo,
                                     int hi, int mask_id) {
   constexpr int N = Vec<T>::N;
   typedef typename Vec<T>::type V;
   if (VECTOR) {
-    constexpr int U = 4, STRIDE = TPB * N, TRIP = U * STRIDE;
+    constexpr int U = TPB > 256 ? 2 : 4, STRIDE = TPB * N, TRIP = U * STRIDE;
     const int base = lo + threadIdx.x * N;
     const int nfull = (hi - lo) / TRIP;
     for (int t = 0; t * TRIP < hi - lo; ++t) {
@@ -179,11 +178,9 @@ __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const
   }
 }
 
-template <typename T, bool VECTOR>
+template <typename T, int TPB, bool VECTOR>
 __global__ __launch_bounds__(TPB) void vocab_stats_kernel(const T* __restrict__ logits, int rows, int vocab, int mask_id, int chunk,
                                                           int nchunks, StatsRows sr, StatsOut o, Part* __restrict__ parts) {
-  constexpr int N = Vec<T>::N;
-  typedef typename Vec<T>::type V;
   __shared__ Part sh[TPB / 64];
   for (int item = blockIdx.x; item < rows * nchunks; item += gridDim.x) {
   const int row = item / nchunks, c = item - row * nchunks;
@@ -197,9 +194,9 @@ __global__ __launch_bounds__(TPB) void vocab_stats_kernel(const T* __restrict__ 
   const int lo = c * chunk, hi = min(vocab, lo + chunk);
 
   Run run = run_init();
-  if (!kl) stream_chunk<T, VECTOR, false, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
-  else if (!prev_sums) stream_chunk<T, VECTOR, true, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
-  else stream_chunk<T, VECTOR, true, true>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  if (!kl) stream_chunk<T, TPB, VECTOR, false, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  else if (!prev_sums) stream_chunk<T, TPB, VECTOR, true, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  else stream_chunk<T, TPB, VECTOR, true, true>(run, z_row, p_row, s_row, lo, hi, mask_id);
   const Part p = run_finish(run);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = p;
   __syncthreads();
@@ -241,15 +238,27 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
 }
 
 constexpr int MAX_CHUNKS = 32;
+constexpr int ROW_MIN = 96, ROW_MAX = 256;  // rows that get a workgroup of 1024 threads each (launch_vocab_stats)
 
-// Chunks per row: a work item is a whole row when the rows alone fill the chip (the per-item reduction across lanes is not free),
-// otherwise rows are cut so that there are about 1536 items, each at least two vectors per lane.
+// Chunks per row: about 1536 work items, each at least two vectors per lane.
 int pick_chunks(int rows, int vocab, int vec) {
   int want = (1536 + rows - 1) / rows;
-  int maxc = (vocab + TPB * vec * 2 - 1) / (TPB * vec * 2);
+  int maxc = (vocab + 256 * vec * 2 - 1) / (256 * vec * 2);
   int c = want < maxc ? want : maxc;
   if (c > MAX_CHUNKS) c = MAX_CHUNKS;
   return c < 1 ? 1 : c;
+}
+
+template <typename T, int TPB>
+void launch_items(const T* logits, int rows, int vocab, int mask_id, int nch, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
+  constexpr int N = Vec<T>::N;
+  int chunk = (vocab + nch - 1) / nch;
+  chunk = (chunk + TPB * N - 1) / (TPB * N) * (TPB * N);
+  nch = (vocab + chunk - 1) / chunk;
+  const int items = rows * nch;  // the hardware dispatcher balances better than a resident grid walking the items
+  if (vocab % N == 0) vocab_stats_kernel<T, TPB, true><<<items, TPB, 0, st>>>(logits, rows, vocab, mask_id, chunk, nch, sr, o, (Part*)workspace);
+  else vocab_stats_kernel<T, TPB, false><<<items, TPB, 0, st>>>(logits, rows, vocab, mask_id, chunk, nch, sr, o, (Part*)workspace);
+  if (nch > 1) vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)workspace, rows, nch, vocab, sr, o);
 }
 
 }  // namespace
@@ -260,19 +269,18 @@ void launch_stats_merge(const void* parts, int rows, int nparts, int vocab, cons
   vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)parts, rows, nparts, vocab, sr, o);
 }
 
+// How a row is cut.  The reduction is bound by its reads; what the cut decides is how evenly they lie on the chip and whether a
+// second launch has to merge.  Chunks for about 1536 workgroups of 256 threads, merged by a second kernel (4 us at 384 rows), are
+// the general form.  With a row for most of the 256 compute units and no second round, one workgroup of 1024 threads takes a whole
+// row and writes its results itself.  A vocabulary of 126464, microseconds per call, chunks -> whole rows:
+//   bf16 with a previous row  96 rows 21.0 -> 20.9, 192: 23.1 -> 21.9, 256: 29.3 -> 25.7, but 272: 31.4 -> 42.9 (a second round
+//   of workgroups, as two of 1024 threads don't fit into a unit's registers); without: 256: 22.7 -> 18.8, 272: 23.4 -> 31.9;
+//   fp32 with a previous row 128: 26.7 -> 24.3, 256: 50.6 -> 47.8, 272: 54.8 -> 69.1.
+// Below 96 rows more than half of the units would be idle, and neither is faster (fp32, 64 rows: 19.9 -> 20.5): chunks.
 template <typename T>
 void launch_vocab_stats(const T* logits, int rows, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
-  constexpr int N = Vec<T>::N;
-  const bool vec = vocab % N == 0;
-  int nch = pick_chunks(rows, vocab, N);
-  int chunk = (vocab + nch - 1) / nch;
-  chunk = (chunk + TPB * N - 1) / (TPB * N) * (TPB * N);
-  nch = (vocab + chunk - 1) / chunk;
-  const int items = rows * nch;
-  const int grid = items;  // the hardware dispatcher balances better than a resident grid walking the items
-  if (vec) vocab_stats_kernel<T, true><<<grid, TPB, 0, st>>>(logits, rows, vocab, mask_id, chunk, nch, sr, o, (Part*)workspace);
-  else vocab_stats_kernel<T, false><<<grid, TPB, 0, st>>>(logits, rows, vocab, mask_id, chunk, nch, sr, o, (Part*)workspace);
-  if (nch > 1) vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)workspace, rows, nch, vocab, sr, o);
+  if (rows >= ROW_MIN && rows <= ROW_MAX) launch_items<T, 1024>(logits, rows, vocab, mask_id, 1, sr, o, workspace, st);
+  else launch_items<T, 256>(logits, rows, vocab, mask_id, pick_chunks(rows, vocab, Vec<T>::N), sr, o, workspace, st);
 }
 
 template void launch_vocab_stats<float>(const float*, int, int, int, const StatsRows&, const StatsOut&, void*, hipStream_t);

@@ -204,6 +204,23 @@ def test_vocab_stats(device, dt, rows, V, mask_id, with_prev):
         _check_stats(got2, ref, z64, zp64, mask_id)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,V", [(95, 16640), (96, 16640), (97, 8199), (256, 32776), (257, 32776)])
+def test_vocab_stats_whole_rows(device, dt, rows, V):
+    """The edges of the row counts at which one workgroup takes a whole row; vocabularies with whole trips, a ragged end, and no
+    16-byte vectors; the mask token in the first, a middle and the last trip.  Tolerances as test_vocab_stats derives them."""
+    tdt = torch.float32 if dt == "f32" else torch.bfloat16
+    z = torch.from_numpy(inputs.peaked_logits(rows, V, rows + V, [(rows - 1, V - 2, 30.0)])).to(tdt)
+    zp = (z.float() + 0.5 * torch.from_numpy(inputs.peaked_logits(rows, V, 99 + rows))).to(tdt)
+    for mask_id, prev in ((0, zp), (V // 2, None), (V - 1, zp)):
+        zm = z.clone()
+        zm[:, mask_id] = 50.0
+        got = api.dlm_vocab_stats(zm.to(device), mask_id, None if prev is None else prev.to(device))
+        torch.cuda.synchronize()
+        z64, zp64 = o_fwd.widen(_np(zm)), None if prev is None else o_fwd.widen(_np(prev))
+        _check_stats(got, o_stats.vocab_stats(z64, mask_id, zp64), z64, zp64, mask_id)
+
+
 # ---- block_boundary ----------------------------------------------------------------------------------
 @pytest.mark.parametrize("norm_mode", [0, 1, 2, 3])
 @pytest.mark.parametrize("rule", [0, 1])
