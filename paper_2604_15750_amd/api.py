@@ -7,6 +7,7 @@ fallback path.
 """
 import ctypes as C
 import os
+import struct
 
 import torch  # loaded first so that libdlm binds to the HIP runtime torch already opened
 
@@ -78,16 +79,17 @@ def lib():
         L.dlm_state_reset.argtypes = [C.c_void_p, C.c_int]
         L.dlm_state_kv_len.argtypes = [C.c_void_p, C.c_int]
         L.dlm_step.argtypes = [C.c_void_p, C.POINTER(dlm_step_desc), C.c_void_p]
-        L.block_boundary.argtypes = [C.c_void_p, C.c_void_p, _I32P, _I32P, _I32P, C.c_int, C.POINTER(dlm_boundary_params), C.c_void_p,
-                                     C.c_void_p, C.c_void_p, C.c_void_p]
-        L.select_parallel.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, _I32P, _I32P, _I32P,
-                                      C.c_int, C.c_int, C.POINTER(dlm_select_params), C.c_int, C.c_void_p, C.c_void_p, C.c_void_p,
-                                      C.c_void_p]
+        # (the host arrays of the two decisions are void pointers: _packed hands them over as bytes)
+        L.block_boundary.argtypes = [C.c_void_p] * 5 + [C.c_int, C.POINTER(dlm_boundary_params)] + [C.c_void_p] * 4
+        L.select_parallel.argtypes = [C.c_void_p, C.c_int, C.c_int] + [C.c_void_p] * 7 + \
+                                     [C.c_int, C.c_int, C.POINTER(dlm_select_params), C.c_int] + [C.c_void_p] * 4
         L.dlm_vocab_stats.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int] + [C.c_void_p] * 7 + \
                                      [C.c_size_t, C.c_void_p]
         L.dlm_vocab_stats_static.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int] + [C.c_void_p] * 7
         L.dlm_gemm_nt.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]
         L.dlm_attention.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p] + [C.c_int] * 6 + [C.c_void_p]
+        L.dlm_probe_hbm_read.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.POINTER(C.c_double), C.c_void_p]
+        L.dlm_probe_mfma.argtypes = [C.c_int, C.POINTER(C.c_double), C.c_void_p]
         L.dlm_state_fuse_stats.argtypes = [C.c_void_p, C.c_int]
         L.dlm_profile_enable.argtypes = [C.c_void_p, C.c_uint]
         L.dlm_profile_read.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int]
@@ -102,15 +104,26 @@ def _check(rc):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _ints(v):
     return None if v is None else (C.c_int32 * len(v))(*[int(x) for x in v])
 
 
+def _packed(v):
+    """A host array as bytes (the two decisions are bound by what their calls cost the host: a ctypes array of 16 takes 2.1 us,
+    this 0.4).  What struct does not take as a 32-bit integer goes the way of _ints."""
+    if v is None:
+        return None
+    try:
+        return struct.pack(f"{len(v)}i", *v)
+    except (struct.error, TypeError, OverflowError):
+        return bytes(_ints(v))
+
+
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())  # (torch.cuda.current_stream() without its Stream object)
 
 
 def dtype_code(t):
@@ -223,7 +236,7 @@ def dlm_step(state, tokens, out, row_offsets, span_start, commit_len, tok_start,
 def block_boundary(I, H, win_start, win_len, L_out, lam, l_min, smooth_radius=1, norm_mode=0, rule=0, cold=None, S_out=None,
                    margin_out=None):
     p = dlm_boundary_params(lam, l_min, smooth_radius, norm_mode, rule)
-    _check(lib().block_boundary(_ptr(I), _ptr(H), _ints(win_start), _ints(win_len), _ints(cold), len(win_start), C.byref(p), _ptr(L_out),
+    _check(lib().block_boundary(_ptr(I), _ptr(H), _packed(win_start), _packed(win_len), _packed(cold), len(win_start), C.byref(p), _ptr(L_out),
                                 _ptr(S_out), _ptr(margin_out), _stream()))
 
 
@@ -231,7 +244,7 @@ def select_parallel(logits, lse, conf, argmax, tokens, row_start, tok_start, blo
                     selected_out, n_selected_out, apply_tokens=True, margin_out=None):
     p = dlm_select_params(tau_low, tau_high, gamma, mode)
     _check(lib().select_parallel(_ptr(logits), logits.shape[-1], dtype_code(logits), _ptr(lse), _ptr(conf), _ptr(argmax), _ptr(tokens),
-                                 _ints(row_start), _ints(tok_start), _ints(block_len), len(row_start), mask_id, C.byref(p),
+                                 _packed(row_start), _packed(tok_start), _packed(block_len), len(row_start), mask_id, C.byref(p),
                                  int(apply_tokens), _ptr(selected_out), _ptr(n_selected_out), _ptr(margin_out), _stream()))
 
 

@@ -4,7 +4,9 @@ import ctypes as C
 import os
 import re
 
+import numpy as np
 import pytest
+import torch
 
 from paper_2604_15750_amd import api
 
@@ -117,3 +119,11 @@ def test_committed_traffic_summary_feeds_the_bench_line():
     t = bench.traffic_from_profile("llada8b_p256_g256")
     algorithmic = 2 * 24576 * 4096  # the gate/up weights of the 8B shape, bf16
     assert t is not None and 0.98 * algorithmic < t < 1.10 * algorithmic
+
+
+@pytest.mark.parametrize("v", [[], [7], (0, -1, 2**31 - 1), list(range(64)), np.arange(5), np.arange(3, dtype=np.int16), torch.arange(4), [3.7, 2],
+                               [True, False], [2**31 + 5, 2**40 + 1], np.array([1.5, 2.5]), torch.tensor([1.5, 2.0])])
+def test_packed_host_arrays(v):
+    """The bytes handed to the two decisions are those of a ctypes int32 array, for whatever that accepts; None stays None."""
+    assert api._packed(v) == bytes(api._ints(v))
+    assert api._packed(None) is None
