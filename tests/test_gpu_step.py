@@ -161,6 +161,17 @@ def test_tiny_f32_replay(device, name):
     print(name, "worst relative logit error", r["worst"], "passes", r["passes"])
 
 
+@pytest.mark.parametrize("dims,P,N,l_max", [((2, 52, 3, 1, 32, 36, 77), 5, 24, 8), ((1, 132, 2, 2, 64, 20, 130), 15, 24, 8),
+                                            ((2, 20, 2, 1, 128, 68, 50), 31, 64, 32)])
+def test_ragged_f32_model_replay(device, dims, P, N, l_max):
+    """Model dimensions that are multiples of 4 only (no whole 16-column tiles or 16-k steps, fewer steps than wavefronts), each head
+    size, and passes of up to 16, up to 32 and more rows; the fp32 model's tolerance."""
+    cfg = inputs.model_config(*dims, "f32")
+    prompt = inputs.make_prompts(cfg, 1, P)[0]
+    r = replay(cfg, _weights(cfg, 3, device), prompt, N, dict(inputs.PAPER_PARAMS, l_min=4, l_max=l_max), device, logit_tol=2e-4, max_passes=12)
+    assert r["passes"] >= 6 and max(len(t["tokens"]) for t in r["trace"] if t["op"] == "pass") > 16
+
+
 MID = inputs.model_config(2, 512, 4, 2, 128, 1536, 4096, "bf16")
 
 
