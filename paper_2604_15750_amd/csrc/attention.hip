@@ -1,6 +1,6 @@
 // Block-vs-prefix attention: every row of a sequence's span attends, without causal mask, to keys
 // [0, n_keys) of the sequence's KV-cache slot (cached prefix + the span's own rows, which the
-// rotary/KV kernel has already written there).  Grouped-query heads share K/V.
+// QKV GEMM's epilogue has already written there).  Grouped-query heads share K/V.
 //
 // fp32 model (head_dim 32/64/128, row-major cache [pos][n_kv*hd]): one workgroup per (16-query
 // tile, head, sequence); keys are streamed in tiles through LDS with an online softmax in fp32.
