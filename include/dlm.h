@@ -272,6 +272,15 @@ int dlm_state_fuse_stats(dlm_state* s, int enable);
 int dlm_profile_enable(dlm_state* s, unsigned class_mask);
 int dlm_profile_read(dlm_state* s, int n, double* ms_out, int64_t* launches_out, int reset);
 
+/* ---- what the launch rules choose for a shape ---------------------------------------------------
+ * Host arithmetic only (no GPU call): for tests that have to reach one variant of a kernel, and for tuning.
+ *
+ * dlm_plan_attention: a bf16 model's attention over n_seqs spans of which the longest has max_seq_rows
+ * rows.  plan[0] wavefronts of a workgroup, plan[1] workgroups that share a head's output dims, plan[2]
+ * 16-query tiles of a workgroup.
+ * Errors: DLM_EINVAL (null), DLM_ESHAPE (a size that is not positive, head_dim not in {32, 64, 128}). */
+int dlm_plan_attention(int max_seq_rows, int n_seqs, int n_q, int head_dim, int32_t plan[3]);
+
 #ifdef __cplusplus
 }
 #endif

@@ -57,7 +57,7 @@ class dlm_select_params(C.Structure):
 EXPORTS = ["dlm_last_error", "dlm_model_create", "dlm_model_destroy", "dlm_state_create", "dlm_state_destroy", "dlm_state_reset",
            "dlm_state_kv_len", "dlm_step", "block_boundary", "select_parallel", "dlm_vocab_stats_workspace", "dlm_vocab_stats",
            "dlm_gemm_nt", "dlm_attention", "dlm_profile_enable", "dlm_profile_read", "dlm_probe_hbm_read", "dlm_probe_mfma",
-           "dlm_state_fuse_stats", "dlm_vocab_stats_static"]
+           "dlm_state_fuse_stats", "dlm_vocab_stats_static", "dlm_plan_attention"]
 
 
 def lib():
@@ -90,6 +90,7 @@ def lib():
         L.dlm_attention.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p] + [C.c_int] * 6 + [C.c_void_p]
         L.dlm_probe_hbm_read.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.POINTER(C.c_double), C.c_void_p]
         L.dlm_probe_mfma.argtypes = [C.c_int, C.POINTER(C.c_double), C.c_void_p]
+        L.dlm_plan_attention.argtypes = [C.c_int] * 4 + [_I32P]
         L.dlm_state_fuse_stats.argtypes = [C.c_void_p, C.c_int]
         L.dlm_profile_enable.argtypes = [C.c_void_p, C.c_uint]
         L.dlm_profile_read.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int]
@@ -303,3 +304,11 @@ def dlm_attention(q, k, v):
     out = torch.empty_like(q)
     _check(lib().dlm_attention(_ptr(q), _ptr(k), _ptr(v), _ptr(out), A, T, n_q, n_kv, hd, dtype_code(q), _stream()))
     return out
+
+
+def plan_attention(max_seq_rows, n_seqs, n_q, head_dim):
+    """How the attention of such a pass is launched (include/dlm.h): wavefronts of a workgroup, workgroups that share a head's
+    output dims, 16-query tiles of a workgroup."""
+    out = (C.c_int32 * 3)()
+    _check(lib().dlm_plan_attention(max_seq_rows, n_seqs, n_q, head_dim, out))
+    return dict(zip(("waves", "shares", "tiles"), out))

@@ -156,35 +156,41 @@ void launch_attention<float>(const float* q, const float* kcache, const float* v
   else attention_kernel<float, 128><<<grid, 256, 0, st>>>(q, kcache, vcache, slot_stride, meta, out, out_tiled, n_q, n_kv);
 }
 
+// How a pass is laid out.  A narrow one (few query tiles x heads): eight wavefronts per workgroup to shorten each wavefront's chain
+// of dependent loads, and the output dims of a head split over four workgroups (two for 64 dims) to spread its K / V traffic.  A
+// wide one has enough workgroups to fill the chip with four wavefronts each.
+// Query tiles per workgroup, where a span has more than one: a wide pass takes two (the K and V traffic is what bounds it); a narrow
+// one the fewest that leave at most one workgroup per compute unit (8B shape, 24 rows x 856 keys, one tile / two: 7.7 / 9.7 us;
+// 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that).  Spans of one tile gain nothing from a second
+// that no row fills (28 heads, 3 sequences of 16 rows x 1516 keys, two tiles / one: 25.7 / 22.2).
+AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_q, int hd) {
+  const int tiles = (max_seq_rows + 15) / 16;
+  const size_t units = (size_t)tiles * n_q * n_seqs;
+  if (units < 128 && hd >= 64) return AttnPlan{8, hd == 128 ? 4 : 2, hd == 128 && tiles > 1 && units * 4 > 256 ? 2 : 1};
+  if (units >= 512) return AttnPlan{4, 1, tiles > 1 ? 2 : 1};
+  return AttnPlan{8, 1, 1};
+}
+
 void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,
                           op_t* out_tiles, bf16_t* out_rows, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st) {
   const int tiles = (max_seq_rows + 15) / 16;
-  // a narrow pass (few query tiles x heads): eight wavefronts per workgroup to shorten each wavefront's chain of dependent
-  // loads, and the output dims of a head split over four workgroups (two for 64 dims) to spread its K / V traffic
-  const bool narrow = (size_t)tiles * n_q * meta.n_seqs < 128 && hd >= 64;
-  const bool wide = (size_t)tiles * n_q * meta.n_seqs >= 512;  // enough workgroups to fill the chip with 4 wavefronts each
+  const AttnPlan p = attention_plan(max_seq_rows, meta.n_seqs, n_q, hd);
   // enough (kv head, sequence) units to keep every XCD busy (four each): the workgroups of a unit share an XCD (see the kernel)
   const int units = n_kv * meta.n_seqs;
   const bool by_unit = units >= 32;
+  const int groups = (tiles + p.tiles - 1) / p.tiles, per_unit = by_unit ? groups * p.shares * (n_q / n_kv) : 0;
+  const dim3 grid = by_unit ? dim3((units + 7) / 8 * 8 * per_unit) : dim3(groups * p.shares, n_q, meta.n_seqs);
 #define GO(HD, NWV, DS, T)                                                                                                                       \
-  do {                                                                                                                                           \
-    const int groups = (tiles + T - 1) / T, per_unit = by_unit ? groups * DS * (n_q / n_kv) : 0;                                                 \
-    const dim3 grid = by_unit ? dim3((units + 7) / 8 * 8 * per_unit) : dim3(groups * DS, n_q, meta.n_seqs);                                      \
-    attention_mfma_kernel<HD, NWV, DS, T><<<grid, NWV * 64, 0, st>>>(q, kcache, vcache, slot_stride, head_stride, meta, out_tiles, out_rows, n_q, \
-                                                                     n_kv, per_unit, groups);                                                    \
-  } while (0)
-  // Query tiles per workgroup.  A wide pass takes two wherever a span has two (the K and V traffic is what bounds it); a narrow one
-  // the fewest that leave at most one workgroup per compute unit (8B shape, 24 rows x 856 keys, one tile / two: 7.7 / 9.7 us;
-  // 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that).
-  const bool pair = wide ? tiles > 1 : (size_t)tiles * n_q * meta.n_seqs * 4 > 256;
+  attention_mfma_kernel<HD, NWV, DS, T><<<grid, NWV * 64, 0, st>>>(q, kcache, vcache, slot_stride, head_stride, meta, out_tiles, out_rows, n_q,   \
+                                                                   n_kv, per_unit, groups)
 #define BY_TILES(HD, NWV, DS)              \
   do {                                     \
-    if (pair) GO(HD, NWV, DS, 2);          \
+    if (p.tiles == 2) GO(HD, NWV, DS, 2);  \
     else GO(HD, NWV, DS, 1);               \
   } while (0)
-  if (hd == 32) { if (wide) BY_TILES(32, 4, 1); else GO(32, 8, 1, 1); }
-  else if (hd == 64) { if (narrow) GO(64, 8, 2, 1); else if (wide) BY_TILES(64, 4, 1); else GO(64, 8, 1, 1); }
-  else { if (narrow) BY_TILES(128, 8, 4); else if (wide) BY_TILES(128, 4, 1); else GO(128, 8, 1, 1); }
+  if (hd == 32) { if (p.waves == 4) BY_TILES(32, 4, 1); else GO(32, 8, 1, 1); }
+  else if (hd == 64) { if (p.shares > 1) GO(64, 8, 2, 1); else if (p.waves == 4) BY_TILES(64, 4, 1); else GO(64, 8, 1, 1); }
+  else { if (p.shares > 1) BY_TILES(128, 8, 4); else if (p.waves == 4) BY_TILES(128, 4, 1); else GO(128, 8, 1, 1); }
 #undef BY_TILES
 #undef GO
 }

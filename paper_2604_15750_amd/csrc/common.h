@@ -260,6 +260,10 @@ void launch_attention(const T* q, const T* kcache, const T* vcache, size_t slot_
                       bool out_tiled, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st);
 // bf16 models: q and the KV cache hold IEEE half; the output goes to out_tiles (fragment tiles [rows, n_q*hd] in half: the O
 // projection's input) if that is given, else to out_rows (row-major bf16)
+struct AttnPlan {
+  int waves, shares, tiles;  // of a workgroup: wavefronts, workgroups that share a head's output dims, 16-query tiles
+};
+AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_q, int hd);
 void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,
                           op_t* out_tiles, bf16_t* out_rows, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st);
 // test helper of dlm_attention: K, V [T, n_kv, hd] row-major bf16 -> the tiled half-precision cache layout of one slot; q -> half

@@ -781,3 +781,13 @@ extern "C" int dlm_attention(const void* q, const void* k, const void* v, void* 
   if (e != hipSuccess) return dlm_fail(DLM_EHIP, "dlm_attention: %s", hipGetErrorString(e));
   return DLM_OK;
 }
+
+// ---- what the launch rules choose for a shape -----------------------------------------------------------
+extern "C" int dlm_plan_attention(int max_seq_rows, int n_seqs, int n_q, int head_dim, int32_t plan[3]) {
+  REQUIRE(plan, DLM_EINVAL, "dlm_plan_attention: null argument");
+  REQUIRE(max_seq_rows >= 1 && n_seqs >= 1 && n_q >= 1, DLM_ESHAPE, "dlm_plan_attention: non-positive size");
+  REQUIRE(head_dim == 32 || head_dim == 64 || head_dim == 128, DLM_ESHAPE, "dlm_plan_attention: head_dim %d not in {32,64,128}", head_dim);
+  const AttnPlan p = attention_plan(max_seq_rows, n_seqs, n_q, head_dim);
+  plan[0] = p.waves; plan[1] = p.shares; plan[2] = p.tiles;
+  return DLM_OK;
+}

@@ -127,3 +127,28 @@ def test_packed_host_arrays(v):
     """The bytes handed to the two decisions are those of a ctypes int32 array, for whatever that accepts; None stays None."""
     assert api._packed(v) == bytes(api._ints(v))
     assert api._packed(None) is None
+
+
+# ---- launch rules (host arithmetic) ---------------------------------------------------------------
+@pytest.mark.parametrize("hd", [32, 64, 128])
+@pytest.mark.parametrize("n_q", [1, 4, 16, 28, 32, 64])
+def test_attention_takes_a_second_query_tile_only_where_a_span_has_one(n_q, hd):
+    for n_seqs in (1, 2, 3, 4, 5, 8, 16, 24, 32):
+        for rows in (1, 8, 15, 16, 17, 31, 32, 33, 37, 48, 64, 100, 512, 3072):
+            p, tiles = api.plan_attention(rows, n_seqs, n_q, hd), (rows + 15) // 16
+            assert p["tiles"] <= tiles, (n_seqs, rows, p)
+            assert p["waves"] in (4, 8) and p["shares"] in ({32: (1,), 64: (1, 2), 128: (1, 4)}[hd])
+            if p["shares"] == 4 and tiles > 1:  # a narrow pass: two tiles exactly where one would leave a second workgroup per compute unit
+                assert (p["tiles"] == 2) == (tiles * n_q * n_seqs * 4 > 256)
+            if p["waves"] == 4:
+                assert p["tiles"] == min(tiles, 2)
+    # spans of one tile: 3 sequences x 32 heads, 3 and 4 x 28 are more than 256 workgroups of one tile
+    assert api.plan_attention(16, 3, 32, 128)["tiles"] == api.plan_attention(8, 4, 28, 128)["tiles"] == 1
+    assert api.plan_attention(37, 1, 32, 128) == dict(waves=8, shares=4, tiles=2)
+
+
+def test_launch_rule_argument_errors():
+    L = api.lib()
+    out = (C.c_int32 * 3)()
+    assert L.dlm_plan_attention(8, 1, 32, 128, None) == -1
+    assert L.dlm_plan_attention(0, 1, 32, 128, out) == -2 and L.dlm_plan_attention(8, 1, 32, 48, out) == -2

@@ -400,6 +400,34 @@ def test_tiny_f32_free_run_equals_stored_decode(device, name):
 WIDE_VOCAB = inputs.model_config(1, 256, 2, 2, 128, 512, 16416, "bf16")
 
 
+# One layer whose attention pairs query tiles in a narrow pass of two or three spans and in a wide one of many
+MANY_HEADS = inputs.model_config(1, 256, 28, 4, 128, 512, 1024, "bf16")
+
+
+@pytest.mark.parametrize("spans", [[8, 3, 16], [16, 1, 9, 8], [17, 1], [33, 16, 17, 5, 1, 32, 48, 2], [16] * 19, [130, 16, 15, 17, 1, 113]])
+def test_packed_spans_of_one_and_more_query_tiles(device, spans):
+    """Spans of one tile beside longer ones: narrow and wide passes, one and two tiles per workgroup, workgroups whose second tile
+    does not exist; every sequence's logits against the oracle's pass over that sequence alone."""
+    cfg = MANY_HEADS
+    W = _weights(cfg, 13, device)
+    Wn = inputs.weights_to_numpy(W)
+    model = api.Model(cfg, W)
+    B, T, look = len(spans), max(spans), 8
+    state = api.State(model, B, T + look, sum(spans), look)
+    out = api.StepOutputs(sum(spans), cfg["vocab"], model.torch_dtype, device)
+    tokens = torch.randint(0, cfg["vocab"] - 1, (B, T + look), generator=torch.Generator().manual_seed(B), dtype=torch.int32)
+    off = [0] + np.cumsum(spans).tolist()
+    api.dlm_step(state, tokens.to(device), out, off, [0] * B, [0] * B, [b * (T + look) for b in range(B)])
+    torch.cuda.synchronize()
+    z = o_fwd.widen(inputs.tensor_to_numpy(out.logits))
+    for b, n in enumerate(spans):
+        ref = o_fwd.forward_span(cfg, Wn, o_fwd.KVCache(cfg), tokens[b, :n].numpy(), 0, 0)
+        scale = np.maximum(np.abs(ref).max(-1, keepdims=True), SIGMA_LOGIT)
+        assert (np.abs(z[off[b]: off[b + 1]] - ref) <= 2e-2 * scale).all(), (b, n, (np.abs(z[off[b]: off[b + 1]] - ref) / scale).max())
+    state.close()
+    model.close()
+
+
 @pytest.mark.parametrize("L", [1, 8, 24, 64])
 def test_statistics_from_the_lm_head_epilogue(device, L):
     """An in-block pass (no row compared, none retained) takes its statistics from the LM head's epilogue: the same pass with that
