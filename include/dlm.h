@@ -278,7 +278,10 @@ int dlm_profile_read(dlm_state* s, int n, double* ms_out, int64_t* launches_out,
  * dlm_plan_attention: a bf16 model's attention over n_seqs spans of which the longest has max_seq_rows
  * rows.  plan[0] wavefronts of a workgroup, plan[1] workgroups that share a head's output dims, plan[2]
  * 16-query tiles of a workgroup.
- * Errors: DLM_EINVAL (null), DLM_ESHAPE (a size that is not positive, head_dim not in {32, 64, 128}). */
+ * dlm_plan_vocab_stats: the streamed vocabulary reduction.  plan[0] threads of a workgroup, plan[1] chunks
+ * a row is cut into (more than one: a second launch merges them).
+ * Errors: DLM_EINVAL (null, bad dtype), DLM_ESHAPE (a size out of range, head_dim not in {32, 64, 128}). */
+int dlm_plan_vocab_stats(int rows, int vocab, int dtype, int32_t plan[2]);
 int dlm_plan_attention(int max_seq_rows, int n_seqs, int n_q, int head_dim, int32_t plan[3]);
 
 #ifdef __cplusplus

@@ -57,7 +57,8 @@ class dlm_select_params(C.Structure):
 EXPORTS = ["dlm_last_error", "dlm_model_create", "dlm_model_destroy", "dlm_state_create", "dlm_state_destroy", "dlm_state_reset",
            "dlm_state_kv_len", "dlm_step", "block_boundary", "select_parallel", "dlm_vocab_stats_workspace", "dlm_vocab_stats",
            "dlm_gemm_nt", "dlm_attention", "dlm_profile_enable", "dlm_profile_read", "dlm_probe_hbm_read", "dlm_probe_mfma",
-           "dlm_state_fuse_stats", "dlm_vocab_stats_static", "dlm_plan_attention"]
+           "dlm_state_fuse_stats", "dlm_vocab_stats_static", "dlm_plan_attention",
+           "dlm_plan_vocab_stats"]
 
 
 def lib():
@@ -91,6 +92,7 @@ def lib():
         L.dlm_probe_hbm_read.argtypes = [C.c_void_p, C.c_size_t, C.c_int, C.POINTER(C.c_double), C.c_void_p]
         L.dlm_probe_mfma.argtypes = [C.c_int, C.POINTER(C.c_double), C.c_void_p]
         L.dlm_plan_attention.argtypes = [C.c_int] * 4 + [_I32P]
+        L.dlm_plan_vocab_stats.argtypes = [C.c_int] * 3 + [_I32P]
         L.dlm_state_fuse_stats.argtypes = [C.c_void_p, C.c_int]
         L.dlm_profile_enable.argtypes = [C.c_void_p, C.c_uint]
         L.dlm_profile_read.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int]
@@ -312,3 +314,10 @@ def plan_attention(max_seq_rows, n_seqs, n_q, head_dim):
     out = (C.c_int32 * 3)()
     _check(lib().dlm_plan_attention(max_seq_rows, n_seqs, n_q, head_dim, out))
     return dict(zip(("waves", "shares", "tiles"), out))
+
+
+def plan_vocab_stats(rows, vocab, dtype):
+    """How the streamed vocabulary reduction is launched (include/dlm.h): threads of a workgroup, chunks of a row."""
+    out = (C.c_int32 * 2)()
+    _check(lib().dlm_plan_vocab_stats(rows, vocab, dtype_code(dtype), out))
+    return dict(zip(("threads", "chunks"), out))

@@ -282,6 +282,12 @@ struct StatsRows {
   const float* prev_lse;    // indexed by prev_row / vocab; null = recompute from the logits
   float* save_lse;          // indexed by save_row / vocab
 };
+struct StatsPlan {
+  int threads;        // of a workgroup
+  int chunk, chunks;  // tokens of a chunk, chunks of a row (more than one: a second launch merges them)
+  bool vector;        // rows are read in 16-byte vectors
+};
+StatsPlan stats_plan(int rows, int vocab, int elem_size);
 size_t stats_workspace_bytes(int rows);
 constexpr size_t STATS_STATE_BYTES = 32;  // one online-softmax state (stats_part.h)
 // Finishes rows whose online-softmax states were written per column group by an EPI_STATS GEMM: parts [rows][nparts] states

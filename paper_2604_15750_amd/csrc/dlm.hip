@@ -791,3 +791,12 @@ extern "C" int dlm_plan_attention(int max_seq_rows, int n_seqs, int n_q, int hea
   plan[0] = p.waves; plan[1] = p.shares; plan[2] = p.tiles;
   return DLM_OK;
 }
+
+extern "C" int dlm_plan_vocab_stats(int rows, int vocab, int dtype, int32_t plan[2]) {
+  REQUIRE(plan, DLM_EINVAL, "dlm_plan_vocab_stats: null argument");
+  REQUIRE(dtype == DLM_F32 || dtype == DLM_BF16, DLM_EINVAL, "dlm_plan_vocab_stats: dtype %d", dtype);
+  REQUIRE(rows >= 1 && vocab >= 2, DLM_ESHAPE, "dlm_plan_vocab_stats: %d rows of %d tokens", rows, vocab);
+  const StatsPlan p = stats_plan(rows, vocab, (int)elem_size(dtype));
+  plan[0] = p.threads; plan[1] = p.chunks;
+  return DLM_OK;
+}

@@ -238,27 +238,13 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
 }
 
 constexpr int MAX_CHUNKS = 32;
-constexpr int ROW_MIN = 96, ROW_MAX = 256;  // rows that get a workgroup of 1024 threads each (launch_vocab_stats)
+constexpr int ROW_MIN = 152, ROW_MAX = 256;  // rows that can get a workgroup of 1024 threads each (stats_plan)
 
-// Chunks per row: about 1536 work items, each at least two vectors per lane.
-int pick_chunks(int rows, int vocab, int vec) {
-  int want = (1536 + rows - 1) / rows;
-  int maxc = (vocab + 256 * vec * 2 - 1) / (256 * vec * 2);
-  int c = want < maxc ? want : maxc;
-  if (c > MAX_CHUNKS) c = MAX_CHUNKS;
-  return c < 1 ? 1 : c;
-}
-
-template <typename T, int TPB>
-void launch_items(const T* logits, int rows, int vocab, int mask_id, int nch, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
-  constexpr int N = Vec<T>::N;
-  int chunk = (vocab + nch - 1) / nch;
-  chunk = (chunk + TPB * N - 1) / (TPB * N) * (TPB * N);
-  nch = (vocab + chunk - 1) / chunk;
-  const int items = rows * nch;  // the hardware dispatcher balances better than a resident grid walking the items
-  if (vocab % N == 0) vocab_stats_kernel<T, TPB, true><<<items, TPB, 0, st>>>(logits, rows, vocab, mask_id, chunk, nch, sr, o, (Part*)workspace);
-  else vocab_stats_kernel<T, TPB, false><<<items, TPB, 0, st>>>(logits, rows, vocab, mask_id, chunk, nch, sr, o, (Part*)workspace);
-  if (nch > 1) vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)workspace, rows, nch, vocab, sr, o);
+template <typename T, int TPB, bool VECTOR>
+void launch_items(const T* logits, int rows, int vocab, int mask_id, const StatsPlan& p, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
+  // (the hardware dispatcher balances better than a resident grid walking the items)
+  vocab_stats_kernel<T, TPB, VECTOR><<<rows * p.chunks, TPB, 0, st>>>(logits, rows, vocab, mask_id, p.chunk, p.chunks, sr, o, (Part*)workspace);
+  if (p.chunks > 1) vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)workspace, rows, p.chunks, vocab, sr, o);
 }
 
 }  // namespace
@@ -270,17 +256,41 @@ void launch_stats_merge(const void* parts, int rows, int nparts, int vocab, cons
 }
 
 // How a row is cut.  The reduction is bound by its reads; what the cut decides is how evenly they lie on the chip and whether a
-// second launch has to merge.  Chunks for about 1536 workgroups of 256 threads, merged by a second kernel (4 us at 384 rows), are
-// the general form.  With a row for most of the 256 compute units and no second round, one workgroup of 1024 threads takes a whole
-// row and writes its results itself.  A vocabulary of 126464, microseconds per call, chunks -> whole rows:
-//   bf16 with a previous row  96 rows 21.0 -> 20.9, 192: 23.1 -> 21.9, 256: 29.3 -> 25.7, but 272: 31.4 -> 42.9 (a second round
-//   of workgroups, as two of 1024 threads don't fit into a unit's registers); without: 256: 22.7 -> 18.8, 272: 23.4 -> 31.9;
-//   fp32 with a previous row 128: 26.7 -> 24.3, 256: 50.6 -> 47.8, 272: 54.8 -> 69.1.
-// Below 96 rows more than half of the units would be idle, and neither is faster (fp32, 64 rows: 19.9 -> 20.5): chunks.
+// second launch has to merge.  Chunks for about 1536 workgroups of 256 threads, each at least two vectors per lane, merged by a second
+// kernel (4 us at 384 rows), are the general form; one chunk (a vocabulary of up to 4096 bf16 or 2048 fp32 logits) needs no merge.
+// Where a merge would be needed, rows are read in 16-byte vectors and there is a row for most of the 256 compute units but no
+// second round, one workgroup of 1024 threads takes a whole row and writes its results itself.  Microseconds of GPU time per call
+// on logits in the memory-side cache, chunks -> whole rows, without / with a previous row:
+//   bf16, 126464 tokens: 96 rows 13.0 -> 16.6 / 15.8 -> 20.4, 128: 16.2 -> 17.3 / 20.1 -> 20.8, 160: 18.2 -> 17.8 / 22.6 -> 20.9,
+//   192: 17.6 -> 17.9 / 22.6 -> 21.6, 256: 22.2 -> 18.3 / 28.8 -> 24.9; 272 rows: 22.7 -> 31.2 / 31.4 -> 42.9 (a second round of
+//   workgroups, as two of 1024 threads don't fit into a unit's registers).  Over 20 shapes the mean of whole / chunks is 1.07 at
+//   104 rows, 0.96 at 136, 0.93 at 152, 0.89 at 184; at 136 and 144 rows single shapes still lose 7 and 3 %, from 152 on one does
+//   (152064 tokens, bf16, no previous row, 160 rows: 17.7 -> 18.8, the cut into chunks being an even one there).
+// Without 16-byte vectors a lane has one scalar load in flight, and fewer lanes are what it loses by: 126463 tokens, bf16, 96 rows
+//   20.5 -> 34.6 / 23.5 -> 58.9, 256: 44.2 -> 55.2 / 48.0 -> 60.0.  With one chunk the larger workgroup has nothing to save:
+//   1024 tokens, fp32, 96 .. 256 rows 4.4 -> 6.4.
+StatsPlan stats_plan(int rows, int vocab, int elem_size) {
+  const int n = 16 / elem_size;  // elements of a vector
+  const int want = (1536 + rows - 1) / rows, most = (vocab + 512 * n - 1) / (512 * n);
+  int nch = want < most ? want : most;
+  if (nch > MAX_CHUNKS) nch = MAX_CHUNKS;
+  if (nch < 1) nch = 1;
+  StatsPlan p;
+  p.vector = vocab % n == 0;
+  p.threads = p.vector && nch > 1 && rows >= ROW_MIN && rows <= ROW_MAX ? 1024 : 256;
+  if (p.threads == 1024) nch = 1;
+  const int unit = p.threads * n;  // chunks are whole strides of the workgroup
+  p.chunk = ((vocab + nch - 1) / nch + unit - 1) / unit * unit;
+  p.chunks = (vocab + p.chunk - 1) / p.chunk;
+  return p;
+}
+
 template <typename T>
 void launch_vocab_stats(const T* logits, int rows, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
-  if (rows >= ROW_MIN && rows <= ROW_MAX) launch_items<T, 1024>(logits, rows, vocab, mask_id, 1, sr, o, workspace, st);
-  else launch_items<T, 256>(logits, rows, vocab, mask_id, pick_chunks(rows, vocab, Vec<T>::N), sr, o, workspace, st);
+  const StatsPlan p = stats_plan(rows, vocab, sizeof(T));
+  if (p.threads == 1024) launch_items<T, 1024, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  else if (p.vector) launch_items<T, 256, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  else launch_items<T, 256, false>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
 }
 
 template void launch_vocab_stats<float>(const float*, int, int, int, const StatsRows&, const StatsOut&, void*, hipStream_t);

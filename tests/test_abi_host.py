@@ -147,8 +147,27 @@ def test_attention_takes_a_second_query_tile_only_where_a_span_has_one(n_q, hd):
     assert api.plan_attention(37, 1, 32, 128) == dict(waves=8, shares=4, tiles=2)
 
 
+@pytest.mark.parametrize("dt,vec", [(torch.bfloat16, 8), (torch.float32, 4)])
+def test_whole_row_statistics_only_where_they_save_a_merge_and_read_in_vectors(dt, vec):
+    whole = set()
+    for rows in (1, 8, 64, 95, 96, 97, 128, 151, 152, 153, 192, 255, 256, 257, 384, 3072):
+        for vocab in (2, 8, 1000, 1001, 1024, 2048, 2056, 4096, 4104, 8199, 16640, 126463, 126464, 152064):
+            p = api.plan_vocab_stats(rows, vocab, dt)
+            assert p["threads"] in (256, 1024) and 1 <= p["chunks"] <= 32
+            if vocab % vec or vocab <= 512 * vec:  # one scalar load in flight per lane; or one chunk, nothing to merge
+                assert p["threads"] == 256, (rows, vocab)
+            if vocab <= 512 * vec:
+                assert p["chunks"] == 1
+            if p["threads"] == 1024:
+                assert p["chunks"] == 1
+                whole.add(rows)
+    assert whole == {152, 153, 192, 255, 256}
+
+
 def test_launch_rule_argument_errors():
     L = api.lib()
     out = (C.c_int32 * 3)()
+    assert L.dlm_plan_vocab_stats(8, 1024, 0, None) == -1 and L.dlm_plan_vocab_stats(8, 1024, 2, out) == -1
+    assert L.dlm_plan_vocab_stats(0, 1024, 0, out) == -2 and L.dlm_plan_vocab_stats(8, 1, 0, out) == -2
     assert L.dlm_plan_attention(8, 1, 32, 128, None) == -1
     assert L.dlm_plan_attention(0, 1, 32, 128, out) == -2 and L.dlm_plan_attention(8, 1, 32, 48, out) == -2
