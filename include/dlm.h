@@ -280,8 +280,14 @@ int dlm_profile_read(dlm_state* s, int n, double* ms_out, int64_t* launches_out,
  * 16-query tiles of a workgroup.
  * dlm_plan_vocab_stats: the streamed vocabulary reduction.  plan[0] threads of a workgroup, plan[1] chunks
  * a row is cut into (more than one: a second launch merges them).
- * Errors: DLM_EINVAL (null, bad dtype), DLM_ESHAPE (a size out of range, head_dim not in {32, 64, 128}). */
+ * dlm_plan_gemm: a bf16 model's product of M rows with a matrix [N, K] (N and K multiples of 32); epilogue:
+ * 0 plain without a workspace (LM head), 1 QKV, 2 gated, 3 residual, 4 plain (dlm_gemm_nt), 5 LM head with
+ * statistics (at most 64 rows).  plan[0] kernel (0 skinny, 1 mid, 2 macro), plan[1], plan[2] rows and columns of
+ * a workgroup's tile, plan[3] workgroups that share a tile by splitting K, plan[4] parts K is summed in,
+ * plan[5] workgroups, plan[6] chunks of the rows' sums of squares per column block (epilogue 3).
+ * Errors: DLM_EINVAL (null, bad dtype or epilogue), DLM_ESHAPE (a size out of range, head_dim not in {32, 64, 128}). */
 int dlm_plan_vocab_stats(int rows, int vocab, int dtype, int32_t plan[2]);
+int dlm_plan_gemm(int M, int N, int K, int epilogue, int32_t plan[7]);
 int dlm_plan_attention(int max_seq_rows, int n_seqs, int n_q, int head_dim, int32_t plan[3]);
 
 #ifdef __cplusplus

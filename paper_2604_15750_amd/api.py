@@ -58,7 +58,7 @@ EXPORTS = ["dlm_last_error", "dlm_model_create", "dlm_model_destroy", "dlm_state
            "dlm_state_kv_len", "dlm_step", "block_boundary", "select_parallel", "dlm_vocab_stats_workspace", "dlm_vocab_stats",
            "dlm_gemm_nt", "dlm_attention", "dlm_profile_enable", "dlm_profile_read", "dlm_probe_hbm_read", "dlm_probe_mfma",
            "dlm_state_fuse_stats", "dlm_vocab_stats_static", "dlm_plan_attention",
-           "dlm_plan_vocab_stats"]
+           "dlm_plan_vocab_stats", "dlm_plan_gemm"]
 
 
 def lib():
@@ -93,6 +93,7 @@ def lib():
         L.dlm_probe_mfma.argtypes = [C.c_int, C.POINTER(C.c_double), C.c_void_p]
         L.dlm_plan_attention.argtypes = [C.c_int] * 4 + [_I32P]
         L.dlm_plan_vocab_stats.argtypes = [C.c_int] * 3 + [_I32P]
+        L.dlm_plan_gemm.argtypes = [C.c_int] * 4 + [_I32P]
         L.dlm_state_fuse_stats.argtypes = [C.c_void_p, C.c_int]
         L.dlm_profile_enable.argtypes = [C.c_void_p, C.c_uint]
         L.dlm_profile_read.argtypes = [C.c_void_p, C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.c_int]
@@ -321,3 +322,13 @@ def plan_vocab_stats(rows, vocab, dtype):
     out = (C.c_int32 * 2)()
     _check(lib().dlm_plan_vocab_stats(rows, vocab, dtype_code(dtype), out))
     return dict(zip(("threads", "chunks"), out))
+
+
+EPILOGUES = ("direct", "qkv", "swiglu", "resid", "sum", "stats")
+
+
+def plan_gemm(M, N, K, epilogue):
+    """How a bf16 model's product is launched (include/dlm.h); epilogue: a name from EPILOGUES."""
+    out = (C.c_int32 * 7)()
+    _check(lib().dlm_plan_gemm(M, N, K, EPILOGUES.index(epilogue), out))
+    return dict(zip(("kernel", "rows", "cols", "splits", "k_parts", "workgroups", "ssq_parts"), (("skinny", "mid", "macro")[out[0]], *out[1:])))

@@ -219,6 +219,15 @@ bool gemm_mid_one_round(int M, int N, int K);   // its workgroups are at most on
 int gemm_mid_counters(int max_n);
 void launch_gemm_mid(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);  // the row counts choose_kernel sends (gemm_bf16.hip)
 int gemm_macro_ssq_chunks(int M, int N, int K);
+struct GemmPlan {
+  int kernel;                // 0 skinny, 1 mid, 2 macro (choose_kernel)
+  int tile_rows, tile_cols;  // of a workgroup
+  int splits, k_parts;       // workgroups that share a tile; parts K is summed in (one workgroup can keep two)
+  int workgroups, ssq_parts; // ...; EPI_RESID: chunks of the sums of squares per column block
+};
+GemmPlan gemm_macro_plan(int M, int N, int K, int kind);  // (kernel left to the caller)
+GemmPlan gemm_mid_plan(int M, int N, int K);
+GemmPlan gemm_bf16_plan(int M, int N, int K, int kind);
 int gemm_macro_splits(int M, int N, int K, int kind);
 int gemm_macro_stat_parts(int M, int N, int K);
 int gemm_macro_counters();

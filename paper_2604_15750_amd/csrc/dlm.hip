@@ -800,3 +800,12 @@ extern "C" int dlm_plan_vocab_stats(int rows, int vocab, int dtype, int32_t plan
   plan[0] = p.threads; plan[1] = p.chunks;
   return DLM_OK;
 }
+
+extern "C" int dlm_plan_gemm(int M, int N, int K, int epilogue, int32_t plan[7]) {
+  REQUIRE(plan && epilogue >= EPI_DIRECT && epilogue <= EPI_STATS, DLM_EINVAL, "dlm_plan_gemm: null argument or bad epilogue");
+  REQUIRE(M >= 1 && N >= 32 && K >= 32 && N % 32 == 0 && K % 32 == 0, DLM_ESHAPE, "dlm_plan_gemm: %d x %d x %d", M, N, K);
+  const GemmPlan p = gemm_bf16_plan(M, N, K, epilogue);
+  const int v[7] = {p.kernel, p.tile_rows, p.tile_cols, p.splits, p.k_parts, p.workgroups, p.ssq_parts};
+  for (int i = 0; i < 7; ++i) plan[i] = v[i];
+  return DLM_OK;
+}

@@ -128,6 +128,13 @@ void launch_pack_act(const bf16_t* x, op_t* out, int M, int K, hipStream_t st) {
   pack_act_kernel<<<512, 256, 0, st>>>((const bf16x8*)x, (op8*)out, M, K);
 }
 
+GemmPlan gemm_bf16_plan(int M, int N, int K, int kind) {
+  const int k = choose_kernel(M, N, K, kind), ct = weight_pack_rows(N);
+  GemmPlan p = k == KERNEL_MID ? gemm_mid_plan(M, N, K) : k == KERNEL_MACRO ? gemm_macro_plan(M, N, K, kind)
+                                                                              : GemmPlan{0, (M + 15) / 16 * 16, 16 * ct, 1, 1, (N / 16 + ct - 1) / ct, 1};
+  p.kernel = k;
+  return p;
+}
 int gemm_bf16_splits(int M, int N, int K, int kind) {
   switch (choose_kernel(M, N, K, kind)) {
     case KERNEL_MID: return gemm_mid_splits(M, N, K);

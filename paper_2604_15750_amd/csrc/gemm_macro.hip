@@ -8,12 +8,14 @@ const MacroTile g_tiles[] = {MACRO_TILES(ROW)};
 #undef ROW
 constexpr int CUS = 256, MAX_SPLITS = 4, MAX_SPLIT_TILES = 1024;
 
-// The order of the sums of a wide launch: over how many ways K is split, and how many 16-column tiles a chunk of the rows' sums
-// of squares has.  A change of that order changes the last bits of everything downstream, so from 512 rows on it is a function
-// of the shape alone, kept apart from the choice of the tile: passes of 512 rows and more give bit for bit what they gave when
-// the tiles below were all there were (rows x columns, relative time per product, and the factor for two or one workgroups on a
-// compute unit).  Not kept: splits of more than two ways, which lose a fifth of the launch (down of an 8B model at 1280 rows:
-// three ways over 256 columns 168 us, unsplit 137).
+// The order of the sums of a wide launch: whether K is summed in one part or two, and how many 16-column tiles a chunk of the rows'
+// sums of squares has.  Another order moves the last bits of everything downstream, and with them the confidences of the narrow
+// passes that read a wide pass's cache: an exponential of a bf16 logit jumps by 6 or 12 % where the logit's rounding flips (in-block
+// passes of 8 .. 37 rows behind prefills of 512 .. 1756 rows, 48 trials: the confidences moved by up to 3.7 % in the 2-norm).  So from
+// 32 row tiles (497 rows) on the order is a function of the shape alone, apart from the choice of the tile and of the workgroups:
+// the constants below say which order a shape has; they are no timings of this kernel's tiles.  Shapes for which they ask for more
+// than two parts are left out: there the order is the plan's (the down projections of an 8B model at 513 .. 640 and 1025 .. 1280 rows,
+// of a 7B one at 513 .. 1024 and 1153 .. 1536).
 struct SumOrder {
   bool fixed;
   int splits, bt;
@@ -46,8 +48,12 @@ SumOrder sum_order(int mt, int N, int K, bool may_split) {
 // its pipeline's start and its epilogue (QKV most: rotary embedding and scattered cache writes).  A K split, for launches that
 // leave compute units idle, adds the hand-off and the partial tiles' traffic.  Against the best of all measured candidates of
 // 220 shapes the choice loses 0.7 % on average.  M enters only through its 16-row tiles.
+// Where the order of the sums is fixed, two parts of K are either a split over two workgroups (as long as all of them are one
+// round) or one workgroup that keeps two sums (fold), and a chunk of the squares is a column block or half of one; the tile is free.
+// With the split and the block width pinned as well, narrow matrices ran a second round: O of an 8B model at 2048 rows 90 us against
+// 74 now, its down 230 / 179, QKV of a 7B model at 945 rows 89 / 48, O of the 8B one at 512 rows 44 / 37.
 MacroPlan macro_plan(int M, int N, int K, int kind) {
-  MacroPlan best{0, 1, 1, 1, 1};
+  MacroPlan best{0, 1, 1, 1, 1, 0, 1};
   double best_us = 1e300;
   const bool may_split = kind != EPI_DIRECT && kind != EPI_STATS;  // the LM head's epilogues have no workspace
   const double round_us = kind == EPI_QKV ? 5.6 : kind == EPI_RESID ? 4.3 : kind == EPI_SWIGLU ? 1.8 : 3.4;
@@ -59,16 +65,22 @@ MacroPlan macro_plan(int M, int N, int K, int kind) {
       ++c;
       if (kind == EPI_STATS && 16 * t.rw * t.wm > GEMM_STATS_MAX_ROWS) continue;  // (not instantiated)
       const int at = t.rw * t.wm, bt = t.cw * t.wn, mb = (mt + at - 1) / at, nb = (nt + bt - 1) / bt, tiles = mb * nb;
+      const int parts = order.fixed && kind == EPI_RESID && bt == 2 * order.bt ? 2 : 1;  // (two chunks of a block of 16 column tiles: bt % 4 == 0)
+      const bool keeps = may_split && macro_can_keep_order(t.wm, t.wn, t.kb);
+      if (order.fixed && kind == EPI_RESID && (bt != order.bt * parts || (parts == 2 && !(keeps && bt % 4 == 0)))) continue;
       const double own = mb == 1 ? 1.0 : mb == 2 ? 0.35 : mb == 3 ? 0.17 : 0.0, ns = t.ns4 + (t.ns1 - t.ns4) * own;
       for (int sp = 1; sp <= (may_split && t.wm * t.wn <= MACRO_SPLIT_FRAGS ? MAX_SPLITS : 1); ++sp) {
-        if (order.fixed && (sp != order.splits || (kind == EPI_RESID && bt != order.bt) || (sp > 1 && tiles > MAX_SPLIT_TILES))) continue;
-        if (!order.fixed && sp > 1 && (tiles * sp > CUS || KT / sp < 16)) break;
+        if (sp > 1 && (tiles * sp > CUS || KT / sp < 16)) break;
+        const bool fold = order.fixed && order.splits == 2 && sp == 1;
+        if (order.fixed && !fold && sp != order.splits) continue;
+        if (fold && !keeps) continue;
         const int kps = ((KT + sp - 1) / sp + t.kb - 1) / t.kb * t.kb;
         if ((KT + kps - 1) / kps != sp) continue;  // an empty split
         const int wgs = tiles * sp, full = (wgs - 1) / CUS, last = wgs - CUS * full;
         double us = kps * ns * 1e-3 * (full + 0.65 + 0.35 * last / CUS) + (full + 1) * round_us;
+        if (parts > 1) us += 2.5;  // (the epilogue of a tile twice as wide: 2048 rows x 2048 columns, K = 512, 16.6 against 18.9 us)
         if (sp > 1) us += 4.6 + 0.6 * (sp - 1) + 0.62 * (sp - 1) * (mt * 16.0 * N * 8e-6);
-        if (us < best_us) { best_us = us; best = MacroPlan{c, nb, mb, sp, kps}; }
+        if (us < best_us) { best_us = us; best = MacroPlan{c, nb, mb, sp, kps, fold ? ((KT + 1) / 2 + 1) / 2 * 2 : 0, parts}; }
       }
     }
     if (best_us < 1e300 || !order.fixed) return best;  // (an order that no tile has: any order)
@@ -77,7 +89,16 @@ MacroPlan macro_plan(int M, int N, int K, int kind) {
 
 }  // namespace
 
-int gemm_macro_ssq_chunks(int M, int N, int K) { return macro_plan(M, N, K, EPI_RESID).nblocks; }  // (the plan of the launch itself)
+int gemm_macro_ssq_chunks(int M, int N, int K) {  // (the plan of the launch itself)
+  const MacroPlan p = macro_plan(M, N, K, EPI_RESID);
+  const int ct = g_tiles[p.tile].cw * g_tiles[p.tile].wn / p.ssq_parts;
+  return ((N >> 4) + ct - 1) / ct;
+}
+GemmPlan gemm_macro_plan(int M, int N, int K, int kind) {
+  const MacroPlan p = macro_plan(M, N, K, kind);
+  const MacroTile& t = g_tiles[p.tile];
+  return GemmPlan{0, 16 * t.rw * t.wm, 16 * t.cw * t.wn, p.splits, p.fold ? 2 : p.splits, p.nblocks * p.mblocks * p.splits, p.ssq_parts};
+}
 int gemm_macro_splits(int M, int N, int K, int kind) { return macro_plan(M, N, K, kind).splits; }
 int gemm_macro_stat_parts(int M, int N, int K) { return macro_plan(M, N, K, EPI_STATS).nblocks; }
 int gemm_macro_counters() { return 2 * MAX_SPLIT_TILES; }  // two per tile of a launch that splits K

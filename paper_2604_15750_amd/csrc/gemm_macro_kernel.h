@@ -49,9 +49,14 @@ struct MacroTile {
 struct MacroPlan {
   int tile;  // index into MACRO_TILES
   int nblocks, mblocks, splits, kps;
+  int fold;       // k-tiles after which a workgroup starts a second sum, added to the first at the end (0: one sum)
+  int ssq_parts;  // EPI_RESID: chunks of the rows' sums of squares per column block (1 or 2)
 };
 // K is split only where a wavefront has at most this many output fragments: the last arriver holds two tiles of them
 constexpr int MACRO_SPLIT_FRAGS = 16;
+// tiles that also come with two sums of K, or two chunks of the squares, per workgroup: an instantiation of its own, so that the plain
+// kernel keeps its loop and its registers (96 x 128: 81 against 108, 128 x 256: 211 against 230)
+constexpr bool macro_can_keep_order(int wm, int wn, int kb) { return kb == 2 && wm * wn >= 6 && wm * wn <= MACRO_SPLIT_FRAGS; }
 
 // gemm_macro_<epilogue>.hip: the launches of one epilogue's instantiations
 template <int EPI>
@@ -86,12 +91,15 @@ struct MacroShape {
   static_assert(S >= 2 && LDS_BYTES <= 160 * 1024, "pipeline shape");
 };
 
-// prs: 1 if the weights are packed in interleaved pairs of column tiles, 0 for single runs (weight_pack_rows - 1)
-template <int WM, int WN, int RW, int CW, int KB, int EPI>
+// form: bit 0: the weights are packed in interleaved pairs of column tiles, not in single runs (weight_pack_rows - 1); and with ORDER
+// bit 1: two chunks of the squares per column block, the other bits: k-tiles after which a second sum starts (0: one sum)
+template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER>
 __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
-                                                                               int prs, int nblocks, int mblocks, int splits, int kt_per_split, GemmEpi e) {
+                                                                               int form, int nblocks, int mblocks, int splits, int kt_per_split, GemmEpi e) {
   typedef MacroShape<WM, WN, RW, CW, KB> SH;
   constexpr int NW = SH::NW, TPB = SH::TPB, AT = SH::AT, BF = SH::BF, NFR = SH::NFR, LPT = SH::LPT, LPS = SH::LPS, STAGE = SH::STAGE, S = SH::S, HJ = SH::HJ;
+  const int prs = ORDER ? form & 1 : form, fold = ORDER ? form >> 2 : 0;
+  const bool two_chunks = ORDER && (form & 2);
   extern __shared__ __align__(16) unsigned char lds[];
   float* s_rinv = (float*)(lds + SH::BODY);  // [AT * 16]
   float* s_ssq = s_rinv + AT * 16;           // [BF][AT * 16]
@@ -209,12 +217,39 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   static_assert(KB == 1 || KB == 2, "k-tiles per stage");
   int buf = 0;
   auto next = [&](int b) { return b + 1 == S ? 0 : b + 1; };
-  if constexpr (KB == 2) {
+  if constexpr (KB == 2 && !ORDER) {
     for (int s = 0; s < nstages; ++s, buf = next(buf)) {
       ktile(std::integral_constant<int, 0>{}, 0, s, buf, next(buf));
       ktile(std::integral_constant<int, 1>{}, 1, s, buf, next(buf));
     }
     if (nkt & 1) multiply(0);  // the odd last k-tile: its operands were read with the stage before it
+  } else if constexpr (KB == 2) {
+    int s = 0;
+    auto walk = [&](int end) __attribute__((always_inline)) {
+      for (; s < end; ++s, buf = next(buf)) {
+        ktile(std::integral_constant<int, 0>{}, 0, s, buf, next(buf));
+        ktile(std::integral_constant<int, 1>{}, 1, s, buf, next(buf));
+      }
+    };
+    walk(fold ? fold / KB : nstages);
+    if (!fold) {
+      if (nkt & 1) multiply(0);
+    } else {  // (uniform) a second sum: what a K split over two workgroups adds, in the same order, without the hand-off
+      f32x4 first[WN][WM];
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int i = 0; i < WM; ++i) {
+          first[j][i] = acc[j][i];
+          acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      walk(nstages);
+      if (nkt & 1) multiply(0);
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int i = 0; i < WM; ++i) acc[j][i] = first[j][i] + acc[j][i];
+    }
   } else {
     int s = 0;
     for (; s + 1 < nstages; s += 2) {
@@ -363,28 +398,39 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
       dst[1] = f32x4{t.m, __int_as_float(t.bi), NEG_BIG, 0.f};
     }
   }
-  if (EPI == EPI_RESID) {  // the workgroup's share of sum h^2 per row: each half of its column tiles in ascending order, then the two
+  if (EPI == EPI_RESID) {  // the workgroup's share of sum h^2 per row, in one chunk or two: each half of its column tiles in ascending order, then the two
     __syncthreads();
+    const bool two = two_chunks && BF % 4 == 0;
+    const int nch = two ? (NT + BF / 2 - 1) / (BF / 2) : nblocks;
     for (int r = tid; r < AT * 16 && m_lo + r < M; r += TPB) {
-      float ss[2] = {0.f, 0.f};
+      float* dst = e.ssq_out + (size_t)(m_lo + r) * nch + (two ? cb * 2 : cb);
+      if (!two) {
+        float ss[2] = {0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < BF; ++j) ss[j >= BF / 2] += s_ssq[j * AT * 16 + r];
-      e.ssq_out[(size_t)(m_lo + r) * nblocks + cb] = ss[0] + ss[1];
+        for (int j = 0; j < BF; ++j) ss[j >= BF / 2] += s_ssq[j * AT * 16 + r];
+        dst[0] = ss[0] + ss[1];
+      } else {
+        float ss[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < BF; ++j) ss[j / ((BF + 3) / 4)] += s_ssq[j * AT * 16 + r];
+        dst[0] = ss[0] + ss[1];
+        if (cb * 2 + 1 < nch) dst[1] = ss[2] + ss[3];
+      }
     }
   }
 }
 
-template <int WM, int WN, int RW, int CW, int KB, int EPI>
+template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER>
 void launch_tile(const op_t* xt, const op_t* wt, int M, int N, int K, const MacroPlan& p, const GemmEpi& e, hipStream_t st) {
   typedef MacroShape<WM, WN, RW, CW, KB> SH;
   static bool configured = false;  // raise the dynamic LDS limit of this instantiation once
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_macro_kernel<WM, WN, RW, CW, KB, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
+    (void)hipFuncSetAttribute((const void*)gemm_macro_kernel<WM, WN, RW, CW, KB, EPI, ORDER>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
     configured = true;
   }
   const int grid = (p.nblocks * p.mblocks * p.splits + 7) / 8 * 8;
-  DLM_LAUNCH((gemm_macro_kernel<WM, WN, RW, CW, KB, EPI>), grid, SH::TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K, weight_pack_rows(N) - 1,
-             p.nblocks, p.mblocks, p.splits, p.kps, e);
+  DLM_LAUNCH((gemm_macro_kernel<WM, WN, RW, CW, KB, EPI, ORDER>), grid, SH::TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
+             (weight_pack_rows(N) - 1) | (p.ssq_parts == 2 ? 2 : 0) | p.fold << 2, p.nblocks, p.mblocks, p.splits, p.kps, e);
 }
 
 }  // namespace
@@ -394,7 +440,10 @@ void launch_macro_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const
   int i = 0;
 #define GO(WM, WN, RW, CW, KB, NS1, NS4)                                                                                       \
   if constexpr (EPI != EPI_STATS || 16 * WM * RW <= GEMM_STATS_MAX_ROWS) {                                                     \
-    if (p.tile == i) return launch_tile<WM, WN, RW, CW, KB, EPI>(xt, wt, M, N, K, p, e, st);                                  \
+    if constexpr (EPI != EPI_STATS && macro_can_keep_order(WM, WN, KB)) {                                                      \
+      if (p.tile == i && (p.fold || p.ssq_parts > 1)) return launch_tile<WM, WN, RW, CW, KB, EPI, true>(xt, wt, M, N, K, p, e, st); \
+    }                                                                                                                          \
+    if (p.tile == i) return launch_tile<WM, WN, RW, CW, KB, EPI, false>(xt, wt, M, N, K, p, e, st);                           \
   }                                                                                                                            \
   ++i;
   MACRO_TILES(GO)

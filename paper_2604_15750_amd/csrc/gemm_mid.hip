@@ -378,6 +378,10 @@ bool gemm_mid_one_round(int M, int N, int K) {
   const MidPlan p = mid_plan(M, N, K);
   return p.groups * p.splits <= 256;
 }
+GemmPlan gemm_mid_plan(int M, int N, int K) {
+  const MidPlan p = mid_plan(M, N, K);
+  return GemmPlan{0, 16 * p.mt, 16 * p.ct, p.splits, p.splits, p.groups * p.splits, 1};
+}
 int gemm_mid_splits(int M, int N, int K) { return mid_plan(M, N, K).splits; }
 int gemm_mid_ssq_chunks(int M, int N, int K) { return mid_plan(M, N, K).groups; }
 int gemm_mid_counters(int max_n) { return (max_n + 31) / 32; }  // 32-column groups are the narrowest

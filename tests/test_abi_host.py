@@ -164,9 +164,28 @@ def test_whole_row_statistics_only_where_they_save_a_merge_and_read_in_vectors(d
     assert whole == {152, 153, 192, 255, 256}
 
 
+LAYER_SHAPES = [(12288, 4096, "qkv"), (4096, 4096, "resid"), (24576, 4096, "swiglu"), (4096, 12288, "resid"),  # an 8B model's layer
+                (4608, 3584, "qkv"), (3584, 3584, "resid"), (37888, 3584, "swiglu"), (3584, 18944, "resid")]   # a 7B one's, grouped-query
+
+
+@pytest.mark.parametrize("N,K,epi", LAYER_SHAPES)
+def test_no_k_split_beyond_one_round_of_workgroups(N, K, epi):
+    """A K split is there to fill idle compute units: its workgroups are never more than the 256 of them, at any row count, and where
+    the order of a wide pass's sums asks for two parts of K beyond that, one workgroup keeps both.  Narrow matrices whose tiles fit
+    one round of any kind take one."""
+    for M in range(1, 3073, 7):
+        p = api.plan_gemm(M, N, K, epi)
+        assert p["splits"] == 1 or p["workgroups"] <= 256, (M, p)
+        assert p["splits"] == p["k_parts"] or (p["splits"], p["k_parts"]) == (1, 2)
+        if p["kernel"] == "macro" and N <= 4608 and M <= 2048:
+            assert p["workgroups"] <= 256, (M, p)
+
+
 def test_launch_rule_argument_errors():
     L = api.lib()
-    out = (C.c_int32 * 3)()
+    out = (C.c_int32 * 7)()
+    assert L.dlm_plan_gemm(8, 64, 64, 3, None) == -1 and L.dlm_plan_gemm(8, 64, 64, 6, out) == -1
+    assert L.dlm_plan_gemm(8, 48, 64, 3, out) == -2 and L.dlm_plan_gemm(0, 64, 64, 3, out) == -2
     assert L.dlm_plan_vocab_stats(8, 1024, 0, None) == -1 and L.dlm_plan_vocab_stats(8, 1024, 2, out) == -1
     assert L.dlm_plan_vocab_stats(0, 1024, 0, out) == -2 and L.dlm_plan_vocab_stats(8, 1, 0, out) == -2
     assert L.dlm_plan_attention(8, 1, 32, 128, None) == -1

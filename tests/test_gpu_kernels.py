@@ -78,6 +78,25 @@ def test_gemm_macro_tiles(device, M, N, K):
     assert torch.equal(y, again)
 
 
+@pytest.mark.parametrize("rows,N,K", [((512, 1345), 4096, 12288), ((796,), 384, 2080), ((653,), 5504, 3616)])
+def test_gemm_k_in_two_parts(device, rows, N, K):
+    """K summed in two parts by two workgroups or by one: the same order, so the rows that two launches share are equal bit for bit.
+    The narrow shapes have an odd number of k-tiles, most of which the first part gets.  Bound as in test_gemm_macro_tiles."""
+    g = torch.Generator(device=device).manual_seed(N + K)
+    x = torch.randn(max(rows), K, generator=g, device=device).to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g, device=device) * 0.05).to(torch.bfloat16)
+    ref = torch.cat([x.double() @ w[lo:lo + 512].double().t() for lo in range(0, N, 512)], -1)
+    got = []
+    for M in rows:
+        p = api.plan_gemm(M, N, K, "sum")
+        assert p["kernel"] == "macro" and p["k_parts"] == 2 and p["splits"] == (2 if M == 512 else 1), p
+        y = api.dlm_gemm_nt(x[:M].contiguous(), w)
+        torch.cuda.synchronize()
+        assert ((y.double() - ref[:M]).abs() <= 2.0 ** -8 * ref[:M].abs() + K * 2.0 ** -24 * 0.05 * K ** 0.5).all()
+        got.append(y)
+    assert all(torch.equal(y[:rows[0]], got[0]) for y in got)
+
+
 @pytest.mark.parametrize("M", [8, 100, 300])
 def test_gemm_operand_conversion_at_the_ends_of_halfs_range(device, M):
     """A bf16 model's matrix-core operands are IEEE half.  Weights far below half's smallest normal number (2^-14) land on its

@@ -428,6 +428,37 @@ def test_packed_spans_of_one_and_more_query_tiles(device, spans):
     model.close()
 
 
+def _one_pass_matches(cfg, M, device, seed):
+    """One pass of M rows of one sequence without a prefix: every row's logits against the oracle's."""
+    W = _weights(cfg, seed, device)
+    model = api.Model(cfg, W)
+    state = api.State(model, 1, M, M, 8)
+    out = api.StepOutputs(M, cfg["vocab"], model.torch_dtype, device)
+    tokens = torch.randint(0, cfg["vocab"] - 1, (M,), generator=torch.Generator().manual_seed(seed), dtype=torch.int32)
+    api.dlm_step(state, tokens.to(device), out, [0, M], [0], [0], [0])
+    torch.cuda.synchronize()
+    z = o_fwd.widen(inputs.tensor_to_numpy(out.logits))
+    ref = o_fwd.forward_span(cfg, inputs.weights_to_numpy(W), o_fwd.KVCache(cfg), tokens.numpy(), 0, 0)
+    scale = np.maximum(np.abs(ref).max(-1, keepdims=True), SIGMA_LOGIT)
+    assert (np.abs(z - ref) <= 2e-2 * scale).all(), (np.abs(z - ref) / scale).max()
+    state.close()
+    model.close()
+
+
+@pytest.mark.parametrize("dims,M,N,K,epi,expect", [
+    # K of the down projection, and of QKV, in two parts kept by one workgroup
+    ((1, 512, 4, 2, 128, 2048, 256), 497, 512, 2048, "resid", dict(splits=1, k_parts=2)),
+    ((1, 2048, 6, 2, 128, 512, 256), 770, 1280, 2048, "qkv", dict(splits=1, k_parts=2)),
+    # two chunks of the sums of squares per column block (O and down)
+    ((1, 4096, 4, 2, 128, 512, 256), 1300, 4096, 512, "resid", dict(cols=256, ssq_parts=2)),
+])
+def test_order_of_a_wide_passs_sums(device, dims, M, N, K, epi, expect):
+    """The ways a wide pass keeps the order of its sums without a split or a tile of that order; each through the epilogues that use it."""
+    p = api.plan_gemm(M, N, K, epi)
+    assert p["kernel"] == "macro" and all(p[k] == v for k, v in expect.items()), p
+    _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 17)
+
+
 @pytest.mark.parametrize("L", [1, 8, 24, 64])
 def test_statistics_from_the_lm_head_epilogue(device, L):
     """An in-block pass (no row compared, none retained) takes its statistics from the LM head's epilogue: the same pass with that
