@@ -181,6 +181,36 @@ def test_no_k_split_beyond_one_round_of_workgroups(N, K, epi):
             assert p["workgroups"] <= 256, (M, p)
 
 
+def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_there_for():
+    """A retuned planner must not leave a variant without a test."""
+    import test_gpu_kernels as k
+    import test_gpu_step as st
+    tiles = set()
+    for (M, N, K), want in k.MACRO_TILE_SHAPES:
+        p = api.plan_gemm(M, N, K, "sum")
+        assert (p["kernel"], p["rows"], p["cols"], p["splits"]) == ("macro", *want), ((M, N, K), p)
+        tiles.add(want[:2])
+    for (M, N, K), want in k.MID_SHAPES:
+        p = api.plan_gemm(M, N, K, "sum")
+        assert (p["kernel"], p["rows"], p["cols"], p["splits"]) == ("mid", *want), ((M, N, K), p)
+    for s in k.BEYOND_MID:
+        assert api.plan_gemm(*s, "sum")["kernel"] == "macro"
+    for V, L, want in st.HEAD_TILES:
+        p = api.plan_gemm(L, V, 256, "stats")
+        assert (p["rows"], p["cols"]) == want, (V, L, p)
+        tiles.add(want)
+    for epi, want, M, dims in st.EPILOGUE_TILES:
+        assert st.epilogue_tile(epi, M, dims) == want, (epi, M, dims)
+    # every tile that any row count of a few shapes is given
+    used = set()
+    for N, K, epi in LAYER_SHAPES + [(126464, 4096, "direct"), (152064, 3584, "direct"), (126464, 4096, "stats"), (152064, 3584, "stats")]:
+        for M in range(1, 65 if epi == "stats" else 3073, 5):
+            p = api.plan_gemm(M, N, K, epi)
+            if p["kernel"] == "macro":
+                used.add((p["rows"], p["cols"]))
+    assert used <= tiles, used - tiles
+
+
 def test_launch_rule_argument_errors():
     L = api.lib()
     out = (C.c_int32 * 7)()

@@ -38,7 +38,7 @@ def _rowtol(ref, rel, floor=0.0):
                                    (17, 16384, 256), (40, 24576, 1024), (33, 4096, 8192), (64, 256, 12288), (8, 4608, 3584), (16, 6144, 512),
                                    # more than 256 rows: the macro-tile kernel (ragged rows, column tails, both weight packings, short K)
                                    (257, 4096, 4096), (513, 8224, 1024), (700, 160, 4096 + 64), (1100, 640, 64), (384, 12288, 32),
-                                   # ... with 192 x 256 tiles (two or four row blocks of 192 instead of three or six of 128)
+                                   # ... with 192 x 192 tiles
                                    (368, 24576, 256), (700, 12288, 128)])
 def test_gemm_bf16(device, M, N, K):
     g = torch.Generator(device="cpu").manual_seed(M * 7 + N + K)
@@ -56,11 +56,23 @@ def test_gemm_bf16(device, M, N, K):
 # One shape for every tile the macro GEMM's planner has for more than 32 rows, each with a ragged last row block, a ragged last
 # column block, an odd number of k-tiles (13: more than the pipeline has stages) and rows that are no multiple of 16; and K splits
 # of three and four ways, whose workgroups hand their partial tiles to the last arriver, run twice (the tickets reset themselves).
-# (The 32-row tiles serve the LM head: every in-block pass of the step tests.)
-@pytest.mark.parametrize("M,N,K", [(209, 96, 416), (17, 16480, 416), (17, 32864, 416), (259, 10976, 416), (17, 24768, 416), (259, 16608, 416),
-                                   (70, 12704, 416), (129, 8704, 416), (97, 24768, 416), (68, 33088, 416), (17, 40992, 416), (199, 24672, 416),
-                                   (129, 24928, 416), (291, 16448, 416), (133, 16448, 416), (164, 24896, 416), (161, 41024, 416), (387, 16640, 416),
-                                   (257, 24608, 416), (300, 160, 4128), (264, 96, 4128), (290, 4064, 8224)])
+# Each with the tile and the split that it is there for.  (The 32-row tiles serve the LM head: test_statistics_of_every_head_tile.)
+MACRO_TILE_SHAPES = [
+    ((209, 96, 416), (64, 64, 1)), ((97, 8320, 416), (64, 96, 1)), ((17, 32864, 416), (64, 160, 1)), ((259, 10976, 416), (64, 256, 1)),
+    ((130, 12224, 416), (96, 128, 1)), ((259, 16608, 416), (96, 256, 1)), ((70, 12704, 416), (128, 64, 1)), ((129, 8704, 416), (128, 96, 1)),
+    ((97, 24768, 416), (128, 128, 1)), ((68, 33088, 416), (128, 160, 1)), ((17, 40992, 416), (128, 192, 1)), ((199, 24672, 416), (128, 256, 1)),
+    ((129, 24928, 416), (160, 128, 1)), ((291, 16448, 416), (160, 192, 1)), ((133, 16448, 416), (192, 96, 1)), ((164, 24896, 416), (192, 160, 1)),
+    ((161, 41024, 416), (192, 192, 1)), ((387, 16640, 416), (256, 192, 1)), ((257, 24608, 416), (256, 256, 1)),
+    ((300, 160, 4128), (64, 64, 3)), ((264, 96, 4128), (64, 64, 4)), ((290, 4064, 8224), (96, 128, 2))]
+# ... and the mid kernel's: (rows, columns of a group, split); both sides of every row count at which choose_kernel leaves it
+MID_SHAPES = [
+    ((17, 16480, 416), (32, 96, 1)), ((17, 24768, 416), (32, 128, 1)), ((64, 24608, 512), (64, 128, 1)), ((48, 24544, 512), (48, 96, 1)),
+    ((65, 12288, 256), (80, 48, 1)), ((80, 12288, 256), (80, 48, 1)), ((81, 12288, 256), (96, 48, 1)), ((96, 12256, 416), (96, 48, 1)),
+    ((128, 4096, 8224), (128, 64, 4)), ((208, 4096, 992), (208, 32, 1))]
+BEYOND_MID = [(97, 12288, 256), (129, 4096, 8224), (209, 4096, 992)]
+
+
+@pytest.mark.parametrize("M,N,K", [s for s, _ in MACRO_TILE_SHAPES + MID_SHAPES] + BEYOND_MID)
 def test_gemm_macro_tiles(device, M, N, K):
     g = torch.Generator(device="cpu").manual_seed(M + N + K)
     x = torch.randn(M, K, generator=g).to(torch.bfloat16)

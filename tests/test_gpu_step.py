@@ -428,8 +428,9 @@ def test_packed_spans_of_one_and_more_query_tiles(device, spans):
     model.close()
 
 
-def _one_pass_matches(cfg, M, device, seed):
-    """One pass of M rows of one sequence without a prefix: every row's logits against the oracle's."""
+def _one_pass_matches(cfg, M, device, seed, stats=False):
+    """One pass of M rows of one sequence without a prefix: every row's logits against the oracle's, and (stats) the statistics
+    against the oracle's of the logits as written."""
     W = _weights(cfg, seed, device)
     model = api.Model(cfg, W)
     state = api.State(model, 1, M, M, 8)
@@ -441,8 +442,42 @@ def _one_pass_matches(cfg, M, device, seed):
     ref = o_fwd.forward_span(cfg, inputs.weights_to_numpy(W), o_fwd.KVCache(cfg), tokens.numpy(), 0, 0)
     scale = np.maximum(np.abs(ref).max(-1, keepdims=True), SIGMA_LOGIT)
     assert (np.abs(z - ref) <= 2e-2 * scale).all(), (np.abs(z - ref) / scale).max()
+    if stats:
+        st = o_stats.vocab_stats(z, cfg["mask_id"])
+        for key in ("max_logit", "lse", "entropy", "conf"):
+            assert (np.abs(getattr(out, key).cpu().numpy() - st[key]) <= 1e-5 * np.maximum(1.0, np.abs(st[key]))).all(), key
+        assert (out.argmax.cpu().numpy() == st["argmax"]).all()
     state.close()
     model.close()
+
+
+# (epilogue, tile, rows, model dimensions): the layer's epilogues on the wavefront shapes with an odd number of column tiles, whose
+# two halves leave through LDS with different counts, and on the narrowest one; rows and columns ragged
+EPILOGUE_TILES = [
+    ("qkv", (64, 64), 215, (1, 256, 2, 1, 128, 64, 256)), ("qkv", (64, 96), 71, (1, 256, 64, 8, 128, 64, 256)),
+    ("qkv", (64, 160), 260, (1, 256, 48, 4, 128, 64, 256)), ("qkv", (128, 96), 134, (1, 256, 64, 8, 128, 64, 256)),
+    ("qkv", (128, 160), 398, (1, 256, 64, 8, 128, 64, 256)), ("qkv", (128, 192), 398, (1, 256, 32, 32, 128, 64, 256)),
+    ("qkv", (160, 192), 582, (1, 256, 32, 32, 128, 64, 256)), ("qkv", (192, 96), 329, (1, 256, 32, 32, 128, 64, 256)),
+    ("qkv", (192, 160), 513, (1, 256, 32, 32, 128, 64, 256)),
+    ("swiglu", (64, 64), 215, (1, 256, 2, 1, 128, 64, 256)), ("swiglu", (64, 96), 71, (1, 256, 2, 1, 128, 4288, 256)),
+    ("swiglu", (64, 160), 17, (1, 256, 2, 1, 128, 16576, 256)), ("swiglu", (128, 96), 134, (1, 256, 2, 1, 128, 4288, 256)),
+    ("swiglu", (128, 160), 71, (1, 256, 2, 1, 128, 16576, 256)), ("swiglu", (128, 192), 197, (1, 256, 2, 1, 128, 10432, 256)),
+    ("swiglu", (160, 192), 306, (1, 256, 2, 1, 128, 8320, 256)), ("swiglu", (192, 96), 134, (1, 256, 2, 1, 128, 8320, 256)),
+    ("swiglu", (192, 160), 161, (1, 256, 2, 1, 128, 12352, 256)),
+    ("resid", (64, 64), 209, (1, 256, 2, 1, 128, 64, 256)), ("resid", (64, 96), 260, (1, 3328, 2, 1, 128, 64, 256)),
+    ("resid", (64, 160), 260, (1, 5632, 2, 1, 128, 64, 256)), ("resid", (128, 96), 398, (1, 4352, 2, 1, 128, 64, 256))]
+
+
+def epilogue_tile(epi, M, dims):
+    _, d, hq, kv, hd, ffn, _ = dims
+    p = api.plan_gemm(M, *{"qkv": ((hq + 2 * kv) * hd, d), "swiglu": (2 * ffn, d), "resid": (d, ffn)}[epi], epi)
+    return (p["rows"], p["cols"]) if p["kernel"] == "macro" else p["kernel"]
+
+
+@pytest.mark.parametrize("epi,tile,M,dims", EPILOGUE_TILES)
+def test_epilogues_of_odd_wavefront_shapes(device, epi, tile, M, dims):
+    assert epilogue_tile(epi, M, dims) == tile
+    _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 19)
 
 
 @pytest.mark.parametrize("dims,M,N,K,epi,expect", [
@@ -491,6 +526,18 @@ def test_statistics_from_the_lm_head_epilogue(device, L):
         assert (got["argmax"] == st["argmax"]).all() and (got["kl"] == 0).all()
     assert (a["max_logit"] == b["max_logit"]).all()
     model.close()
+
+
+# (vocabulary, rows, tile): every tile the LM head's statistics epilogue has, with a ragged last column block where the tile allows one
+HEAD_TILES = [(64, 1, (64, 64)), (16416, 37, (64, 96)), (24704, 17, (64, 160)), (41696, 24, (32, 256)), (41696, 33, (64, 256)), (67552, 8, (32, 320))]
+
+
+@pytest.mark.parametrize("V,L,tile", HEAD_TILES)
+def test_statistics_of_every_head_tile(device, V, L, tile):
+    cfg = inputs.model_config(1, 256, 2, 2, 128, 64, V, "bf16")
+    p = api.plan_gemm(L, V, 256, "stats")
+    assert (p["rows"], p["cols"]) == tile
+    _one_pass_matches(cfg, L, device, 23, stats=True)
 
 
 def test_sweep_harness_reports_the_oracles_counts(device):
