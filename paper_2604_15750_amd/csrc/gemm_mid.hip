@@ -301,7 +301,8 @@ MidPlan mid_plan(int M, int N, int K) {
     if (s < 1) s = 1;
     p.kps = (KT + s - 1) / s;
     p.splits = (KT + p.kps - 1) / p.kps;  // no empty split
-    // more groups of the widest kind than compute units (the LM head): several rounds anyway, the widest re-reads X least
+    // as many groups of the widest kind as compute units, or more: the widest re-reads X least (more than one round of them is not
+    // launched: choose_kernel gives such a shape to another kernel)
     if (c == 0 && p.groups >= 256) return p;
     // otherwise, of the group widths, the one whose workgroups fill the chip's 256 compute units best; on a near tie the
     // one without a K split, then the wider
@@ -369,7 +370,7 @@ void launch_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPl
 
 }  // namespace
 
-// one compute unit's worth of workgroups per 96-column group, no K split: the shapes the mid kernel takes even below 17 rows
+// whole rounds of workgroups without a K split, whatever the width of the groups: the shapes the mid kernel takes even below 17 rows
 bool gemm_mid_fills_chip(int M, int N, int K) {
   const MidPlan p = mid_plan(M, N, K);
   return p.splits == 1 && p.groups % 256 == 0;

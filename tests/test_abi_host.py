@@ -181,6 +181,16 @@ def test_no_k_split_beyond_one_round_of_workgroups(N, K, epi):
             assert p["workgroups"] <= 256, (M, p)
 
 
+def test_paired_column_tiles_leave_the_skinny_kernel_at_17_rows():
+    """Beyond 16 rows the skinny kernel is built for single column tiles only."""
+    for M in (17, 24, 32, 33, 48, 49, 64, 65, 200, 384):
+        for N in list(range(32, 60000, 32 * 17)) + [8192, 8224, 12288, 24576, 37888, 4608]:
+            for K in (32, 512, 3584, 8192, 18944):
+                for epi in ("qkv", "swiglu", "resid", "sum"):
+                    p = api.plan_gemm(M, N, K, epi)
+                    assert p["kernel"] != "skinny" or p["cols"] == 16, (M, N, K, epi)
+
+
 def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_there_for():
     """A retuned planner must not leave a variant without a test."""
     import test_gpu_kernels as k
