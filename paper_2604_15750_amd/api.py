@@ -126,8 +126,14 @@ def _packed(v):
         return bytes(_ints(v))
 
 
+# what torch.cuda.current_stream() asks, without its Stream object (0.7 us of a call); a private name, so the public way stays beside it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())  # (torch.cuda.current_stream() without its Stream object)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def dtype_code(t):

@@ -129,6 +129,14 @@ def test_packed_host_arrays(v):
     assert api._packed(None) is None
 
 
+def test_current_stream_without_torchs_private_query(monkeypatch):
+    class Stream:
+        cuda_stream = 0x1234
+    monkeypatch.setattr(api, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    assert api._stream() == 0x1234
+
+
 # ---- launch rules (host arithmetic) ---------------------------------------------------------------
 @pytest.mark.parametrize("hd", [32, 64, 128])
 @pytest.mark.parametrize("n_q", [1, 4, 16, 28, 32, 64])

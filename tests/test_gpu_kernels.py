@@ -383,6 +383,17 @@ def test_select_parallel_chain_of_conflicts(device, L):
     assert (tok.cpu().numpy() == np.where(ref, y.numpy(), mask_id)).all()
 
 
+# ---- streams ---------------------------------------------------------------------------------------
+def test_calls_run_on_the_current_stream(device, monkeypatch):
+    """Both ways to ask for the current stream name it, inside and outside a stream context."""
+    side = torch.cuda.Stream()
+    for raw in (api._raw_stream, None):
+        monkeypatch.setattr(api, "_raw_stream", raw)
+        assert api._stream() == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert api._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+
+
 # ---- measurement helpers --------------------------------------------------------------------------
 def test_probes_report_plausible_rates(device):
     """The two probes bench.py quotes rooflines against: a plain streaming read reaches most of, and no more than, the
