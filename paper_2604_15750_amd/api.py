@@ -126,7 +126,7 @@ def _packed(v):
         return bytes(_ints(v))
 
 
-# what torch.cuda.current_stream() asks, without its Stream object (0.7 us of a call); a private name, so the public way stays beside it
+# what torch.cuda.current_stream() asks, without its Stream object (0.3 us against 2.7); a private name, so the public way stays beside it
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
