@@ -238,7 +238,7 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
 }
 
 constexpr int MAX_CHUNKS = 32;
-constexpr int ROW_MIN = 152, ROW_MAX = 256;  // rows that can get a workgroup of 1024 threads each (stats_plan)
+constexpr int ROW_MIN = 136, ROW_MAX = 256;  // rows that can get a workgroup of 1024 threads each (stats_plan)
 
 template <typename T, int TPB, bool VECTOR>
 void launch_items(const T* logits, int rows, int vocab, int mask_id, const StatsPlan& p, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
@@ -264,8 +264,10 @@ void launch_stats_merge(const void* parts, int rows, int nparts, int vocab, cons
 //   bf16, 126464 tokens: 96 rows 13.0 -> 16.6 / 15.8 -> 20.4, 128: 16.2 -> 17.3 / 20.1 -> 20.8, 160: 18.2 -> 17.8 / 22.6 -> 20.9,
 //   192: 17.6 -> 17.9 / 22.6 -> 21.6, 256: 22.2 -> 18.3 / 28.8 -> 24.9; 272 rows: 22.7 -> 31.2 / 31.4 -> 42.9 (a second round of
 //   workgroups, as two of 1024 threads don't fit into a unit's registers).  Over 20 shapes the mean of whole / chunks is 1.07 at
-//   104 rows, 0.96 at 136, 0.93 at 152, 0.89 at 184; at 136 and 144 rows single shapes still lose 7 and 3 %, from 152 on one does
-//   (152064 tokens, bf16, no previous row, 160 rows: 17.7 -> 18.8, the cut into chunks being an even one there).
+//   104 rows, 0.96 at 136, 0.93 at 152, 0.89 at 184; below 152 rows single shapes still lose up to 7 % on given logits (126464 tokens,
+//   bf16, no previous row, 136 rows: 16.5 -> 17.3).  Within dlm_step, behind the LM head that has just written the logits, the two
+//   meet at about 130 rows (launches included, 104 rows: 24.6 -> 26.4, 114: 27.0 -> 28.8, 132: 29.3 -> 28.5, 147: 28.0 -> 24.9, 148: 30.5
+//   -> 28.7).  The line is the first row count at which both means are ahead.
 // Without 16-byte vectors a lane has one scalar load in flight, and fewer lanes are what it loses by: 126463 tokens, bf16, 96 rows
 //   20.5 -> 34.6 / 23.5 -> 58.9, 256: 44.2 -> 55.2 / 48.0 -> 60.0.  With one chunk the larger workgroup has nothing to save:
 //   1024 tokens, fp32, 96 .. 256 rows 4.4 -> 6.4.
