@@ -21,6 +21,7 @@ struct SumOrder {
   int splits, bt;
 };
 SumOrder sum_order(int mt, int N, int K, bool may_split) {
+  // rows x columns; weight of a product; of two workgroups, and of one, that share a compute unit
   const struct { int bm, bn; double rel, pair, single; } tiles[] = {{256, 256, 0.63, 0, 0}, {128, 256, 1.0, 1.45, 1.15}, {128, 128, 0.96, 1.83, 1.12},
                                                                     {192, 256, 0.86, 0, 0}, {256, 192, 0.72, 0, 0},      {192, 192, 0.83, 0, 0}};
   const int M = mt * 16, KT = K >> 5;
