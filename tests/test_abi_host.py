@@ -189,6 +189,12 @@ def test_no_k_split_beyond_one_round_of_workgroups(N, K, epi):
             assert p["workgroups"] <= 256, (M, p)
 
 
+def test_gated_launches_take_fewer_rounds_where_the_estimates_are_close():
+    for M in (481, 500, 512):  # two rounds of 256 x 192, not three of 128 x 256
+        p = api.plan_gemm(M, 37888, 3584, "swiglu")
+        assert (p["rows"], p["cols"], p["workgroups"]) == (256, 192, 396), (M, p)
+
+
 def test_paired_column_tiles_leave_the_skinny_kernel_at_17_rows():
     """Beyond 16 rows the skinny kernel is built for single column tiles only."""
     for M in (17, 24, 32, 33, 48, 49, 64, 65, 200, 384):
