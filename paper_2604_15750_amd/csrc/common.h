@@ -153,7 +153,7 @@ void launch_pack_weight_steps(const bf16_t* w, op_t* out, int N, int K, int ct, 
 int gemm_bf16_steps_ct(int N, int K, int kind);  // ct of that layout for (N, K) under epilogue `kind`, 0 if the kernel that serves 16 rows has none
 int gemm_mid_steps_ct(int N, int K);   // ... if the mid kernel serves (N, K) at up to 16 rows without a K split, else 0
 void launch_pack_act(const bf16_t* x, op_t* out, int M, int K, hipStream_t st);  // row-major bf16 -> fragment tiles in half (rows padded to 16 with zeros)
-int gemm_bf16_splits(int M, int N, int K, int kind);  // partial tiles [splits][M][N] the launch of this shape and epilogue needs in GemmEpi::part (1: none)
+size_t gemm_bf16_part_elems(int M, int N, int K, int kind);  // floats of GemmEpi::part a launch of this shape and epilogue needs (0: it does not split K)
 int gemm_bf16_ssq_chunks(int M, int N, int K);     // chunks per row of the sums of squares an EPI_RESID launch of this shape writes
 int gemm_bf16_counters(int max_n);                 // counters a state needs in GemmEpi::counters (zero-initialised, self-resetting)
 // rs (optional): every output row m is multiplied by rsqrt(sum_c rs.ssq[m][c] * rs.inv_d + rs.eps).
@@ -166,7 +166,7 @@ enum { EPI_DIRECT = 0, EPI_QKV = 1, EPI_SWIGLU = 2, EPI_RESID = 3, EPI_SUM = 4, 
 // What the bf16 GEMM does with a finished output tile (see gemm_bf16.hip).
 struct GemmEpi {
   int kind;
-  float* part;        // [gemm_bf16_splits][M][N] fp32 partial tiles of a launch that splits K
+  float* part;        // gemm_bf16_part_elems floats: the partial tiles of a launch that splits K
   int* counters;      // gemm_bf16_counters tickets of such a launch
   RowScale rs;        // 1/rms of the GEMM's input rows (QKV, SWIGLU, DIRECT, SUM; ssq may be null)
   // EPI_QKV (weights packed with PERM_ROTARY)
@@ -212,7 +212,7 @@ extern thread_local LaunchStamp g_launch_stamp;
 void launch_gemm_bf16(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);
 #define GEMM_SKINNY_MAX_ROWS 64
 void launch_gemm_skinny(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, const GemmEpi& e, hipStream_t st);  // M <= GEMM_SKINNY_MAX_ROWS
-int gemm_mid_splits(int M, int N, int K);
+size_t gemm_mid_part_elems(int M, int N, int K);
 int gemm_mid_ssq_chunks(int M, int N, int K);
 bool gemm_mid_fills_chip(int M, int N, int K);  // its column groups are a whole number of rounds over the compute units, without a K split
 bool gemm_mid_one_round(int M, int N, int K);   // its workgroups are at most one round
@@ -228,7 +228,7 @@ struct GemmPlan {
 GemmPlan gemm_macro_plan(int M, int N, int K, int kind);  // (kernel left to the caller)
 GemmPlan gemm_mid_plan(int M, int N, int K);
 GemmPlan gemm_bf16_plan(int M, int N, int K, int kind);
-int gemm_macro_splits(int M, int N, int K, int kind);
+size_t gemm_macro_part_elems(int M, int N, int K, int kind);
 int gemm_macro_stat_parts(int M, int N, int K);
 int gemm_macro_counters();
 void launch_gemm_macro(const op_t* xt, const op_t* wt, int M, int N, int K, const GemmEpi& e, hipStream_t st);

@@ -257,17 +257,15 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
   s->head_stride = (size_t)((max_seq_len + 31) / 32 * 32) * c.head_dim;
   s->slot_stride = c.dtype == DLM_BF16 ? s->head_stride * c.n_kv_heads : (size_t)max_seq_len * kvw;
   s->layer_stride = s->slot_stride * max_seqs;
-  // split-K workspace: the largest [splits][rows][N] over the four per-layer GEMMs
+  // split-K workspace: the partial tiles of the widest split launch over the four per-layer GEMMs
   size_t pe = 0;
   const int shapes[4][3] = {{qkv, c.d_model, EPI_QKV}, {c.d_model, qd, EPI_RESID}, {2 * c.d_ffn, c.d_model, EPI_SWIGLU}, {c.d_model, c.d_ffn, EPI_RESID}};
   for (auto& sh : shapes) {
-    size_t e = 0;
     if (c.dtype == DLM_BF16)
-      for (int mt = 1; mt <= (max_rows + 15) / 16; ++mt) {  // the split count depends on the rows only through their 16-row tiles
-        const int rows = mt * 16 < max_rows ? mt * 16 : max_rows, sp = gemm_bf16_splits(rows, sh[0], sh[1], sh[2]);
-        if (sp > 1 && (size_t)sp * rows * sh[0] > e) e = (size_t)sp * rows * sh[0];
+      for (int mt = 1; mt <= (max_rows + 15) / 16; ++mt) {  // a plan depends on the rows only through their 16-row tiles
+        const size_t e = gemm_bf16_part_elems(mt * 16 < max_rows ? mt * 16 : max_rows, sh[0], sh[1], sh[2]);
+        if (e > pe) pe = e;
       }
-    if (e > pe) pe = e;
   }
   s->part_elems = pe;
   const int xw = c.d_model > qd ? c.d_model : qd;
@@ -461,8 +459,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   {
     const int shapes[4][3] = {{qd + 2 * nkv * hd, dm, EPI_QKV}, {dm, qd, EPI_RESID}, {2 * ffn, dm, EPI_SWIGLU}, {dm, ffn, EPI_RESID}};
     for (auto& sh : shapes) {
-      const int sp = gemm_bf16_splits(rows, sh[0], sh[1], sh[2]);
-      if (sp > 1 && (size_t)sp * rows * sh[0] > s->part_elems)
+      if (gemm_bf16_part_elems(rows, sh[0], sh[1], sh[2]) > s->part_elems)
         return dlm_fail(DLM_ECAPACITY, "dlm_step: split-K workspace too small for %d rows x %d columns", rows, sh[0]);
     }
   }
@@ -725,7 +722,7 @@ extern "C" int dlm_gemm_nt(const void* x, const void* w, void* y, int M, int N, 
   const size_t mp = (size_t)(M + 15) / 16 * 16;
   const int n_counters = gemm_bf16_counters(N);
   const size_t tiled_bytes = ((mp * K + (size_t)N * K) * 2 + 15) / 16 * 16;
-  const size_t part_bytes = (size_t)gemm_bf16_splits(M, N, K, EPI_SUM) * M * N * 4;
+  const size_t part_elems = gemm_bf16_part_elems(M, N, K, EPI_SUM), part_bytes = part_elems * 4;
   void* ws = nullptr;
   if (hipMalloc(&ws, tiled_bytes + part_bytes + (size_t)n_counters * 4) != hipSuccess) { (void)hipGetLastError(); return dlm_fail(DLM_ENOMEM, "dlm_gemm_nt: workspace allocation failed"); }
   op_t* xt = (op_t*)ws;
@@ -733,7 +730,6 @@ extern "C" int dlm_gemm_nt(const void* x, const void* w, void* y, int M, int N, 
   float* part = (float*)((char*)ws + tiled_bytes);
   launch_pack_act((const bf16_t*)x, xt, M, K, st);
   launch_pack_weight((const bf16_t*)w, wt, N, K, PERM_NONE, 0, st);
-  const int splits = gemm_bf16_splits(M, N, K, EPI_SUM);
   GemmEpi ge;
   memset(&ge, 0, sizeof ge);
   ge.out_bf16 = (bf16_t*)y;
@@ -741,7 +737,7 @@ extern "C" int dlm_gemm_nt(const void* x, const void* w, void* y, int M, int N, 
   // partial tiles and ticket counters (used when a launch splits K) follow the tiled operands in the scratch
   ge.kind = EPI_SUM;
   ge.part = part;
-  ge.counters = (int*)(part + (size_t)splits * M * N);
+  ge.counters = (int*)(part + part_elems);
   e = hipMemsetAsync(ge.counters, 0, (size_t)n_counters * 4, st);
   launch_gemm_bf16(xt, wt, M, N, K, ge, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);

@@ -135,11 +135,11 @@ GemmPlan gemm_bf16_plan(int M, int N, int K, int kind) {
   p.kernel = k;
   return p;
 }
-int gemm_bf16_splits(int M, int N, int K, int kind) {
+size_t gemm_bf16_part_elems(int M, int N, int K, int kind) {
   switch (choose_kernel(M, N, K, kind)) {
-    case KERNEL_MID: return gemm_mid_splits(M, N, K);
-    case KERNEL_MACRO: return gemm_macro_splits(M, N, K, kind);
-    default: return 1;
+    case KERNEL_MID: return gemm_mid_part_elems(M, N, K);
+    case KERNEL_MACRO: return gemm_macro_part_elems(M, N, K, kind);
+    default: return 0;
   }
 }
 int gemm_bf16_ssq_chunks(int M, int N, int K) {

@@ -35,33 +35,40 @@ __device__ inline void block_rinv(const RowScale& rs, int m_lo, int rows, float*
   }
 }
 
-// block_rinv for a workgroup of NT threads and at most ROWS rows with every load of a thread issued before the first is used
-// (one trip to memory): sixteen lanes per row, each adding every sixteenth chunk in ascending order, then the same fixed
-// butterfly.  Up to 64 chunks per row in one trip (what the wide-pass producers write); more fall back to block_rinv.
+// block_rinv in two parts, for a workgroup of NT threads and at most ROWS rows of up to 64 chunks each (what the wide-pass
+// producers write), so that a kernel can do its work in between: fetch issues all of a thread's loads, publish adds them (sixteen
+// lanes per row, each every sixteenth chunk in ascending order, then block_rinv's butterfly, here by lane rotation: after the
+// first step the values repeat every eight lanes, and so on, so the sums are the same) and writes the rows' values.
 template <int NT, int ROWS>
-__device__ inline void block_rinv_batched(const RowScale& rs, int m_lo, int rows, float* s_rinv) {
-  if (rs.ssq && rs.nch > 64) { block_rinv<NT>(rs, m_lo, rows, s_rinv); return; }
-  constexpr int RPT = (ROWS + NT / 16 - 1) / (NT / 16);  // rows per thread
-  const int sub = threadIdx.x & 15;
+struct RinvBatch {
+  static constexpr int RPT = (ROWS + NT / 16 - 1) / (NT / 16);  // rows per thread
   float v[RPT][4];
+  __device__ __attribute__((always_inline)) inline void fetch(const RowScale& rs, int m_lo, int rows) {
+    const int sub = threadIdx.x & 15;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const int row = (threadIdx.x >> 4) + r * (NT / 16);
+    for (int r = 0; r < RPT; ++r) {
+      const int row = (threadIdx.x >> 4) + r * (NT / 16);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int c = sub + 16 * k;
-      v[r][k] = (rs.ssq && row < rows && c < rs.nch) ? rs.ssq[(size_t)(m_lo + row) * rs.nch + c] : 0.f;
+      for (int k = 0; k < 4; ++k) {
+        const int c = sub + 16 * k;
+        v[r][k] = (rs.ssq && row < rows && c < rs.nch) ? rs.ssq[(size_t)(m_lo + row) * rs.nch + c] : 0.f;
+      }
     }
   }
-#pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    const int row = (threadIdx.x >> 4) + r * (NT / 16);
-    float ss = ((v[r][0] + v[r][1]) + v[r][2]) + v[r][3];
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-    if (sub == 0 && row < rows) s_rinv[row] = rs.ssq ? rsqrtf(ss * rs.inv_d + rs.eps) : 1.f;
+  template <int CTRL>
+  static __device__ inline float rotate_add(float a) {
+    return a + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), CTRL, 0xf, 0xf, false));
   }
-}
+  __device__ __attribute__((always_inline)) inline void publish(const RowScale& rs, int rows, float* s_rinv) const {
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      const int row = (threadIdx.x >> 4) + r * (NT / 16);
+      // row_ror:8, 4, 2, 1
+      const float ss = rotate_add<0x121>(rotate_add<0x122>(rotate_add<0x124>(rotate_add<0x128>(((v[r][0] + v[r][1]) + v[r][2]) + v[r][3]))));
+      if ((threadIdx.x & 15) == 0 && row < rows) s_rinv[row] = rs.ssq ? rsqrtf(ss * rs.inv_d + rs.eps) : 1.f;
+    }
+  }
+};
 
 // What an epilogue reads from memory besides the product, fetched ahead (at the start of the kernel, while the first weights
 // are in flight) for the fragment a wavefront finishes first, so that the end of a short kernel does not wait for a round

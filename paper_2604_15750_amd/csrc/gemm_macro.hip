@@ -109,7 +109,11 @@ GemmPlan gemm_macro_plan(int M, int N, int K, int kind) {
   const MacroTile& t = g_tiles[p.tile];
   return GemmPlan{0, 16 * t.rw * t.wm, 16 * t.cw * t.wn, p.splits, p.fold ? 2 : p.splits, p.nblocks * p.mblocks * p.splits, p.ssq_parts};
 }
-int gemm_macro_splits(int M, int N, int K, int kind) { return macro_plan(M, N, K, kind).splits; }
+size_t gemm_macro_part_elems(int M, int N, int K, int kind) {
+  const MacroPlan p = macro_plan(M, N, K, kind);
+  const MacroTile& t = g_tiles[p.tile];
+  return p.splits > 1 ? (size_t)p.splits * p.nblocks * p.mblocks * (t.rw * t.wm) * (t.cw * t.wn) * 256 : 0;
+}
 int gemm_macro_stat_parts(int M, int N, int K) { return macro_plan(M, N, K, EPI_STATS).nblocks; }
 int gemm_macro_counters() { return 2 * MAX_SPLIT_TILES; }  // two per tile of a launch that splits K
 

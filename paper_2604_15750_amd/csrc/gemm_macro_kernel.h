@@ -105,12 +105,12 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   float* s_ssq = s_rinv + AT * 16;           // [BF][AT * 16]
   __shared__ int s_ticket;
 
-  // Workgroup id -> (column block, K split, row block), row blocks fastest.  Ids congruent mod 8 share an XCD: each XCD takes one
+  // Workgroup id -> (K split, column block, row block), row blocks fastest.  Ids congruent mod 8 share an XCD: each XCD takes one
   // contiguous eighth of the tiles, so the row blocks of a column block (which stream the same W) meet in one L2 and no XCD has
-  // more than its share.
-  const int total = nblocks * mblocks * splits, lin = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  if (lin >= total) return;
-  const int rb = lin % mblocks, cs = lin / mblocks, split = cs % splits, cb = cs / splits;
+  // more than its share; with a K split it walks one part of K (or few), so that X's other parts never enter its L2.
+  const int tiles = nblocks * mblocks, lin = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (lin >= tiles * splits) return;
+  const int split = lin / tiles, tile = lin - split * tiles, cb = tile / mblocks, rb = tile - cb * mblocks;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / CW, wn = wave % CW;
@@ -163,10 +163,29 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
       for (int i = 0; i < WM; ++i) acc[j][i] = mfma_op(wf[set][j], xf[set][i], acc[j][i]);
   };
 
-  // 1/rms of the workgroup's input rows, needed only by the epilogue: fetched before the pipeline starts (its loads are counted
-  // by the compiler, the pipeline's by hand: the two must not be in flight together), all of a thread's loads in one trip;
-  // published to the other wavefronts by the loop's barriers
-  if (EPI != EPI_RESID) block_rinv_batched<TPB, AT * 16>(e.rs, m_lo, max(0, min(M, m_lo + AT * 16) - m_lo), s_rinv);
+  // K split: a ticket per workgroup and tile, taken here, where its trip to memory hides behind the pipeline's start
+  int my_ticket = 0;
+  if constexpr (WM * WN <= MACRO_SPLIT_FRAGS) {
+    if (splits > 1 && tid == 0) my_ticket = __hip_atomic_fetch_add(e.counters + 2 * tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+
+  // 1/rms of the workgroup's input rows, needed only by the epilogue: fetched ahead of the pipeline's loads, in one trip where a row
+  // has up to 64 chunks (wide passes).  Where the registers hold what was fetched, it stays there until the loop is over (touching
+  // it while copies to LDS are in flight would make the compiler wait for all of them); published to the other wavefronts by
+  // the barrier of the epilogue, or by the loop's.
+  typedef RinvBatch<TPB, AT * 16> Rinv;
+  constexpr bool RINV_LATE = 4 * WM * WN + 8 * (WM + WN) + 4 * Rinv::RPT <= 210;
+  const int rows = max(0, min(M, m_lo + AT * 16) - m_lo);
+  const bool rinv_batched = EPI != EPI_RESID && !(e.rs.ssq && e.rs.nch > 64);
+  Rinv rinv;
+  if (EPI != EPI_RESID) {
+    if (rinv_batched) {
+      rinv.fetch(e.rs, m_lo, rows);
+      if (!RINV_LATE) rinv.publish(e.rs, rows, s_rinv);
+    } else {
+      block_rinv<TPB>(e.rs, m_lo, rows, s_rinv);
+    }
+  }
 
 #pragma unroll
   for (int s = 0; s < S - 1; ++s) issue(s, s, 0, LPS);
@@ -264,29 +283,32 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
 
   const int g = lane >> 4, ml = lane & 15;
   if constexpr (WM * WN <= MACRO_SPLIT_FRAGS) if (splits > 1) {
-    // K split (shapes whose tiles cover less than the chip).  Every workgroup of a tile takes a ticket; all but the last to arrive
-    // write their partial tile to the fp32 workspace, in the accumulator layout and through to device scope, and then raise the
-    // tile's count of finished partials.  The last one keeps its own in registers, waits for that count (every workgroup it
-    // waits for has taken its ticket, so it is running and finishes without waiting for anyone), adds the partial tiles in
-    // split order, its own in its place (deterministic whoever is last), and runs the epilogue.
-    const size_t stride = (size_t)M * N;
-    auto offset = [&](int j, int i) { return ((unsigned)((wm * WM + i) * 16 + ml) * N + (nt0 + wn * WN + j) * 16 + 4 * g) * 4u; };
-    auto exists = [&](int j, int i) { return nt0 + wn * WN + j < NT && m_lo + (wm * WM + i) * 16 + ml < M; };
-    int* ticket = e.counters + 2 * (cb * mblocks + rb);
-    if (tid == 0) s_ticket = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // K split (shapes whose tiles cover less than the chip).  The workgroup that took a tile's last ticket finishes it; the others
+    // write their partial tile to the fp32 workspace, whole fragments in the accumulator layout, and then raise the tile's count
+    // of finished partials.  The last one keeps its own in registers, waits for that count (every workgroup it waits for took its
+    // ticket before, so it is running and finishes without waiting for anyone), adds the partial tiles in split order, its own in
+    // its place (deterministic whoever is last), and runs the epilogue.
+    // The hand-off crosses XCDs, whose L2s are separate.  Partials and counts are written and read at device scope themselves (SC1;
+    // relaxed atomics), and a wavefront waits for the acknowledgement of its stores before the barrier in front of the count, so
+    // neither side needs a fence: a release would write back the L2's dirty lines and an acquire drop its clean ones, under
+    // the feet of the workgroups that still multiply.  From the end of the loop to the epilogue 10 us with fences, tickets taken
+    // behind the loop and row-major partials (half lines), 3 to 4 now: down of an 8B model at 384 rows 71 -> 62 us.
+    const unsigned slot = (unsigned)(AT * BF) * 256;  // floats of a tile's partial
+    auto offset = [&](int j, int i) { return (unsigned)((((wm * WM + i) * BF + wn * WN + j) * 64 + lane) * 16); };
+    auto exists = [&](int j, int i) { return nt0 + wn * WN + j < NT && mt0 + wm * WM + i < MTILES; };  // (uniform in the wavefront)
+    int* ticket = e.counters + 2 * tile;
+    if (tid == 0) s_ticket = my_ticket;
     __syncthreads();
     if (s_ticket != splits - 1) {
+      const __amdgpu_buffer_rsrc_t mine = part_rsrc(e.part + (size_t)(split * tiles + tile) * slot);
 #pragma unroll
       for (int j = 0; j < WN; ++j)
 #pragma unroll
         for (int i = 0; i < WM; ++i)
-          if (exists(j, i))
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j][i]), part_rsrc(e.part + split * stride + (size_t)m_lo * N), offset(j, i), 0, SC1);
-      // hand-off across workgroups (possibly across XCDs, whose L2s are separate): every wavefront waits until its own stores,
-      // written through to device scope, have been acknowledged; then the count is raised with release order at device scope
+          if (exists(j, i)) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[j][i]), mine, offset(j, i), 0, SC1);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      if (tid == 0) (void)__hip_atomic_fetch_add(ticket + 1, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) (void)__hip_atomic_fetch_add(ticket + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
     if (tid == 0) {
@@ -295,7 +317,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
       __hip_atomic_store(ticket + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    asm volatile("" ::: "memory");
     f32x4 sum[WN][WM];
 #pragma unroll
     for (int j = 0; j < WN; ++j)
@@ -309,12 +331,12 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
           for (int i = 0; i < WM; ++i) sum[j][i] += acc[j][i];
         continue;
       }
+      const __amdgpu_buffer_rsrc_t theirs = part_rsrc(e.part + (size_t)(s0 * tiles + tile) * slot);
       u32x4 t[WN][WM];
 #pragma unroll
       for (int j = 0; j < WN; ++j)
 #pragma unroll
-        for (int i = 0; i < WM; ++i)
-          t[j][i] = __builtin_amdgcn_raw_buffer_load_b128(part_rsrc(e.part + s0 * stride + (size_t)m_lo * N), exists(j, i) ? offset(j, i) : 0u, 0, SC1);
+        for (int i = 0; i < WM; ++i) t[j][i] = __builtin_amdgcn_raw_buffer_load_b128(theirs, exists(j, i) ? offset(j, i) : 0u, 0, SC1);
 #pragma unroll
       for (int j = 0; j < WN; ++j)
 #pragma unroll
@@ -327,6 +349,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   }
 
   // ---- epilogue
+  if (RINV_LATE && rinv_batched) rinv.publish(e.rs, rows, s_rinv);
   __syncthreads();
   // The accumulators leave the registers through LDS (each wavefront its own region, half of its column tiles at a time), so
   // that the epilogue runs as a loop over fragments instead of WM WN unrolled copies with every accumulator live.

@@ -189,8 +189,8 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   // ---- the four partial accumulators -> one finished (or, with a K split, one partial) value per output fragment
   const int g = lane >> 4, ml = lane & 15;
   f32x4* red = (f32x4*)lds;  // [NWV][FR][64]
-  const size_t stride = (size_t)M * N;
-  float* mine = e.part + split * stride;
+  // K split: partial tiles lie fragment by fragment in the accumulator layout, [split][group][fragment][lane]
+  auto partial = [&](int s) { return part_rsrc(e.part + (size_t)(s * groups + group) * (F * 256)); };
   // fragment f = r * MT + j (column tile r, row tile j) in the accumulator layout -> its epilogue
   auto finish = [&](int f, f32x4 v) {
     const int r = f / MT, j = f - r * MT;
@@ -213,44 +213,42 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
         finish(f, v);
       } else {  // partial tile -> workspace, written through to device scope
         const int r = f / MT, j = f - r * MT;
-        const int nt = nt0 + r, m = j * 16 + ml;
-        if (nt < NT && m < M)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), part_rsrc(mine), ((unsigned)m * N + nt * 16 + 4 * g) * 4u, 0, SC1);
+        if (nt0 + r < NT && j * 16 < M) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), partial(split), (unsigned)(f * 64 + lane) * 16u, 0, SC1);
       }
     }
   }
   if (splits > 1) {
     // Hand-off across workgroups (possibly across XCDs, whose L2s are separate): every wavefront waits until its own partial
-    // stores, written through to device scope, have been acknowledged; then the workgroup takes its ticket with release order
-    // at device scope, and the last arriver reads the partial tiles (device-scope loads) behind an acquire.
+    // stores, written through to device scope, have been acknowledged; then the workgroup takes its ticket, and the last
+    // arriver reads the partial tiles at device scope.  Tickets and data are device-scope accesses themselves, so neither side
+    // needs a fence: a release would write back the L2's dirty lines, an acquire drop its clean ones.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
       int* ticket = e.counters + group;
-      const int last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == splits - 1;
+      const int last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == splits - 1;
       if (last) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
       s_last = last;
     }
     __syncthreads();
     if (!s_last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    asm volatile("" ::: "memory");
     // the finished tile = the partial tiles added in split order; a wavefront fetches one split of all its fragments per trip
     f32x4 v[FW];
     unsigned off[FW];
 #pragma unroll
     for (int i = 0; i < FW; ++i) {
       const int f = wave + NWV * i, r = f / MT, j = f - r * MT;
-      const int nt = nt0 + r, m = j * 16 + ml;
-      off[i] = (f < F && nt < NT && m < M) ? ((unsigned)m * N + nt * 16 + 4 * g) * 4u : 0u;  // fragments that do not exist re-read element 0
+      off[i] = (f < F && nt0 + r < NT && j * 16 < M) ? (unsigned)(f * 64 + lane) * 16u : 0u;  // fragments that do not exist re-read element 0
       v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     for (int s = 0; s < splits; s += 2) {  // two splits per trip to memory
       const int s1 = min(s + 1, splits - 1);
       u32x4 ta[FW], tb[FW];
 #pragma unroll
-      for (int i = 0; i < FW; ++i) ta[i] = __builtin_amdgcn_raw_buffer_load_b128(part_rsrc(e.part + s * stride), off[i], 0, SC1);
+      for (int i = 0; i < FW; ++i) ta[i] = __builtin_amdgcn_raw_buffer_load_b128(partial(s), off[i], 0, SC1);
 #pragma unroll
-      for (int i = 0; i < FW; ++i) tb[i] = __builtin_amdgcn_raw_buffer_load_b128(part_rsrc(e.part + s1 * stride), off[i], 0, SC1);
+      for (int i = 0; i < FW; ++i) tb[i] = __builtin_amdgcn_raw_buffer_load_b128(partial(s1), off[i], 0, SC1);
 #pragma unroll
       for (int i = 0; i < FW; ++i) v[i] += __builtin_bit_cast(f32x4, ta[i]);
       if (s + 1 < splits)
@@ -383,7 +381,10 @@ GemmPlan gemm_mid_plan(int M, int N, int K) {
   const MidPlan p = mid_plan(M, N, K);
   return GemmPlan{0, 16 * p.mt, 16 * p.ct, p.splits, p.splits, p.groups * p.splits, 1};
 }
-int gemm_mid_splits(int M, int N, int K) { return mid_plan(M, N, K).splits; }
+size_t gemm_mid_part_elems(int M, int N, int K) {
+  const MidPlan p = mid_plan(M, N, K);
+  return p.splits > 1 ? (size_t)p.splits * p.groups * p.ct * p.mt * 256 : 0;
+}
 int gemm_mid_ssq_chunks(int M, int N, int K) { return mid_plan(M, N, K).groups; }
 int gemm_mid_counters(int max_n) { return (max_n + 31) / 32; }  // 32-column groups are the narrowest
 
