@@ -136,16 +136,12 @@ __global__ void pack_kv_kernel(const bf16_t* __restrict__ k, const bf16_t* __res
     vt[(size_t)h * head_stride + kv_v_index(pos, d, hd)] = to_f16_sat((float)v[i]);
   }
 }
-__global__ void to_f16_kernel(const bf16_t* __restrict__ src, f16_t* __restrict__ dst, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) dst[i] = to_f16_sat((float)src[i]);
-}
 
 }  // namespace
 
 void launch_pack_kv(const bf16_t* k, const bf16_t* v, f16_t* kt, f16_t* vt, int T, int n_kv, int hd, size_t head_stride, hipStream_t st) {
   pack_kv_kernel<<<256, 256, 0, st>>>(k, v, kt, vt, T, n_kv, hd, head_stride);
 }
-void launch_to_f16(const bf16_t* src, f16_t* dst, size_t n, hipStream_t st) { to_f16_kernel<<<256, 256, 0, st>>>(src, dst, n); }
 
 template <>
 void launch_attention<float>(const float* q, const float* kcache, const float* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,

@@ -49,7 +49,7 @@ __device__ inline float sum4(float v) {
   return t.a + t.b;
 }
 
-// q: row-major [rows, n_q * HD]; kt / vt: the (slot, kv head) region of the tiled cache; rows [row0, row_end) (at most 16 T of
+// q: fragment tiles [rows, n_q * HD] (as every GEMM input: the QKV epilogue writes whole 16-byte slots, 256 bytes of 16 rows together); kt / vt: the (slot, kv head) region of the tiled cache; rows [row0, row_end) (at most 16 T of
 // them) x head `head` against keys [0, n_keys); output to out_tiles (fragment tiles [rows, n_q * HD] in half: the O projection's
 // input) if given, else to out_rows (row-major bf16).  Called by every thread of a workgroup of NWV wavefronts.
 // DS > 1: the workgroup produces only dims [dpart * HD / DS, (dpart + 1) * HD / DS) of the output: it reads all of K (the
@@ -73,7 +73,7 @@ __device__ inline void attention_tiles(const f16_t* __restrict__ q, const f16_t*
     const int r = row0 + 16 * u + c;
 #pragma unroll
     for (int t = 0; t < KS; ++t)
-      qf[u][t] = r < row_end ? *(const f16x8*)(q + (size_t)r * n_q * HD + (size_t)head * HD + 32 * t + 8 * g) : zero8;
+      qf[u][t] = r < row_end ? *(const f16x8*)(q + tile_index(r, head * HD + 32 * t + 8 * g, n_q * HD)) : zero8;
   }
   const f16x8* kt = (const f16x8*)kregion + lane;
   const f16x8* vt = (const f16x8*)vregion + lane;

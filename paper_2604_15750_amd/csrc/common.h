@@ -172,7 +172,7 @@ struct GemmEpi {
   // EPI_QKV (weights packed with PERM_ROTARY)
   const int32_t *row_pos, *row_slot;
   const float *rope_cos, *rope_sin;
-  f16_t *q, *kcache, *vcache;  // IEEE half (see f16_t)
+  f16_t *q, *kcache, *vcache;  // IEEE half (see f16_t); q in fragment tiles [rows, n_q * hd]
   size_t slot_stride, head_stride;
   int n_q, n_kv, hd;
   // EPI_SWIGLU (weights packed with PERM_GATED): act in fragment tiles
@@ -183,9 +183,8 @@ struct GemmEpi {
   const float* gain;
   op_t* x;
   float* ssq_out;
-  // EPI_DIRECT (bf16) / EPI_SUM (either)
+  // EPI_DIRECT / EPI_SUM
   bf16_t* out_bf16;
-  float* out_f32;
   // EPI_STATS (the LM head of a pass that compares and retains no row; at most GEMM_STATS_MAX_ROWS rows): logits to out_bf16 as
   // EPI_DIRECT does, and per row and column group the online-softmax state of the group's logits as written (rounded to bf16,
   // token skip_col left out) to stat_parts[m][gemm_bf16_stat_parts(M, N, K)]
@@ -267,7 +266,7 @@ void launch_embed(const SeqMeta& meta, const StatsMeta& sm, const T* embed, cons
 template <typename T>
 void launch_attention(const T* q, const T* kcache, const T* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta, T* out,
                       bool out_tiled, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st);
-// bf16 models: q and the KV cache hold IEEE half; the output goes to out_tiles (fragment tiles [rows, n_q*hd] in half: the O
+// bf16 models: q (fragment tiles [rows, n_q*hd]) and the KV cache hold IEEE half; the output goes to out_tiles (fragment tiles [rows, n_q*hd] in half: the O
 // projection's input) if that is given, else to out_rows (row-major bf16)
 struct AttnPlan {
   int waves, shares, tiles;  // of a workgroup: wavefronts, workgroups that share a head's output dims, 16-query tiles
@@ -275,9 +274,8 @@ struct AttnPlan {
 AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_q, int hd);
 void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,
                           op_t* out_tiles, bf16_t* out_rows, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st);
-// test helper of dlm_attention: K, V [T, n_kv, hd] row-major bf16 -> the tiled half-precision cache layout of one slot; q -> half
+// test helper of dlm_attention: K, V [T, n_kv, hd] row-major bf16 -> the tiled half-precision cache layout of one slot
 void launch_pack_kv(const bf16_t* k, const bf16_t* v, f16_t* kt, f16_t* vt, int T, int n_kv, int hd, size_t head_stride, hipStream_t st);
-void launch_to_f16(const bf16_t* src, f16_t* dst, size_t n, hipStream_t st);
 
 struct StatsOut {
   float *max_logit, *lse, *entropy, *kl, *conf;

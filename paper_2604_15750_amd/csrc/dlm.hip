@@ -280,7 +280,7 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
   A(s->x, (size_t)s->max_rows_pad * xw * es);
   A(s->x2, (size_t)s->max_rows_pad * xw * es);
   A(s->act, (size_t)s->max_rows_pad * c.d_ffn * es);
-  A(s->q, (size_t)max_rows * qd * es);
+  A(s->q, (size_t)s->max_rows_pad * qd * es);
   A(s->part, pe * 4);
   size_t stats_bytes = stats_workspace_bytes(max_rows);
   if (c.dtype == DLM_BF16) {  // or one state per row and column group of the LM head, for the passes that take the statistics from its epilogue
@@ -760,9 +760,9 @@ extern "C" int dlm_attention(const void* q, const void* k, const void* v, void* 
     launch_attention<float>((const float*)q, (const float*)k, (const float*)v, 0, 0, am, (float*)out, false, A, A, n_q, n_kv, head_dim, st);
     return DLM_OK;
   }
-  // bf16: K and V re-tiled into the half-precision cache layout, q converted to half (test helper: allocates and synchronises)
+  // bf16: K and V re-tiled into the half-precision cache layout, q converted to half fragment tiles (test helper: allocates and synchronises)
   const size_t head_stride = (size_t)((T + 31) / 32 * 32) * head_dim, bytes = head_stride * n_kv * 2;
-  const size_t q_elems = (size_t)A * n_q * head_dim, q_bytes = (q_elems * 2 + 255) / 256 * 256;
+  const size_t q_bytes = (size_t)(A + 15) / 16 * 16 * n_q * head_dim * 2;
   void* ws = nullptr;
   if (hipMalloc(&ws, 2 * bytes + q_bytes) != hipSuccess) { (void)hipGetLastError(); return dlm_fail(DLM_ENOMEM, "dlm_attention: workspace allocation failed"); }
   f16_t* kt = (f16_t*)ws;
@@ -770,7 +770,7 @@ extern "C" int dlm_attention(const void* q, const void* k, const void* v, void* 
   f16_t* qh = vt + head_stride * n_kv;
   hipError_t e = hipMemsetAsync(ws, 0, 2 * bytes, st);
   launch_pack_kv((const bf16_t*)k, (const bf16_t*)v, kt, vt, T, n_kv, head_dim, head_stride, st);
-  launch_to_f16((const bf16_t*)q, qh, q_elems, st);
+  launch_pack_act((const bf16_t*)q, qh, A, n_q * head_dim, st);
   launch_attention_f16(qh, kt, vt, 0, head_stride, am, nullptr, (bf16_t*)out, A, A, n_q, n_kv, head_dim, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   (void)hipFree(ws);

@@ -2,10 +2,67 @@
 // v_mfma_f32_16x16x32_f16 (transposed product): in a 16 x 16 output tile, lane ml + 16 g holds
 // columns 4g .. 4g+3 of row ml.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 __device__ inline bf16x4 to_bf16x4(f32x4 v) { return bf16x4{(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]}; }
 __device__ inline f16x4 to_f16x4_sat(f32x4 v) { return f16x4{to_f16_sat(v[0]), to_f16_sat(v[1]), to_f16_sat(v[2]), to_f16_sat(v[3])}; }
+
+// ---- exchanges between the lanes of a wavefront, on fragments in the accumulator layout (all 64 lanes together)
+// The halves of two fragments: lo = the lower 32 lanes' values of u and, in the upper 32 lanes, of v; hi = the upper 32 lanes'.  So
+// where a fragment's columns 0 .. 7 meet its columns 8 .. 15 (gate and up, rotary partners), each lane gets one pair.
+struct Halves { f32x4 lo, hi; };
+__device__ __attribute__((always_inline)) inline Halves pair_halves(f32x4 u, f32x4 v) {
+  Halves r;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(u[t]), __float_as_uint(v[t]), false, false);
+    r.lo[t] = __uint_as_float(x[0]);
+    r.hi[t] = __uint_as_float(x[1]);
+  }
+  return r;
+}
+// Two groups of 16-bit values per lane -> 16 consecutive bytes per lane: the lanes of group g (16 lanes each) get group 2 (g / 2)'s
+// and then group 2 (g / 2) + 1's values, of u where g is even and of v where it is odd.
+template <typename V4>
+__device__ __attribute__((always_inline)) inline auto join_slots(V4 u, V4 v) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned int u32x4_ __attribute__((ext_vector_type(4)));
+  typedef typename std::conditional<std::is_same<V4, bf16x4>::value, bf16x8, f16x8>::type V8;
+  const u32x2 a = __builtin_bit_cast(u32x2, u), b = __builtin_bit_cast(u32x2, v);
+  const auto x = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), y = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  const u32x4_ o = {x[0], y[0], x[1], y[1]};
+  return __builtin_bit_cast(V8, o);
+}
+template <int CTRL>
+__device__ __attribute__((always_inline)) inline unsigned dpp(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+}
+// 4 x 4 transpose within each quad of lanes: lane q of the quad gets element q of its four lanes
+__device__ __attribute__((always_inline)) inline f16x4 transpose_quad(f16x4 v) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 a = __builtin_bit_cast(u32x2, v);
+  const bool up = threadIdx.x & 2, odd = threadIdx.x & 1;
+  const unsigned got = dpp<0x4e>(up ? a[0] : a[1]);  // quad_perm [2, 3, 0, 1]
+  const unsigned r0 = up ? got : a[0], r1 = up ? a[1] : got;
+  const unsigned sel = odd ? 0x03020706u : 0x05040100u;
+  const u32x2 o = {__builtin_amdgcn_perm(dpp<0xb1>(r0), r0, sel), __builtin_amdgcn_perm(dpp<0xb1>(r1), r1, sel)};  // quad_perm [1, 0, 3, 2]
+  return __builtin_bit_cast(f16x4, o);
+}
+__device__ __attribute__((always_inline)) inline void quad_rows(int v, int (&out)[4]) {  // the quad's four values, in every lane of it
+  out[0] = (int)dpp<0x00>((unsigned)v);
+  out[1] = (int)dpp<0x55>((unsigned)v);
+  out[2] = (int)dpp<0xaa>((unsigned)v);
+  out[3] = (int)dpp<0xff>((unsigned)v);
+}
+// sum over the four lanes of a row: lanes 16 apart, then lanes 32 apart
+__device__ __attribute__((always_inline)) inline float sum_row4(float v) {
+  auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const float s = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  x = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+  return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+}
 
 // 1/rms of rows [m_lo, m_lo + rows) from the producer's partial sums of squares into s_rinv, by the whole workgroup of NT
 // threads: sixteen lanes per row, each adding every sixteenth chunk in ascending order, then a fixed butterfly
@@ -56,9 +113,7 @@ struct RinvBatch {
     }
   }
   template <int CTRL>
-  static __device__ inline float rotate_add(float a) {
-    return a + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), CTRL, 0xf, 0xf, false));
-  }
+  static __device__ inline float rotate_add(float a) { return a + __uint_as_float(dpp<CTRL>(__float_as_uint(a))); }
   __device__ __attribute__((always_inline)) inline void publish(const RowScale& rs, int rows, float* s_rinv) const {
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
@@ -123,9 +178,8 @@ __device__ inline void finish_qkv(const GemmEpi& e, int m, int nc, int gp, f32x4
   }
   const f16x4 ab = to_f16x4_sat(a), bb = to_f16x4_sat(b);
   if (head < e.n_q) {
-    f16_t* dst = e.q + (size_t)m * e.n_q * hd + (size_t)head * hd;
-    *(f16x4*)(dst + i) = ab;
-    *(f16x4*)(dst + i + half) = bb;
+    *(f16x4*)(e.q + tile_index(m, head * hd + i, e.n_q * hd)) = ab;
+    *(f16x4*)(e.q + tile_index(m, head * hd + i + half, e.n_q * hd)) = bb;
     return;
   }
   const bool is_k = head < e.n_q + e.n_kv;
@@ -149,11 +203,14 @@ __device__ inline void finish_qkv(const GemmEpi& e, int m, int nc, int gp, f32x4
 }
 
 // gate = packed columns nc+4gp .. +3, up = the same + 8: output columns 8 (nc/16) + 4gp .. +3 (weights packed with PERM_GATED)
-__device__ inline void finish_swiglu(const GemmEpi& e, int m, int nc, int gp, f32x4 g, f32x4 u) {
+__device__ inline f32x4 gated(f32x4 g, f32x4 u) {
   f32x4 a;
 #pragma unroll
   for (int t = 0; t < 4; ++t) a[t] = g[t] * __builtin_amdgcn_rcpf(1.f + __expf(-g[t])) * u[t];  // (the hardware reciprocal: 1 ulp)
-  *(op4*)(e.act + tile_index(m, 8 * (nc >> 4) + 4 * gp, e.ffn)) = to_f16x4_sat(a);
+  return a;
+}
+__device__ inline void finish_swiglu(const GemmEpi& e, int m, int nc, int gp, f32x4 g, f32x4 u) {
+  *(op4*)(e.act + tile_index(m, 8 * (nc >> 4) + 4 * gp, e.ffn)) = to_f16x4_sat(gated(g, u));
 }
 
 // residual add and next norm's x for columns n .. n+3 of row m; returns the four columns' share of sum h^2
@@ -168,9 +225,7 @@ __device__ inline float finish_resid(const GemmEpi& e, int m, int n, int N, f32x
 }
 
 __device__ inline void finish_sum(const GemmEpi& e, int m, int n, int N, f32x4 v) {
-  const size_t o = (size_t)m * N + n;
-  if (e.out_bf16) *(bf16x4*)(e.out_bf16 + o) = to_bf16x4(v);
-  else *(f32x4*)(e.out_f32 + o) = v;
+  *(bf16x4*)(e.out_bf16 + (size_t)m * N + n) = to_bf16x4(v);
 }
 
 // One 16 x 16 tile starting at packed column nc: v = this lane's four finished columns of row m, rinv = 1/rms of the input row.

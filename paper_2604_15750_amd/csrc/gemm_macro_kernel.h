@@ -13,7 +13,7 @@
 //   * the waits on the direct-to-LDS loads are counted by hand (every stage is the same number of loads per wavefront; indices
 //     past the end are clamped, so the count never varies), and so are the waits on the LDS reads (once per k-tile, behind the
 //     products: the compiler counts the copies to LDS as possibly out of order on that counter and could only wait for all);
-//   * the accumulators reach the epilogue through LDS, half of a wavefront's column tiles at a time.
+//   * the epilogue works straight from the accumulators.
 // What bounds it: with operands of random values the chip's power limit and the L2 -> LDS fetch rate (16 .. 18 TB/s over the
 // chip in this access pattern, loads alone) meet at about half of the published matrix-core rate for every tile from 128 x 128
 // up (macro_tiles has the measured time per k-tile of each); below that, the fixed cost of a step.  So a larger tile is no
@@ -85,8 +85,7 @@ struct MacroShape {
   static constexpr int S_FIT = (152 * 1024) / STAGE, S_CNT = 63 / LPS + 1;  // what LDS holds, and what the memory counter counts
   static constexpr int S_ = S_FIT < S_CNT ? S_FIT : S_CNT;
   static constexpr int S = S_ > 6 ? 6 : S_;
-  static constexpr int HJ = (WN + 1) / 2;           // column tiles of a wavefront that leave through LDS together
-  static constexpr int BODY = S * STAGE > NW * HJ * WM * 1024 ? S * STAGE : NW * HJ * WM * 1024;
+  static constexpr int BODY = S * STAGE;            // (also holds the states of EPI_STATS, CW AT 256 bytes)
   static constexpr int LDS_BYTES = BODY + AT * 16 * 4 * (1 + BF);  // + 1/rms of the rows, sums of squares per row and column tile
   static_assert(S >= 2 && LDS_BYTES <= 160 * 1024, "pipeline shape");
 };
@@ -97,7 +96,7 @@ template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER>
 __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
                                                                                int form, int nblocks, int mblocks, int splits, int kt_per_split, GemmEpi e) {
   typedef MacroShape<WM, WN, RW, CW, KB> SH;
-  constexpr int NW = SH::NW, TPB = SH::TPB, AT = SH::AT, BF = SH::BF, NFR = SH::NFR, LPT = SH::LPT, LPS = SH::LPS, STAGE = SH::STAGE, S = SH::S, HJ = SH::HJ;
+  constexpr int NW = SH::NW, TPB = SH::TPB, AT = SH::AT, BF = SH::BF, NFR = SH::NFR, LPT = SH::LPT, LPS = SH::LPS, STAGE = SH::STAGE, S = SH::S;
   const int prs = ORDER ? form & 1 : form, fold = ORDER ? form >> 2 : 0;
   const bool two_chunks = ORDER && (form & 2);
   extern __shared__ __align__(16) unsigned char lds[];
@@ -162,6 +161,21 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
 #pragma unroll
       for (int i = 0; i < WM; ++i) acc[j][i] = mfma_op(wf[set][j], xf[set][i], acc[j][i]);
   };
+
+  // EPI_RESID: residual and gain of the outputs are fetched here too where the registers hold them (only this workgroup touches them);
+  // of a split tile by the workgroup that finishes it, while it waits for the others
+  constexpr bool H_EARLY = EPI == EPI_RESID && (ORDER ? 12 : 10) * WM * WN + 8 * (WM + WN) <= 200;
+  f32x4 h_ahead[WN][WM], g_ahead[WN];
+  auto fetch_resid = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      const int n = min(nt0 + wn * WN + j, NT - 1) * 16 + 4 * (lane >> 4);
+      g_ahead[j] = *(const f32x4*)(e.gain + n);
+#pragma unroll
+      for (int i = 0; i < WM; ++i) h_ahead[j][i] = *(const f32x4*)(e.h + (size_t)min(m_lo + (wm * WM + i) * 16 + (lane & 15), M - 1) * N + n);
+    }
+  };
+  if (H_EARLY && splits == 1) fetch_resid();
 
   // K split: a ticket per workgroup and tile, taken here, where its trip to memory hides behind the pipeline's start
   int my_ticket = 0;
@@ -311,6 +325,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
       if (tid == 0) (void)__hip_atomic_fetch_add(ticket + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return;
     }
+    if (H_EARLY) fetch_resid();
     if (tid == 0) {
       while (__hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != splits - 1) __builtin_amdgcn_s_sleep(1);
       __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
@@ -348,56 +363,153 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
       for (int i = 0; i < WM; ++i) acc[j][i] = sum[j][i];
   }
 
-  // ---- epilogue
+  // ---- epilogue, straight from the accumulators.  What bounds it is the instructions it issues, then the trips to memory of what
+  // it reads: so every lane finishes outputs of its own, values move between lanes by permlane and DPP, and loads go out ahead
+  // of the stores before them (the memory counter retires in order).  From the end of the loop to the end of the kernel, 8B model
+  // at 384 rows, with fragments staged through LDS, exchanged there and finished by half of the lanes / now: QKV 8.3 / 5.1 us,
+  // gate/up 8.8 / 3.9, down (the finishing workgroup) 5.0 / 2.2, a 256 x 256 gate/up tile 9.1 / 4.2.
   if (RINV_LATE && rinv_batched) rinv.publish(e.rs, rows, s_rinv);
-  __syncthreads();
-  // The accumulators leave the registers through LDS (each wavefront its own region, half of its column tiles at a time), so
-  // that the epilogue runs as a loop over fragments instead of WM WN unrolled copies with every accumulator live.
-  f32x4* mine = (f32x4*)lds + wave * (HJ * WM * 64) + lane;
-  LiteState state[WM];  // EPI_STATS
+  if (EPI != EPI_RESID) __syncthreads();
+  float ri[WM];  // 1/rms of the lane's row of each row tile
 #pragma unroll
-  for (int i = 0; i < WM; ++i) state[i] = lite_init();
+  for (int i = 0; i < WM; ++i) ri[i] = EPI == EPI_RESID ? 1.f : s_rinv[(wm * WM + i) * 16 + ml];
+  const int nt_w = nt0 + wn * WN, mt_w = mt0 + wm * WM;  // the wavefront's first column and row tile
+  const bool hi = lane >= 32;
+  auto row = [&](int i) { return (mt_w + i) * 16 + ml; };
+  if constexpr (EPI == EPI_SWIGLU) {
+    // two fragments at a time (column tiles fastest): the lower 32 lanes finish the first's outputs, the upper ones the second's
+    constexpr int F = WM * WN;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    // what the fragments' epilogues read from memory (residual and gain; rotary cosines and sines) is fetched for up to twelve
-    // fragments per trip instead of one trip per fragment
+    for (int f = 0; f < F; f += 2) {
+      const int f1 = f + 1 < F ? f + 1 : f, i0 = f / WN, j0 = f % WN, i1 = f1 / WN, j1 = f1 % WN;
+      const bool there = hi ? (f1 != f && nt_w + j1 < NT && row(i1) < M) : (nt_w + j0 < NT && row(i0) < M);
+      const Halves v = pair_halves(acc[j0][i0], acc[j1][i1]);
+      const float r = hi ? ri[i1] : ri[i0];
+      const int second = i1 == i0 ? 128 * (j1 - j0) : 16 * e.ffn + 128 * (j1 - j0);  // from the first fragment's outputs to the second's
+      op_t* dst = e.act + ((size_t)(mt_w + i0) * e.ffn * 16 + (size_t)(nt_w + j0) * 128) + ((hi ? second : 0) + ml * 8 + 4 * (g & 1));
+      if (there) *(op4*)dst = to_f16x4_sat(gated(v.lo * r, v.hi * r));
+    }
+  } else if constexpr (EPI == EPI_QKV) {
+    const int hd = e.hd, tph = hd >> 4, half = hd >> 1, heads_rot = e.n_q + e.n_kv;
+    constexpr int PR = (WM + 1) / 2;  // pairs of row tiles of a column tile: rotated two at a time, the lower lanes the first's outputs
+    int pos[WM], slot[WM];
+    if ((min(nt_w + WN, NT) - 1) / tph >= e.n_q) {
 #pragma unroll
-    for (int jj = 0; jj < HJ; ++jj)
+      for (int i = 0; i < WM; ++i) {
+        const int m = min(row(i), M - 1);
+        pos[i] = e.row_pos[m];
+        slot[i] = e.row_slot[m];
+      }
+    }
+    f32x4 rc[2][PR], rsn[2][PR];  // rotary cosines and sines of a column tile's pairs: the next tile's are in flight
+    auto fetch_rope = [&](int j) __attribute__((always_inline)) {
+      const int nt = nt_w + j;
+      if (nt >= NT || nt / tph >= heads_rot) return;
 #pragma unroll
-      for (int i = 0; i < WM; ++i)
-        if (h * HJ + jj < WN) mine[(jj * WM + i) * 64] = acc[h * HJ + jj < WN ? h * HJ + jj : 0][i];
-    constexpr int IB = WM * HJ <= 12 ? WM : WM % 2 == 0 ? WM / 2 : 1;  // row tiles per trip: at most 12 fragments' worth of registers
+      for (int p = 0; p < PR; ++p) {
+        const int m = min(row(2 * p + (hi && 2 * p + 1 < WM)), M - 1);
+        const size_t o = (size_t)m * half + 8 * (nt % tph) + 4 * (g & 1);
+        rc[j & 1][p] = *(const f32x4*)(e.rope_cos + o);
+        rsn[j & 1][p] = *(const f32x4*)(e.rope_sin + o);
+      }
+    };
+    fetch_rope(0);
 #pragma unroll
-    for (int i0 = 0; i0 < WM; i0 += IB) {
-      EpiAhead ah[IB][HJ];
+    for (int j = 0; j < WN; ++j) {
+      if (j + 1 < WN) fetch_rope(j + 1);
+      const int nt = nt_w + j, head = nt / tph, bt = nt % tph;  // (uniform)
+      if (nt >= NT) continue;
+      if (head < heads_rot) {
 #pragma unroll
-      for (int i = 0; i < IB; ++i)
-#pragma unroll
-        for (int jj = 0; jj < HJ; ++jj) {
-          const int nt = nt0 + wn * WN + h * HJ + jj;
-          ah[i][jj] = (EPI == EPI_RESID || EPI == EPI_QKV) && h * HJ + jj < WN && nt < NT
-                          ? epi_ahead<EPI>(e, M, N, m_lo + (wm * WM + i0 + i) * 16 + ml, nt * 16, g) : epi_none();
-        }
-#pragma unroll
-      for (int i = 0; i < IB; ++i) {
-        const int rl = (wm * WM + i0 + i) * 16 + ml;
-        const float rinv = EPI == EPI_RESID ? 1.f : s_rinv[rl];
-#pragma unroll
-        for (int jj = 0; jj < HJ; ++jj) {
-          const int nt = nt0 + wn * WN + h * HJ + jj;
-          if (EPI == EPI_STATS) {  // the logits, and the states of their values as written
-            const int m = m_lo + rl, n = nt * 16 + 4 * g;
-            if (h * HJ + jj < WN && nt < NT) {
-              const f32x4 v = mine[(jj * WM + i0 + i) * 64] * rinv;
-              if (m < M) *(bf16x4*)(e.out_bf16 + (size_t)m * N + n) = to_bf16x4(v);
-              state[i0 + i] = lite_merge(state[i0 + i], lite_of(v, n, e.skip_col));
+        for (int p = 0; p < PR; ++p) {
+          const int i0 = 2 * p, i1 = 2 * p + 1 < WM ? 2 * p + 1 : i0, i = hi ? i1 : i0;
+          const Halves v = pair_halves(acc[j][i0], acc[j][i1]);
+          const float r = hi ? ri[i1] : ri[i0];
+          const f32x4 x = v.lo * r, y = v.hi * r, c = rc[j & 1][p], sn = rsn[j & 1][p];
+          // the lane's four dims 4 (g & 1) .. of the tile's eight, and their partners half a head up; then eight consecutive dims
+          // per lane: even lane groups the tile's, odd ones their partners
+          const op8 o = join_slots(to_f16x4_sat(x * c - y * sn), to_f16x4_sat(y * c + x * sn));
+          const int m = row(i), d = 8 * bt + ((g & 1) ? half : 0);
+          if (m < M && !(hi && i1 == i0)) {
+            if (head < e.n_q) {
+              *(op8*)(e.q + ((size_t)(mt_w + i) * e.n_q * hd + head * hd + d) * 16 + ml * 8) = o;
+            } else {
+              const size_t region = (size_t)(hi ? slot[i1] : slot[i0]) * e.slot_stride + (size_t)(head - e.n_q) * e.head_stride;
+              *(op8*)(e.kcache + region + kv_k_index(hi ? pos[i1] : pos[i0], d, hd)) = o;
             }
-          } else if (h * HJ + jj < WN) {
-            float ss = 0.f;
-            if (nt < NT) ss = finish_frag<EPI>(e, M, N, m_lo + rl, nt * 16, g, mine[(jj * WM + i0 + i) * 64], rinv, ah[i][jj]);  // uniform in the wavefront
-            if (EPI == EPI_RESID && g == 0) s_ssq[(wn * WN + h * HJ + jj) * AT * 16 + rl] = ss;
           }
         }
+      } else {
+#pragma unroll
+        for (int i = 0; i < WM; ++i) {
+          // V keeps eight positions of a dim together: 4 x 4 transposed within each quad of lanes, so that a lane has one dim of the
+          // quad's four rows; one store where these are four aligned positions of one sequence, four of one value each elsewhere
+          const op4 t = transpose_quad(to_f16x4_sat(acc[j][i] * ri[i]));
+          const int d = ((g & 2) ? half : 0) + 8 * bt + 4 * (g & 1) + (ml & 3), m_quad = row(i) & ~3;
+          int qp[4], qs[4];
+          quad_rows(pos[i], qp);
+          quad_rows(slot[i], qs);
+          f16_t* v = e.vcache + (size_t)(head - heads_rot) * e.head_stride;
+          if ((qp[0] & 3) == 0 && qp[3] == qp[0] + 3 && qs[3] == qs[0] && m_quad + 3 < M) {
+            *(op4*)(v + (size_t)qs[0] * e.slot_stride + kv_v_index(qp[0], d, hd)) = t;
+          } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (m_quad + k < M) v[(size_t)qs[k] * e.slot_stride + kv_v_index(qp[k], d, hd)] = t[k];
+          }
+        }
+      }
+    }
+  } else if constexpr (EPI == EPI_RESID) {
+    f32x4 hc[2][WM], gc[2];  // (without H_EARLY) residual and gain of a column tile: the next tile's are in flight
+    auto fetch_col = [&](int j) __attribute__((always_inline)) {
+      if (nt_w + j >= NT) return;
+      gc[j & 1] = *(const f32x4*)(e.gain + (nt_w + j) * 16 + 4 * g);
+#pragma unroll
+      for (int i = 0; i < WM; ++i) hc[j & 1][i] = *(const f32x4*)(e.h + (size_t)min(row(i), M - 1) * N + (nt_w + j) * 16 + 4 * g);
+    };
+    if (!H_EARLY) fetch_col(0);
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      if (!H_EARLY && j + 1 < WN) fetch_col(j + 1);
+      const int nt = nt_w + j;
+#pragma unroll
+      for (int i = 0; i < WM; ++i) {
+        const int m = row(i);
+        float ss = 0.f;  // (a column tile that does not exist adds nothing)
+        if (m < M && nt < NT) ss = finish_resid(e, m, nt * 16 + 4 * g, N, acc[j][i], EpiAhead{H_EARLY ? h_ahead[j][i] : hc[j & 1][i], H_EARLY ? g_ahead[j] : gc[j & 1], true, -1, -1});
+        ss = sum_row4(ss);
+        if (g == 0) s_ssq[(wn * WN + j) * AT * 16 + (wm * WM + i) * 16 + ml] = ss;
+      }
+    }
+  } else if constexpr (EPI != EPI_STATS) {  // the product in bf16: two column tiles at a time, eight consecutive columns per lane
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+      const int m = row(i);
+      bf16_t* out = e.out_bf16 + (size_t)m * N + nt_w * 16;
+#pragma unroll
+      for (int j = 0; j < WN; j += 2) {
+        if (j + 1 < WN && nt_w + j + 1 < NT) {
+          const bf16x8 o = join_slots(to_bf16x4(acc[j][i] * ri[i]), to_bf16x4(acc[j + 1 < WN ? j + 1 : j][i] * ri[i]));
+          if (m < M) *(bf16x8*)(out + (j + (g & 1)) * 16 + 8 * (g >> 1)) = o;
+        } else if (nt_w + j < NT && m < M) {
+          *(bf16x4*)(out + j * 16 + 4 * g) = to_bf16x4(acc[j][i] * ri[i]);
+        }
+      }
+    }
+  }
+  LiteState state[WM];  // EPI_STATS: the logits, and the states of their values as written
+  if constexpr (EPI == EPI_STATS) {
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+      state[i] = lite_init();
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        const int m = row(i), n = (nt_w + j) * 16 + 4 * g;
+        if (nt_w + j >= NT) continue;
+        const f32x4 v = acc[j][i] * ri[i];
+        if (m < M) *(bf16x4*)(e.out_bf16 + (size_t)m * N + n) = to_bf16x4(v);
+        state[i] = lite_merge(state[i], lite_of(v, n, e.skip_col));
       }
     }
   }
