@@ -108,7 +108,7 @@ __global__ __launch_bounds__(NWV * 64, T > 1 ? 2 : 1) void attention_mfma_kernel
                                                                   const f16_t* __restrict__ vcache, size_t slot_stride, size_t head_stride,
                                                                   AttnMeta meta, op_t* __restrict__ out_tiles, bf16_t* __restrict__ out_rows, int n_q, int n_kv,
                                                                   int per_unit, int groups) {
-  __shared__ AttnLds<HD, NWV, DS> L;
+  __shared__ AttnLds<HD, NWV, DS, T> L;
   int b = blockIdx.z, head = blockIdx.y, x = blockIdx.x;
   if (per_unit > 0) {
     const int j = blockIdx.x >> 3, w = j % per_unit, unit = (j / per_unit) * 8 + (blockIdx.x & 7);
@@ -157,14 +157,15 @@ void launch_attention<float>(const float* q, const float* kcache, const float* v
 // wide one has enough workgroups to fill the chip with four wavefronts each.
 // Query tiles per workgroup, where a span has more than one: a wide pass takes two (the K and V traffic is what bounds it); a narrow
 // one the fewest that leave at most one workgroup per compute unit (8B shape, 24 rows x 856 keys, one tile / two: 7.7 / 9.7 us;
-// 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that).  Spans of one tile gain nothing from a second
+// 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that); so does a middling one with eight
+// wavefronts, of which a unit holds one workgroup (28 heads, 152 rows x 792 keys, 280 workgroups / 140: 15.3 / 12.0).  Spans of one tile gain nothing from a second
 // that no row fills (28 heads, 3 sequences of 16 rows x 1516 keys, two tiles / one: 25.7 / 22.2).
 AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_q, int hd) {
   const int tiles = (max_seq_rows + 15) / 16;
   const size_t units = (size_t)tiles * n_q * n_seqs;
   if (units < 128 && hd >= 64) return AttnPlan{8, hd == 128 ? 4 : 2, hd == 128 && tiles > 1 && units * 4 > 256 ? 2 : 1};
   if (units >= 512) return AttnPlan{4, 1, tiles > 1 ? 2 : 1};
-  return AttnPlan{8, 1, 1};
+  return AttnPlan{8, 1, units > 256 && tiles > 1 ? 2 : 1};
 }
 
 void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,
@@ -184,9 +185,9 @@ void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcac
     if (p.tiles == 2) GO(HD, NWV, DS, 2);  \
     else GO(HD, NWV, DS, 1);               \
   } while (0)
-  if (hd == 32) { if (p.waves == 4) BY_TILES(32, 4, 1); else GO(32, 8, 1, 1); }
-  else if (hd == 64) { if (p.shares > 1) GO(64, 8, 2, 1); else if (p.waves == 4) BY_TILES(64, 4, 1); else GO(64, 8, 1, 1); }
-  else { if (p.shares > 1) BY_TILES(128, 8, 4); else if (p.waves == 4) BY_TILES(128, 4, 1); else GO(128, 8, 1, 1); }
+  if (hd == 32) { if (p.waves == 4) BY_TILES(32, 4, 1); else BY_TILES(32, 8, 1); }
+  else if (hd == 64) { if (p.shares > 1) GO(64, 8, 2, 1); else if (p.waves == 4) BY_TILES(64, 4, 1); else BY_TILES(64, 8, 1); }
+  else { if (p.shares > 1) BY_TILES(128, 8, 4); else if (p.waves == 4) BY_TILES(128, 4, 1); else BY_TILES(128, 8, 1); }
 #undef BY_TILES
 #undef GO
 }

@@ -189,6 +189,14 @@ def test_attention_pairs_of_query_tiles(device, A, T, nq, nkv, hd):
     assert (np.abs(got - ref) <= bound).all(), (np.abs(got - ref) / bound).max()
 
 
+# ... of eight wavefronts, where one tile each would leave a second workgroup per compute unit: each head dim, odd tiles, fewer key
+# blocks than wavefronts, the last of them with one key
+@pytest.mark.parametrize("A,T,nq,nkv,hd", [(161, 97, 28, 4, 128), (152, 792, 28, 4, 128), (145, 257, 30, 10, 64), (257, 33, 16, 16, 32)])
+def test_attention_pairs_of_query_tiles_with_eight_wavefronts(device, A, T, nq, nkv, hd):
+    assert api.plan_attention(A, 1, nq, hd) == dict(waves=8, shares=1, tiles=2)
+    test_attention_pairs_of_query_tiles(device, A, T, nq, nkv, hd)
+
+
 # ---- vocabulary statistics -------------------------------------------------------------------------
 def _check_stats(got, ref, z64, zp64, mask_id):
     for key in ("max_logit", "lse", "entropy", "conf"):
