@@ -5,6 +5,8 @@
 //     of the workgroup, four pairs of loads in flight per thread, over a compacted list of the pooled rows: 1024 threads for
 //     blocks of more than 32 rows, whose pairs would otherwise take several trips one after another; the conflicts are a bit
 //     matrix in LDS;
+//   * the order of the rows is a bit matrix too, a ballot per row and 64 others; ranks are counts of its bits.  (A loop over the
+//     rows in each lane, twice, took 7 of the kernel's 10.6 us at 64 rows; SELECT_US now);
 //   * the greedy walk of phase 2 (in the order of confidence: take a row, drop its conflicts) runs in rounds: a row whose
 //     undecided conflicts all come later in that order is taken, and what conflicts with a row just taken is dropped.  That is
 //     the same set as the walk's, in as many rounds as the longest chain of conflicts instead of as many steps as rows.
@@ -14,27 +16,29 @@
 
 namespace {
 
-constexpr int MAXL = 256;       // rows of a block
-constexpr int RW = MAXL / 64;   // wavefronts that own rows
-constexpr int WORDS = MAXL / 32;
 constexpr float INF = __builtin_inff();
 
+template <int MAXL>
 union RowSet {  // one bit per row
-  unsigned long long q[RW];
-  uint32_t w[WORDS];
-  __device__ bool has(int j) const { return (w[j >> 5] >> (j & 31)) & 1u; }
+  unsigned long long q[MAXL / 64];
+  uint32_t w[MAXL / 32];
 };
 
-template <typename T, int TPB>
+// MAXL: rows a block can have
+template <typename T, int TPB, int MAXL>
 __global__ __launch_bounds__(TPB) void select_kernel(const T* __restrict__ logits, int vocab, const float* __restrict__ lse_g,
                                                      const float* __restrict__ conf_g, const int32_t* __restrict__ argmax_g,
                                                      int32_t* __restrict__ tokens, SelectMeta meta, int mask_id, dlm_select_params p,
                                                      int apply, uint8_t* __restrict__ sel_out, int32_t* __restrict__ nsel_out,
                                                      float* __restrict__ margin_out) {
+  constexpr int RW = MAXL / 64, WORDS = MAXL / 32;  // wavefronts that own rows
+  typedef RowSet<MAXL> Rows;
   __shared__ float c[MAXL], lse[MAXL], fbuf[TPB / 64];
   __shared__ int yh[MAXL], list[MAXL];
   __shared__ uint32_t bits[MAXL][WORDS + 1];  // conflicts of a row (padded: lanes read the same word of neighbouring rows)
-  __shared__ RowSet s_elig, s_pool, s_high, s_und, s_new, s_sel;
+  __shared__ uint32_t ahead[MAXL][WORDS + 1];  // rows that come before a row in the order of confidence
+  __shared__ float sorted[MAXL + 1];
+  __shared__ Rows s_elig, s_pool, s_high, s_und, s_new, s_sel;
   __shared__ int top_row, second_row;
 
   const int b = blockIdx.x, i = threadIdx.x, wave = i >> 6;
@@ -42,7 +46,7 @@ __global__ __launch_bounds__(TPB) void select_kernel(const T* __restrict__ logit
   const bool own = i < MAXL, act = i < L;  // (L <= MAXL)
   float margin = INF;
   // publishes one bit per row: called by every thread, read after the next barrier
-  auto publish = [&](RowSet& s, bool v) {
+  auto publish = [&](Rows& s, bool v) {
     const unsigned long long m = __ballot(v);
     if (own && (i & 63) == 0) s.q[wave] = m;
   };
@@ -57,7 +61,7 @@ __global__ __launch_bounds__(TPB) void select_kernel(const T* __restrict__ logit
   }
   if (own) c[i] = ci;
   publish(s_elig, e);
-  for (int k = i; k < MAXL * (WORDS + 1); k += TPB) ((uint32_t*)bits)[k] = 0;
+  for (int k = i; k < L * (WORDS + 1); k += TPB) ((uint32_t*)bits)[k] = 0;
   if (i == 0) { top_row = -1; second_row = -1; }
   bool pool = false, sel = false;
   if (p.mode == 0) {
@@ -70,16 +74,28 @@ __global__ __launch_bounds__(TPB) void select_kernel(const T* __restrict__ logit
   }
   __syncthreads();
 
-  // a row comes before another in the order of confidence: descending, ties by ascending row
-  auto before = [&](int j) { return c[j] > ci || (c[j] == ci && j < i); };
-  // most confident eligible row and the runner-up (for the safeguard and modes 1, 2)
-  if (e) {
-    int r = 0;
-#pragma unroll 8
-    for (int j = 0; j < L; ++j) r += s_elig.has(j) && before(j);
-    if (r == 0) top_row = i;
-    if (r == 1) second_row = i;
+  // a row comes before another in the order of confidence: descending, ties by ascending row.  A wavefront takes every TPB/64-th
+  // row against 64 others at a time.
+  for (int r = wave; r < L; r += TPB / 64) {
+    const float cr = c[r];
+    for (int j0 = 0; j0 < L; j0 += 64) {
+      const int j = j0 + (i & 63);
+      const float cj = c[j];
+      const unsigned long long m = __ballot(j < L && (cj > cr || (cj == cr && j < r)));
+      if ((i & 63) < 2) ahead[r][(j0 >> 5) + (i & 1)] = (uint32_t)(m >> (32 * (i & 1)));
+    }
   }
+  __syncthreads();
+  uint32_t before[WORDS];  // the rows before this one
+  // most confident eligible row and the runner-up (for the safeguard and modes 1, 2)
+  int rank = 0;
+#pragma unroll
+  for (int w = 0; w < WORDS; ++w) {
+    before[w] = act && 32 * w < L ? ahead[i][w] : 0;
+    rank += __popc(before[w] & s_elig.w[w]);
+  }
+  if (e && rank == 0) top_row = i;
+  if (e && rank == 1) second_row = i;
 
   if (p.mode == 0) {
     int np = 0, at = 0;  // pooled rows, in ascending order
@@ -128,31 +144,32 @@ __global__ __launch_bounds__(TPB) void select_kernel(const T* __restrict__ logit
     uint32_t blk[WORDS];  // the row's conflicts; then those of them that come before it in the order
 #pragma unroll
     for (int w = 0; w < WORDS; ++w) {
-      blk[w] = own ? bits[i][w] : 0;
+      blk[w] = act ? bits[i][w] : 0;
       und = und && (blk[w] & s_high.w[w]) == 0;
     }
     publish(s_und, und);
     __syncthreads();
     sel = high;
-    float next = -INF;  // the next smaller confidence among the rows phase 2 starts with
-    if (und) {
+    // the rows phase 2 starts with in their order: the margin includes the smallest step between two different confidences
+    int at_und = 0, n_und = 0;
 #pragma unroll
-      for (int w = 0; w < WORDS; ++w) {
-        if (32 * w >= L) break;
-        uint32_t m = 0;
-#pragma unroll 8
-        for (int j = 32 * w; j < 32 * w + 32; ++j) {
-          const bool a = s_und.has(j);
-          m |= (uint32_t)(a && before(j)) << (j & 31);
-          next = a && c[j] < ci ? fmaxf(next, c[j]) : next;
-        }
-        blk[w] &= m;
-      }
-      if (next > -INF) margin = fminf(margin, ci - next);
+    for (int w = 0; w < WORDS; ++w) {
+      blk[w] &= before[w] & s_und.w[w];
+      at_und += __popc(before[w] & s_und.w[w]);
+      n_und += __popc(s_und.w[w]);
+    }
+    if (und) sorted[at_und] = ci;
+    __syncthreads();
+    if (und && at_und + 1 < n_und) {
+      const float next = sorted[at_und + 1];
+      if (next < ci) margin = fminf(margin, ci - next);
     }
     // phase 2.  Every round decides at least the first undecided row of the order, so it ends after at most L of them.
     while (true) {
-      if ((s_und.q[0] | s_und.q[1] | s_und.q[2] | s_und.q[3]) == 0) break;  // (uniform: read between two barriers)
+      unsigned long long left = 0;
+#pragma unroll
+      for (int w = 0; w < RW; ++w) left |= s_und.q[w];
+      if (left == 0) break;  // (uniform: read between two barriers)
       bool take = und;
 #pragma unroll
       for (int w = 0; w < WORDS; ++w) take = take && (blk[w] & s_und.w[w]) == 0;
@@ -198,11 +215,14 @@ void launch_select(const T* logits, int vocab, const float* lse, const float* co
                         int32_t* nsel, float* margin, hipStream_t st) {
   int longest = 0;
   for (int b = 0; b < n_seqs; ++b) longest = meta.block_len[b] > longest ? meta.block_len[b] : longest;
-  // up to 32 rows: at most 1024 pairs, one trip of 256 threads; more threads would only make the barriers slower
-  if (longest <= 32 || p.mode != 0)
-    select_kernel<T, 256><<<n_seqs, 256, 0, st>>>(logits, vocab, lse, conf, argmax, tokens, meta, mask_id, p, apply, sel, nsel, margin);
-  else
-    select_kernel<T, 1024><<<n_seqs, 1024, 0, st>>>(logits, vocab, lse, conf, argmax, tokens, meta, mask_id, p, apply, sel, nsel, margin);
+  // Up to 32 rows: at most 1024 pairs, one trip of 256 threads; more threads would only make the barriers slower.  Up to 64 rows:
+  // sets of two words instead of eight, as most of a short kernel's time is fetching its instructions.
+  const bool few = longest <= 32 || p.mode != 0;
+#define GO(TPB, MAXL) \
+  select_kernel<T, TPB, MAXL><<<n_seqs, TPB, 0, st>>>(logits, vocab, lse, conf, argmax, tokens, meta, mask_id, p, apply, sel, nsel, margin)
+  if (longest <= 64) { if (few) GO(256, 64); else GO(1024, 64); }
+  else { if (few) GO(256, 256); else GO(1024, 256); }
+#undef GO
 }
 template void launch_select<float>(const float*, int, const float*, const float*, const int32_t*, int32_t*, const SelectMeta&, int,
                                         int, dlm_select_params, int, uint8_t*, int32_t*, float*, hipStream_t);
