@@ -3,8 +3,8 @@
 // differences of a prefix sum, the cumulative rule a second prefix sum; both are wavefront-shuffle
 // scans with a cross-wave carry, in fp64 so the decision does not depend on summation order.
 // What bounds it is that chain of dependent exchanges: the two signals go through it side by side, and windows of up to 64
-// positions get one wavefront, which waits for no other (4.1 us at 64 positions with one signal after the other on 256 threads,
-// BOUND_US now).
+// positions get one wavefront, which waits for no other (64 positions, one signal after the other on 256 threads / now:
+// 4.1 / 2.4 us for one sequence, 4.4 / 3.5 for 16).
 #include "common.h"
 
 namespace {

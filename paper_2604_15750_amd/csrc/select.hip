@@ -5,13 +5,15 @@
 //     of the workgroup, four pairs of loads in flight per thread, over a compacted list of the pooled rows: 1024 threads for
 //     blocks of more than 32 rows, whose pairs would otherwise take several trips one after another; the conflicts are a bit
 //     matrix in LDS;
-//   * the order of the rows is a bit matrix too, a ballot per row and 64 others; ranks are counts of its bits.  (A loop over the
-//     rows in each lane, twice, took 7 of the kernel's 10.6 us at 64 rows; SELECT_US now);
+//   * the order of the rows is a bit matrix too, a ballot per row and 64 others; ranks are counts of its bits;
 //   * the greedy walk of phase 2 (in the order of confidence: take a row, drop its conflicts) runs in rounds: a row whose
 //     undecided conflicts all come later in that order is taken, and what conflicts with a row just taken is dropped.  That is
 //     the same set as the walk's, in as many rounds as the longest chain of conflicts instead of as many steps as rows.
-// 16 sequences x 64 rows, one thread walking and one pair per thread and trip against now: 32 / 13 us a call on logits in the caches,
-// 37 / 14 with 1 GiB read and written between the calls; two calls on buffers never touched before 94 / 54, launches included.
+//   * blocks of up to 64 rows have kernels of their own with sets of two words: straight-line code that runs once is bound by the
+//     fetching of its instructions.
+// Kernel time on logits in the caches, 16 sequences x 64 rows: 32 us with one thread walking and one pair per thread and trip, 14.6
+// with a loop over the rows in each lane for the order and the margin, 7.0 without, 5.7 with sets of two words; one sequence x 8 rows
+// 4.3 -> 3.6.
 #include "common.h"
 
 namespace {
