@@ -6,6 +6,7 @@ arrays are plain int lists.  A missing library is an error: there is no
 fallback path.
 """
 import ctypes as C
+import functools
 import os
 import struct
 
@@ -80,10 +81,10 @@ def lib():
         L.dlm_state_reset.argtypes = [C.c_void_p, C.c_int]
         L.dlm_state_kv_len.argtypes = [C.c_void_p, C.c_int]
         L.dlm_step.argtypes = [C.c_void_p, C.POINTER(dlm_step_desc), C.c_void_p]
-        # (the host arrays of the two decisions are void pointers: _packed hands them over as bytes)
-        L.block_boundary.argtypes = [C.c_void_p] * 5 + [C.c_int, C.POINTER(dlm_boundary_params)] + [C.c_void_p] * 4
+        # (the host arrays and parameters of the two decisions are void pointers: they are handed over as bytes)
+        L.block_boundary.argtypes = [C.c_void_p] * 5 + [C.c_int] + [C.c_void_p] * 5
         L.select_parallel.argtypes = [C.c_void_p, C.c_int, C.c_int] + [C.c_void_p] * 7 + \
-                                     [C.c_int, C.c_int, C.POINTER(dlm_select_params), C.c_int] + [C.c_void_p] * 4
+                                     [C.c_int, C.c_int, C.c_void_p, C.c_int] + [C.c_void_p] * 4
         L.dlm_vocab_stats.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int] + [C.c_void_p] * 7 + \
                                      [C.c_size_t, C.c_void_p]
         L.dlm_vocab_stats_static.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int] + [C.c_void_p] * 7
@@ -115,15 +116,33 @@ def _ints(v):
     return None if v is None else (C.c_int32 * len(v))(*[int(x) for x in v])
 
 
+# The two decisions are bound by what their calls cost the host: their host arrays and parameters are handed over as bytes
+# (marshalling alone 3.8 and 6.1 us with ctypes structs and a format string per array, HOST_US now).
+@functools.lru_cache(maxsize=64)
+def _int_packer(n):
+    return struct.Struct(f"{n}i").pack
+
+
 def _packed(v):
-    """A host array as bytes (the two decisions are bound by what their calls cost the host: a ctypes array of 16 takes 2.1 us,
-    this 0.4).  What struct does not take as a 32-bit integer goes the way of _ints."""
+    """A host array as bytes (a ctypes array of 16 takes 2.1 us, this 0.3).  What struct does not take as a 32-bit integer goes
+    the way of _ints."""
     if v is None:
         return None
     try:
-        return struct.pack(f"{len(v)}i", *v)
+        return _int_packer(len(v))(*v)
     except (struct.error, TypeError, OverflowError):
         return bytes(_ints(v))
+
+
+_pack_boundary, _pack_select = struct.Struct("f4i").pack, struct.Struct("3fi").pack
+
+
+def _params(pack, cls, v):
+    """A parameter struct as bytes; values that struct does not take go the way of the ctypes struct."""
+    try:
+        return pack(*v)
+    except (struct.error, TypeError, OverflowError):
+        return bytes(cls(*v))
 
 
 # what torch.cuda.current_stream() asks, without its Stream object (0.3 us against 2.7); a private name, so the public way stays beside it
@@ -136,8 +155,11 @@ def _stream():
     return _raw_stream(torch.cuda.current_device())
 
 
+_DTYPE_CODES = {torch.float32: DLM_F32, torch.bfloat16: DLM_BF16}
+
+
 def dtype_code(t):
-    return {torch.float32: DLM_F32, torch.bfloat16: DLM_BF16}[t if isinstance(t, torch.dtype) else t.dtype]
+    return _DTYPE_CODES[t if isinstance(t, torch.dtype) else t.dtype]
 
 
 class Model:
@@ -245,17 +267,17 @@ def dlm_step(state, tokens, out, row_offsets, span_start, commit_len, tok_start,
 
 def block_boundary(I, H, win_start, win_len, L_out, lam, l_min, smooth_radius=1, norm_mode=0, rule=0, cold=None, S_out=None,
                    margin_out=None):
-    p = dlm_boundary_params(lam, l_min, smooth_radius, norm_mode, rule)
-    _check(lib().block_boundary(_ptr(I), _ptr(H), _packed(win_start), _packed(win_len), _packed(cold), len(win_start), C.byref(p), _ptr(L_out),
+    _check(lib().block_boundary(_ptr(I), _ptr(H), _packed(win_start), _packed(win_len), _packed(cold), len(win_start),
+                                _params(_pack_boundary, dlm_boundary_params, (lam, l_min, smooth_radius, norm_mode, rule)), _ptr(L_out),
                                 _ptr(S_out), _ptr(margin_out), _stream()))
 
 
 def select_parallel(logits, lse, conf, argmax, tokens, row_start, tok_start, block_len, mask_id, tau_low, tau_high, gamma, mode,
                     selected_out, n_selected_out, apply_tokens=True, margin_out=None):
-    p = dlm_select_params(tau_low, tau_high, gamma, mode)
-    _check(lib().select_parallel(_ptr(logits), logits.shape[-1], dtype_code(logits), _ptr(lse), _ptr(conf), _ptr(argmax), _ptr(tokens),
-                                 _packed(row_start), _packed(tok_start), _packed(block_len), len(row_start), mask_id, C.byref(p),
-                                 int(apply_tokens), _ptr(selected_out), _ptr(n_selected_out), _ptr(margin_out), _stream()))
+    _check(lib().select_parallel(_ptr(logits), logits.size(-1), dtype_code(logits), _ptr(lse), _ptr(conf), _ptr(argmax), _ptr(tokens),
+                                 _packed(row_start), _packed(tok_start), _packed(block_len), len(row_start), mask_id,
+                                 _params(_pack_select, dlm_select_params, (tau_low, tau_high, gamma, mode)), int(apply_tokens),
+                                 _ptr(selected_out), _ptr(n_selected_out), _ptr(margin_out), _stream()))
 
 
 def dlm_vocab_stats(logits, mask_id, prev=None, workspace=None, prev_lse=None):
