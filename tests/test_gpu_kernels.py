@@ -261,6 +261,14 @@ def test_vocab_stats_whole_rows(device, dt, rows, V):
         _check_stats(got, o_stats.vocab_stats(z64, mask_id, zp64), z64, zp64, mask_id)
 
 
+# ... and the row counts from which on a workgroup of 256 threads takes a whole row, six or four vectors of it in flight: one whole
+# trip, a ragged end of one vector, less than a trip, no vectors
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,V", [(351, 12296), (352, 12288), (353, 12296), (352, 8199), (1023, 4104), (1024, 8200)])
+def test_vocab_stats_whole_rows_of_many(device, dt, rows, V):
+    test_vocab_stats_whole_rows(device, dt, rows, V)
+
+
 # ---- block_boundary ----------------------------------------------------------------------------------
 @pytest.mark.parametrize("norm_mode", [0, 1, 2, 3])
 @pytest.mark.parametrize("rule", [0, 1])
