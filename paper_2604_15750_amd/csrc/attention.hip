@@ -12,15 +12,21 @@ constexpr int QT = 16;        // query rows per workgroup
 constexpr int KTILE = 32;     // keys per LDS tile
 constexpr float NEG_BIG = -3.0e38f;
 
-template <typename T, int HD>
-__global__ __launch_bounds__(256) void attention_kernel(const T* __restrict__ q, const T* __restrict__ kcache, const T* __restrict__ vcache,
-                                                        size_t slot_stride, AttnMeta meta, T* __restrict__ out, bool out_tiled, int n_q,
-                                                        int n_kv) {
-  __shared__ float qs[QT][HD];
-  __shared__ float ks[KTILE][HD + 1];
-  __shared__ float vs[KTILE][HD];
-  __shared__ float ps[QT][KTILE];
-  constexpr int EPT = HD / 16;  // output elements per thread
+// What bounds it is latency (the fp32 model's passes are small): K and V of the next tile are in flight while a tile is computed, and
+// LDS is read four values at a time (8 rows x 72 keys, 4 heads: 8.2 us with a trip to memory per tile and one value per read, 5.7 now).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));  // (a caller's rows need not lie on 16 bytes)
+
+template <int HD>
+__global__ __launch_bounds__(256) void attention_kernel(const float* __restrict__ q, const float* __restrict__ kcache, const float* __restrict__ vcache,
+                                                        size_t slot_stride, AttnMeta meta, float* __restrict__ out, int n_q, int n_kv) {
+  constexpr int EPT = HD / 16;                   // output elements per thread: consecutive ones
+  constexpr int VPT = KTILE * HD / (256 * 4);    // vectors of a tile per thread
+  constexpr int PAD = 4;                         // (rows of 16 lanes start four banks apart)
+  __shared__ __align__(16) float qs[QT][HD];
+  __shared__ __align__(16) float ks[KTILE][HD + PAD];
+  __shared__ __align__(16) float vs[KTILE][HD];
+  __shared__ __align__(16) float ps[QT][KTILE];
+  typedef float vec_t __attribute__((ext_vector_type(EPT)));
 
   const int b = blockIdx.z, head = blockIdx.y;
   const int row0 = meta.row_off[b] + blockIdx.x * QT;
@@ -29,35 +35,53 @@ __global__ __launch_bounds__(256) void attention_kernel(const T* __restrict__ q,
   const int n_keys = meta.n_keys[b];
   const int kvh = head / (n_q / n_kv);
   const size_t kv_row = (size_t)n_kv * HD;
-  const T* kbase = kcache + (size_t)meta.slot[b] * slot_stride + (size_t)kvh * HD;
-  const T* vbase = vcache + (size_t)meta.slot[b] * slot_stride + (size_t)kvh * HD;
+  const float* kbase = kcache + (size_t)meta.slot[b] * slot_stride + (size_t)kvh * HD;
+  const float* vbase = vcache + (size_t)meta.slot[b] * slot_stride + (size_t)kvh * HD;
   const int tid = threadIdx.x, qi = tid >> 4, lx = tid & 15;
   const float scale = rsqrtf((float)HD);
 
-  for (int i = tid; i < QT * HD; i += 256) {
-    const int r = i / HD, e = i % HD;
-    qs[r][e] = (row0 + r < row_end) ? to_f32(q[(size_t)(row0 + r) * n_q * HD + (size_t)head * HD + e]) * scale : 0.f;
-  }
-  float m = NEG_BIG, l = 0.f, o[EPT];
+  f32x4 kn[VPT], vn[VPT];  // the next tile's vectors; keys past the end re-read the last one (they are masked below)
+  auto fetch = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
-  for (int n = 0; n < EPT; ++n) o[n] = 0.f;
+    for (int i = 0; i < VPT; ++i) {
+      const int at = (tid + 256 * i) * 4;
+      const size_t o = (size_t)min(k0 + at / HD, n_keys - 1) * kv_row + at % HD;
+      kn[i] = *(const f32x4_any*)(kbase + o);
+      vn[i] = *(const f32x4_any*)(vbase + o);
+    }
+  };
+  fetch(0);
+  for (int i = tid * 4; i < QT * HD; i += 256 * 4) {
+    const int r = i / HD, e = i % HD;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (row0 + r < row_end) v = *(const f32x4_any*)(q + (size_t)(row0 + r) * n_q * HD + (size_t)head * HD + e) * scale;
+    *(f32x4*)&qs[r][e] = v;
+  }
+  float m = NEG_BIG, l = 0.f;
+  vec_t o = {};
 
   for (int k0 = 0; k0 < n_keys; k0 += KTILE) {
-    __syncthreads();
-    for (int i = tid; i < KTILE * HD; i += 256) {
-      const int kk = i / HD, e = i % HD;
-      const bool ok = k0 + kk < n_keys;
-      ks[kk][e] = ok ? to_f32(kbase[(size_t)(k0 + kk) * kv_row + e]) : 0.f;
-      vs[kk][e] = ok ? to_f32(vbase[(size_t)(k0 + kk) * kv_row + e]) : 0.f;
+    if (k0) __syncthreads();  // the previous tile has been read
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      const int at = (tid + 256 * i) * 4;
+      const bool ok = k0 + at / HD < n_keys;
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      *(f32x4*)&ks[at / HD][at % HD] = ok ? kn[i] : zero;
+      *(f32x4*)&vs[at / HD][at % HD] = ok ? vn[i] : zero;
     }
     __syncthreads();
+    if (k0 + KTILE < n_keys) fetch(k0 + KTILE);
     // scores: thread (qi, lx) handles keys lx and lx + 16
     float s0 = 0.f, s1 = 0.f;
 #pragma unroll 8
-    for (int e = 0; e < HD; ++e) {
-      const float qv = qs[qi][e];
-      s0 = fmaf(qv, ks[lx][e], s0);
-      s1 = fmaf(qv, ks[lx + 16][e], s1);
+    for (int e = 0; e < HD; e += 4) {
+      const f32x4 qv = *(const f32x4*)&qs[qi][e], a = *(const f32x4*)&ks[lx][e], c = *(const f32x4*)&ks[lx + 16][e];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        s0 = fmaf(qv[t], a[t], s0);
+        s1 = fmaf(qv[t], c[t], s1);
+      }
     }
     if (k0 + lx >= n_keys) s0 = NEG_BIG;
     if (k0 + lx + 16 >= n_keys) s1 = NEG_BIG;
@@ -76,23 +100,23 @@ __global__ __launch_bounds__(256) void attention_kernel(const T* __restrict__ q,
     ps[qi][lx] = p0;
     ps[qi][lx + 16] = p1;
     __syncthreads();
+    o *= corr;
+#pragma unroll 4
+    for (int kk = 0; kk < KTILE; kk += 4) {
+      const f32x4 p = *(const f32x4*)&ps[qi][kk];
 #pragma unroll
-    for (int n = 0; n < EPT; ++n) o[n] *= corr;
-    for (int kk = 0; kk < KTILE; ++kk) {
-      const float p = ps[qi][kk];
+      for (int t = 0; t < 4; ++t) {
+        const vec_t v = *(const vec_t*)&vs[kk + t][lx * EPT];
 #pragma unroll
-      for (int n = 0; n < EPT; ++n) o[n] = fmaf(p, vs[kk][lx + 16 * n], o[n]);
+        for (int n = 0; n < EPT; ++n) o[n] = fmaf(p[t], v[n], o[n]);
+      }
     }
   }
   const int r = row0 + qi;
   if (r < row_end) {
-    const int width = n_q * HD;
+    float* dst = out + (size_t)r * n_q * HD + head * HD + lx * EPT;
 #pragma unroll
-    for (int n = 0; n < EPT; ++n) {
-      const int col = head * HD + lx + 16 * n;
-      const size_t idx = out_tiled ? Act<T>::idx(r, col, width) : (size_t)r * width + col;
-      out[idx] = from_f32<T>(o[n] / l);
-    }
+    for (int n = 0; n < EPT; ++n) dst[n] = o[n] / l;
   }
 }
 
@@ -143,13 +167,12 @@ void launch_pack_kv(const bf16_t* k, const bf16_t* v, f16_t* kt, f16_t* vt, int 
   pack_kv_kernel<<<256, 256, 0, st>>>(k, v, kt, vt, T, n_kv, hd, head_stride);
 }
 
-template <>
-void launch_attention<float>(const float* q, const float* kcache, const float* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,
-                             float* out, bool out_tiled, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st) {
+void launch_attention_f32(const float* q, const float* kcache, const float* vcache, size_t slot_stride, const AttnMeta& meta, float* out,
+                          int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st) {
   dim3 grid((max_seq_rows + QT - 1) / QT, n_q, meta.n_seqs);
-  if (hd == 32) attention_kernel<float, 32><<<grid, 256, 0, st>>>(q, kcache, vcache, slot_stride, meta, out, out_tiled, n_q, n_kv);
-  else if (hd == 64) attention_kernel<float, 64><<<grid, 256, 0, st>>>(q, kcache, vcache, slot_stride, meta, out, out_tiled, n_q, n_kv);
-  else attention_kernel<float, 128><<<grid, 256, 0, st>>>(q, kcache, vcache, slot_stride, meta, out, out_tiled, n_q, n_kv);
+  if (hd == 32) attention_kernel<32><<<grid, 256, 0, st>>>(q, kcache, vcache, slot_stride, meta, out, n_q, n_kv);
+  else if (hd == 64) attention_kernel<64><<<grid, 256, 0, st>>>(q, kcache, vcache, slot_stride, meta, out, n_q, n_kv);
+  else attention_kernel<128><<<grid, 256, 0, st>>>(q, kcache, vcache, slot_stride, meta, out, n_q, n_kv);
 }
 
 // How a pass is laid out.  A narrow one (few query tiles x heads): eight wavefronts per workgroup to shorten each wavefront's chain

@@ -259,13 +259,13 @@ int norm_chunks(int d);
 // The first launch of a pass: row tables and rotary tables, h = embedding row, x = h * gain, ssq
 template <typename T>
 void launch_embed(const SeqMeta& meta, const StatsMeta& sm, const T* embed, const int32_t* tokens, const RowTables& t, const float* gain, float* h,
-                  typename Act<T>::x_t* x, float* ssq, int rows, int d, int vocab, int head_dim, float theta, hipStream_t st);
-// softmax(q k^T / sqrt(hd)) v over keys [0, n_keys) of the row's slot; q row-major, out in the activation layout [rows, n_q*hd]
-// (out_tiled) or row-major.  fp32 cache: row-major [pos][n_kv*hd] per slot (head_stride unused); bf16 cache: per (slot, kv head)
-// a region of head_stride elements in the fragment tiling below.
-template <typename T>
-void launch_attention(const T* q, const T* kcache, const T* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta, T* out,
-                      bool out_tiled, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st);
+                  typename Act<T>::x_t* x, float* ssq, int rows, int d, int vocab, int head_dim, const float* rope_table, hipStream_t st);
+// cosines and sines of every position, [positions][hd]: hd/2 cosines, then hd/2 sines (computed in 64 bits)
+void launch_rope_table(float* table, int positions, int head_dim, float theta, hipStream_t st);
+// softmax(q k^T / sqrt(hd)) v over keys [0, n_keys) of the row's slot.  fp32 model: q, out [rows, n_q*hd] and the cache (row-major
+// [pos][n_kv*hd] per slot) are row-major; bf16 models' cache: per (slot, kv head) a region of head_stride elements in the fragment tiling above.
+void launch_attention_f32(const float* q, const float* kcache, const float* vcache, size_t slot_stride, const AttnMeta& meta, float* out,
+                          int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st);
 // bf16 models: q (fragment tiles [rows, n_q*hd]) and the KV cache hold IEEE half; the output goes to out_tiles (fragment tiles [rows, n_q*hd] in half: the O
 // projection's input) if that is given, else to out_rows (row-major bf16)
 struct AttnPlan {

@@ -109,7 +109,7 @@ struct dlm_state {
   size_t layer_stride;  // elements per layer
   DevBuf kcache, vcache, prev_logits, prev_lse;
   DevBuf h, x, x2, act, q, part, stats_ws, ssq, counters;
-  DevBuf row_pos, row_slot, rope_cos, rope_sin, prev_row, save_row;
+  DevBuf row_pos, row_slot, rope_cos, rope_sin, rope_table, prev_row, save_row;
   std::vector<int> kv_len, covered_end, prev_cur, prev_base, prev_count;  // covered_end: positions [0, covered_end) hold K and V of some pass
   size_t part_elems;
   bool fuse_stats = true;  // passes that qualify take their statistics from the LM head's epilogue (dlm_state_fuse_stats)
@@ -299,6 +299,7 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
   A(s->counters, (size_t)n_counters * 4);
   A(s->row_pos, (size_t)max_rows * 4); A(s->row_slot, (size_t)max_rows * 4);
   A(s->rope_cos, (size_t)max_rows * (c.head_dim / 2) * 4); A(s->rope_sin, (size_t)max_rows * (c.head_dim / 2) * 4);
+  A(s->rope_table, (size_t)max_seq_len * c.head_dim * 4);
   A(s->prev_row, (size_t)max_rows * 8); A(s->save_row, (size_t)max_rows * 8);
   if (rc == DLM_OK) {
     // padding rows of the tiled activations are read by the matrix cores: keep them finite
@@ -309,6 +310,11 @@ extern "C" int dlm_state_create(const dlm_model* m, int max_seqs, int max_seq_le
     if (e == hipSuccess) e = hipMemset(s->x2.p, 0, (size_t)s->max_rows_pad * xw * es);
     if (e == hipSuccess) e = hipMemset(s->act.p, 0, (size_t)s->max_rows_pad * c.d_ffn * es);
     if (e == hipSuccess) e = hipMemset(s->counters.p, 0, (size_t)n_counters * 4);
+    if (e == hipSuccess) {
+      launch_rope_table((float*)s->rope_table.p, max_seq_len, c.head_dim, c.rope_theta, nullptr);
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) rc = dlm_fail(DLM_EHIP, "dlm_state_create: hipMemset: %s", hipGetErrorString(e));
   }
   if (rc != DLM_OK) { delete s; return rc; }
@@ -388,7 +394,7 @@ int run_step_f32(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, cons
   };
   {
     ProfScope ps(pf, st, PC_OTHER);
-    launch_embed<T>(meta, sm, (const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, hd, c.rope_theta, st);
+    launch_embed<T>(meta, sm, (const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, hd, (const float*)s->rope_table.p, st);
   }
   int nch = norm_chunks(dm);  // chunks of the row sums of squares the next consumer reads: the embedding's, then those of EPI_RESID
   auto scale = [&]() { return RowScale{ssq, nch, 1.f / (float)dm, c.rms_eps}; };
@@ -403,7 +409,7 @@ int run_step_f32(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, cons
       gemm(PC_QKV, EPI_QKV, x, m->wqkv[l].p, qd + 2 * nkv * hd, dm, e);
     }
     { ProfScope ps(pf, st, PC_ATTENTION);
-      launch_attention<T>(q, kc, vc, s->slot_stride, s->head_stride, am, x2, true, rows, max_seq_rows, nq, nkv, hd, st); }
+      launch_attention_f32(q, kc, vc, s->slot_stride, am, x2, max_seq_rows, nq, nkv, hd, st); }
     {
       GemmF32Epi e = base;
       e.h = h; e.gain = (const float*)m->norm2[l].p; e.x = x; e.ssq_out = ssq;
@@ -469,7 +475,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   };
   {
     ProfScope ps(pf, st, PC_OTHER);
-    launch_embed<T>(meta, sm, (const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, hd, c.rope_theta, st);
+    launch_embed<T>(meta, sm, (const T*)m->embed.p, d->tokens, t, (const float*)m->norm1[0].p, h, x, ssq, rows, dm, c.vocab, hd, (const float*)s->rope_table.p, st);
   }
   // chunks of the row sums of squares the next consumer reads: the embedding's, then those of the GEMM that produced them
   int nch = norm_chunks(dm);
@@ -757,7 +763,7 @@ extern "C" int dlm_attention(const void* q, const void* k, const void* v, void* 
   am.n_seqs = 1; am.row_off[1] = A; am.n_keys[0] = T;
   hipStream_t st = (hipStream_t)stream;
   if (dtype == DLM_F32) {
-    launch_attention<float>((const float*)q, (const float*)k, (const float*)v, 0, 0, am, (float*)out, false, A, A, n_q, n_kv, head_dim, st);
+    launch_attention_f32((const float*)q, (const float*)k, (const float*)v, 0, am, (float*)out, A, n_q, n_kv, head_dim, st);
     return DLM_OK;
   }
   // bf16: K and V re-tiled into the half-precision cache layout, q converted to half fragment tiles (test helper: allocates and synchronises)

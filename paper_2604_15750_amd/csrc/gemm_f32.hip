@@ -157,8 +157,10 @@ void launch_mt(const float* x, const float* w, int M, int N, int K, const GemmF3
 
 template <int EPI>
 void launch_epi(const float* x, const float* w, int M, int N, int K, const GemmF32Epi& e, bool vec, hipStream_t st) {
-  // as many steps per trip as a quarter of K usually is (K = 384: 6) where the registers hold them
-  if (M <= 16) launch_mt<1, 6, EPI>(x, w, M, N, K, e, vec, st);
+  // as many steps per trip as a quarter of K usually is (K = 384: 6, K = 128: 2) where the registers hold them; a step too many is four
+  // products of zeros per column tile
+  if (M <= 32 && K <= 128) { if (M <= 16) launch_mt<1, 2, EPI>(x, w, M, N, K, e, vec, st); else launch_mt<2, 2, EPI>(x, w, M, N, K, e, vec, st); }
+  else if (M <= 16) launch_mt<1, 6, EPI>(x, w, M, N, K, e, vec, st);
   else if (M <= 32) launch_mt<2, 4, EPI>(x, w, M, N, K, e, vec, st);
   else launch_mt<4, 2, EPI>(x, w, M, N, K, e, vec, st);
 }
