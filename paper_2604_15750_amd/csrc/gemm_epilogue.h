@@ -67,8 +67,9 @@ __device__ __attribute__((always_inline)) inline float sum_row4(float v) {
 // 1/rms of rows [m_lo, m_lo + rows) from the producer's partial sums of squares into s_rinv, by the whole workgroup of NT
 // threads: sixteen lanes per row, each adding every sixteenth chunk in ascending order, then a fixed butterfly
 // (deterministic).  A lane's sixteen loads of a block of 256 chunks are issued together and waited for once: one trip to
-// memory per block instead of one per chunk.
-template <int NT>
+// memory per block instead of one per chunk.  STRAIGHT: chunks past the end re-read the last one instead of being skipped by a path
+// per load.
+template <int NT, bool STRAIGHT = false>
 __device__ inline void block_rinv(const RowScale& rs, int m_lo, int rows, float* s_rinv) {
   const int sub = threadIdx.x & 15;
   for (int row = threadIdx.x >> 4; row < rows; row += NT / 16) {
@@ -80,7 +81,12 @@ __device__ inline void block_rinv(const RowScale& rs, int m_lo, int rows, float*
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
           const int c = c0 + sub + 16 * k;
-          v[k] = c < rs.nch ? src[c] : 0.f;
+          if (STRAIGHT) {
+            const float t = src[min(c, rs.nch - 1)];
+            v[k] = c < rs.nch ? t : 0.f;
+          } else {
+            v[k] = c < rs.nch ? src[c] : 0.f;
+          }
         }
 #pragma unroll
         for (int k = 0; k < 16; ++k) ss += v[k];
@@ -102,13 +108,15 @@ struct RinvBatch {
   float v[RPT][4];
   __device__ __attribute__((always_inline)) inline void fetch(const RowScale& rs, int m_lo, int rows) {
     const int sub = threadIdx.x & 15;
+    if (!rs.ssq) return;
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       const int row = (threadIdx.x >> 4) + r * (NT / 16);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const int c = sub + 16 * k;
-        v[r][k] = (rs.ssq && row < rows && c < rs.nch) ? rs.ssq[(size_t)(m_lo + row) * rs.nch + c] : 0.f;
+        const float t = rs.ssq[(size_t)(m_lo + min(row, rows - 1)) * rs.nch + min(c, rs.nch - 1)];
+        v[r][k] = c < rs.nch ? t : 0.f;
       }
     }
   }

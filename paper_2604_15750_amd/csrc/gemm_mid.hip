@@ -172,7 +172,9 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   }
   // 1/rms of the input rows, needed only by the epilogue: fetched while the first k-tiles are in flight (published by the
   // barriers of the reduction)
-  if (EPI != EPI_RESID) block_rinv<TPB>(e.rs, 0, min(M, MT * 16), s_rinv);
+  // (one straight run of loads for gate/up of up to 16 rows: 34.9 -> 33.5 us; with more rows, or before the rotary epilogue, it costs: 37.6 ->
+  // 42.7 us at 37 rows, QKV 18.8 -> 20.0 at 8)
+  if (EPI != EPI_RESID) block_rinv<TPB, MT == 1 && EPI == EPI_SWIGLU>(e.rs, 0, min(M, MT * 16), s_rinv);
   // ... and so is what the epilogue of the fragment this wavefront finishes first (fragment `wave`) reads from memory, in the
   // variants of narrow passes, which are short enough for that round trip to show
   EpiAhead ahead = epi_none();

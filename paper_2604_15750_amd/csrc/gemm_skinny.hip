@@ -21,19 +21,18 @@ __global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __rest
                                                                int K, GemmEpi e) {
   __shared__ f32x4 red[NWV][R * MT][64];
   __shared__ float s_rinv[MT * 16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int KT = K >> 5, MTILES = (M + 15) >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int KT = K >> 5;
   const int per = (KT + NWV - 1) / NWV;
   const int t_begin = wave * per, t_end = min(KT, t_begin + per);
   const op8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   // lanes of the last row tile whose row does not exist re-read row 0 of their k-group (whatever they get is never stored)
-  const int xlane_last = (MTILES - 1) * 16 + (lane & 15) < M ? lane : (lane & ~15);
+  const int xlane_last = (MT - 1) * 16 + (lane & 15) < M ? lane : (lane & ~15);
   // the workgroup's R tiles are one interleaved run; in the step-major copy (KT a multiple of NWV: the host checks) the
   // wavefront's step s is the R fragments from ((s * workgroups + this workgroup) * NWV + wave) * R on
-  constexpr bool steps = STEPS;
-  const op8* wbase = steps ? (const op8*)e.w_steps + ((size_t)blockIdx.x * NWV + wave) * R * 64 + lane : wt + (size_t)blockIdx.x * KT * R * 64 + lane;
-  const size_t wstride = steps ? (size_t)gridDim.x * NWV * R * 64 : R * 64;
-  const int tsub = steps ? t_begin : 0;
+  const op8* wbase = STEPS ? (const op8*)e.w_steps + ((size_t)blockIdx.x * NWV + wave) * R * 64 : wt + (size_t)blockIdx.x * KT * R * 64;
+  const size_t wstride = STEPS ? (size_t)gridDim.x * NWV * R * 64 : R * 64;
+  const int tsub = STEPS ? t_begin : 0;
 
   f32x4 acc[R][MT];
 #pragma unroll
@@ -42,38 +41,55 @@ __global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __rest
     for (int j = 0; j < MT; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   op8 wreg[2][D][R], xreg[2][D][MT];
 
-  auto load = [&](int buf, int tb) {
+  // k-tiles past the wavefront's last one re-read that: the loads are unconditional, as a path around them is one the compiler's count
+  // of outstanding loads cannot follow, and scalar in everything but the lane, as a short kernel is bound by the fetching of its
+  // instructions first (a test per fragment and addresses in vectors: 2.4 us from the start
+  // to the last load of the first batch, 1.0 now; down of an 8B model at 8 rows 18.6 -> 18.0)
+  auto load = [&](int buf, int tb) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      const int t = tb + i;
-      const bool ok = t < t_end;
+      const int t = min(tb + i, t_end - 1);
 #pragma unroll
-      for (int r = 0; r < R; ++r) wreg[buf][i][r] = ok ? wbase[(size_t)(t - tsub) * wstride + r * 64] : zero8;
+      for (int r = 0; r < R; ++r) wreg[buf][i][r] = (wbase + (size_t)(t - tsub) * wstride + r * 64)[lane];
 #pragma unroll
-      for (int j = 0; j < MT; ++j) xreg[buf][i][j] = (ok && j < MTILES) ? xt[((size_t)j * KT + t) * 64 + (j == MTILES - 1 ? xlane_last : lane)] : zero8;
+      for (int j = 0; j < MT; ++j) xreg[buf][i][j] = (xt + ((size_t)j * KT + t) * 64)[j == MT - 1 ? xlane_last : lane];
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto compute = [&](int buf) {
+  auto compute = [&](int buf, int tb, bool whole) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < D; ++i)
+    for (int i = 0; i < D; ++i) {
+      const bool past = !whole && tb + i >= t_end;  // (multiplies zeros)
 #pragma unroll
-      for (int j = 0; j < MT; ++j)
+      for (int j = 0; j < MT; ++j) {
+        const op8 x = past ? zero8 : xreg[buf][i][j];
 #pragma unroll
-        for (int r = 0; r < R; ++r) acc[r][j] = mfma_op(wreg[buf][i][r], xreg[buf][i][j], acc[r][j]);
+        for (int r = 0; r < R; ++r) acc[r][j] = mfma_op(wreg[buf][i][r], x, acc[r][j]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  load(0, t_begin);
+  const bool any = t_begin < t_end;  // (uniform: a wavefront beyond a short K has no k-tiles)
+  if (any) load(0, t_begin);
   // 1/rms of the input rows, needed only by the epilogue: fetched while the first batch is in flight; so is what the epilogue
   // of the tile this wavefront finishes first reads from memory (tile rj = wave of the R * MT)
   if (EPI != EPI_RESID) block_rinv<NWV * 64>(e.rs, 0, min(M, MT * 16), s_rinv);
   EpiAhead ahead = epi_none();
   if ((EPI == EPI_RESID || EPI == EPI_QKV) && wave < R * MT)
     ahead = epi_ahead<EPI>(e, M, N, (wave % MT) * 16 + (lane & 15), (blockIdx.x * R + wave / MT) * 16, lane >> 4);
-  for (int tb = t_begin; tb < t_end; tb += 2 * D) {
-    load(1, tb + D);
-    compute(0);
-    load(0, tb + 2 * D);
-    compute(1);
+  if (any) {
+    int tb = t_begin;
+    for (; tb + 2 * D < t_end; tb += 2 * D) {
+      load(1, tb + D);
+      compute(0, tb, true);
+      load(0, tb + 2 * D);
+      compute(1, tb + D, true);
+    }
+    const bool second = tb + D < t_end;  // the last one or two batches
+    if (second) load(1, tb + D);
+    compute(0, tb, false);
+    if (second) compute(1, tb + D, false);
   }
 
 #pragma unroll
