@@ -11,7 +11,7 @@
 //     consecutive output columns of one row.
 // gemm_skinny.hip and gemm_mid.hip (all rows of a column group in one workgroup) serve narrow passes, gemm_macro*.hip (both
 // operands through LDS, output tiles of 32 .. 256 rows) everything wider and the LM head (choose_kernel below); the layer's row-wise glue runs in their epilogues (gemm_epilogue.h):
-//   QKV     1/rms of the input row, rotary embedding, Q row-major, K and V into the tiled KV cache
+//   QKV     1/rms of the input row, rotary embedding, Q into fragment tiles, K and V into the tiled KV cache
 //   SWIGLU  1/rms, silu(gate) * up into the fragment tiling of the down projection
 //   RESID   residual add, x = h * gain of the next RMSNorm into fragment tiling, and the share of
 //           sum(h^2) per row of each column tile

@@ -428,6 +428,37 @@ def test_packed_spans_of_one_and_more_query_tiles(device, spans):
     model.close()
 
 
+@pytest.mark.parametrize("hd", [32, 64, 128])
+@pytest.mark.parametrize("commits,spans", [([4, 8], [120, 100]), ([5, 18, 31], [97, 65, 71]), ([1, 2, 3, 7], [57, 131, 16, 30])])
+def test_wide_spans_behind_prefixes_of_any_length(device, hd, commits, spans):
+    """Packed spans of a wide pass whose positions and rows are out of step with the cache's quads of positions (V is written in
+    quads where four rows of one sequence fill one, value by value elsewhere), next to spans that are in step: every sequence's
+    logits against the oracle's."""
+    cfg = inputs.model_config(1, 256, 512 // hd, 256 // hd, hd, 512, 1024, "bf16")
+    assert api.plan_gemm(sum(spans), 1024, 256, "qkv")["kernel"] == "macro"
+    W = _weights(cfg, 23, device)
+    Wn = inputs.weights_to_numpy(W)
+    model = api.Model(cfg, W)
+    B, T = len(spans), max(c + n for c, n in zip(commits, spans))
+    state = api.State(model, B, T, max(sum(spans), sum(commits)), 8)
+    out = api.StepOutputs(max(sum(spans), sum(commits)), cfg["vocab"], model.torch_dtype, device)
+    tokens = torch.randint(0, cfg["vocab"] - 1, (B, T), generator=torch.Generator().manual_seed(hd + B), dtype=torch.int32)
+    toks, at = tokens.to(device), [b * T for b in range(B)]
+    api.dlm_step(state, toks, out, [0] + np.cumsum(commits).tolist(), [0] * B, commits, at)
+    off = [0] + np.cumsum(spans).tolist()
+    api.dlm_step(state, toks, out, off, commits, [0] * B, [a + c for a, c in zip(at, commits)])
+    torch.cuda.synchronize()
+    z = o_fwd.widen(inputs.tensor_to_numpy(out.logits))
+    for b, (c, n) in enumerate(zip(commits, spans)):
+        cache, row = o_fwd.KVCache(cfg), tokens[b].numpy()
+        o_fwd.forward_span(cfg, Wn, cache, row[:c], 0, c)
+        ref = o_fwd.forward_span(cfg, Wn, cache, row[c: c + n], c, 0)
+        err = np.abs(z[off[b]: off[b + 1]] - ref) / np.maximum(np.abs(ref).max(-1, keepdims=True), SIGMA_LOGIT)
+        assert (err <= 2e-2).all(), (b, c, n, err.max())
+    state.close()
+    model.close()
+
+
 def _one_pass_matches(cfg, M, device, seed, stats=False):
     """One pass of M rows of one sequence without a prefix: every row's logits against the oracle's, and (stats) the statistics
     against the oracle's of the logits as written."""
