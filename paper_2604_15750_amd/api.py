@@ -117,7 +117,7 @@ def _ints(v):
 
 
 # The two decisions are bound by what their calls cost the host: their host arrays and parameters are handed over as bytes
-# (marshalling alone 3.8 and 6.1 us with ctypes structs and a format string per array, HOST_US now).
+# (marshalling alone 3.8 and 6.1 us with ctypes structs and a format string per array, 2.7 and 4.8 now).
 @functools.lru_cache(maxsize=64)
 def _int_packer(n):
     return struct.Struct(f"{n}i").pack

@@ -55,7 +55,7 @@ struct MacroPlan {
 // K is split only where a wavefront has at most this many output fragments: the last arriver holds two tiles of them
 constexpr int MACRO_SPLIT_FRAGS = 16;
 // tiles that also come with two sums of K, or two chunks of the squares, per workgroup: an instantiation of its own, so that the plain
-// kernel keeps its loop and its registers (96 x 128: 81 against 108, 128 x 256: 211 against 230)
+// kernel keeps its loop and its registers (QKV, 96 x 128: 95 against 124, 128 x 256: 229 against 250)
 constexpr bool macro_can_keep_order(int wm, int wn, int kb) { return kb == 2 && wm * wn >= 6 && wm * wn <= MACRO_SPLIT_FRAGS; }
 
 // gemm_macro_<epilogue>.hip: the launches of one epilogue's instantiations
