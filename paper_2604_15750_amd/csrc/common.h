@@ -291,7 +291,6 @@ struct StatsRows {
 };
 struct StatsPlan {
   int threads;        // of a workgroup
-  int trip;           // vectors of a row a lane has in flight
   int chunk, chunks;  // tokens of a chunk, chunks of a row (more than one: a second launch merges them)
   bool vector;        // rows are read in 16-byte vectors
 };

@@ -83,20 +83,15 @@ __device__ inline void absorb(Run& p, const float (&z)[N], const float (&zp)[N],
 #pragma unroll
   for (int i = 0; i < N; ++i) vm = fmaxf(vm, (ALL || ((valid >> i) & 1u)) ? z[i] : RUN_MIN);
   if (__builtin_amdgcn_ballot_w64(vm > p.m) != 0) new_maximum<N>(p, z, ALL ? 0xffffffffu : valid, vm, v0);
-  // the N elements' sums first, then one addition each to the running ones: a lane that walks a whole row adds 62 times, not 494
-  float s = 0.f, t2 = 0.f, w = 0.f;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const float d2 = (z[i] - p.m) * LOG2E;  // the difference first: exact for nearby values
     float e = __builtin_amdgcn_exp2f(d2);
     if (!ALL) e = ((valid >> i) & 1u) ? e : 0.f;
-    s += e;
-    t2 = fmaf(e, ALL ? d2 : (((valid >> i) & 1u) ? d2 : 0.f), t2);
-    if (KL) w = fmaf(e, ALL ? z[i] - zp[i] : (((valid >> i) & 1u) ? z[i] - zp[i] : 0.f), w);
+    p.s += e;
+    p.t2 = fmaf(e, ALL ? d2 : (((valid >> i) & 1u) ? d2 : 0.f), p.t2);
+    if (KL) p.w = fmaf(e, ALL ? z[i] - zp[i] : (((valid >> i) & 1u) ? z[i] - zp[i] : 0.f), p.w);
   }
-  p.s += s;
-  p.t2 += t2;
-  p.w += w;
   if (KL && PREV_SUMS) {
     float pv = RUN_MIN;
 #pragma unroll
@@ -126,13 +121,13 @@ __device__ inline void finalize(const Part& p, int row, bool has_prev, float pre
 // l-th vector of every stride).  Whole trips of U vectors (16 bytes each) per lane are loaded together and absorbed one after
 // the other without a bounds or mask test; the trip that holds the mask token and the ragged last one take the path with
 // per-element validity.  Loop bounds are uniform in the workgroup: the absorb steps exchange values between lanes.
-template <typename T, int TPB, int U, bool VECTOR, bool KL, bool PREV_SUMS>
+template <typename T, int TPB, bool VECTOR, bool KL, bool PREV_SUMS>
 __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const T* __restrict__ p_row, T* __restrict__ s_row, int lo,
                                     int hi, int mask_id) {
   constexpr int N = Vec<T>::N;
   typedef typename Vec<T>::type V;
   if (VECTOR) {
-    constexpr int STRIDE = TPB * N, TRIP = U * STRIDE;
+    constexpr int U = TPB > 256 ? 2 : 4, STRIDE = TPB * N, TRIP = U * STRIDE;
     const int base = lo + threadIdx.x * N;
     const int nfull = (hi - lo) / TRIP;
     for (int t = 0; t * TRIP < hi - lo; ++t) {
@@ -183,7 +178,7 @@ __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const
   }
 }
 
-template <typename T, int TPB, int U, bool VECTOR>
+template <typename T, int TPB, bool VECTOR>
 __global__ __launch_bounds__(TPB) void vocab_stats_kernel(const T* __restrict__ logits, int rows, int vocab, int mask_id, int chunk,
                                                           int nchunks, StatsRows sr, StatsOut o, Part* __restrict__ parts) {
   __shared__ Part sh[TPB / 64];
@@ -199,9 +194,9 @@ __global__ __launch_bounds__(TPB) void vocab_stats_kernel(const T* __restrict__ 
   const int lo = c * chunk, hi = min(vocab, lo + chunk);
 
   Run run = run_init();
-  if (!kl) stream_chunk<T, TPB, U, VECTOR, false, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
-  else if (!prev_sums) stream_chunk<T, TPB, U, VECTOR, true, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
-  else stream_chunk<T, TPB, U, VECTOR, true, true>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  if (!kl) stream_chunk<T, TPB, VECTOR, false, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  else if (!prev_sums) stream_chunk<T, TPB, VECTOR, true, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  else stream_chunk<T, TPB, VECTOR, true, true>(run, z_row, p_row, s_row, lo, hi, mask_id);
   const Part p = run_finish(run);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = p;
   __syncthreads();
@@ -244,12 +239,11 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
 
 constexpr int MAX_CHUNKS = 32;
 constexpr int ROW_MIN = 136, ROW_MAX = 256;  // rows that can get a workgroup of 1024 threads each (stats_plan)
-constexpr int ROW_MANY = 352;                // ... and from which on they get one of 256 threads each
 
-template <typename T, int TPB, int U, bool VECTOR>
+template <typename T, int TPB, bool VECTOR>
 void launch_items(const T* logits, int rows, int vocab, int mask_id, const StatsPlan& p, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
   // (the hardware dispatcher balances better than a resident grid walking the items)
-  vocab_stats_kernel<T, TPB, U, VECTOR><<<rows * p.chunks, TPB, 0, st>>>(logits, rows, vocab, mask_id, p.chunk, p.chunks, sr, o, (Part*)workspace);
+  vocab_stats_kernel<T, TPB, VECTOR><<<rows * p.chunks, TPB, 0, st>>>(logits, rows, vocab, mask_id, p.chunk, p.chunks, sr, o, (Part*)workspace);
   if (p.chunks > 1) vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)workspace, rows, p.chunks, vocab, sr, o);
 }
 
@@ -277,11 +271,10 @@ void launch_stats_merge(const void* parts, int rows, int nparts, int vocab, cons
 // Without 16-byte vectors a lane has one scalar load in flight, and fewer lanes are what it loses by: 126463 tokens, bf16, 96 rows
 //   20.5 -> 34.6 / 23.5 -> 58.9, 256: 44.2 -> 55.2 / 48.0 -> 60.0.  With one chunk the larger workgroup has nothing to save:
 //   1024 tokens, fp32, 96 .. 256 rows 4.4 -> 6.4.
-// From 352 rows on a workgroup of 256 threads per row: several are on a unit and all of them (to about 1500 rows) on the chip at once, so
-//   there is no second round, and they share the memory's rate evenly enough to end together.  Six vectors of a row in flight per
-//   lane below 1024 rows, where the workgroups are few.  Logits from memory, chunks -> whole rows, without / with a previous row, launches
-//   included: 320 rows 27.1 -> 27.7 / 38.1 -> 37.9, 384: 28.6 -> 28.8 / 44.3 -> 41.2, 486: 31.7 -> 30.1 / 51.7 -> 47.7, 512: 37.6 -> 30.4 / 57.0 ->
-//   50.0, 576: 39.4 -> 36.1 / 60.4 -> 64.3, 768: 49.3 -> 40.1 / 80.2 -> 72.2, 1280: 67.3 -> 63.8 / 117.2 -> 114.8.
+// More rows keep their chunks.  A workgroup of 256 threads per row saves the merge there, but a lane then walks five times as far: each
+// addend straight into the running sum, KL left 1e-5 of its value behind; a partial sum per vector first, all values were others than
+// those of the same row in a call of fewer rows, and units that got a row more than the mean took longer (528 rows with a
+// previous row, logits from memory: 57 -> 62 us).
 StatsPlan stats_plan(int rows, int vocab, int elem_size) {
   const int n = 16 / elem_size;  // elements of a vector
   const int want = (1536 + rows - 1) / rows, most = (vocab + 512 * n - 1) / (512 * n);
@@ -291,9 +284,7 @@ StatsPlan stats_plan(int rows, int vocab, int elem_size) {
   StatsPlan p;
   p.vector = vocab % n == 0;
   p.threads = p.vector && nch > 1 && rows >= ROW_MIN && rows <= ROW_MAX ? 1024 : 256;
-  const bool whole = p.vector && nch > 1 && rows >= ROW_MANY;
-  p.trip = whole && rows < 1024 ? 6 : 4;
-  if (p.threads == 1024 || whole) nch = 1;
+  if (p.threads == 1024) nch = 1;
   const int unit = p.threads * n;  // chunks are whole strides of the workgroup
   p.chunk = ((vocab + nch - 1) / nch + unit - 1) / unit * unit;
   p.chunks = (vocab + p.chunk - 1) / p.chunk;
@@ -303,10 +294,9 @@ StatsPlan stats_plan(int rows, int vocab, int elem_size) {
 template <typename T>
 void launch_vocab_stats(const T* logits, int rows, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
   const StatsPlan p = stats_plan(rows, vocab, sizeof(T));
-  if (p.threads == 1024) launch_items<T, 1024, 2, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
-  else if (p.trip == 6) launch_items<T, 256, 6, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
-  else if (p.vector) launch_items<T, 256, 4, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
-  else launch_items<T, 256, 4, false>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  if (p.threads == 1024) launch_items<T, 1024, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  else if (p.vector) launch_items<T, 256, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  else launch_items<T, 256, false>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
 }
 
 template void launch_vocab_stats<float>(const float*, int, int, int, const StatsRows&, const StatsOut&, void*, hipStream_t);

@@ -261,12 +261,86 @@ def test_vocab_stats_whole_rows(device, dt, rows, V):
         _check_stats(got, o_stats.vocab_stats(z64, mask_id, zp64), z64, zp64, mask_id)
 
 
-# ... and the row counts from which on a workgroup of 256 threads takes a whole row, six or four vectors of it in flight: one whole
-# trip, a ragged end of one vector, less than a trip, no vectors
+# ... and many rows, a workgroup of 256 threads per chunk: chunks of whole trips, with a ragged end of one vector, of less than a
+# trip, and without vectors
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 @pytest.mark.parametrize("rows,V", [(351, 12296), (352, 12288), (353, 12296), (352, 8199), (1023, 4104), (1024, 8200)])
 def test_vocab_stats_whole_rows_of_many(device, dt, rows, V):
     test_vocab_stats_whole_rows(device, dt, rows, V)
+
+
+def _walked_kl_sum(x, threads, chunks, vec):
+    """Sum of the columns of x [rows, V] in the order of the streamed statistics, in fp32: a row is cut into `chunks` runs of whole strides
+    (`threads` lanes of `vec` consecutive columns); a lane adds its columns of a chunk one by one; 64 lanes are added by a butterfly
+    (32, 16, .. 1 apart), the wavefronts of a workgroup in order, and the chunks by a butterfly of 64 places again."""
+    rows, V = x.shape
+    stride = threads * vec
+    chunk = -(-(-(-V // chunks)) // stride) * stride
+    n = -(-V // chunk)
+    wide = np.zeros((rows, n * chunk), np.float32)  # (columns past the end add zeros)
+    wide[:, :V] = x
+    wide = wide.reshape(rows, n, chunk // stride, threads, vec)
+    lanes = np.zeros((rows, n, threads), np.float32)
+    for s in range(chunk // stride):
+        for i in range(vec):
+            lanes = lanes + wide[:, :, s, :, i]
+
+    def butterfly(v):
+        for o in (32, 16, 8, 4, 2, 1):
+            v = v + v[..., np.arange(64) ^ o]
+        return v[..., 0]
+
+    waves = butterfly(lanes.reshape(rows, n, threads // 64, 64))
+    parts = waves[..., 0]
+    for w in range(1, threads // 64):
+        parts = parts + waves[..., w]
+    if n == 1:
+        return parts[:, 0]
+    return butterfly(np.concatenate([parts, np.zeros((rows, 64 - n), np.float32)], axis=1))
+
+
+@pytest.mark.parametrize("dt,rows,V", [("bf16", 2, 126464), ("bf16", 200, 126464), ("bf16", 340, 126464), ("bf16", 352, 126464), ("bf16", 400, 126464),
+                                       ("bf16", 600, 126464), ("bf16", 1100, 126464), ("bf16", 1600, 126464), ("bf16", 352, 12296),
+                                       ("f32", 3, 30000), ("f32", 150, 30000), ("f32", 360, 30000), ("f32", 1030, 30000), ("f32", 1700, 30000)])
+def test_order_of_the_streamed_sums(device, dt, rows, V):
+    """KL is w / s - lse + lse' with w = sum e^(z - m) (z - z').  On a flat row every exponential is one and s a whole number, so that w is a
+    plain fp32 sum whose value says in which order it was taken; values of z' whose sum cancels make that show.  Bit for bit."""
+    tdt, vec = (torch.bfloat16, 8) if dt == "bf16" else (torch.float32, 4)
+    g = torch.Generator(device="cpu").manual_seed(rows + V)
+    base = (torch.randn(3, V, generator=g) * 1.0e6).to(tdt)
+    z = torch.full((rows, V), 1.25, dtype=tdt, device=device)
+    zp = base.to(device)[torch.arange(rows, device=device) % 3]
+    mask_id = V // 3
+    got = api.dlm_vocab_stats(z, mask_id, zp, prev_lse=torch.zeros(rows, device=device))
+    torch.cuda.synchronize()
+    x = np.float32(1.25) - base.float().numpy()
+    x[:, mask_id] = 0.0
+    # a workgroup of 1024 threads per row at 136 .. 256 rows, else chunks of 256 threads for about 1536 workgroups
+    threads, chunks = (1024, 1) if 136 <= rows <= 256 else (256, max(1, min(-(-1536 // rows), -(-V // (512 * vec)), 32)))
+    w = _walked_kl_sum(x, threads, chunks, vec)
+    lse = _np(got["lse"])
+    want = (w / np.float32(V - 1))[np.arange(rows) % 3] - lse
+    assert (_np(got["kl"]) == want).all(), np.abs(_np(got["kl"]) - want).max()
+
+
+@pytest.mark.parametrize("dt,rows,few", [("bf16", 360, 345), ("bf16", 500, 384), ("f32", 383, 308)])
+@pytest.mark.parametrize("own_lse", [True, False])
+def test_vocab_stats_of_many_rows_at_a_real_vocabulary(device, dt, rows, few, own_lse):
+    """126464 tokens, compared with a previous row whose log-sum-exp is given or recomputed: a sample of rows against 64 bits, and every row
+    bit for bit as in a call with fewer rows that are cut into as many chunks."""
+    V, mask_id, tdt = 126464, 126463, torch.bfloat16 if dt == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    z = (torch.randn(rows, V, generator=g, device=device) * 4).to(tdt)
+    zp = (z.float() + 0.5 * torch.randn(rows, V, generator=g, device=device)).to(tdt)
+    lse_prev = None if own_lse else api.dlm_vocab_stats(zp, mask_id)["lse"]
+    got = api.dlm_vocab_stats(z, mask_id, zp, prev_lse=lse_prev)
+    part = api.dlm_vocab_stats(z[:few], mask_id, zp[:few], prev_lse=None if own_lse else lse_prev[:few].contiguous())
+    torch.cuda.synchronize()
+    for k, v in part.items():
+        assert torch.equal(got[k][:few], v), k
+    at = [0, 1, 63, few - 1, few, rows - 1]
+    z64, zp64 = o_fwd.widen(_np(z[at])), o_fwd.widen(_np(zp[at]))
+    _check_stats({k: v[at] for k, v in got.items()}, o_stats.vocab_stats(z64, mask_id, zp64), z64, zp64, mask_id)
 
 
 # ---- block_boundary ----------------------------------------------------------------------------------
