@@ -293,6 +293,7 @@ struct StatsPlan {
   int threads;        // of a workgroup
   int chunk, chunks;  // tokens of a chunk, chunks of a row (more than one: a second launch merges them)
   bool vector;        // rows are read in 16-byte vectors
+  int per_unit;       // workgroups of 256 threads of that path on a compute unit
 };
 StatsPlan stats_plan(int rows, int vocab, int elem_size);
 size_t stats_workspace_bytes(int rows);

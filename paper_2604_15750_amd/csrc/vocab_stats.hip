@@ -30,10 +30,31 @@ struct Run {
 constexpr float RUN_MIN = -2.0e38f;  // start of the running maximum: (RUN_MIN - m) * log2(e) stays finite for real maxima m
 __device__ inline Run run_init() { return Run{RUN_MIN, 0x7fffffff, 0.f, 0.f, 0.f, RUN_MIN, 0.f}; }
 
-__device__ inline int wave_min_int(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-  return v;
+// A value over the 64 lanes, in every lane, by the butterfly of wave_sum (lanes 32, 16, 8, 4, 2, 1 apart, so the same sums) without its
+// six trips through LDS: permlane swaps across the rows of 16 lanes, then rotations within a row, which behind the step before them meet
+// the butterfly's values (they repeat every 8, 4 and 2 lanes).  A wavefront makes these trips at its end and at every new maximum, and
+// a chunk is short: 384 rows of 126464 bf16 logits from memory, without / with a previous row, 28.3 / 43.5 -> 24.7 / 40.2 us.
+template <int CTRL>
+__device__ inline unsigned rotate(unsigned v) { return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false); }
+template <typename Op>
+__device__ inline unsigned butterfly(unsigned v, Op op) {
+  auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  v = op(x[0], x[1]);
+  x = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = op(x[0], x[1]);
+  v = op(v, rotate<0x128>(v));  // row_ror:8, 4, 2, 1
+  v = op(v, rotate<0x124>(v));
+  v = op(v, rotate<0x122>(v));
+  return op(v, rotate<0x121>(v));
+}
+__device__ inline float lanes_sum(float v) {
+  return __uint_as_float(butterfly(__float_as_uint(v), [](unsigned a, unsigned b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }));
+}
+__device__ inline float lanes_max(float v) {
+  return __uint_as_float(butterfly(__float_as_uint(v), [](unsigned a, unsigned b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); }));
+}
+__device__ inline int lanes_min(int v) {
+  return (int)butterfly((unsigned)v, [](unsigned a, unsigned b) { return (unsigned)min((int)a, (int)b); });
 }
 
 // The 64 lane states -> the wavefront's Part (valid in every lane): the lanes share m, so the sums are plain butterflies in a
@@ -41,13 +62,13 @@ __device__ inline int wave_min_int(int v) {
 __device__ inline Part run_finish(const Run& r) {
   Part p;
   p.m = r.m;
-  p.s = wave_sum(r.s);
-  p.t = wave_sum(r.t2) * LN2;
-  p.w = wave_sum(r.w);
+  p.s = lanes_sum(r.s);
+  p.t = lanes_sum(r.t2) * LN2;
+  p.w = lanes_sum(r.w);
   p.bv = r.m;
   p.bi = r.bi;
   p.pm = r.pm > RUN_MIN ? r.pm : NEG_BIG;
-  p.ps = wave_sum(r.ps);
+  p.ps = lanes_sum(r.ps);
   return p;
 }
 
@@ -55,7 +76,7 @@ __device__ inline Part run_finish(const Run& r) {
 // reference.  Called by all 64 lanes together, from a wavefront-uniform branch.
 template <int N>
 __device__ inline void new_maximum(Run& p, const float (&z)[N], unsigned valid, float vm, int v0) {
-  const float wmax = wave_max(vm);
+  const float wmax = lanes_max(vm);
   int cand = 0x7fffffff;
 #pragma unroll
   for (int i = N - 1; i >= 0; --i)
@@ -65,11 +86,11 @@ __device__ inline void new_maximum(Run& p, const float (&z)[N], unsigned valid, 
   p.s *= a;
   p.w *= a;
   p.m = wmax;
-  p.bi = wave_min_int(cand);
+  p.bi = lanes_min(cand);
 }
 template <int N>
 __device__ inline void new_prev_maximum(Run& p, float vm) {
-  const float wmax = wave_max(vm);
+  const float wmax = lanes_max(vm);
   p.ps *= __builtin_amdgcn_exp2f((p.pm - wmax) * LOG2E);
   p.pm = wmax;
 }
@@ -178,12 +199,14 @@ __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const
   }
 }
 
-template <typename T, int TPB, bool VECTOR>
-__global__ __launch_bounds__(TPB) void vocab_stats_kernel(const T* __restrict__ logits, int rows, int vocab, int mask_id, int chunk,
+// Workgroups of 256 threads of the vector path on a compute unit, held (stats_plan) where the registers would let one more in
+template <typename T> constexpr int HELD = sizeof(T) == 2 ? 5 : 6;
+
+template <typename T, int TPB, bool VECTOR, int PER_UNIT>
+__global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(1, TPB == 256 ? PER_UNIT : 8))) void vocab_stats_kernel(const T* __restrict__ logits, int vocab, int mask_id, int chunk,
                                                           int nchunks, StatsRows sr, StatsOut o, Part* __restrict__ parts) {
   __shared__ Part sh[TPB / 64];
-  for (int item = blockIdx.x; item < rows * nchunks; item += gridDim.x) {
-  const int row = item / nchunks, c = item - row * nchunks;
+  const int row = blockIdx.x / nchunks, c = blockIdx.x - row * nchunks;
   const T* z_row = logits + (size_t)row * vocab;
   const int64_t prow = sr.prev_row ? sr.prev_row[row] : (sr.prev_base ? (int64_t)row * vocab : -1);
   const int64_t srow = sr.save_row ? sr.save_row[row] : -1;
@@ -210,8 +233,6 @@ __global__ __launch_bounds__(TPB) void vocab_stats_kernel(const T* __restrict__ 
     } else {
       parts[(size_t)row * nchunks + c] = r;
     }
-  }
-  __syncthreads();  // sh is reused by the next item
   }
 }
 
@@ -240,10 +261,10 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
 constexpr int MAX_CHUNKS = 32;
 constexpr int ROW_MIN = 136, ROW_MAX = 256;  // rows that can get a workgroup of 1024 threads each (stats_plan)
 
-template <typename T, int TPB, bool VECTOR>
+template <typename T, int TPB, bool VECTOR, int PER_UNIT = 8>
 void launch_items(const T* logits, int rows, int vocab, int mask_id, const StatsPlan& p, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
   // (the hardware dispatcher balances better than a resident grid walking the items)
-  vocab_stats_kernel<T, TPB, VECTOR><<<rows * p.chunks, TPB, 0, st>>>(logits, rows, vocab, mask_id, p.chunk, p.chunks, sr, o, (Part*)workspace);
+  vocab_stats_kernel<T, TPB, VECTOR, PER_UNIT><<<rows * p.chunks, TPB, 0, st>>>(logits, vocab, mask_id, p.chunk, p.chunks, sr, o, (Part*)workspace);
   if (p.chunks > 1) vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)workspace, rows, p.chunks, vocab, sr, o);
 }
 
@@ -263,14 +284,18 @@ void launch_stats_merge(const void* parts, int rows, int nparts, int vocab, cons
 // on logits in the memory-side cache, chunks -> whole rows, without / with a previous row:
 //   bf16, 126464 tokens: 96 rows 13.0 -> 16.6 / 15.8 -> 20.4, 128: 16.2 -> 17.3 / 20.1 -> 20.8, 160: 18.2 -> 17.8 / 22.6 -> 20.9,
 //   192: 17.6 -> 17.9 / 22.6 -> 21.6, 256: 22.2 -> 18.3 / 28.8 -> 24.9; 272 rows: 22.7 -> 31.2 / 31.4 -> 42.9 (a second round of
-//   workgroups, as two of 1024 threads don't fit into a unit's registers).  Over 20 shapes the mean of whole / chunks is 1.07 at
-//   104 rows, 0.96 at 136, 0.93 at 152, 0.89 at 184; below 152 rows single shapes still lose up to 7 % on given logits (126464 tokens,
-//   bf16, no previous row, 136 rows: 16.5 -> 17.3).  Within dlm_step, behind the LM head that has just written the logits, the two
-//   meet at about 130 rows (launches included, 104 rows: 24.6 -> 26.4, 114: 27.0 -> 28.8, 132: 29.3 -> 28.5, 147: 28.0 -> 24.9, 148: 30.5
-//   -> 28.7).  The line is the first row count at which both means are ahead.
+//   workgroups, as two of 1024 threads don't fit into a unit's registers).  These are with lane exchanges through LDS, which cost chunks more.
+//   With the present ones and logits from memory: 136 rows 15.6 -> 17.6 / 20.0 -> 21.2, 152: 17.2 -> 17.8 / 21.9 -> 21.3, 192: 16.0 -> 18.1 /
+//   23.1 -> 22.6, 256: 20.7 -> 18.5 / 29.7 -> 27.5; the mean of whole / chunks over 4 vocabularies, both types, without / with, is 0.99 at 136 rows,
+//   0.96 at 152, 0.92 at 176, 0.94 at 192, 0.90 at 208, 0.87 at 224.  Single shapes lose up to 13 % below 200 rows; the line
+//   stands where the mean first is ahead, and a row's values depend on it (the cut is the order of the sums).
 // Without 16-byte vectors a lane has one scalar load in flight, and fewer lanes are what it loses by: 126463 tokens, bf16, 96 rows
 //   20.5 -> 34.6 / 23.5 -> 58.9, 256: 44.2 -> 55.2 / 48.0 -> 60.0.  With one chunk the larger workgroup has nothing to save:
 //   1024 tokens, fp32, 96 .. 256 rows 4.4 -> 6.4.
+// A compute unit holds five workgroups of 256 threads (fp32: six), one more where that puts all of them on the chip at once.  One more
+// always would leave other counts with a last round of few: 126464 tokens from memory, with a previous row, six a unit -> five: bf16,
+// 384 rows (1536 workgroups) 40.3 -> 41.9, 768: 73.2 -> 77.0, 1536: 133.6 -> 141.1, but 896 (1792): 88.0 -> 83.4, 1756: 159.3 -> 152.8; seven ->
+// six: fp32, 448 rows (1792) 81.6 -> 84.5, 896: 155.6 -> 161.3, but 1024 (2048): 182.1 -> 175.6, 2048: 355.3 -> 343.0.
 // More rows keep their chunks.  A workgroup of 256 threads per row saves the merge there, but a lane then walks five times as far: each
 // addend straight into the running sum, KL left 1e-5 of its value behind; a partial sum per vector first, all values were others than
 // those of the same row in a call of fewer rows, and units that got a row more than the mean took longer (528 rows with a
@@ -288,6 +313,9 @@ StatsPlan stats_plan(int rows, int vocab, int elem_size) {
   const int unit = p.threads * n;  // chunks are whole strides of the workgroup
   p.chunk = ((vocab + nch - 1) / nch + unit - 1) / unit * unit;
   p.chunks = (vocab + p.chunk - 1) / p.chunk;
+  const int held = elem_size == 2 ? HELD<bf16_t> : HELD<float>;
+  const int64_t workgroups = (int64_t)rows * p.chunks;
+  p.per_unit = workgroups > 256 * held && workgroups <= 256 * (held + 1) ? held + 1 : held;
   return p;
 }
 
@@ -295,7 +323,8 @@ template <typename T>
 void launch_vocab_stats(const T* logits, int rows, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
   const StatsPlan p = stats_plan(rows, vocab, sizeof(T));
   if (p.threads == 1024) launch_items<T, 1024, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
-  else if (p.vector) launch_items<T, 256, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  else if (p.vector && p.per_unit > HELD<T>) launch_items<T, 256, true, HELD<T> + 1>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  else if (p.vector) launch_items<T, 256, true, HELD<T>>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
   else launch_items<T, 256, false>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
 }
 

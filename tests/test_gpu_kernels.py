@@ -301,7 +301,10 @@ def _walked_kl_sum(x, threads, chunks, vec):
 
 @pytest.mark.parametrize("dt,rows,V", [("bf16", 2, 126464), ("bf16", 200, 126464), ("bf16", 340, 126464), ("bf16", 352, 126464), ("bf16", 400, 126464),
                                        ("bf16", 600, 126464), ("bf16", 1100, 126464), ("bf16", 1600, 126464), ("bf16", 352, 12296),
-                                       ("f32", 3, 30000), ("f32", 150, 30000), ("f32", 360, 30000), ("f32", 1030, 30000), ("f32", 1700, 30000)])
+                                       ("f32", 3, 30000), ("f32", 150, 30000), ("f32", 360, 30000), ("f32", 1030, 30000), ("f32", 1700, 30000),
+                                       # five workgroups of 256 threads on each compute unit, six, more than six; fp32: six, seven, more
+                                       ("bf16", 1280, 4096), ("bf16", 1281, 4096), ("bf16", 384, 126464), ("bf16", 1537, 8200),
+                                       ("f32", 768, 30000), ("f32", 350, 30000), ("f32", 1793, 2048)])
 def test_order_of_the_streamed_sums(device, dt, rows, V):
     """KL is w / s - lse + lse' with w = sum e^(z - m) (z - z').  On a flat row every exponential is one and s a whole number, so that w is a
     plain fp32 sum whose value says in which order it was taken; values of z' whose sum cancels make that show.  Bit for bit."""
