@@ -23,10 +23,16 @@
 #pragma once
 #include "common.h"
 
+typedef float f32x4_lds __attribute__((ext_vector_type(4), aligned(8)));
+
 template <int HD, int NWV, int DS, int T>
 struct AttnLds {  // merge buffers of one workgroup (T query tiles, HD / DS of the head's dims)
   float sm[T][NWV][16], sl[T][NWV][16];
-  float so[T][NWV][16][HD / DS + 4];  // a query's dims in a row (padded: the rows of 16 lanes start four banks apart)
+  // a query's dims in a row, padded by two banks and accessed in 8-byte halves (rows padded to 16 bytes, accessed whole: 152 rows x
+  // 792 keys, 32 heads, 15.6 us against 14.9).  The struct is its kernel's only LDS object, at address 0; told so by alignas, the
+  // compiler orders the loads of the shortest passes worse (24 rows x 124 keys 6.6 -> 6.9 us).
+  float so[T][NWV][16][HD / DS + 2];
+  static_assert(HD / DS % 2 == 0, "rows start on 8 bytes");
 };
 
 // v of the lane and of its partner 16 (32) lanes away, in one order or the other (for commutative uses)
@@ -92,9 +98,9 @@ __device__ inline void attention_tiles(const f16_t* __restrict__ q, const f16_t*
   f16x8 kf[2][2 * KS], vf[DT];
   // A step's loads are pinned in front of it, K of the next block too: past the last block a line per fragment of this one, which
   // nothing uses, as a path around the loads would be one that the compiler's count of them cannot follow (it would wait for all of
-  // them).  Not in the kernel of the shortest passes, a block or two per wavefront: there the copies it makes of what is in
-  // flight cost more (8 rows x 392 keys 6.9 us against 6.5).
-  constexpr bool PINNED = T > 1 || DS == 1;
+  // them).  Not for one query tile with eight wavefronts, which are few blocks each: there the copies it makes of what is in
+  // flight cost more (8 rows x 392 keys, four shares, 6.9 us against 6.5; 128 rows x 228 keys, one share, 9.4 against 8.3).
+  constexpr bool PINNED = T > 1 || (DS == 1 && NWV == 4);
   auto load_k = [&](int buf, int blk) {
     const bool there = blk < nblk;
     const f16x8* from = there || !PINNED ? kt : (const f16x8*)kregion;
@@ -170,16 +176,19 @@ __device__ inline void attention_tiles(const f16_t* __restrict__ q, const f16_t*
   }
   // Merge the wavefronts: all query tiles together, four dims per access, and a thread finishes 8 (4) consecutive dims of a query,
   // which are one slot (half of one) of the output tile.  One tile and one value at a time, written two bytes at a time, this
-  // took 3.8 us of a workgroup's 21 at 1280 rows x 1280 keys (3.1 now) and 4.2 of 19 at 16 spans of 30 rows x 400 (2.8).
+  // took 3.8 us of a workgroup's 21 at 1280 rows x 1280 keys (3.1 now) and 4.2 of 19 at 16 spans of 30 rows x 400 (2.8).  In the kernels
+  // of the shortest passes, which share a head's dims, there is a thread for every dim (4 rows x 492 keys 9.0 us with four dims
+  // each, 8.6 with one).
 #pragma unroll
   for (int u = 0; u < T; ++u) {
     if (row0 + 16 * u >= row_end) break;  // (uniform)
     if (g == 0) { L.sm[u][wave][c] = m[u]; L.sl[u][wave][c] = l[u]; }
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) *(f32x4*)&L.so[u][wave][c][16 * dt + 4 * g] = o[u][dt];
+    for (int dt = 0; dt < DT; ++dt) *(f32x4_lds*)&L.so[u][wave][c][16 * dt + 4 * g] = o[u][dt];
   }
   __syncthreads();
-  constexpr int CH = 2 * HDP >= NWV * 64 ? 8 : 4, PER_TILE = 16 * HDP / CH;
+  constexpr int CH = 2 * HDP >= NWV * 64 ? 8 : T == 1 && DS > 1 ? 1 : 4, V = CH < 4 ? CH : 4, PER_TILE = 16 * HDP / CH;
+  typedef float vec_t __attribute__((ext_vector_type(V), aligned(V == 4 ? 8 : 4)));
   for (int item = tid; item < T * PER_TILE; item += NWV * 64) {
     const int u = item / PER_TILE, qi = item & 15, d0 = (item % PER_TILE >> 4) * CH, r = row0 + 16 * u + qi;
     if (r >= row_end) continue;
@@ -192,10 +201,10 @@ __device__ inline void attention_tiles(const f16_t* __restrict__ q, const f16_t*
 #pragma unroll
     for (int wv = 0; wv < NWV; ++wv)
 #pragma unroll
-      for (int j = 0; j < CH; j += 4) {
-        const f32x4 t = *(const f32x4*)&L.so[u][wv][qi][d0 + j];
+      for (int j = 0; j < CH; j += V) {
+        const vec_t t = *(const vec_t*)&L.so[u][wv][qi][d0 + j];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[j + k] += w[wv] * t[k];
+        for (int k = 0; k < V; ++k) acc[j + k] += w[wv] * t[k];
       }
     const int width = n_q * HD, col = head * HD + dpart * HDP + d0;
     if (out_tiles) {
