@@ -180,21 +180,31 @@ void launch_attention_f32(const float* q, const float* kcache, const float* vcac
 // wide one has enough workgroups to fill the chip with four wavefronts each.
 // Query tiles per workgroup, where a span has more than one: a wide pass takes two (the K and V traffic is what bounds it); a narrow
 // one the fewest that leave at most one workgroup per compute unit (8B shape, 24 rows x 856 keys, one tile / two: 7.7 / 9.7 us;
-// 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that); so does a middling one with eight
-// wavefronts, of which a unit holds one workgroup (28 heads, 152 rows x 792 keys, 280 workgroups / 140: 15.3 / 12.0).  Spans of one tile gain nothing from a second
+// 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that).  Spans of one tile gain nothing from a second
 // that no row fills (28 heads, 3 sequences of 16 rows x 1516 keys, two tiles / one: 25.7 / 22.2).
-AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_q, int hd) {
+// A middling pass has eight wavefronts, of which a unit holds one workgroup: two tiles where that makes one round of two (28 heads,
+// 152 rows x 792 keys, 280 workgroups / 140: 17.9 / 13.9).  Not where two tiles are more than a round themselves (32 heads, 5 spans of 40
+// rows x 640, 480 / 320: 24.8 / 28.5), nor where spans of other lengths leave so many workgroups without rows that one tile each is a
+// round as well (40 + 8 + 8 rows x 640, 160 of 288 / 128 of 192: 14.2 / 16.4; 40 + 4 x 8, 224 of 480 / 192 of 320: 16.8 / 25.0).  But workgroups
+// go round the 8 XCDs and each XCD's 4 shader engines by their number: where the longest span has 2, or 4, 8, .. tiles, those of the spans
+// of one tile, every 2nd, 4th .. of the numbers, meet in a few of these places and take a second round of them after all (17 + 4 x 8
+// rows x 640, 192 of 320 / 160 of 160: 23.1 / 18.5; 64 + 8 + 8, 192 of 384 / 128 of 192: 21.8 / 16.3).
+AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_tiles, int n_q, int hd) {
   const int tiles = (max_seq_rows + 15) / 16;
   const size_t units = (size_t)tiles * n_q * n_seqs;
   if (units < 128 && hd >= 64) return AttnPlan{8, hd == 128 ? 4 : 2, hd == 128 && tiles > 1 && units * 4 > 256 ? 2 : 1};
   if (units >= 512) return AttnPlan{4, 1, tiles > 1 ? 2 : 1};
-  return AttnPlan{8, 1, units > 256 && tiles > 1 ? 2 : 1};
+  const bool one_round_of_pairs = (size_t)(tiles + 1) / 2 * n_q * n_seqs <= 256;
+  const bool two_rounds_of_tiles = n_tiles * n_q >= 256 || tiles == 2 || tiles % 4 == 0;
+  return AttnPlan{8, 1, units > 256 && tiles > 1 && one_round_of_pairs && two_rounds_of_tiles ? 2 : 1};
 }
 
 void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,
                           op_t* out_tiles, bf16_t* out_rows, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st) {
   const int tiles = (max_seq_rows + 15) / 16;
-  const AttnPlan p = attention_plan(max_seq_rows, meta.n_seqs, n_q, hd);
+  int n_tiles = 0;
+  for (int b = 0; b < meta.n_seqs; ++b) n_tiles += (meta.row_off[b + 1] - meta.row_off[b] + 15) / 16;
+  const AttnPlan p = attention_plan(max_seq_rows, meta.n_seqs, n_tiles, n_q, hd);
   // enough (kv head, sequence) units to keep every XCD busy (four each): the workgroups of a unit share an XCD (see the kernel)
   const int units = n_kv * meta.n_seqs;
   const bool by_unit = units >= 32;

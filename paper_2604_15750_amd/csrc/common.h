@@ -271,7 +271,7 @@ void launch_attention_f32(const float* q, const float* kcache, const float* vcac
 struct AttnPlan {
   int waves, shares, tiles;  // of a workgroup: wavefronts, workgroups that share a head's output dims, 16-query tiles
 };
-AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_q, int hd);
+AttnPlan attention_plan(int max_seq_rows, int n_seqs, int n_tiles, int n_q, int hd);  // n_tiles: of all sequences together
 void launch_attention_f16(const f16_t* q, const f16_t* kcache, const f16_t* vcache, size_t slot_stride, size_t head_stride, const AttnMeta& meta,
                           op_t* out_tiles, bf16_t* out_rows, int rows, int max_seq_rows, int n_q, int n_kv, int hd, hipStream_t st);
 // test helper of dlm_attention: K, V [T, n_kv, hd] row-major bf16 -> the tiled half-precision cache layout of one slot

@@ -789,7 +789,7 @@ extern "C" int dlm_plan_attention(int max_seq_rows, int n_seqs, int n_q, int hea
   REQUIRE(plan, DLM_EINVAL, "dlm_plan_attention: null argument");
   REQUIRE(max_seq_rows >= 1 && n_seqs >= 1 && n_q >= 1, DLM_ESHAPE, "dlm_plan_attention: non-positive size");
   REQUIRE(head_dim == 32 || head_dim == 64 || head_dim == 128, DLM_ESHAPE, "dlm_plan_attention: head_dim %d not in {32,64,128}", head_dim);
-  const AttnPlan p = attention_plan(max_seq_rows, n_seqs, n_q, head_dim);
+  const AttnPlan p = attention_plan(max_seq_rows, n_seqs, (max_seq_rows + 15) / 16 * n_seqs, n_q, head_dim);
   plan[0] = p.waves; plan[1] = p.shares; plan[2] = p.tiles;
   return DLM_OK;
 }

@@ -155,6 +155,18 @@ def test_attention_takes_a_second_query_tile_only_where_a_span_has_one(n_q, hd):
     assert api.plan_attention(37, 1, 32, 128) == dict(waves=8, shares=4, tiles=2)
 
 
+def test_attention_pairs_tiles_of_a_middling_pass_only_into_one_round():
+    """Eight wavefronts and no shares: two tiles a workgroup where one each would be more than the chip's 256 and two are not."""
+    for n_q in (4, 16, 28, 30, 32):
+        for n_seqs in range(1, 33):
+            for rows in range(1, 260, 3):
+                p, tiles = api.plan_attention(rows, n_seqs, n_q, 128), (rows + 15) // 16
+                if p["waves"] == 8 and p["shares"] == 1:
+                    assert (p["tiles"] == 2) == (tiles > 1 and tiles * n_q * n_seqs > 256 and (tiles + 1) // 2 * n_q * n_seqs <= 256), (rows, n_seqs, n_q)
+    assert api.plan_attention(40, 5, 32, 128)["tiles"] == api.plan_attention(72, 3, 32, 128)["tiles"] == 1
+    assert api.plan_attention(48, 4, 32, 128)["tiles"] == api.plan_attention(240, 1, 32, 128)["tiles"] == 2
+
+
 @pytest.mark.parametrize("dt,vec", [(torch.bfloat16, 8), (torch.float32, 4)])
 def test_whole_row_statistics_only_where_they_save_a_merge_and_read_in_vectors(dt, vec):
     whole = set()

@@ -428,6 +428,13 @@ def test_packed_spans_of_one_and_more_query_tiles(device, spans):
     model.close()
 
 
+# ... middling passes: two tiles a workgroup and one, decided by the rows that the spans have (28 heads: fewer than 256 workgroups of
+# one tile, 256 and more; a longest span of 2, 3, 4, 5 and 6 tiles; more than a round of pairs)
+@pytest.mark.parametrize("spans", [[17, 8, 8, 8, 8], [40, 8, 8, 8], [33, 12, 12, 12, 12], [64, 8, 8], [65, 40, 3], [80, 80], [96, 32], [48, 48, 48, 48]])
+def test_packed_spans_of_middling_passes(device, spans):
+    test_packed_spans_of_one_and_more_query_tiles(device, spans)
+
+
 @pytest.mark.parametrize("hd", [32, 64, 128])
 @pytest.mark.parametrize("commits,spans", [([4, 8], [120, 100]), ([5, 18, 31], [97, 65, 71]), ([1, 2, 3, 7], [57, 131, 16, 30])])
 def test_wide_spans_behind_prefixes_of_any_length(device, hd, commits, spans):
