@@ -218,12 +218,14 @@ void launch_select(const T* logits, int vocab, const float* lse, const float* co
   int longest = 0;
   for (int b = 0; b < n_seqs; ++b) longest = meta.block_len[b] > longest ? meta.block_len[b] : longest;
   // Up to 32 rows: at most 1024 pairs, one trip of 256 threads; more threads would only make the barriers slower.  Up to 64 rows:
-  // sets of two words instead of eight, as most of a short kernel's time is fetching its instructions.
-  const bool few = longest <= 32 || p.mode != 0;
+  // sets of two words instead of eight, as most of a short kernel's time is fetching its instructions.  Beyond that 1024 threads, also
+  // where no pairs are scored (modes 1, 2): 16 wavefronts for the order's matrix of L x L bits, which with four is the longest part (one
+  // sequence, 4 / 16 wavefronts: 65 rows 7.3 / 5.4 us, 128: 11.6 / 5.7, 256: 35.6 / 13.1).
 #define GO(TPB, MAXL) \
   select_kernel<T, TPB, MAXL><<<n_seqs, TPB, 0, st>>>(logits, vocab, lse, conf, argmax, tokens, meta, mask_id, p, apply, sel, nsel, margin)
-  if (longest <= 64) { if (few) GO(256, 64); else GO(1024, 64); }
-  else { if (few) GO(256, 256); else GO(1024, 256); }
+  if (longest > 64) GO(1024, 256);
+  else if (longest > 32 && p.mode == 0) GO(1024, 64);
+  else GO(256, 64);
 #undef GO
 }
 template void launch_select<float>(const float*, int, const float*, const float*, const int32_t*, int32_t*, const SelectMeta&, int,

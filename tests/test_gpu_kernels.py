@@ -448,6 +448,31 @@ def test_select_parallel(device, dt, mode):
         assert fired["fallback"] > 0 and fired["dropped"] > 3, fired
 
 
+# The rules without pair scores at the edges of the kernels' block sizes, beside a short and an empty block; confidences in ties
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("L", [32, 33, 64, 65, 128, 129, 255, 256])
+def test_select_parallel_without_pairs(device, mode, L):
+    rng = np.random.default_rng(L + mode)
+    V, mask_id, lens = 64, 63, [L, 5, 0]
+    rows = sum(lens)
+    conf = (rng.integers(1, 40, rows) / 41.0).astype(np.float32)
+    y = rng.integers(0, V - 1, rows).astype(np.int32)
+    tokens = np.where(rng.random(rows) < 0.7, mask_id, 5).astype(np.int32)
+    tokens[0] = tokens[L] = mask_id
+    high = float(np.float32(0.503))
+    z = torch.zeros(rows, V, device=device)
+    d = lambda x: torch.from_numpy(x.copy()).to(device)  # noqa: E731
+    tok, sel, nsel = d(tokens), torch.zeros(rows, dtype=torch.uint8, device=device), torch.empty(3, dtype=torch.int32, device=device)
+    api.select_parallel(z, torch.zeros(rows, device=device), d(conf), d(y), tok, [0, L, 0], [0, L, 0], lens, mask_id, 0.1, high, 0.0, mode, sel, nsel)
+    torch.cuda.synchronize()
+    for b, at in ((0, 0), (1, L)):
+        sl = slice(at, at + lens[b])
+        ref, _ = o_select.select_parallel(np.zeros((lens[b], V)), np.zeros(lens[b]), conf[sl], y[sl], tokens[sl] == mask_id, 0.1, high, 0.0, mode)
+        assert (_np(sel)[sl].astype(bool) == ref).all() and nsel[b].item() == ref.sum(), b
+        assert (_np(tok)[sl] == np.where(ref, y[sl], tokens[sl])).all()
+    assert nsel[2].item() == 0
+
+
 @pytest.mark.parametrize("L", [2, 31, 32, 33, 63, 64, 65, 255, 256])
 def test_select_parallel_chain_of_conflicts(device, L):
     """Every row conflicts with its two neighbours and the confidences descend along the block: the greedy walk takes every other
