@@ -380,6 +380,43 @@ def test_block_boundary(device, norm_mode, rule):
                 assert abs(mg[b] - mr) <= 1e-5 * max(1.0, mr)
 
 
+# Calls whose windows all fit one wavefront, which have a kernel of their own, and the first that does not: every normalisation and rule;
+# a window that never crosses, one that does at once, one in between, identical steps
+@pytest.mark.parametrize("norm_mode", [0, 1, 2, 3])
+@pytest.mark.parametrize("rule", [0, 1])
+@pytest.mark.parametrize("Ws", [[1], [64, 64], [63, 64, 2], [32, 33, 64, 64, 64, 64, 5], [64, 65]])
+def test_block_boundary_of_short_windows(device, norm_mode, rule, Ws):
+    rng = np.random.default_rng(norm_mode * 2 + rule + 16 * len(Ws))
+    n, off = len(Ws), np.concatenate([[0], np.cumsum(Ws)])
+    I, H = rng.exponential(0.3, off[-1]).astype(np.float32), rng.uniform(0.1, 6.0, off[-1]).astype(np.float32)
+    for b in range(n):  # S = I~ - lambda H~: how much larger than H the signal I is decides where it falls below zero
+        sl = slice(off[b], off[b + 1])
+        if b % 4 == 1:
+            I[sl] = 2 * H[sl] + 1
+        elif b % 4 == 2:
+            I[sl] = H[sl] / 4
+        elif b % 4 == 3:
+            I[sl] = 0.5
+    crossed = []
+    for lam, l_min, r, cold in ((0.6, 1, 0, None), (0.9, 8, 1, [b % 5 == 4 for b in range(n)]), (1.6, 3, 3, None)):
+        lam = float(np.float32(lam))
+        L, S, mg = (torch.empty(k, dtype=t, device=device) for k, t in ((n, torch.int32), (int(off[-1]), torch.float32), (n, torch.float32)))
+        api.block_boundary(torch.from_numpy(I).to(device), torch.from_numpy(H).to(device), off[:-1].tolist(), Ws, L, lam, l_min, r, norm_mode,
+                           rule, cold=cold, S_out=S, margin_out=mg)
+        torch.cuda.synchronize()
+        for b in range(n):
+            sl = slice(off[b], off[b + 1])
+            Lr, Sr, mr = o_boundary.block_boundary(I[sl], H[sl], lam, l_min, r, norm_mode, rule, cold_start=bool(cold and cold[b]))
+            # (S is an fp64 result rounded to fp32)
+            assert (np.abs(_np(S)[sl] - Sr) <= 2.0 ** -23 * np.maximum(1.0, np.abs(Sr))).all(), (b, np.abs(_np(S)[sl] - Sr).max())
+            if mr > 1e-9:
+                assert L[b].item() == Lr, (b, Ws[b], L[b].item(), Lr, mr)
+            if np.isfinite(mr):
+                assert abs(mg[b].item() - mr) <= 2.0 ** -23 * max(1.0, mr) + 1e-9
+            crossed.append(Lr < Ws[b])
+    assert (any(crossed) and not all(crossed)) or Ws == [1]
+
+
 # ---- select_parallel -----------------------------------------------------------------------------------
 def _select_case(rng, L, V, dt):
     peaks = []
