@@ -57,8 +57,8 @@ struct MidShape {
 };
 
 // grid.x = groups * splits; MT >= ceil(M / 16), and X has MT row tiles (the activation buffers are padded to 16 rows).
-// STEPS: W is read from the step-major copy (e.w_steps) instead of wt.
-template <int MT, int CT, int PR, int EPI, bool STEPS = false>
+// STEPS: W is read from the step-major copy (e.w_steps) instead of wt.  STRAIGHT: the rows' sums of squares in one run of loads.
+template <int MT, int CT, int PR, int EPI, bool STEPS, bool STRAIGHT>
 __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
                                                        int kt_per_split, int splits, GemmEpi e) {
   typedef MidShape<MT, CT> SH;
@@ -172,9 +172,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   }
   // 1/rms of the input rows, needed only by the epilogue: fetched while the first k-tiles are in flight (published by the
   // barriers of the reduction)
-  // (one straight run of loads for gate/up of up to 16 rows: 34.9 -> 33.5 us; with more rows, or before the rotary epilogue, it costs: 37.6 ->
-  // 42.7 us at 37 rows, QKV 18.8 -> 20.0 at 8)
-  if (EPI != EPI_RESID) block_rinv<TPB, MT == 1 && EPI == EPI_SWIGLU>(e.rs, 0, min(M, MT * 16), s_rinv);
+  if (EPI != EPI_RESID) block_rinv<TPB, STRAIGHT>(e.rs, 0, min(M, MT * 16), s_rinv);
   // ... and so is what the epilogue of the fragment this wavefront finishes first (fragment `wave`) reads from memory, in the
   // variants of narrow passes, which are short enough for that round trip to show
   EpiAhead ahead = epi_none();
@@ -313,26 +311,33 @@ MidPlan mid_plan(int M, int N, int K) {
   return best;
 }
 
-template <int MT, int CT, int PR, int EPI>
-void launch_one(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
+template <int MT, int CT, int PR, int EPI, bool STEPS, bool STRAIGHT>
+void launch_kernel(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
   typedef MidShape<MT, CT> SH;
   static bool configured = false;  // raise the dynamic LDS limit of this instantiation once
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_mid_kernel<MT, CT, PR, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
+    (void)hipFuncSetAttribute((const void*)gemm_mid_kernel<MT, CT, PR, EPI, STEPS, STRAIGHT>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
     configured = true;
   }
+  DLM_LAUNCH((gemm_mid_kernel<MT, CT, PR, EPI, STEPS, STRAIGHT>), p.groups * p.splits, TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
+             p.kps, p.splits, e);
+}
+template <int MT, int CT, int PR, int EPI, bool STRAIGHT = false>
+void launch_steps(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
   if constexpr (MT <= MID_STEPS_MAX_MT) {
-    if (e.w_steps) {
-      static bool configured_steps = false;
-      if (!configured_steps) {
-        (void)hipFuncSetAttribute((const void*)gemm_mid_kernel<MT, CT, PR, EPI, true>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
-        configured_steps = true;
-      }
-      DLM_LAUNCH((gemm_mid_kernel<MT, CT, PR, EPI, true>), p.groups * p.splits, TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K, p.kps, p.splits, e);
-      return;
-    }
+    if (e.w_steps) return launch_kernel<MT, CT, PR, EPI, true, STRAIGHT>(xt, wt, M, N, K, p, e, st);
   }
-  DLM_LAUNCH((gemm_mid_kernel<MT, CT, PR, EPI>), p.groups * p.splits, TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K, p.kps, p.splits, e);
+  launch_kernel<MT, CT, PR, EPI, false, STRAIGHT>(xt, wt, M, N, K, p, e, st);
+}
+// Gate/up of 5 to 8 rows, whose sums of squares are two wavefronts' work, fetches them in one straight run of loads (8 rows 33.9 -> 32.8
+// us).  Elsewhere that costs: 1 to 4 rows, one wavefront, 34.1 -> 34.5; 16 rows, four, 33.9 -> 35.5; 37 rows 37.6 -> 42.7; before the
+// rotary epilogue, QKV of 8 rows, 18.8 -> 20.0.
+template <int MT, int CT, int PR, int EPI>
+void launch_one(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
+  if constexpr (MT == 1 && EPI == EPI_SWIGLU) {
+    if (M > 4 && M <= 8) return launch_steps<MT, CT, PR, EPI, true>(xt, wt, M, N, K, p, e, st);
+  }
+  launch_steps<MT, CT, PR, EPI>(xt, wt, M, N, K, p, e, st);
 }
 
 template <int MT, int EPI>

@@ -489,8 +489,8 @@ def _one_pass_matches(cfg, M, device, seed, stats=False):
     model.close()
 
 
-# (epilogue, tile, rows, model dimensions): the layer's epilogues on the wavefront shapes with an odd number of column tiles, whose
-# two halves leave through LDS with different counts, and on the narrowest one; rows and columns ragged
+# (epilogue, tile, rows, model dimensions): the layer's epilogues on the wavefront shapes with an odd number of column tiles, whose last
+# one has no partner to pair with, and on the narrowest one; rows and columns ragged
 EPILOGUE_TILES = [
     ("qkv", (64, 64), 215, (1, 256, 2, 1, 128, 64, 256)), ("qkv", (64, 96), 71, (1, 256, 64, 8, 128, 64, 256)),
     ("qkv", (64, 160), 260, (1, 256, 48, 4, 128, 64, 256)), ("qkv", (128, 96), 134, (1, 256, 64, 8, 128, 64, 256)),
@@ -516,6 +516,15 @@ def epilogue_tile(epi, M, dims):
 def test_epilogues_of_odd_wavefront_shapes(device, epi, tile, M, dims):
     assert epilogue_tile(epi, M, dims) == tile
     _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 19)
+
+
+# Gate/up of the mid kernel, whose rows' sums of squares are fetched in one run at 5 to 8 rows: the edges, two widths of its column groups
+@pytest.mark.parametrize("M", [1, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("d,ffn", [(256, 2112), (256, 6144)])
+def test_gate_up_of_few_rows(device, M, d, ffn):
+    cfg = inputs.model_config(1, d, 2, 1, 128, ffn, 256, "bf16")
+    assert api.plan_gemm(M, 2 * ffn, d, "swiglu")["kernel"] == "mid"
+    _one_pass_matches(cfg, M, device, 60 + M)
 
 
 @pytest.mark.parametrize("dims,M,N,K,epi,expect", [
