@@ -21,7 +21,8 @@ __global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __rest
                                                                int K, GemmEpi e) {
   __shared__ f32x4 red[NWV][R * MT][64];
   __shared__ float s_rinv[MT * 16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = MT == 2 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);  // (a scalar but for two row tiles: see load)
   const int KT = K >> 5;
   const int per = (KT + NWV - 1) / NWV;
   const int t_begin = wave * per, t_end = min(KT, t_begin + per);
@@ -44,7 +45,8 @@ __global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __rest
   // k-tiles past the wavefront's last one re-read that: the loads are unconditional, as a path around them is one the compiler's count
   // of outstanding loads cannot follow, and scalar in everything but the lane, as a short kernel is bound by the fetching of its
   // instructions first (a test per fragment and addresses in vectors: 2.4 us from the start
-  // to the last load of the first batch, 1.0 now; down of an 8B model at 8 rows 18.6 -> 18.0)
+  // to the last load of the first batch, 1.0 now; down of an 8B model at 8 rows 18.6 -> 18.0).  With two row tiles addresses in vectors
+  // and batches of two are faster (O of 20 rows, K = 3584 10.2 -> 9.6 us, K = 4096 10.3 -> 10.1).
   auto load = [&](int buf, int tb) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < D; ++i) {
@@ -112,11 +114,12 @@ __global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __rest
 }
 
 // batch depth: 8 KiB of W in flight per wavefront for up to 32 rows, half of that beyond (the X fragments take the registers);
-// the step-major copy reads best with batches of four (measured: deeper batches add queueing, not bandwidth).  Interleaved pairs
+// the step-major copy reads best with batches of four (measured: deeper batches add queueing, not bandwidth), of two with two row
+// tiles, where a wavefront has few k-tiles and those past its last are read again.  Interleaved pairs
 // of column tiles (wide matrices) come here with one row tile only: from 17 rows on the mid or the macro kernel has them.
 template <int MT, int EPI>
 void launch_skinny(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, const GemmEpi& e, hipStream_t st) {
-  if (pr == 1 && e.w_steps) DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, 4, EPI, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
+  if (pr == 1 && e.w_steps) DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 ? 2 : 4), EPI, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
   else if (pr == 1) DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT <= 2 ? 8 : 4), EPI>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
   else if constexpr (MT == 1) {
     if (e.w_steps) DLM_LAUNCH((gemm_skinny_kernel<MT, 2, 4, 4, EPI, true>), N / 32, 256, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
