@@ -68,10 +68,6 @@ __device__ inline float to_f32(float x) { return x; }
 __device__ inline float to_f32(bf16_t x) { return (float)x; }
 __device__ inline float to_f32(f16_t x) { return (float)x; }
 __device__ inline f16_t to_f16_sat(float x) { return (f16_t)__builtin_amdgcn_fmed3f(x, -65504.f, 65504.f); }
-template <typename T> __device__ inline T from_f32(float x);
-template <> __device__ inline float from_f32<float>(float x) { return x; }
-template <> __device__ inline bf16_t from_f32<bf16_t>(float x) { return (bf16_t)x; }
-template <> __device__ inline f16_t from_f32<f16_t>(float x) { return to_f16_sat(x); }
 __device__ inline f32x4 mfma_op(op8 a, op8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
 __device__ inline float wave_sum(float v) {
