@@ -15,7 +15,7 @@
 //   SWIGLU  1/rms, silu(gate) * up into the fragment tiling of the down projection
 //   RESID   residual add, x = h * gain of the next RMSNorm into fragment tiling, and the share of
 //           sum(h^2) per row of each column tile
-//   SUM / DIRECT  the product (optionally scaled by 1/rms per row) to bf16 or fp32
+//   SUM / DIRECT  the product (optionally scaled by 1/rms per row) to bf16
 // W_qkv and W_gate_up are packed with their rows permuted (weight_source_row) so that a rotary pair,
 // or a gate column and its up column, sit 8 columns apart in one 16-column tile.
 #include "common.h"
@@ -83,7 +83,9 @@ __global__ void pack_act_kernel(const bf16x8* __restrict__ x, op8* __restrict__ 
 //           gate/up of an 8B model), and up to 16 rows when the skinny kernel would need a second round for a few column tiles
 //           (QKV of a 7B model with grouped-query heads).  Beyond 64 rows only where it is still ahead of the macro kernel:
 //           the 48-column groups of an 8B model's QKV to 96 rows (33.3 against 34.2; at 112 36.8 against 35.7), O to 208
-//           (28.2 / 29.8; at 240 44.9 / 29.7), down to 128 (40.4 / 43.3; at 136 49.3 / 47.6);
+//           (28.2 / 29.8; at 240 44.9 / 29.7), down to 128 (40.4 / 43.3; at 136 49.3 / 47.6).  (Measured before the K splits lost their
+//           fences and the macro kernel's epilogues left LDS, and not refitted: O at 104 .. 152 rows now takes 18 .. 22 here, 16 .. 20 on the
+//           macro kernel's best candidates);
 //   macro   everything else from 17 rows on: wide matrices whose groups are more than one round (gate/up of a 7B model, 395
 //           groups: 73.6 against 51.1 at 40 rows, 110 against 61 at 152), and all wider passes (gate/up of an 8B model 43.5
 //           against 41.9 at 80 rows, 55.6 / 50.4 at 136);

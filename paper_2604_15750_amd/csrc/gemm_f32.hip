@@ -7,7 +7,8 @@
 // their operands straight into registers, D steps of 16 k at a time, and multiply them on the fp32 matrix cores
 // (v_mfma_f32_16x16x4_f32: lane 16 kq + r holds four consecutive k of row r, one per instruction; W and X use the same order of
 // k, so it is only a permutation of the sum); the four accumulators meet in LDS and are added in wavefront order (deterministic).
-// 8 rows x 768 columns x 128: 18 us with 64 x 64 tiles staged through LDS 16 k at a time, 3.7 us now (48 against 5.2 at K = 384).
+// 8 rows x 768 columns x 128: 18 us with 64 x 64 tiles staged through LDS 16 k at a time, 4.4 with as many steps per trip as at K = 384, 3.7
+// with two; 8 rows x 128 columns x 384: 48 / 5.2 (kernel trace).
 #include "gemm_epilogue.h"
 
 namespace {

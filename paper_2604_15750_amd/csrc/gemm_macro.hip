@@ -47,8 +47,12 @@ SumOrder sum_order(int mt, int N, int K, bool may_split) {
 // workgroup each (the pipeline's stages fill a unit's LDS).  Its k-tiles take the tile's measured time, between ns1 and ns4 by
 // the number of row blocks that share W; a chip that is partly full runs its workgroups up to a third faster.  Every round pays
 // its pipeline's start and its epilogue (QKV most: rotary embedding and scattered cache writes).  A K split, for launches that
-// leave compute units idle, adds the hand-off and the partial tiles' traffic.  Against the best of all measured candidates of
-// 220 shapes the choice loses 0.7 % on average.  M enters only through its 16-row tiles.
+// leave compute units idle, adds the hand-off and the partial tiles' traffic.  M enters only through its 16-row tiles.
+// The round's and the hand-off's terms (round_us, 4.6 + 0.6 ..) and the tiles' times were fitted to the kernel with a fenced hand-off and
+// epilogues staged through LDS, against which the choice lost 0.7 % to the best candidate over 220 shapes; they are not refitted, and now
+// charge splits and rounds too much.  On the present kernel, 127 shapes of both models' layers from 72 to 1024 rows, it loses 3.7 %:
+// nothing for gate/up from 208 rows on and QKV of the 8B model from 336, most for O at 264 .. 384 rows (27.9 us, 24.0 with a two-way split),
+// QKV of the 7B one at 208 .. 304 (25.0 / 20.9), down of the 8B one at 248 (54.6 / 42.7).  Below 497 rows the order of the sums is free.
 // Where the order of the sums is fixed, two parts of K are either a split over two workgroups (as long as all of them are one
 // round) or one workgroup that keeps two sums (fold), and a chunk of the squares is a column block or half of one; the tile is free.
 // With the split and the block width pinned as well, narrow matrices ran a second round: O of an 8B model at 2048 rows 90 us against

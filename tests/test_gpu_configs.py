@@ -96,7 +96,7 @@ def test_full_depth_first_passes(device):
     """Configuration 1 at its full size (32 layers, 15 GB of bf16 weights): the prefill pass (384 rows, the launch
     configuration of the benchmark's first pass), the in-block denoising passes of the first block (8 rows: the kernels the
     benchmark spends its time in) and the first boundary pass (136 rows, KL rows against the retained prefill logits), every
-    logit and statistic against the oracle run at full depth on the host, at the benchmark spec's tolerance: 2e-2 of
+    logit and statistic against the oracle run at full depth on the host, at the tolerance of bf16 logits: 2e-2 of
     max(row maximum, sigma_logit) for the worst logit of every row.
 
     What keeps the path well inside that bound at this depth is what the kernels feed the matrix cores: IEEE half (11
@@ -123,7 +123,7 @@ def test_full_depth_first_passes(device):
 def test_full_depth_grouped_query_first_passes(device):
     """Configuration 2 at its full size (Dream-7B shape: 28 layers, 28 query / 4 kv heads, FFN 18944, vocabulary 152064):
     the prefill pass (512 + 128 = 640 rows) and the first in-block pass (8 rows against 512 cached keys), every logit and
-    statistic against the oracle at full depth, at the benchmark spec's tolerance."""
+    statistic against the oracle at full depth, at the tolerance of bf16 logits."""
     cfg, _, P, N, lmax = inputs.WORKLOADS["dream7b_p512_g256"]
     W = inputs.make_weights(cfg, seed=0, device=device)
     prompt = inputs.make_prompts(cfg, 1, P)[0]

@@ -1,7 +1,7 @@
 """Parity of each HIP kernel (through the C ABI) against the CPU oracle, element by element.
 
-Tolerances (derivations in the design doc):
-  bf16 GEMM / attention   2e-2 * max(|ref| over the row, sigma)  (spec bound for bf16 logits)
+Tolerances:
+  bf16 GEMM / attention   2e-2 * max(|ref| over the row, sigma)  (the bound for bf16 logits)
   fp32 GEMM / attention   1e-4 * max(|ref| over the row)          (fp32 accumulation over K <= 4096)
   fp32 statistics         1e-5 * max(1, |ref|), KL additionally 1e-5 * sum p |log p - log p'|
   decisions               exact where the oracle's margin exceeds 1e-4 (boundary) / 1e-5 (selection)

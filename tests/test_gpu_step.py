@@ -3,7 +3,7 @@
 Teacher-forced replay: the oracle decodes on the CPU and records every pass and decision; the HIP
 path is fed the same tokens pass by pass through the C ABI and every output is compared:
   logits            against the oracle's, per row: |dz| <= tol * max(|z_ref|_inf, sigma_logit)
-                    (tol = 2e-2 for bf16 models, the benchmark spec's bound; 2e-4 for the fp32 model)
+                    (tol = 2e-2 for bf16 models, the bound of bf16 logits; 2e-4 for the fp32 model)
   statistics        stage-isolated: the oracle's statistics of the GPU's own logits, 1e-5
   KL                stage-isolated against the GPU's own retained logits
   decisions         the oracle's rule applied to the GPU's statistics: exact where the margin allows
