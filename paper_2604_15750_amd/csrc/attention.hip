@@ -182,7 +182,7 @@ void launch_attention_f32(const float* q, const float* kcache, const float* vcac
 // one the fewest that leave at most one workgroup per compute unit (8B shape, 24 rows x 856 keys, one tile / two: 7.7 / 9.7 us;
 // 37 rows x 1537: 22.3 / 16.1; two shares of a 64-dim head never are more than that).  Spans of one tile gain nothing from a second
 // that no row fills (28 heads, 3 sequences of 16 rows x 1516 keys, two tiles / one: 25.7 / 22.2).
-// A middling pass has eight wavefronts, of which a unit holds one workgroup: two tiles where that makes one round of two (28 heads,
+// A middling pass has eight wavefronts, of which a unit holds one workgroup (128 dims): two tiles where that makes one round of two (by events, 28 heads,
 // 152 rows x 792 keys, 280 workgroups / 140: 17.9 / 13.9).  Not where two tiles are more than a round themselves (32 heads, 5 spans of 40
 // rows x 640, 480 / 320: 24.8 / 28.5), nor where spans of other lengths leave so many workgroups without rows that one tile each is a
 // round as well (40 + 8 + 8 rows x 640, 160 of 288 / 128 of 192: 14.2 / 16.4; 40 + 4 x 8, 224 of 480 / 192 of 320: 16.8 / 25.0).  But workgroups

@@ -28,7 +28,7 @@ typedef float f32x4_lds __attribute__((ext_vector_type(4), aligned(8)));
 template <int HD, int NWV, int DS, int T>
 struct AttnLds {  // merge buffers of one workgroup (T query tiles, HD / DS of the head's dims)
   float sm[T][NWV][16], sl[T][NWV][16];
-  // a query's dims in a row, padded by two banks and accessed in 8-byte halves (rows padded to 16 bytes, accessed whole: 152 rows x
+  // a query's dims in a row, padded by two banks and accessed in 8-byte halves (by events, rows padded to 16 bytes and accessed whole: 152 rows x
   // 792 keys, 32 heads, 15.6 us against 14.9).  The struct is its kernel's only LDS object, at address 0; told so by alignas, the
   // compiler orders the loads of the shortest passes worse (24 rows x 124 keys 6.6 -> 6.9 us).
   float so[T][NWV][16][HD / DS + 2];
@@ -99,7 +99,7 @@ __device__ inline void attention_tiles(const f16_t* __restrict__ q, const f16_t*
   // A step's loads are pinned in front of it, K of the next block too: past the last block a line per fragment of this one, which
   // nothing uses, as a path around the loads would be one that the compiler's count of them cannot follow (it would wait for all of
   // them).  Not for one query tile with eight wavefronts, which are few blocks each: there the copies it makes of what is in
-  // flight cost more (8 rows x 392 keys, four shares, 6.9 us against 6.5; 128 rows x 228 keys, one share, 9.4 against 8.3).
+  // flight cost more (8 rows x 392 keys, four shares, 6.9 us against 6.5; 128 rows x 228 keys, one share, by events 9.4 against 8.3).
   constexpr bool PINNED = T > 1 || (DS == 1 && NWV == 4);
   auto load_k = [&](int buf, int blk) {
     const bool there = blk < nblk;
