@@ -69,7 +69,7 @@ __device__ __attribute__((always_inline)) inline float sum_row4(float v) {
 // (deterministic).  A lane's sixteen loads of a block of 256 chunks are issued together and waited for once: one trip to
 // memory per block instead of one per chunk.  STRAIGHT: chunks past the end re-read the last one instead of being skipped by a path
 // per load.
-template <int NT, bool STRAIGHT = false>
+template <int NT>
 __device__ inline void block_rinv(const RowScale& rs, int m_lo, int rows, float* s_rinv) {
   const int sub = threadIdx.x & 15;
   for (int row = threadIdx.x >> 4; row < rows; row += NT / 16) {
@@ -81,12 +81,7 @@ __device__ inline void block_rinv(const RowScale& rs, int m_lo, int rows, float*
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
           const int c = c0 + sub + 16 * k;
-          if (STRAIGHT) {
-            const float t = src[min(c, rs.nch - 1)];
-            v[k] = c < rs.nch ? t : 0.f;
-          } else {
-            v[k] = c < rs.nch ? src[c] : 0.f;
-          }
+          v[k] = c < rs.nch ? src[c] : 0.f;
         }
 #pragma unroll
         for (int k = 0; k < 16; ++k) ss += v[k];
@@ -98,26 +93,34 @@ __device__ inline void block_rinv(const RowScale& rs, int m_lo, int rows, float*
   }
 }
 
-// block_rinv in two parts, for a workgroup of NT threads and at most ROWS rows of up to 64 chunks each (what the wide-pass
-// producers write), so that a kernel can do its work in between: fetch issues all of a thread's loads, publish adds them (sixteen
-// lanes per row, each every sixteenth chunk in ascending order, then block_rinv's butterfly, here by lane rotation: after the
-// first step the values repeat every eight lanes, and so on, so the sums are the same) and writes the rows' values.
-template <int NT, int ROWS>
+// block_rinv in two parts, for a workgroup of NT threads and at most ROWS rows of up to 16 CH chunks each, so that a kernel can do its
+// work in between: fetch issues all of a thread's loads and touches none of what they bring, publish adds the values (sixteen lanes per
+// row, each every sixteenth chunk in ascending order, then block_rinv's butterfly, here by lane rotation: after the first step the
+// values repeat every eight lanes, and so on, so the sums are the same) and writes the rows' values.  (block_rinv in front of a loop,
+// which the compiler makes a chain of up to sixteen trips, kept the wavefronts that run it from their weights.)
+template <int NT, int ROWS, int CH = 4>
 struct RinvBatch {
   static constexpr int RPT = (ROWS + NT / 16 - 1) / (NT / 16);  // rows per thread
-  float v[RPT][4];
+  static constexpr int LOADS = RPT * CH;
+  float v[RPT][CH];
+  static __device__ inline bool fits(const RowScale& rs) { return rs.nch <= 16 * CH; }
   __device__ __attribute__((always_inline)) inline void fetch(const RowScale& rs, int m_lo, int rows) {
+    if (rs.ssq) fetch(rs.ssq, rs.nch, m_lo, rows);
+  }
+  // ... with no path around the loads, which the compiler's count of loads in flight could not follow (it would let the first products
+  // wait for all of them): where there are no sums of squares, `any_floats` (at least one of them) is read instead
+  __device__ __attribute__((always_inline)) inline void fetch_always(const RowScale& rs, int rows, const void* any_floats) {
+    const bool there = rs.ssq != nullptr;
+    fetch(there ? rs.ssq : (const float*)any_floats, there ? rs.nch : 1, 0, there ? rows : 1);
+  }
+  __device__ __attribute__((always_inline)) inline void fetch(const float* ssq, int nch, int m_lo, int rows) {
     const int sub = threadIdx.x & 15;
-    if (!rs.ssq) return;
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       const int row = (threadIdx.x >> 4) + r * (NT / 16);
+      const float* src = ssq + (size_t)(m_lo + min(row, rows - 1)) * nch;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int c = sub + 16 * k;
-        const float t = rs.ssq[(size_t)(m_lo + min(row, rows - 1)) * rs.nch + min(c, rs.nch - 1)];
-        v[r][k] = c < rs.nch ? t : 0.f;
-      }
+      for (int k = 0; k < CH; ++k) v[r][k] = src[min(sub + 16 * k, nch - 1)];  // (past the end: the last one, left out below)
     }
   }
   template <int CTRL>
@@ -126,8 +129,11 @@ struct RinvBatch {
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       const int row = (threadIdx.x >> 4) + r * (NT / 16);
+      float ss = 0.f;
+#pragma unroll
+      for (int k = 0; k < CH; ++k) ss += (int)(threadIdx.x & 15) + 16 * k < rs.nch ? v[r][k] : 0.f;
       // row_ror:8, 4, 2, 1
-      const float ss = rotate_add<0x121>(rotate_add<0x122>(rotate_add<0x124>(rotate_add<0x128>(((v[r][0] + v[r][1]) + v[r][2]) + v[r][3]))));
+      ss = rotate_add<0x121>(rotate_add<0x122>(rotate_add<0x124>(rotate_add<0x128>(ss))));
       if ((threadIdx.x & 15) == 0 && row < rows) s_rinv[row] = rs.ssq ? rsqrtf(ss * rs.inv_d + rs.eps) : 1.f;
     }
   }

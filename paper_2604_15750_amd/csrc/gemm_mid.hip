@@ -7,10 +7,14 @@
 // column tiles (32 .. 128 columns) and a range of K; its wavefronts split that range among themselves,
 // and each multiplies its k-tiles of the CT W fragments against all MT X fragments (CT MT products
 // per CT + MT fragments fetched), everything in registers:
-//   * W goes HBM -> registers, the step in use and the two to four after it, as many as the registers hold (a step is one
-//     k-tile, two for the narrowest groups; a wavefront keeps 8 .. 24 KiB of W in flight, a workgroup 32 .. 96 KiB: what it takes to keep HBM busy with 128 .. 256 workgroups);
-//     X goes L2 -> registers one step ahead, issued BEFORE the W loads of the same step, so that
-//     waiting for it never waits for younger W loads (the memory counter retires in order);
+//   * W goes HBM -> registers, three steps at a time (a step is one k-tile, two for the narrowest groups; a wavefront keeps 8 .. 24 KiB
+//     of W in flight, a workgroup 32 .. 96 KiB: what it takes to keep HBM busy with 128 .. 256 workgroups), non-temporally: one workgroup
+//     reads a column group's W, once a pass, and the memory-side cache never holds it until the next (a plain read of HBM 6.2 -> 7.1
+//     TB/s; gate/up of an 8B model at 8 rows, this and the loads' start below, 33.6 -> 31.4 us, at 37 rows 37.4 -> 33.2, QKV 19.0 -> 17.2);
+//     X goes L2 -> registers as many steps ahead (one for more than four row tiles), issued BEFORE the W loads of
+//     the same step, because the memory counter retires in order and a wait for X must not wait for younger W loads;
+//   * the first loads need nothing from memory (their arguments arrive in registers), and no load in front of the loop is waited for
+//     before the products are: the rows' 1/rms is finished behind it;
 //   * no barrier, no LDS inside the loop: a wavefront never waits for another.  (X through
 //     direct-to-LDS loads would save a third of the registers, but the compiler then no longer counts
 //     the register loads beside them and waits for every load in flight once per trip.)
@@ -27,9 +31,6 @@ namespace {
 
 constexpr int TPB = 256, NWV = 4;
 constexpr int MID_STEPS_MAX_MT = 4;  // row tiles up to which a launch may read the step-major copy of W
-#ifndef MID_WD_MAX
-#define MID_WD_MAX 4
-#endif
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 constexpr int SC1 = 16;  // cache-policy bit of the raw-buffer builtins: device scope
@@ -41,13 +42,11 @@ __device__ inline __amdgpu_buffer_rsrc_t part_rsrc(const float* base) {
 template <int MT, int CT>
 struct MidShape {
   static constexpr int KB = CT <= 3 ? 2 : 1;  // k-tiles per step: narrow column groups take two, so that a step's loads are still 6 KiB of W
-  // steps of W per register ring (one in use, the others in flight): as many as fit beside the accumulators and two steps of
-  // X in about 370 registers, and whose loads the memory counter can count; 3 .. MID_WD_MAX
-  static constexpr int WD_FIT = (92 - CT * MT - 2 * KB * MT) / (KB * CT);
-  static constexpr int WD_CNT = (63 / KB - MT) / CT + 1;
-  static constexpr int WD_ = WD_FIT < WD_CNT ? WD_FIT : WD_CNT;
-  static constexpr int WD = WD_ < 3 ? 3 : WD_ > MID_WD_MAX ? MID_WD_MAX : WD_;
-  static constexpr int TRIP = WD % 2 ? 2 * WD : WD;  // steps after which both the W ring and the two X sets are back where they started
+  // steps of W and of X per register ring (one in use, the others in flight).  Three of each: the memory counter retires in order, so X
+  // one step ahead lets W be no more than two ahead either; with three or four steps of both ahead HBM serves the chip more slowly
+  // (gate/up of an 8B model, 8 rows, W 3 / 4 / 5 deep: 31.4 / 32.0 / 31.7 us; X 2 deep and W 4: 32.2).  X two deep where its fragments are many.
+  static constexpr int WD = 3, XD = MT <= 4 ? 3 : 2;
+  static constexpr int TRIP = WD * XD / (WD == XD ? XD : 1);  // steps after which both rings are back where they started
   static constexpr int F = CT * MT;                 // output fragments of a workgroup
   static constexpr int FW = (F + NWV - 1) / NWV;    // ... finished by one wavefront
   static constexpr int FR = F < 32 ? (F + 3) / 4 * 4 : 32;  // fragments per reduction round (a multiple of 4: fragment f stays with wavefront f % 4)
@@ -57,20 +56,22 @@ struct MidShape {
 };
 
 // grid.x = groups * splits; MT >= ceil(M / 16), and X has MT row tiles (the activation buffers are padded to 16 rows).
-// STEPS: W is read from the step-major copy (e.w_steps) instead of wt.  STRAIGHT: the rows' sums of squares in one run of loads.
-template <int MT, int CT, int PR, int EPI, bool STEPS, bool STRAIGHT>
+// STEPS: wt is the step-major copy of W.
+template <int MT, int CT, int PR, int EPI, bool STEPS>
 __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
                                                        int kt_per_split, int splits, GemmEpi e) {
   typedef MidShape<MT, CT> SH;
   constexpr int F = SH::F, FW = SH::FW, FR = SH::FR, ROUNDS = SH::ROUNDS;
-  constexpr int KB = SH::KB, WD = SH::WD, TRIP = SH::TRIP;
-  static_assert(KB * (MT + (WD - 1) * CT) < 64, "the loads in flight must fit the memory counter");
+  constexpr int KB = SH::KB, WD = SH::WD, XD = SH::XD, TRIP = SH::TRIP;
+  static_assert(KB * ((XD - 1) * MT + (WD - 1) * CT) < 64, "the loads in flight must fit the memory counter");
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int s_last;
   float* s_rinv = (float*)(lds + SH::BODY);  // [MT * 16]
   float* s_ssq = s_rinv + MT * 16;           // [CT][MT * 16]
 
-  const int group = blockIdx.x / splits, split = blockIdx.x - group * splits, groups = gridDim.x / splits;
+  // (nothing up to the first loads comes from memory: the arguments in front of e arrive in registers, and the grid's size is not asked for)
+  const int group = STEPS ? blockIdx.x : blockIdx.x / splits, split = STEPS ? 0 : blockIdx.x - group * splits;  // (the copy: no K split)
+  const int groups = (N + 16 * CT - 1) / (16 * CT);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int KT = K >> 5, NT = N >> 4;
   const int nt0 = group * CT;
@@ -88,20 +89,19 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
 #pragma unroll
   for (int r = 0; r < CT; ++r) {
     const int nt = min(nt0 + r, NT - 1);
-    wptr[r] = steps ? (const op8*)e.w_steps + ((size_t)(group * NWV + wave) * CT + r) * 64 + lane
-                    : PR == 2 ? wt + ((size_t)(nt >> 1) * KT * 2 + (nt & 1)) * 64 + lane : wt + (size_t)nt * KT * 64 + lane;
+    wptr[r] = steps ? wt + ((size_t)(group * NWV + wave) * CT + r) * 64
+                    : PR == 2 ? wt + ((size_t)(nt >> 1) * KT * 2 + (nt & 1)) * 64 : wt + (size_t)nt * KT * 64;
   }
-  const op8* xptr = xt + lane;  // fragment (j, t) = xptr[(j * KT + t) * 64]
   // In the last row tile, lanes whose row does not exist re-read row 0 of their k-group instead of fetching lines of their
   // own (a fragment's 128-byte lines hold 8 rows each: a block of 8 rows reads half of them); what they get is never stored.
-  const op8* xptr_last = xt + ((MT - 1) * 16 + (lane & 15) < M ? lane : (lane & ~15));
+  const int lane_last = (MT - 1) * 16 + (lane & 15) < M ? lane : (lane & ~15);
 
   f32x4 acc[CT][MT];
 #pragma unroll
   for (int r = 0; r < CT; ++r)
 #pragma unroll
     for (int j = 0; j < MT; ++j) acc[r][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  op8 w[WD][KB][CT], x[2][KB][MT];
+  op8 w[WD][KB][CT], x[XD][KB][MT];
   const int nsteps = (t1 - t0 + KB - 1) / KB;
   const op8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
     for (int i = 0; i < KB; ++i) {
       const int tc = min(t0 + st * KB + i, t1 - 1);
 #pragma unroll
-      for (int j = 0; j < MT; ++j) x[slot][i][j] = (j == MT - 1 ? xptr_last : xptr)[((size_t)j * KT + tc) * 64];
+      for (int j = 0; j < MT; ++j) x[slot][i][j] = (xt + ((size_t)j * KT + tc) * 64)[j == MT - 1 ? lane_last : lane];
     }
   };
   auto load_w = [&](const int slot, int st) __attribute__((always_inline)) {
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
     for (int i = 0; i < KB; ++i) {
       const int tc = min(t0 + st * KB + i, t1 - 1);
 #pragma unroll
-      for (int r = 0; r < CT; ++r) w[slot][i][r] = wptr[r][(size_t)(tc - tsub) * wstep];
+      for (int r = 0; r < CT; ++r) w[slot][i][r] = __builtin_nontemporal_load(wptr[r] + (size_t)(tc - tsub) * wstep + lane);
     }
   };
   auto compute = [&](const int ws, const int xs, int st) __attribute__((always_inline)) {
@@ -134,15 +134,14 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
       }
     }
   };
-  // step S of a trip: X of the next step first, then W of the step WD - 1 ahead, so that the wait for this step's operands
-  // (the oldest loads) leaves W WD - 1 steps deep and X one step deep in flight; the scheduling barriers keep the compiler
-  // from sinking the loads down to their uses (which it does under register pressure, undoing the prefetch)
+  // step S of a trip: X of the step XD - 1 ahead first, then W of the step WD - 1 ahead, so that the wait for this step's operands
+  // (the oldest loads) leaves XD - 1 steps of both in flight; the scheduling barriers keep the compiler from sinking the loads down to their uses (which it does under register pressure, undoing the prefetch)
   auto step = [&](auto Sc, int st) __attribute__((always_inline)) {
     constexpr int S = decltype(Sc)::value;
-    load_x((S + 1) & 1, st + 1);
+    load_x((S + XD - 1) % XD, st + XD - 1);
     load_w((S + WD - 1) % WD, st + WD - 1);
     __builtin_amdgcn_sched_barrier(0);
-    compute(S % WD, S & 1, st);
+    compute(S % WD, S % XD, st);
     __builtin_amdgcn_sched_barrier(0);
   };
   // (every lambda here is forced inline: left to its own judgement the compiler keeps the largest variants' steps as
@@ -165,14 +164,22 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
       }
     }
   };
-  if (nsteps > 0) {
-    load_x(0, 0);
+  const bool any = STEPS || nsteps > 0;  // (the copy: every wavefront has k-tiles)
+  if (any) {
 #pragma unroll
-    for (int i = 0; i < WD - 1; ++i) load_w(i, i);
+    for (int i = 0; i < WD - 1; ++i) {
+      if (i < XD - 1) load_x(i, i);
+      load_w(i, i);
+    }
   }
-  // 1/rms of the input rows, needed only by the epilogue: fetched while the first k-tiles are in flight (published by the
-  // barriers of the reduction)
-  if (EPI != EPI_RESID) block_rinv<TPB, STRAIGHT>(e.rs, 0, min(M, MT * 16), s_rinv);
+  __builtin_amdgcn_sched_barrier(0);
+  // 1/rms of the input rows, needed only by the epilogue: fetched behind the first k-tiles, and kept until the loop is over (published
+  // by the barriers of the reduction)
+  typedef RinvBatch<TPB, MT * 16, ((MT > 1 && EPI == EPI_QKV) || MT > 4) ? 4 : 16> Rinv;  // (down's chunks are few from 17 rows on)
+  const int rows = min(M, MT * 16);
+  Rinv rinv;
+  if (EPI != EPI_RESID) rinv.fetch_always(e.rs, rows, xt);
+  __builtin_amdgcn_sched_barrier(0);
   // ... and so is what the epilogue of the fragment this wavefront finishes first (fragment `wave`) reads from memory, in the
   // variants of narrow passes, which are short enough for that round trip to show
   EpiAhead ahead = epi_none();
@@ -180,12 +187,16 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
     if (splits == 1 && wave < F && nt0 + wave / MT < NT)
       ahead = epi_ahead<EPI>(e, M, N, (wave % MT) * 16 + (lane & 15), (nt0 + wave / MT) * 16, lane >> 4);
   }
-  if (nsteps > 0) {
+  if (any) {
     int st = 0;
     for (; st + TRIP <= nsteps; st += TRIP) trip(trip, std::integral_constant<int, 0>{}, st);
     rest(rest, std::integral_constant<int, 0>{}, st);
   }
 
+  if (EPI != EPI_RESID) {
+    if (Rinv::fits(e.rs)) rinv.publish(e.rs, rows, s_rinv);
+    else block_rinv<TPB>(e.rs, 0, rows, s_rinv);
+  }
   // ---- the four partial accumulators -> one finished (or, with a K split, one partial) value per output fragment
   const int g = lane >> 4, ml = lane & 15;
   f32x4* red = (f32x4*)lds;  // [NWV][FR][64]
@@ -311,33 +322,23 @@ MidPlan mid_plan(int M, int N, int K) {
   return best;
 }
 
-template <int MT, int CT, int PR, int EPI, bool STEPS, bool STRAIGHT>
+template <int MT, int CT, int PR, int EPI, bool STEPS>
 void launch_kernel(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
   typedef MidShape<MT, CT> SH;
   static bool configured = false;  // raise the dynamic LDS limit of this instantiation once
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_mid_kernel<MT, CT, PR, EPI, STEPS, STRAIGHT>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
+    (void)hipFuncSetAttribute((const void*)gemm_mid_kernel<MT, CT, PR, EPI, STEPS>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
     configured = true;
   }
-  DLM_LAUNCH((gemm_mid_kernel<MT, CT, PR, EPI, STEPS, STRAIGHT>), p.groups * p.splits, TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
+  DLM_LAUNCH((gemm_mid_kernel<MT, CT, PR, EPI, STEPS>), p.groups * p.splits, TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
              p.kps, p.splits, e);
 }
-template <int MT, int CT, int PR, int EPI, bool STRAIGHT = false>
-void launch_steps(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
-  if constexpr (MT <= MID_STEPS_MAX_MT) {
-    if (e.w_steps) return launch_kernel<MT, CT, PR, EPI, true, STRAIGHT>(xt, wt, M, N, K, p, e, st);
-  }
-  launch_kernel<MT, CT, PR, EPI, false, STRAIGHT>(xt, wt, M, N, K, p, e, st);
-}
-// Gate/up of 5 to 8 rows, whose sums of squares are two wavefronts' work, fetches them in one straight run of loads (8 rows 33.9 -> 32.8
-// us).  Elsewhere that costs: 1 to 4 rows, one wavefront, 34.1 -> 34.5; 16 rows, four, 33.9 -> 35.5; 37 rows 37.6 -> 42.7; before the
-// rotary epilogue, QKV of 8 rows, 18.8 -> 20.0.
 template <int MT, int CT, int PR, int EPI>
 void launch_one(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
-  if constexpr (MT == 1 && EPI == EPI_SWIGLU) {
-    if (M > 4 && M <= 8) return launch_steps<MT, CT, PR, EPI, true>(xt, wt, M, N, K, p, e, st);
+  if constexpr (MT <= MID_STEPS_MAX_MT) {
+    if (e.w_steps) return launch_kernel<MT, CT, PR, EPI, true>(xt, e.w_steps, M, N, K, p, e, st);
   }
-  launch_steps<MT, CT, PR, EPI>(xt, wt, M, N, K, p, e, st);
+  launch_kernel<MT, CT, PR, EPI, false>(xt, wt, M, N, K, p, e, st);
 }
 
 template <int MT, int EPI>
