@@ -58,6 +58,9 @@ constexpr int MACRO_SPLIT_FRAGS = 16;
 // kernel keeps its loop and its registers (QKV, 96 x 128: 95 against 124, 128 x 256: 229 against 250)
 constexpr bool macro_can_keep_order(int wm, int wn, int kb) { return kb == 2 && wm * wn >= 6 && wm * wn <= MACRO_SPLIT_FRAGS; }
 
+// tiles that also come with non-temporal copies of W, for launches of one row block (see issue)
+constexpr bool macro_non_temporal(int rw, int cw, int wn) { return cw * wn > rw * cw; }
+
 // gemm_macro_<epilogue>.hip: the launches of one epilogue's instantiations
 template <int EPI>
 void launch_macro_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const MacroPlan& p, const GemmEpi& e, hipStream_t st);
@@ -92,7 +95,8 @@ struct MacroShape {
 
 // form: bit 0: the weights are packed in interleaved pairs of column tiles, not in single runs (weight_pack_rows - 1); and with ORDER
 // bit 1: two chunks of the squares per column block, the other bits: k-tiles after which a second sum starts (0: one sum)
-template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER>
+// NT: W is read once (a single row block), so most of its copies are non-temporal (see issue)
+template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER, bool NT>
 __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
                                                                                int form, int nblocks, int mblocks, int splits, int kt_per_split, GemmEpi e) {
   typedef MacroShape<WM, WN, RW, CW, KB> SH;
@@ -107,38 +111,48 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   // Workgroup id -> (K split, column block, row block), row blocks fastest.  Ids congruent mod 8 share an XCD: each XCD takes one
   // contiguous eighth of the tiles, so the row blocks of a column block (which stream the same W) meet in one L2 and no XCD has
   // more than its share; with a K split it walks one part of K (or few), so that X's other parts never enter its L2.
-  const int tiles = nblocks * mblocks, lin = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int tiles = nblocks * mblocks, lin = (blockIdx.x & 7) * ((tiles * splits + 7) >> 3) + (blockIdx.x >> 3);  // (the grid is a multiple of 8)
   if (lin >= tiles * splits) return;
   const int split = lin / tiles, tile = lin - split * tiles, cb = tile / mblocks, rb = tile - cb * mblocks;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / CW, wn = wave % CW;
-  const int KT = K >> 5, MTILES = (M + 15) >> 4, NT = N >> 4;
+  const int KT = K >> 5, MTILES = (M + 15) >> 4, NTILES = N >> 4;
   const int mt0 = rb * AT, nt0 = cb * BF, m_lo = mt0 * 16;
   // the workgroup's k-tiles kb .. kb + nkt - 1; stage s holds k-tiles s KB .. s KB + KB - 1 of them
   const int kb = split * kt_per_split, nkt = min(KT, kb + kt_per_split) - kb, nstages = nkt / KB;
 
-  // Copies lo .. hi - 1 (of this wavefront's LPS) of stage s -> buffer buf: fragment f of a k-tile (f < AT: X row tile mt0 + f, else
-  // W column tile nt0 + f - AT) is moved by wavefront f % NW; a wavefront without a fragment of its own in the last round moves
-  // the last one again.  The fragments' addresses at the first k-tile are kept, so that a copy costs one scalar shift and one add
+  // Copies lo .. hi - 1 (of this wavefront's LPS) of stage s -> buffer buf: of a k-tile's fragments, one operand's first and then the
+  // other's, wavefront w moves the ones congruent w mod NW, in rounds of NW; a wavefront without a fragment of its own in the last round
+  // moves the last one again.  The fragments' addresses at the first k-tile are kept, so that a copy costs one scalar shift and one add
   // (recomputing them from the tile indices each time took 3 .. 5 % of a wide launch).
+  // Where W is read by one workgroup only, the rounds that are all W (which comes first then) are non-temporal: they do not enter the memory-side cache, in which
+  // W never stays from pass to pass (a plain read of HBM 6.2 -> 7.1 TB/s; the LM head of the 8B model, 8 rows 180 -> 158 us, 96 rows 196 ->
+  // 185).  Where row blocks share W it loses what the L2 keeps for the second of them (two readers of a stream 5.1 -> 4.7 TB/s, four 3.6 ->
+  // 2.9), and so does a fragment that several wavefronts move; with one such round and nothing else of W, 96 x 128 tiles, it loses as well
+  // (head of the 7B model at 96 rows 229 -> 238).
+  constexpr bool W_FIRST = macro_non_temporal(RW, CW, WN);
+  constexpr int FIRST_OP = W_FIRST ? BF : AT;
+  static_assert(W_FIRST || !NT, "whole rounds of W come first");
   const unsigned lane16 = lane * 16;
   const char* fbase[LPT];
 #pragma unroll
   for (int i = 0; i < LPT; ++i) {
-    const int f = i * NW + wave, nt = min(nt0 + min(max(f - AT, 0), BF - 1), NT - 1);
-    fbase[i] = f < AT ? (const char*)xt + ((size_t)min(mt0 + f, MTILES - 1) * KT + kb) * 1024
-                      : (const char*)wt + ((((size_t)(nt >> prs) * KT + kb) << prs) + (nt & prs)) * 1024;
+    const int f = min(i * NW + wave, NFR - 1), fw = W_FIRST ? f : f - AT, fx = W_FIRST ? f - BF : f;
+    const int ntile = min(nt0 + max(fw, 0), NTILES - 1), mtile = min(mt0 + max(fx, 0), MTILES - 1);
+    fbase[i] = (W_FIRST ? fx >= 0 : fw < 0) ? (const char*)xt + ((size_t)mtile * KT + kb) * 1024
+                                            : (const char*)wt + ((((size_t)(ntile >> prs) * KT + kb) << prs) + (ntile & prs)) * 1024;
   }
   auto issue = [&](int s, int buf, int lo, int hi) __attribute__((always_inline)) {
 #pragma unroll
     for (int c = lo; c < hi; ++c) {
-      const int sub = c / LPT, i = c % LPT, f = i * NW + wave;
+      const int sub = c / LPT, i = c % LPT, f = min(i * NW + wave, NFR - 1);
       const unsigned t = min(s * KB + sub, nkt - 1);
-      const bool is_x = AT % NW == 0 ? i < AT / NW : f < AT;  // (uniform in the wavefront)
+      const bool first = FIRST_OP % NW == 0 ? i < FIRST_OP / NW : f < FIRST_OP, is_x = first != W_FIRST;  // (uniform in the wavefront)
       const char* src = fbase[i] + (is_x ? t << 10 : t << (10 + prs));
-      unsigned char* dst = lds + buf * STAGE + (sub * NFR + min(f, NFR - 1)) * 1024;
-      __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src + lane16), LDS_PTR(dst), 16, 0, 0);
+      unsigned char* dst = lds + buf * STAGE + (sub * NFR + (!W_FIRST ? f : first ? AT + f : f - BF)) * 1024;  // (X lies in front)
+      if (NT && (i + 1) * NW <= BF) __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src + lane16), LDS_PTR(dst), 16, 0, 2);
+      else __builtin_amdgcn_global_load_lds(GLOBAL_PTR(src + lane16), LDS_PTR(dst), 16, 0, 0);
     }
   };
 
@@ -169,12 +183,22 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   auto fetch_resid = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < WN; ++j) {
-      const int n = min(nt0 + wn * WN + j, NT - 1) * 16 + 4 * (lane >> 4);
+      const int n = min(nt0 + wn * WN + j, NTILES - 1) * 16 + 4 * (lane >> 4);
       g_ahead[j] = *(const f32x4*)(e.gain + n);
 #pragma unroll
       for (int i = 0; i < WM; ++i) h_ahead[j][i] = *(const f32x4*)(e.h + (size_t)min(m_lo + (wm * WM + i) * 16 + (lane & 15), M - 1) * N + n);
     }
   };
+  // The first stage's copies go out before anything is read from memory (the arguments in front of e arrive in registers), then what
+  // the epilogue reads, then the other stages: the wait for the first stage waits for these loads too, whatever their number.  Not where
+  // 1/rms has to be published in front of the loop, for which the compiler waits for every load in flight.
+  typedef RinvBatch<TPB, AT * 16> Rinv;
+  constexpr bool RINV_LATE = 4 * WM * WN + 8 * (WM + WN) + 4 * Rinv::RPT <= 210;
+  constexpr bool FIRST = EPI == EPI_RESID || RINV_LATE;
+  if (FIRST) {
+    issue(0, 0, 0, LPS);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   if (H_EARLY && splits == 1) fetch_resid();
 
   // K split: a ticket per workgroup and tile, taken here, where its trip to memory hides behind the pipeline's start
@@ -187,10 +211,8 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   // has up to 64 chunks (wide passes).  Where the registers hold what was fetched, it stays there until the loop is over (touching
   // it while copies to LDS are in flight would make the compiler wait for all of them); published to the other wavefronts by
   // the barrier of the epilogue, or by the loop's.
-  typedef RinvBatch<TPB, AT * 16> Rinv;
-  constexpr bool RINV_LATE = 4 * WM * WN + 8 * (WM + WN) + 4 * Rinv::RPT <= 210;
   const int rows = max(0, min(M, m_lo + AT * 16) - m_lo);
-  const bool rinv_batched = EPI != EPI_RESID && !(e.rs.ssq && e.rs.nch > 64);
+  const bool rinv_batched = EPI != EPI_RESID && Rinv::fits(e.rs);
   Rinv rinv;
   if (EPI != EPI_RESID) {
     if (rinv_batched) {
@@ -201,8 +223,9 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     }
   }
 
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s) issue(s, s, 0, LPS);
+  for (int s = FIRST ? 1 : 0; s < S - 1; ++s) issue(s, s, 0, LPS);
   issue(S - 1, S - 1, 0, LPS / KB);  // (the rest of it goes out during stage 0, as for every later stage)
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * LPS + LPS / KB) : "memory");  // stage 0 has landed (this wavefront's share)
   __builtin_amdgcn_s_barrier();
@@ -309,7 +332,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     // behind the loop and row-major partials (half lines), 3 to 4 now: down of an 8B model at 384 rows 71 -> 62 us.
     const unsigned slot = (unsigned)(AT * BF) * 256;  // floats of a tile's partial
     auto offset = [&](int j, int i) { return (unsigned)((((wm * WM + i) * BF + wn * WN + j) * 64 + lane) * 16); };
-    auto exists = [&](int j, int i) { return nt0 + wn * WN + j < NT && mt0 + wm * WM + i < MTILES; };  // (uniform in the wavefront)
+    auto exists = [&](int j, int i) { return nt0 + wn * WN + j < NTILES && mt0 + wm * WM + i < MTILES; };  // (uniform in the wavefront)
     int* ticket = e.counters + 2 * tile;
     if (tid == 0) s_ticket = my_ticket;
     __syncthreads();
@@ -382,7 +405,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
 #pragma unroll
     for (int f = 0; f < F; f += 2) {
       const int f1 = f + 1 < F ? f + 1 : f, i0 = f / WN, j0 = f % WN, i1 = f1 / WN, j1 = f1 % WN;
-      const bool there = hi ? (f1 != f && nt_w + j1 < NT && row(i1) < M) : (nt_w + j0 < NT && row(i0) < M);
+      const bool there = hi ? (f1 != f && nt_w + j1 < NTILES && row(i1) < M) : (nt_w + j0 < NTILES && row(i0) < M);
       const Halves v = pair_halves(acc[j0][i0], acc[j1][i1]);
       const float r = hi ? ri[i1] : ri[i0];
       const int second = i1 == i0 ? 128 * (j1 - j0) : 16 * e.ffn + 128 * (j1 - j0);  // from the first fragment's outputs to the second's
@@ -393,7 +416,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     const int hd = e.hd, tph = hd >> 4, half = hd >> 1, heads_rot = e.n_q + e.n_kv;
     constexpr int PR = (WM + 1) / 2;  // pairs of row tiles of a column tile: rotated two at a time, the lower lanes the first's outputs
     int pos[WM], slot[WM];
-    if ((min(nt_w + WN, NT) - 1) / tph >= e.n_q) {
+    if ((min(nt_w + WN, NTILES) - 1) / tph >= e.n_q) {
 #pragma unroll
       for (int i = 0; i < WM; ++i) {
         const int m = min(row(i), M - 1);
@@ -404,7 +427,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     f32x4 rc[2][PR], rsn[2][PR];  // rotary cosines and sines of a column tile's pairs: the next tile's are in flight
     auto fetch_rope = [&](int j) __attribute__((always_inline)) {
       const int nt = nt_w + j;
-      if (nt >= NT || nt / tph >= heads_rot) return;
+      if (nt >= NTILES || nt / tph >= heads_rot) return;
 #pragma unroll
       for (int p = 0; p < PR; ++p) {
         const int m = min(row(2 * p + (hi && 2 * p + 1 < WM)), M - 1);
@@ -418,7 +441,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     for (int j = 0; j < WN; ++j) {
       if (j + 1 < WN) fetch_rope(j + 1);
       const int nt = nt_w + j, head = nt / tph, bt = nt % tph;  // (uniform)
-      if (nt >= NT) continue;
+      if (nt >= NTILES) continue;
       if (head < heads_rot) {
 #pragma unroll
         for (int p = 0; p < PR; ++p) {
@@ -466,7 +489,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     constexpr int RING = 4;
     f32x4 hc[RING][WM], gc[RING];
     auto fetch_col = [&](int j) __attribute__((always_inline)) {
-      if (nt_w + j >= NT) return;
+      if (nt_w + j >= NTILES) return;
       gc[j % RING] = *(const f32x4*)(e.gain + (nt_w + j) * 16 + 4 * g);
 #pragma unroll
       for (int i = 0; i < WM; ++i) hc[j % RING][i] = *(const f32x4*)(e.h + (size_t)min(row(i), M - 1) * N + (nt_w + j) * 16 + 4 * g);
@@ -482,7 +505,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
       for (int i = 0; i < WM; ++i) {
         const int m = row(i);
         float ss = 0.f;  // (a column tile that does not exist adds nothing)
-        if (m < M && nt < NT) ss = finish_resid(e, m, nt * 16 + 4 * g, N, acc[j][i], EpiAhead{H_EARLY ? h_ahead[j][i] : hc[j % RING][i], H_EARLY ? g_ahead[j] : gc[j % RING], true, -1, -1});
+        if (m < M && nt < NTILES) ss = finish_resid(e, m, nt * 16 + 4 * g, N, acc[j][i], EpiAhead{H_EARLY ? h_ahead[j][i] : hc[j % RING][i], H_EARLY ? g_ahead[j] : gc[j % RING], true, -1, -1});
         ss = sum_row4(ss);
         if (g == 0) s_ssq[(wn * WN + j) * AT * 16 + (wm * WM + i) * 16 + ml] = ss;
       }
@@ -494,10 +517,10 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
       bf16_t* out = e.out_bf16 + (size_t)m * N + nt_w * 16;
 #pragma unroll
       for (int j = 0; j < WN; j += 2) {
-        if (j + 1 < WN && nt_w + j + 1 < NT) {
+        if (j + 1 < WN && nt_w + j + 1 < NTILES) {
           const bf16x8 o = join_slots(to_bf16x4(acc[j][i] * ri[i]), to_bf16x4(acc[j + 1 < WN ? j + 1 : j][i] * ri[i]));
           if (m < M) *(bf16x8*)(out + (j + (g & 1)) * 16 + 8 * (g >> 1)) = o;
-        } else if (nt_w + j < NT && m < M) {
+        } else if (nt_w + j < NTILES && m < M) {
           *(bf16x4*)(out + j * 16 + 4 * g) = to_bf16x4(acc[j][i] * ri[i]);
         }
       }
@@ -511,7 +534,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
 #pragma unroll
       for (int j = 0; j < WN; ++j) {
         const int m = row(i), n = (nt_w + j) * 16 + 4 * g;
-        if (nt_w + j >= NT) continue;
+        if (nt_w + j >= NTILES) continue;
         const f32x4 v = acc[j][i] * ri[i];
         if (m < M) *(bf16x4*)(e.out_bf16 + (size_t)m * N + n) = to_bf16x4(v);
         state[i] = lite_merge(state[i], lite_of(v, n, e.skip_col));
@@ -541,7 +564,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   if (EPI == EPI_RESID) {  // the workgroup's share of sum h^2 per row, in one chunk or two: each half of its column tiles in ascending order, then the two
     __syncthreads();
     const bool two = two_chunks && BF % 4 == 0;
-    const int nch = two ? (NT + BF / 2 - 1) / (BF / 2) : nblocks;
+    const int nch = two ? (NTILES + BF / 2 - 1) / (BF / 2) : nblocks;
     for (int r = tid; r < AT * 16 && m_lo + r < M; r += TPB) {
       float* dst = e.ssq_out + (size_t)(m_lo + r) * nch + (two ? cb * 2 : cb);
       if (!two) {
@@ -560,16 +583,16 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   }
 }
 
-template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER>
+template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER, bool NT>
 void launch_tile(const op_t* xt, const op_t* wt, int M, int N, int K, const MacroPlan& p, const GemmEpi& e, hipStream_t st) {
   typedef MacroShape<WM, WN, RW, CW, KB> SH;
   static bool configured = false;  // raise the dynamic LDS limit of this instantiation once
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_macro_kernel<WM, WN, RW, CW, KB, EPI, ORDER>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
+    (void)hipFuncSetAttribute((const void*)gemm_macro_kernel<WM, WN, RW, CW, KB, EPI, ORDER, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
     configured = true;
   }
   const int grid = (p.nblocks * p.mblocks * p.splits + 7) / 8 * 8;
-  DLM_LAUNCH((gemm_macro_kernel<WM, WN, RW, CW, KB, EPI, ORDER>), grid, SH::TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
+  DLM_LAUNCH((gemm_macro_kernel<WM, WN, RW, CW, KB, EPI, ORDER, NT>), grid, SH::TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
              (weight_pack_rows(N) - 1) | (p.ssq_parts == 2 ? 2 : 0) | p.fold << 2, p.nblocks, p.mblocks, p.splits, p.kps, e);
 }
 
@@ -581,9 +604,12 @@ void launch_macro_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const
 #define GO(WM, WN, RW, CW, KB, NS1, NS4)                                                                                       \
   if constexpr (EPI != EPI_STATS || 16 * WM * RW <= GEMM_STATS_MAX_ROWS) {                                                     \
     if constexpr (EPI != EPI_STATS && macro_can_keep_order(WM, WN, KB)) {                                                      \
-      if (p.tile == i && (p.fold || p.ssq_parts > 1)) return launch_tile<WM, WN, RW, CW, KB, EPI, true>(xt, wt, M, N, K, p, e, st); \
+      if (p.tile == i && (p.fold || p.ssq_parts > 1)) return launch_tile<WM, WN, RW, CW, KB, EPI, true, false>(xt, wt, M, N, K, p, e, st); \
     }                                                                                                                          \
-    if (p.tile == i) return launch_tile<WM, WN, RW, CW, KB, EPI, false>(xt, wt, M, N, K, p, e, st);                           \
+    if constexpr (macro_non_temporal(RW, CW, WN)) {                                                                            \
+      if (p.tile == i && p.mblocks == 1) return launch_tile<WM, WN, RW, CW, KB, EPI, false, true>(xt, wt, M, N, K, p, e, st);  \
+    }                                                                                                                          \
+    if (p.tile == i) return launch_tile<WM, WN, RW, CW, KB, EPI, false, false>(xt, wt, M, N, K, p, e, st);                    \
   }                                                                                                                            \
   ++i;
   MACRO_TILES(GO)
