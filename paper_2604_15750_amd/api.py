@@ -116,8 +116,21 @@ def _ints(v):
     return None if v is None else (C.c_int32 * len(v))(*[int(x) for x in v])
 
 
-# The two decisions are bound by what their calls cost the host: their host arrays and parameters are handed over as bytes
-# (marshalling alone 3.8 and 6.1 us with ctypes structs and a format string per array, 2.7 and 4.8 now).
+# The two decisions are bound by what their calls cost the host: plain arguments go through a small extension (csrc/decisions_py.c),
+# any others through ctypes, host arrays and parameters as bytes (marshalling alone 3.8 and 6.1 us with ctypes structs and a format
+# string per array, 2.7 and 4.8 as bytes, 1.2 and 2.1 through the extension; one sequence x 8 rows, both decisions 11.6 -> 8.8 us a pass, 16 x 64 12.1 -> 8.5).
+@functools.lru_cache(maxsize=None)
+def _decisions():
+    """The extension, bound to the library; None where it has not been built."""
+    try:
+        from . import _decisions as m
+    except ImportError:
+        return None
+    L = lib()
+    m.bind(C.cast(L.block_boundary, C.c_void_p).value, C.cast(L.select_parallel, C.c_void_p).value, torch.float32, torch.bfloat16)
+    return m
+
+
 @functools.lru_cache(maxsize=64)
 def _int_packer(n):
     return struct.Struct(f"{n}i").pack
@@ -267,6 +280,13 @@ def dlm_step(state, tokens, out, row_offsets, span_start, commit_len, tok_start,
 
 def block_boundary(I, H, win_start, win_len, L_out, lam, l_min, smooth_radius=1, norm_mode=0, rule=0, cold=None, S_out=None,
                    margin_out=None):
+    ext = _decisions()
+    if ext is not None:
+        rc = ext.boundary(I, H, win_start, win_len, cold, L_out, S_out, margin_out, lam, l_min, smooth_radius, norm_mode, rule, _stream())
+        if rc is not None:  # (None: not plain arguments, nothing has been called)
+            if rc < 0:
+                _check(rc)
+            return
     _check(lib().block_boundary(_ptr(I), _ptr(H), _packed(win_start), _packed(win_len), _packed(cold), len(win_start),
                                 _params(_pack_boundary, dlm_boundary_params, (lam, l_min, smooth_radius, norm_mode, rule)), _ptr(L_out),
                                 _ptr(S_out), _ptr(margin_out), _stream()))
@@ -274,6 +294,14 @@ def block_boundary(I, H, win_start, win_len, L_out, lam, l_min, smooth_radius=1,
 
 def select_parallel(logits, lse, conf, argmax, tokens, row_start, tok_start, block_len, mask_id, tau_low, tau_high, gamma, mode,
                     selected_out, n_selected_out, apply_tokens=True, margin_out=None):
+    ext = _decisions()
+    if ext is not None:
+        rc = ext.select(logits, lse, conf, argmax, tokens, row_start, tok_start, block_len, mask_id, tau_low, tau_high, gamma, mode,
+                        selected_out, n_selected_out, apply_tokens, margin_out, _stream())
+        if rc is not None:
+            if rc < 0:
+                _check(rc)
+            return
     _check(lib().select_parallel(_ptr(logits), logits.size(-1), dtype_code(logits), _ptr(lse), _ptr(conf), _ptr(argmax), _ptr(tokens),
                                  _packed(row_start), _packed(tok_start), _packed(block_len), len(row_start), mask_id,
                                  _params(_pack_select, dlm_select_params, (tau_low, tau_high, gamma, mode)), int(apply_tokens),

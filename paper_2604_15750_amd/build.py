@@ -1,12 +1,14 @@
-"""Compile csrc/*.hip into paper_2604_15750_amd/libdlm.so for gfx950 (in-tree, no torch dependency)."""
+"""Compile csrc/*.hip into paper_2604_15750_amd/libdlm.so for gfx950 and csrc/decisions_py.c into _decisions.so (in-tree, no torch dependency)."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libdlm.so")
+OUT_PY = os.path.join(HERE, "_decisions.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # amdgpu-kernarg-preload-count: a kernel's first arguments (14 dwords at most, up to the first struct) arrive in scalar registers with the
 # launch instead of by a trip to memory, so its first loads go out at once (161 launches of an in-block pass of the 8B model: 2888 -> 2864 us;
@@ -36,6 +38,10 @@ def build(verbose=False):
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", OUT, *objs], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    r = subprocess.run(["gcc", "-O2", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-o", OUT_PY, os.path.join(CSRC, "decisions_py.c")],
+                       capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("gcc failed on decisions_py.c:\n" + r.stderr)
     return OUT
 
 

@@ -1,0 +1,87 @@
+"""The two decisions called through the extension and through ctypes: the same C call for every form of arguments (a recorder in
+place of the library's entry points; nothing is launched)."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_15750_amd import api
+
+I32, F32, VP = C.c_int32, C.c_float, C.c_void_p
+BOUNDARY = C.CFUNCTYPE(C.c_int, VP, VP, VP, VP, VP, C.c_int, VP, VP, VP, VP, VP)
+SELECT = C.CFUNCTYPE(C.c_int, VP, C.c_int, C.c_int, VP, VP, VP, VP, VP, VP, VP, C.c_int, C.c_int, VP, C.c_int, VP, VP, VP, VP)
+
+
+@pytest.fixture
+def calls(monkeypatch):
+    """Runs a function through both ways, the extension first; gives the recorded calls of each."""
+    ext = api._decisions()
+    assert ext is not None, "the extension has not been built"
+    seen = []
+
+    def ints(p, n):
+        return None if not p else tuple((I32 * n).from_address(p))
+
+    def boundary(I, H, ws, wl, cold, n, p, L, S, m, st):
+        q = C.cast(p, C.POINTER(api.dlm_boundary_params))[0]
+        seen.append((I, H, ints(ws, n), ints(wl, n), ints(cold, n), n, q.lam, q.l_min, q.smooth_radius, q.norm_mode, q.rule, L, S, m, st))
+        return 0
+
+    def select(z, V, dt, lse, cf, am, tok, rs, ts, bl, n, mask, p, ap, sel, ns, m, st):
+        q = C.cast(p, C.POINTER(api.dlm_select_params))[0]
+        seen.append((z, V, dt, lse, cf, am, tok, ints(rs, n), ints(ts, n), ints(bl, n), n, mask, q.tau_low, q.tau_high, q.gamma, q.mode, ap, sel, ns, m, st))
+        return 0
+
+    cb, cs, L = BOUNDARY(boundary), SELECT(select), api.lib()
+    real = [C.cast(f, VP).value for f in (L.block_boundary, L.select_parallel)]
+
+    class Recorder:
+        block_boundary, select_parallel, dlm_last_error = cb, cs, L.dlm_last_error
+
+    def run(f):
+        out = []
+        for through_ext in (True, False):
+            seen.clear()
+            monkeypatch.setattr(api, "_decisions", (lambda: ext) if through_ext else (lambda: None))
+            try:
+                f()
+                out.append(list(seen))
+            except Exception as e:
+                out.append(type(e))
+        return out
+
+    monkeypatch.setattr(api, "lib", lambda: Recorder)
+    monkeypatch.setattr(api, "_stream", lambda: 0x1230)
+    ext.bind(C.cast(cb, VP).value, C.cast(cs, VP).value, torch.float32, torch.bfloat16)
+    yield run
+    ext.bind(*real, torch.float32, torch.bfloat16)
+
+
+f = torch.zeros(64)
+i = torch.zeros(64, dtype=torch.int32)
+ARRAYS = [[0, 8], (0, 8), [True, 8], np.array([0, 8], dtype=np.int32), [np.int64(0), 8], torch.tensor([0, 8]), [0.0, 8.9], [0, 2**31], [], ["a", 1], None, list(range(33))]
+
+
+@pytest.mark.parametrize("arr", range(len(ARRAYS)))
+@pytest.mark.parametrize("lam,l_min", [(1.2, 8), (np.float32(1.2), 8), (1, True), (1e300, 8), (float("inf"), 8), (1.2, 2**40), (1.2, 8.0)])
+def test_block_boundary_forms(calls, arr, lam, l_min):
+    for cold in (None, [0, 1] * 17, (True,) * 34):
+        for S in (None, f):
+            a, b = calls(lambda: api.block_boundary(f, f, ARRAYS[arr], [8] * 40, i, lam, l_min, 1, 0, 1, cold=cold, S_out=S))
+            assert a == b
+
+
+@pytest.mark.parametrize("arr", range(len(ARRAYS)))
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+def test_select_parallel_forms(calls, arr, dtype):
+    z = torch.zeros((8, 16), dtype=dtype)
+    for tau in (0.5, 1, np.float64(0.5), -1e39):
+        for apply, mask in ((True, 15), (0, np.int32(15)), (2, 2**33), ("x", 15)):
+            a, b = calls(lambda: api.select_parallel(z, f, f, i, i, ARRAYS[arr], [0, 8] * 17, [8, 8] * 17, mask, tau, 0.9, -16.0, 0, i, i, apply, margin_out=None))
+            assert a == b
+    for bad in (None, 3, "x"):
+        a, b = calls(lambda: api.select_parallel(bad, f, f, i, i, [0], [0], [8], 15, 0.5, 0.9, -16.0, 0, i, i))
+        assert a == b
+        a, b = calls(lambda: api.select_parallel(z, bad, f, i, i, [0], [0], [8], 15, 0.5, 0.9, -16.0, 0, i, i))
+        assert a == b
