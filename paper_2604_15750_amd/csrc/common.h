@@ -70,16 +70,44 @@ __device__ inline float to_f32(f16_t x) { return (float)x; }
 __device__ inline f16_t to_f16_sat(float x) { return (f16_t)__builtin_amdgcn_fmed3f(x, -65504.f, 65504.f); }
 __device__ inline f32x4 mfma_op(op8 a, op8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// ---- values over the lanes of a wavefront without trips through LDS (all 64 lanes together).  A butterfly (lanes 32, 16, 8, 4, 2, 1 apart):
+// permlane swaps across the rows of 16 lanes, then rotations within a row, which behind the step before them meet the butterfly's
+// values (they repeat every 8, 4 and 2 lanes), so sums are those of a chain of __shfl_xor.
+template <int CTRL>
+__device__ inline unsigned rotate(unsigned v) { return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false); }
+template <typename Op>
+__device__ inline unsigned row_butterfly(unsigned v, Op op) {  // over the 16 lanes of a row
+  v = op(v, rotate<0x128>(v));  // row_ror:8, 4, 2, 1
+  v = op(v, rotate<0x124>(v));
+  v = op(v, rotate<0x122>(v));
+  return op(v, rotate<0x121>(v));
 }
-__device__ inline float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+template <typename Op>
+__device__ inline unsigned butterfly(unsigned v, Op op) {
+  auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  v = op(x[0], x[1]);
+  x = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return row_butterfly(op(x[0], x[1]), op);
 }
+struct BitsAdd { __device__ unsigned operator()(unsigned a, unsigned b) const { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); } };
+struct BitsMax { __device__ unsigned operator()(unsigned a, unsigned b) const { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); } };
+__device__ inline float wave_sum(float v) { return __uint_as_float(butterfly(__float_as_uint(v), BitsAdd())); }
+__device__ inline float wave_max(float v) { return __uint_as_float(butterfly(__float_as_uint(v), BitsMax())); }
+__device__ inline float row_sum(float v) { return __uint_as_float(row_butterfly(__float_as_uint(v), BitsAdd())); }
+__device__ inline float row_max(float v) { return __uint_as_float(row_butterfly(__float_as_uint(v), BitsMax())); }
+// the value `ofs` lanes up (1, 2, 4, 8, 16 or 32; the same for all), in the lanes below ofs: what a reduction into lane 0 needs
+__device__ inline unsigned from_up(unsigned v, int ofs) {
+  switch (ofs) {
+    case 32: return __builtin_amdgcn_permlane32_swap(v, v, false, false)[1];
+    case 16: return __builtin_amdgcn_permlane16_swap(v, v, false, false)[1];  // (also in lanes 32 .. 47)
+    case 8: return rotate<0x108>(v);  // row_shl:8, 4, 2, 1
+    case 4: return rotate<0x104>(v);
+    case 2: return rotate<0x102>(v);
+    default: return rotate<0x101>(v);
+  }
+}
+__device__ inline float from_up(float v, int ofs) { return __uint_as_float(from_up(__float_as_uint(v), ofs)); }
+__device__ inline int from_up(int v, int ofs) { return (int)from_up((unsigned)v, ofs); }
 
 // ---- per-pass metadata, passed to kernels by value -------------------------------------------
 #define DLM_MAX_SEQS 32

@@ -248,9 +248,7 @@ __device__ inline void finish_sum(const GemmEpi& e, int m, int n, int N, f32x4 v
 template <int EPI>
 __device__ inline float finish_frag(const GemmEpi& e, int M, int N, int m, int nc, int g, f32x4 v, float rinv, const EpiAhead ahead = epi_none()) {
   if (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
-    f32x4 b;  // the partner group, columns + 8, sits 32 lanes up
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b[i] = __shfl_xor(v[i], 32, 64);
+    const f32x4 b = pair_halves(v, v).hi;  // the partner group, columns + 8, sits 32 lanes up
     if (g < 2 && m < M) {
       if (EPI == EPI_QKV) finish_qkv(e, m, nc, g, v * rinv, b * rinv, ahead);
       else finish_swiglu(e, m, nc, g, v * rinv, b * rinv);
@@ -258,10 +256,7 @@ __device__ inline float finish_frag(const GemmEpi& e, int M, int N, int m, int n
     return 0.f;
   }
   if (EPI == EPI_RESID) {
-    float ss = m < M ? finish_resid(e, m, nc + 4 * g, N, v, ahead) : 0.f;
-    ss += __shfl_xor(ss, 16, 64);
-    ss += __shfl_xor(ss, 32, 64);
-    return ss;
+    return sum_row4(m < M ? finish_resid(e, m, nc + 4 * g, N, v, ahead) : 0.f);
   }
   if (m < M) finish_sum(e, m, nc + 4 * g, N, v * rinv);
   return 0.f;

@@ -546,8 +546,8 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
-      state[i] = lite_merge(state[i], lite_shfl_xor(state[i], 16));
-      state[i] = lite_merge(state[i], lite_shfl_xor(state[i], 32));
+      state[i] = lite_merge(state[i], lite_from(state[i], 16));  // (of the lanes' groups 0 and 2, then of group 0)
+      state[i] = lite_merge(state[i], lite_from(state[i], 32));
       if (g == 0) s_state[wn * AT * 16 + (wm * WM + i) * 16 + ml] = state[i];
     }
     __syncthreads();

@@ -34,11 +34,8 @@ __device__ inline Part part_merge(const Part& a, const Part& b) {
   return r;
 }
 
-__device__ inline Part part_shfl_xor(const Part& p, int o) {
-  Part r;
-  r.m = __shfl_xor(p.m, o, 64); r.s = __shfl_xor(p.s, o, 64); r.t = __shfl_xor(p.t, o, 64); r.w = __shfl_xor(p.w, o, 64);
-  r.bv = __shfl_xor(p.bv, o, 64); r.bi = __shfl_xor(p.bi, o, 64); r.pm = __shfl_xor(p.pm, o, 64); r.ps = __shfl_xor(p.ps, o, 64);
-  return r;
+__device__ inline Part part_from(const Part& p, int ofs) {  // (from_up)
+  return Part{from_up(p.m, ofs), from_up(p.s, ofs), from_up(p.t, ofs), from_up(p.w, ofs), from_up(p.bv, ofs), from_up(p.bi, ofs), from_up(p.pm, ofs), from_up(p.ps, ofs)};
 }
 
 // The part of a row's online-softmax state that a pass without a previous-step distribution needs (stats_part.h has the whole):
@@ -58,8 +55,8 @@ __device__ __attribute__((always_inline)) inline LiteState lite_merge(const Lite
   r.bi = (b.m > a.m || (b.m == a.m && b.bi < a.bi)) ? b.bi : a.bi;
   return r;
 }
-__device__ __attribute__((always_inline)) inline LiteState lite_shfl_xor(const LiteState p, int o) {
-  return LiteState{__shfl_xor(p.m, o, 64), __shfl_xor(p.s, o, 64), __shfl_xor(p.t, o, 64), __shfl_xor(p.bi, o, 64)};
+__device__ __attribute__((always_inline)) inline LiteState lite_from(const LiteState p, int ofs) {  // (from_up)
+  return LiteState{from_up(p.m, ofs), from_up(p.s, ofs), from_up(p.t, ofs), from_up(p.bi, ofs)};
 }
 // state of four consecutive logits, token ids n .. n+3, token `skip` left out
 __device__ __attribute__((always_inline)) inline LiteState lite_of(f32x4 v, int n, int skip) {

@@ -30,29 +30,9 @@ struct Run {
 constexpr float RUN_MIN = -2.0e38f;  // start of the running maximum: (RUN_MIN - m) * log2(e) stays finite for real maxima m
 __device__ inline Run run_init() { return Run{RUN_MIN, 0x7fffffff, 0.f, 0.f, 0.f, RUN_MIN, 0.f}; }
 
-// A value over the 64 lanes, in every lane, by the butterfly of wave_sum (lanes 32, 16, 8, 4, 2, 1 apart, so the same sums) without its
-// six trips through LDS: permlane swaps across the rows of 16 lanes, then rotations within a row, which behind the step before them meet
-// the butterfly's values (they repeat every 8, 4 and 2 lanes).  A wavefront makes these trips at its end and at every new maximum, and
-// a chunk is short: 384 rows of 126464 bf16 logits from memory, without / with a previous row, 28.3 / 43.5 -> 24.7 / 40.2 us.
-template <int CTRL>
-__device__ inline unsigned rotate(unsigned v) { return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false); }
-template <typename Op>
-__device__ inline unsigned butterfly(unsigned v, Op op) {
-  auto x = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  v = op(x[0], x[1]);
-  x = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = op(x[0], x[1]);
-  v = op(v, rotate<0x128>(v));  // row_ror:8, 4, 2, 1
-  v = op(v, rotate<0x124>(v));
-  v = op(v, rotate<0x122>(v));
-  return op(v, rotate<0x121>(v));
-}
-__device__ inline float lanes_sum(float v) {
-  return __uint_as_float(butterfly(__float_as_uint(v), [](unsigned a, unsigned b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); }));
-}
-__device__ inline float lanes_max(float v) {
-  return __uint_as_float(butterfly(__float_as_uint(v), [](unsigned a, unsigned b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); }));
-}
+// (wave_sum and wave_max of common.h, and the same for the least token id: a wavefront makes these trips at its end and at every new
+// maximum, and a chunk is short: 384 rows of 126464 bf16 logits from memory, without / with a previous row, 28.3 / 43.5 us through LDS, 24.7 /
+// 40.2 now.)
 __device__ inline int lanes_min(int v) {
   return (int)butterfly((unsigned)v, [](unsigned a, unsigned b) { return (unsigned)min((int)a, (int)b); });
 }
@@ -62,13 +42,13 @@ __device__ inline int lanes_min(int v) {
 __device__ inline Part run_finish(const Run& r) {
   Part p;
   p.m = r.m;
-  p.s = lanes_sum(r.s);
-  p.t = lanes_sum(r.t2) * LN2;
-  p.w = lanes_sum(r.w);
+  p.s = wave_sum(r.s);
+  p.t = wave_sum(r.t2) * LN2;
+  p.w = wave_sum(r.w);
   p.bv = r.m;
   p.bi = r.bi;
   p.pm = r.pm > RUN_MIN ? r.pm : NEG_BIG;
-  p.ps = lanes_sum(r.ps);
+  p.ps = wave_sum(r.ps);
   return p;
 }
 
@@ -76,7 +56,7 @@ __device__ inline Part run_finish(const Run& r) {
 // reference.  Called by all 64 lanes together, from a wavefront-uniform branch.
 template <int N>
 __device__ inline void new_maximum(Run& p, const float (&z)[N], unsigned valid, float vm, int v0) {
-  const float wmax = lanes_max(vm);
+  const float wmax = wave_max(vm);
   int cand = 0x7fffffff;
 #pragma unroll
   for (int i = N - 1; i >= 0; --i)
@@ -90,7 +70,7 @@ __device__ inline void new_maximum(Run& p, const float (&z)[N], unsigned valid, 
 }
 template <int N>
 __device__ inline void new_prev_maximum(Run& p, float vm) {
-  const float wmax = lanes_max(vm);
+  const float wmax = wave_max(vm);
   p.ps *= __builtin_amdgcn_exp2f((p.pm - wmax) * LOG2E);
   p.pm = wmax;
 }
@@ -249,7 +229,7 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
     for (int i = 0; i < 8; ++i) r = part_merge(r, q[i]);
   }
 #pragma unroll
-  for (int ofs = 32; ofs > 0; ofs >>= 1) r = part_merge(r, part_shfl_xor(r, ofs));
+  for (int ofs = 32; ofs > 0; ofs >>= 1) r = part_merge(r, part_from(r, ofs));
   if (lane != 0) return;
   const int64_t prow = sr.prev_row ? sr.prev_row[row] : (sr.prev_base ? (int64_t)row * vocab : -1);
   const int64_t srow = sr.save_row ? sr.save_row[row] : -1;
