@@ -131,42 +131,77 @@ __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const
     constexpr int U = TPB > 256 ? 2 : 4, STRIDE = TPB * N, TRIP = U * STRIDE;
     const int base = lo + threadIdx.x * N;
     const int nfull = (hi - lo) / TRIP;
-    for (int t = 0; t * TRIP < hi - lo; ++t) {
-      const int t0 = lo + t * TRIP;  // first element of the trip (uniform)
-      const bool plain = t < nfull && !(mask_id >= t0 && mask_id < t0 + TRIP);
+    auto fetch = [&](V (&zv)[U], V (&pv)[U], int t) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        zv[u] = *(const V*)(z_row + base + t * TRIP + u * STRIDE);
+        if (KL) pv[u] = *(const V*)(p_row + base + t * TRIP + u * STRIDE);
+      }
+    };
+    auto take = [&](const V (&zv)[U], const V (&pv)[U], int t) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int v = base + t * TRIP + u * STRIDE;
+        float z[N], zp[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) { z[i] = to_f32(zv[u][i]); zp[i] = KL ? to_f32(pv[u][i]) : 0.f; }
+        if (s_row) *(V*)(s_row + v) = zv[u];
+        absorb<N, KL, PREV_SUMS, true>(run, z, zp, v, 0xffffffffu);
+      }
+    };
+    const int mask_trip = mask_id >= lo ? (mask_id - lo) / TRIP : -1;  // (a trip of another chunk where it is past the end)
+    for (int t = 0; t * TRIP < hi - lo;) {
+      const int end = mask_trip >= t && mask_trip < nfull ? mask_trip : nfull;  // whole trips without the mask token
       V zv[U], pv[U];
-      if (plain) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          zv[u] = *(const V*)(z_row + base + t * TRIP + u * STRIDE);
-          if (KL) pv[u] = *(const V*)(p_row + base + t * TRIP + u * STRIDE);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int v = base + t * TRIP + u * STRIDE;
-          float z[N], zp[N];
-#pragma unroll
-          for (int i = 0; i < N; ++i) { z[i] = to_f32(zv[u][i]); zp[i] = KL ? to_f32(pv[u][i]) : 0.f; }
-          if (s_row) *(V*)(s_row + v) = zv[u];
-          absorb<N, KL, PREV_SUMS, true>(run, z, zp, v, 0xffffffffu);
+      if constexpr (TPB > 256) {
+        if (t < end) {
+          V zw[U], pw[U];
+          fetch(zv, pv, t);
+          for (; end - t > 2; t += 2) {
+            fetch(zw, pw, t + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            take(zv, pv, t);
+            fetch(zv, pv, t + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            take(zw, pw, t + 1);
+          }
+          if (end - t == 2) {
+            fetch(zw, pw, t + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            take(zv, pv, t);
+            take(zw, pw, t + 1);
+          } else {
+            take(zv, pv, t);
+          }
+          t = end;
+          continue;
         }
       } else {
-#pragma unroll 1
-        for (int u = 0; u < U; ++u) {
-          const int v = base + t * TRIP + u * STRIDE;
-          if (t0 + u * STRIDE >= hi) break;  // uniform
-          const bool in = v < hi;            // vocab % N == 0 and lo % N == 0: a vector is inside or outside as a whole
-          float z[N], zp[N];
-          V a, b;
-          if (in) { a = *(const V*)(z_row + v); if (KL) b = *(const V*)(p_row + v); }
-#pragma unroll
-          for (int i = 0; i < N; ++i) { z[i] = in ? to_f32(a[i]) : 0.f; zp[i] = (KL && in) ? to_f32(b[i]) : 0.f; }
-          if (s_row && in) *(V*)(s_row + v) = a;
-          unsigned valid = in ? (1u << N) - 1u : 0u;
-          if (mask_id >= v && mask_id < v + N) valid &= ~(1u << (mask_id - v));  // the mask token takes no part
-          absorb<N, KL, PREV_SUMS, false>(run, z, zp, v, valid);
+        if (t < end) {
+          for (; t < end; ++t) {
+            fetch(zv, pv, t);
+            take(zv, pv, t);
+          }
+          continue;
         }
       }
+      const int t0 = lo + t * TRIP;  // first element of the trip (uniform)
+#pragma unroll 1
+      for (int u = 0; u < U; ++u) {
+        const int v = base + t * TRIP + u * STRIDE;
+        if (t0 + u * STRIDE >= hi) break;  // uniform
+        const bool in = v < hi;            // vocab % N == 0 and lo % N == 0: a vector is inside or outside as a whole
+        float z[N], zp[N];
+        V a, b;
+        if (in) { a = *(const V*)(z_row + v); if (KL) b = *(const V*)(p_row + v); }
+#pragma unroll
+        for (int i = 0; i < N; ++i) { z[i] = in ? to_f32(a[i]) : 0.f; zp[i] = (KL && in) ? to_f32(b[i]) : 0.f; }
+        if (s_row && in) *(V*)(s_row + v) = a;
+        unsigned valid = in ? (1u << N) - 1u : 0u;
+        if (mask_id >= v && mask_id < v + N) valid &= ~(1u << (mask_id - v));  // the mask token takes no part
+        absorb<N, KL, PREV_SUMS, false>(run, z, zp, v, valid);
+      }
+      ++t;
     }
   } else {
     for (int v0 = lo; v0 < hi; v0 += TPB) {  // uniform bounds; a lane past the end or on the mask token feeds an invalid element
@@ -220,6 +255,9 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(1, TPB == 2
 __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __restrict__ parts, int rows, int nchunks, int vocab, StatsRows sr,
                                                                StatsOut o) {
   const int row = blockIdx.x, lane = threadIdx.x;
+  // (what the row's results need besides, read beside its states: two trips and a division that would come after the merge)
+  const int64_t prow = sr.prev_row ? sr.prev_row[row] : (sr.prev_base ? (int64_t)row * vocab : -1);
+  const int64_t srow = sr.save_row ? sr.save_row[row] : -1;
   Part r = lane < nchunks ? parts[(size_t)row * nchunks + lane] : part_init();
   for (int c0 = 64; c0 < nchunks; c0 += 512) {  // more states than lanes (the LM-head epilogue's): eight loads in flight, added in order
     Part q[8];
@@ -228,14 +266,13 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
 #pragma unroll
     for (int i = 0; i < 8; ++i) r = part_merge(r, q[i]);
   }
+  const float prev_lse = prow >= 0 && sr.prev_lse ? sr.prev_lse[prow / vocab] : 0.f;
+  float* save_slot = srow >= 0 && sr.save_lse ? sr.save_lse + srow / vocab : nullptr;
 #pragma unroll
   for (int ofs = 32; ofs > 0; ofs >>= 1) r = part_merge(r, part_from(r, ofs));
   if (lane != 0) return;
-  const int64_t prow = sr.prev_row ? sr.prev_row[row] : (sr.prev_base ? (int64_t)row * vocab : -1);
-  const int64_t srow = sr.save_row ? sr.save_row[row] : -1;
-  float pl = 0.f;
-  if (prow >= 0) pl = sr.prev_lse ? sr.prev_lse[prow / vocab] : r.pm + __logf(r.ps);
-  finalize(r, row, prow >= 0, pl, o, srow >= 0 && sr.save_lse ? sr.save_lse + srow / vocab : nullptr);
+  const float pl = prow < 0 ? 0.f : sr.prev_lse ? prev_lse : r.pm + __logf(r.ps);
+  finalize(r, row, prow >= 0, pl, o, save_slot);
 }
 
 constexpr int MAX_CHUNKS = 32;
