@@ -31,7 +31,7 @@
 // workgroups when each streams a W of its own (one row block) and when four or more row blocks share it (operands of random
 // values; fitted to 3500 launches of the layer and head matrices of an 8B and a 7B grouped-query model at 24 .. 2822 rows).
 #define MACRO_TILES(X)                                                                                            \
-  X(2, 2, 1, 8, 2, 683, 399) X(1, 5, 2, 4, 2, 822, 487)                                                           \
+  X(2, 2, 1, 8, 2, 683, 399) X(1, 5, 2, 4, 2, 822, 487) X(2, 5, 2, 4, 2, 823, 1000) X(4, 5, 2, 4, 1, 834, 1000) \
   X(2, 1, 2, 4, 2, 174, 130) X(1, 3, 4, 2, 2, 262, 195) X(1, 5, 4, 2, 2, 429, 236) X(2, 4, 2, 4, 2, 696, 330)     \
   X(3, 2, 2, 4, 2, 348, 244) X(3, 4, 2, 4, 2, 706, 395)                                                           \
   X(2, 2, 4, 2, 2, 252, 193) X(2, 3, 4, 2, 2, 301, 232) X(4, 2, 2, 4, 2, 361, 278)                                \
@@ -39,8 +39,13 @@
   X(5, 2, 2, 4, 2, 432, 338) X(5, 3, 2, 4, 2, 571, 443)                                                           \
   X(3, 3, 4, 2, 2, 389, 322) X(3, 5, 4, 2, 2, 532, 433) X(3, 6, 4, 2, 2, 615, 513)                                \
   X(4, 6, 4, 2, 1, 746, 695) X(4, 8, 4, 2, 1, 922, 831)
-// rows:  32 (x 256, 320 columns), 64 (x 64, 96, 160, 256), 96 (x 128, 256), 128 (x 64, 96, 128, 160, 192, 256), 160 (x 128, 192),
+// rows:  32 (x 256, 320 columns), 64 (x 64, 96, 160, 256, 320), 96 (x 128, 256), 128 (x 64, 96, 128, 160, 192, 256, 320), 160 (x 128, 192),
 //        192 (x 96, 160, 192), 256 (x 192, 256)
+
+// 64 and 128 x 320, for the plain product only: a vocabulary whose 160-column blocks are a little under four rounds and whose 256-column
+// ones a little over two takes two of these (head of a 7B model, 152064 columns, in the pass: 64 rows 200 -> 187 us, 96 rows 229 -> 189).  Never
+// faster where row blocks share W (the second figure keeps them out).
+constexpr bool macro_product_only(int wm, int wn, int cw) { return wm > 1 && wn * cw == 20; }
 
 struct MacroTile {
   int wm, wn, rw, cw, kb;
@@ -602,7 +607,7 @@ template <int EPI>
 void launch_macro_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const MacroPlan& p, const GemmEpi& e, hipStream_t st) {
   int i = 0;
 #define GO(WM, WN, RW, CW, KB, NS1, NS4)                                                                                       \
-  if constexpr (EPI != EPI_STATS || 16 * WM * RW <= GEMM_STATS_MAX_ROWS) {                                                     \
+  if constexpr ((EPI != EPI_STATS || 16 * WM * RW <= GEMM_STATS_MAX_ROWS) && !(macro_product_only(WM, WN, CW) && EPI != EPI_STATS && EPI != EPI_SUM)) {                                                     \
     if constexpr (EPI != EPI_STATS && macro_can_keep_order(WM, WN, KB)) {                                                      \
       if (p.tile == i && (p.fold || p.ssq_parts > 1)) return launch_tile<WM, WN, RW, CW, KB, EPI, true, false>(xt, wt, M, N, K, p, e, st); \
     }                                                                                                                          \

@@ -63,7 +63,7 @@ MACRO_TILE_SHAPES = [
     ((97, 24768, 416), (128, 128, 1)), ((68, 33088, 416), (128, 160, 1)), ((17, 40992, 416), (128, 192, 1)), ((199, 24672, 416), (128, 256, 1)),
     ((129, 24928, 416), (160, 128, 1)), ((291, 16448, 416), (160, 192, 1)), ((133, 16448, 416), (192, 96, 1)), ((164, 24896, 416), (192, 160, 1)),
     ((161, 41024, 416), (192, 192, 1)), ((387, 16640, 416), (256, 192, 1)), ((257, 24608, 416), (256, 256, 1)),
-    ((300, 160, 4128), (64, 64, 3)), ((264, 96, 4128), (64, 64, 4)), ((290, 4064, 8224), (96, 128, 2))]
+    ((97, 66400, 416), (128, 320, 1)), ((300, 160, 4128), (64, 64, 3)), ((264, 96, 4128), (64, 64, 4)), ((290, 4064, 8224), (96, 128, 2))]
 # ... and the mid kernel's: (rows, columns of a group, split); both sides of every row count at which choose_kernel leaves it
 MID_SHAPES = [
     ((17, 16480, 416), (32, 96, 1)), ((17, 24768, 416), (32, 128, 1)), ((64, 24608, 512), (64, 128, 1)), ((48, 24544, 512), (48, 96, 1)),

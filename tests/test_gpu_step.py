@@ -576,7 +576,8 @@ def test_statistics_from_the_lm_head_epilogue(device, L):
 
 
 # (vocabulary, rows, tile): every tile the LM head's statistics epilogue has, with a ragged last column block where the tile allows one
-HEAD_TILES = [(64, 1, (64, 64)), (16416, 37, (64, 96)), (24704, 17, (64, 160)), (41696, 24, (32, 256)), (41696, 33, (64, 256)), (67552, 8, (32, 320))]
+HEAD_TILES = [(64, 1, (64, 64)), (16416, 37, (64, 96)), (24704, 17, (64, 160)), (41696, 24, (32, 256)), (41696, 33, (64, 256)), (67552, 8, (32, 320)),
+              (67552, 45, (64, 320))]
 
 
 @pytest.mark.parametrize("V,L,tile", HEAD_TILES)
