@@ -18,8 +18,9 @@ namespace {
 // grid.x = N / (16 R) workgroups of NWV wavefronts; wavefront w multiplies k-tiles [w*per, (w+1)*per) of the
 // workgroup's R column tiles against all MT row tiles, D k-tiles per batch, two batches of registers.
 // STEPS: wt is the step-major copy of W.
-template <int MT, int R, int NWV, int D, int EPI, bool STEPS = false>
-__global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N,
+// TWO: registers for two workgroups on a compute unit.
+template <int MT, int R, int NWV, int D, int EPI, bool STEPS = false, bool TWO = false>
+__global__ __launch_bounds__(NWV * 64, TWO ? NWV / 2 : 1) void gemm_skinny_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N,
                                                                int K, GemmEpi e) {
   __shared__ f32x4 red[NWV][R * MT][64];
   __shared__ float s_rinv[MT * 16];
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __rest
   }
   // 1/rms of the input rows, needed only by the epilogue: fetched behind the first batches; so is what the epilogue of the tile this
   // wavefront finishes first reads from memory (tile rj = wave of the R * MT)
-  typedef RinvBatch<NWV * 64, MT * 16, 16> Rinv;
+  typedef RinvBatch<NWV * 64, MT * 16, (MT > 1 && EPI == EPI_QKV ? 4 : 16)> Rinv;  // (down's chunks are few from 17 rows on)
   const int rows = min(M, MT * 16);
   Rinv rinv;
   if (EPI != EPI_RESID) rinv.fetch_always(e.rs, rows, xt);
@@ -137,9 +138,19 @@ __global__ __launch_bounds__(NWV * 64) void gemm_skinny_kernel(const op8* __rest
 // of column tiles (wide matrices) come here with one row tile only: from 17 rows on the mid or the macro kernel has them.
 template <int MT, int EPI>
 void launch_skinny(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, const GemmEpi& e, hipStream_t st) {
-  if (pr == 1 && e.w_steps) DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 ? 2 : 4), EPI, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
-  else if (pr == 1) DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT <= 2 ? 8 : 4), EPI>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
-  else if constexpr (MT == 1) {
+  if (pr == 1 && e.w_steps) {
+    DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 ? 2 : 4), EPI, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
+  } else if (pr == 1) {
+    // More column tiles than compute units: two workgroups a unit, with batches that leave them the registers, instead of a second round of few
+    // (QKV of a 7B model, 288 tiles: 24 rows 16.9 -> 13.7 us, 32 rows 18.7 -> 15.7, 48 rows 22.4 -> 19.2, 64 rows 26.3 -> 22.4).
+    if constexpr (MT > 1) {
+      if (N / 16 > 256) {
+        DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 || (MT == 3 && EPI == EPI_QKV) ? 2 : 1), EPI, false, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
+        return;
+      }
+    }
+    DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT <= 2 ? 8 : 4), EPI>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
+  } else if constexpr (MT == 1) {
     if (e.w_steps) DLM_LAUNCH((gemm_skinny_kernel<MT, 2, 4, 4, EPI, true>), N / 32, 256, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
     else DLM_LAUNCH((gemm_skinny_kernel<MT, 2, 4, 4, EPI>), N / 32, 256, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
   }

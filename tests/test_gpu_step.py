@@ -576,6 +576,16 @@ def test_statistics_from_the_lm_head_epilogue(device, L):
 
 
 # (vocabulary, rows, tile): every tile the LM head's statistics epilogue has, with a ragged last column block where the tile allows one
+# A narrow matrix of more column tiles than compute units (QKV: 384 of them) shares its units between two of the skinny kernel's
+# workgroups: every number of row tiles, ragged, and rows' scales of one chunk and of more than the kernel keeps (down of 2304 columns)
+@pytest.mark.parametrize("M", [17, 33, 50, 64])
+@pytest.mark.parametrize("dims", [(1, 256, 32, 8, 128, 64, 256), (2, 2304, 32, 8, 128, 64, 256)])
+def test_skinny_two_workgroups_a_unit(device, M, dims):
+    p = api.plan_gemm(M, 6144, dims[1], "qkv")
+    assert (p["kernel"], p["workgroups"]) == ("skinny", 384)
+    _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 31 + M)
+
+
 HEAD_TILES = [(64, 1, (64, 64)), (16416, 37, (64, 96)), (24704, 17, (64, 160)), (41696, 24, (32, 256)), (41696, 33, (64, 256)), (67552, 8, (32, 320)),
               (67552, 45, (64, 320))]
 
