@@ -64,7 +64,7 @@ __device__ inline float sum4(float v) {
 // bounds a narrow pass is what one compute unit can pull through its L2 (about 50 GB/s), and K and V of a head are its whole
 // traffic: four workgroups per head move 5/8 of it each, with nothing to merge.
 template <int HD, int NWV, int DS, int T>
-__device__ inline void attention_tiles(const f16_t* __restrict__ q, const f16_t* __restrict__ kregion, const f16_t* __restrict__ vregion,
+__device__ __attribute__((always_inline)) inline void attention_tiles(const f16_t* __restrict__ q, const f16_t* __restrict__ kregion, const f16_t* __restrict__ vregion,
                                        int row0, int row_end, int n_keys, int head, int n_q, op_t* __restrict__ out_tiles, bf16_t* __restrict__ out_rows,
                                        AttnLds<HD, NWV, DS, T>& L, int dpart) {
   constexpr int KS = HD / 32, DT = HD / 16 / DS, HDP = HD / DS;
@@ -101,18 +101,19 @@ __device__ inline void attention_tiles(const f16_t* __restrict__ q, const f16_t*
   // them).  Not for one query tile with eight wavefronts, which are few blocks each: there the copies it makes of what is in
   // flight cost more (8 rows x 392 keys, four shares, 6.9 us against 6.5; 128 rows x 228 keys, one share, by events 9.4 against 8.3).
   constexpr bool PINNED = T > 1 || (DS == 1 && NWV == 4);
-  auto load_k = [&](int buf, int blk) {
+  // (inlined by force: where two kernels of one shape call them the compiler leaves them as functions, and what they share lies in scratch)
+  auto load_k = [&](int buf, int blk) __attribute__((always_inline)) {
     const bool there = blk < nblk;
     const f16x8* from = there || !PINNED ? kt : (const f16x8*)kregion;
     const int b = there || !PINNED ? blk : blk - NWV;
 #pragma unroll
     for (int t = 0; t < 2 * KS; ++t) kf[buf][t] = there || PINNED ? from[((size_t)b * 2 * KS + t) * 64] : zero8;
   };
-  auto load_v = [&](int blk) {
+  auto load_v = [&](int blk) __attribute__((always_inline)) {
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) vf[dt] = vt[((size_t)blk * (DT * DS) + dpart * DT + dt) * 64];
   };
-  auto step = [&](int buf, int blk) {
+  auto step = [&](int buf, int blk) __attribute__((always_inline)) {
     load_v(blk);
     load_k(buf ^ 1, blk + NWV);
     if (PINNED) __builtin_amdgcn_sched_barrier(0);  // (left alone the scheduler sinks the loads behind the products, and each step waits for its own)
