@@ -212,8 +212,8 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
     if (splits > 1 && tid == 0) my_ticket = __hip_atomic_fetch_add(e.counters + 2 * tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 
-  // 1/rms of the workgroup's input rows, needed only by the epilogue: fetched ahead of the pipeline's loads, in one trip where a row
-  // has up to 64 chunks (wide passes).  Where the registers hold what was fetched, it stays there until the loop is over (touching
+  // 1/rms of the workgroup's input rows, needed only by the epilogue: fetched behind the first stage's copies and ahead of the others, in one
+  // trip where a row has up to 64 chunks (wide passes).  Where the registers hold what was fetched, it stays there until the loop is over (touching
   // it while copies to LDS are in flight would make the compiler wait for all of them); published to the other wavefronts by
   // the barrier of the epilogue, or by the loop's.
   const int rows = max(0, min(M, m_lo + AT * 16) - m_lo);

@@ -135,7 +135,8 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
     }
   };
   // step S of a trip: X of the step XD - 1 ahead first, then W of the step WD - 1 ahead, so that the wait for this step's operands
-  // (the oldest loads) leaves XD - 1 steps of both in flight; the scheduling barriers keep the compiler from sinking the loads down to their uses (which it does under register pressure, undoing the prefetch)
+  // (the oldest loads) leaves XD - 1 steps of both in flight; the scheduling barriers keep the compiler from sinking the loads down to
+  // their uses (which it does under register pressure, undoing the prefetch)
   auto step = [&](auto Sc, int st) __attribute__((always_inline)) {
     constexpr int S = decltype(Sc)::value;
     load_x((S + XD - 1) % XD, st + XD - 1);
