@@ -112,8 +112,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-def _ints(v):
-    return None if v is None else (C.c_int32 * len(v))(*[int(x) for x in v])
+def _enough(v, n):
+    """The library reads n entries of a host array, whatever its length: one that is shorter is refused here."""
+    if v is not None and len(v) < n:
+        raise ValueError(f"a host array of {len(v)} entries where the call reads {n}")
+    return v
+
+
+def _ints(v, n=0):
+    return None if v is None else (C.c_int32 * len(_enough(v, n)))(*[int(x) for x in v])
 
 
 # The two decisions are bound by what their calls cost the host: plain arguments go through a small extension (csrc/decisions_py.c),
@@ -272,8 +279,10 @@ class StepOutputs:
 def dlm_step(state, tokens, out, row_offsets, span_start, commit_len, tok_start, slot=None, kl_first=None, kl_count=None,
              save_first=None, save_count=None, suffix_len=None):
     """tokens: device int32 tensor; out: StepOutputs; the rest: host int lists (see include/dlm.h)."""
-    keep = [_ints(v) for v in (slot, row_offsets, span_start, commit_len, kl_first, kl_count, save_first, save_count, tok_start, suffix_len)]
-    d = dlm_step_desc(len(span_start), *keep, tokens.data_ptr(), out.logits.data_ptr(), out.max_logit.data_ptr(), out.lse.data_ptr(),
+    n = len(span_start)
+    keep = [_ints(slot, n), _ints(row_offsets, n + 1)]
+    keep += [_ints(v, n) for v in (span_start, commit_len, kl_first, kl_count, save_first, save_count, tok_start, suffix_len)]
+    d = dlm_step_desc(n, *keep, tokens.data_ptr(), out.logits.data_ptr(), out.max_logit.data_ptr(), out.lse.data_ptr(),
                       out.entropy.data_ptr(), out.kl.data_ptr(), out.conf.data_ptr(), out.argmax.data_ptr())
     _check(lib().dlm_step(state.handle, C.byref(d), _stream()))
 
@@ -287,7 +296,8 @@ def block_boundary(I, H, win_start, win_len, L_out, lam, l_min, smooth_radius=1,
             if rc < 0:
                 _check(rc)
             return
-    _check(lib().block_boundary(_ptr(I), _ptr(H), _packed(win_start), _packed(win_len), _packed(cold), len(win_start),
+    n = len(win_start)
+    _check(lib().block_boundary(_ptr(I), _ptr(H), _packed(win_start), _packed(_enough(win_len, n)), _packed(_enough(cold, n)), n,
                                 _params(_pack_boundary, dlm_boundary_params, (lam, l_min, smooth_radius, norm_mode, rule)), _ptr(L_out),
                                 _ptr(S_out), _ptr(margin_out), _stream()))
 
@@ -302,8 +312,9 @@ def select_parallel(logits, lse, conf, argmax, tokens, row_start, tok_start, blo
             if rc < 0:
                 _check(rc)
             return
+    n = len(row_start)
     _check(lib().select_parallel(_ptr(logits), logits.size(-1), dtype_code(logits), _ptr(lse), _ptr(conf), _ptr(argmax), _ptr(tokens),
-                                 _packed(row_start), _packed(tok_start), _packed(block_len), len(row_start), mask_id,
+                                 _packed(row_start), _packed(_enough(tok_start, n)), _packed(_enough(block_len, n)), n, mask_id,
                                  _params(_pack_select, dlm_select_params, (tau_low, tau_high, gamma, mode)), int(apply_tokens),
                                  _ptr(selected_out), _ptr(n_selected_out), _ptr(margin_out), _stream()))
 

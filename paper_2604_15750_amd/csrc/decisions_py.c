@@ -1,7 +1,8 @@
 // Python calls of the two decisions (block_boundary, select_parallel of dlm.h) without ctypes.  Their kernels take a few microseconds,
 // so a call is bound by what marshalling its arguments costs the host: 2.7 and 4.8 us through ctypes with packed arrays, 1.2 and 2.1 here.
 // Only plain arguments are taken: lists or tuples of ints that fit 32 bits, each at least as long as the first, numbers, tensors.
-// Anything else returns None before anything is launched, and the caller goes the ctypes way, which knows every form.
+// Anything else returns None before anything is launched, and the caller goes the ctypes way, which takes every other form that has
+// enough entries and refuses the rest.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stdint.h>

@@ -85,3 +85,40 @@ def test_select_parallel_forms(calls, arr, dtype):
         assert a == b
         a, b = calls(lambda: api.select_parallel(z, bad, f, i, i, [0], [0], [8], 15, 0.5, 0.9, -16.0, 0, i, i))
         assert a == b
+
+
+@pytest.mark.parametrize("form", [list, tuple, lambda v: np.array(v, dtype=np.int32)])
+def test_short_host_arrays_are_refused(calls, form):
+    """The library reads an entry per sequence (of dlm_step's row_offsets one more): no call with fewer reaches it."""
+    full, short = form([0, 8]), form([8])
+    for ws, wl, cold in ((full, short, None), (full, full, short), (full, form([]), None)):
+        assert calls(lambda: api.block_boundary(f, f, ws, wl, i, 1.2, 8, cold=cold)) == [ValueError, ValueError]
+    for rs, ts, bl in ((full, short, full), (full, full, short), (full, form([]), full)):
+        assert calls(lambda: api.select_parallel(torch.zeros(8, 16), f, f, i, i, rs, ts, bl, 15, 0.5, 0.9, -16.0, 0, i, i)) == [ValueError, ValueError]
+
+
+STEP = dict(row_offsets=[0, 1, 2], commit_len=[0, 0], tok_start=[0, 4], slot=[0, 1], kl_first=[0, 0], kl_count=[0, 0], save_first=[0, 0], save_count=[0, 0],
+            suffix_len=[0, 0])
+
+
+@pytest.mark.parametrize("short", [None, *STEP])
+def test_short_host_arrays_of_a_step_are_refused(monkeypatch, short):
+    seen = []
+
+    class Recorder:
+        dlm_step = staticmethod(lambda *a: seen.append(a) or 0)
+
+    class Buffers:
+        handle = None
+        logits = max_logit = lse = entropy = kl = conf = argmax = f
+
+    monkeypatch.setattr(api, "lib", lambda: Recorder)
+    monkeypatch.setattr(api, "_stream", lambda: None)
+    args = {k: v[:-1] if k == short else v for k, v in STEP.items()}
+    step = lambda: api.dlm_step(Buffers, i, Buffers, span_start=[0, 0], **args)  # noqa: E731
+    if short is None:
+        step()
+    else:
+        with pytest.raises(ValueError, match="entries"):
+            step()
+    assert len(seen) == (short is None)
