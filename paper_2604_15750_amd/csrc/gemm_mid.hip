@@ -194,10 +194,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
     rest(rest, std::integral_constant<int, 0>{}, st);
   }
 
-  if (EPI != EPI_RESID) {
-    if (Rinv::fits(e.rs)) rinv.publish(e.rs, rows, s_rinv);
-    else block_rinv<TPB>(e.rs, 0, rows, s_rinv);
-  }
+  if (EPI != EPI_RESID) rinv.publish_all(e.rs, rows, s_rinv);
   // ---- the four partial accumulators -> one finished (or, with a K split, one partial) value per output fragment
   const int g = lane >> 4, ml = lane & 15;
   f32x4* red = (f32x4*)lds;  // [NWV][FR][64]

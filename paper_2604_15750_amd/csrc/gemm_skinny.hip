@@ -109,10 +109,7 @@ __global__ __launch_bounds__(NWV * 64, TWO ? NWV / 2 : 1) void gemm_skinny_kerne
     }
   }
 
-  if (EPI != EPI_RESID) {
-    if (Rinv::fits(e.rs)) rinv.publish(e.rs, rows, s_rinv);
-    else block_rinv<NWV * 64>(e.rs, 0, rows, s_rinv);
-  }
+  if (EPI != EPI_RESID) rinv.publish_all(e.rs, rows, s_rinv);
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll

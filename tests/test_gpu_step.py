@@ -527,6 +527,21 @@ def test_gate_up_of_few_rows(device, M, d, ffn):
     _one_pass_matches(cfg, M, device, 60 + M)
 
 
+# Rows' sums of squares in more chunks than a kernel fetches ahead (256, or 64 where the consumer is QKV of 17 rows or more): the residual
+# product leaves one per 16 columns (skinny) or 64 (mid).  Consumers: gate/up of the mid and of the skinny kernel, QKV of the second layer
+# in both; at d_model 4352 the skinny residual products also run two workgroups a compute unit (272 column tiles)
+@pytest.mark.parametrize("dims,M,resid,gate_up,qkv", [
+    ((2, 4352, 34, 2, 128, 6144, 256), 17, "skinny", "mid", "skinny"), ((2, 4352, 34, 2, 128, 6144, 256), 33, "skinny", "mid", "skinny"),
+    ((1, 4352, 34, 2, 128, 6144, 256), 64, "skinny", "mid", "skinny"), ((1, 6400, 2, 1, 128, 4224, 256), 8, "skinny", "skinny", "skinny"),
+    ((1, 6400, 2, 1, 128, 4224, 256), 20, "skinny", "mid", "skinny"), ((2, 4352, 64, 2, 128, 8192, 256), 37, "mid", "mid", "mid")])
+def test_more_chunks_than_are_fetched_ahead(device, dims, M, resid, gate_up, qkv):
+    _, d, n_q, n_kv, hd, ffn, _ = dims
+    o, down = (api.plan_gemm(M, d, k, "resid") for k in (n_q * hd, ffn))
+    assert o["kernel"] == down["kernel"] == resid and down["workgroups"] // down["splits"] > (256 if resid == "skinny" else 64)
+    assert api.plan_gemm(M, 2 * ffn, d, "swiglu")["kernel"] == gate_up and api.plan_gemm(M, (n_q + 2 * n_kv) * hd, d, "qkv")["kernel"] == qkv
+    _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 41 + M)
+
+
 @pytest.mark.parametrize("dims,M,N,K,epi,expect", [
     # K of the down projection, and of QKV, in two parts kept by one workgroup
     ((1, 512, 4, 2, 128, 2048, 256), 497, 512, 2048, "resid", dict(splits=1, k_parts=2)),
