@@ -120,7 +120,12 @@ def _enough(v, n):
 
 
 def _ints(v, n=0):
-    return None if v is None else (C.c_int32 * len(_enough(v, n)))(*[int(x) for x in v])
+    if v is None:
+        return None
+    k = len(v)
+    if k < n:
+        _enough(v, n)
+    return (C.c_int32 * k)(*map(int, v))
 
 
 # The two decisions are bound by what their calls cost the host: plain arguments go through a small extension (csrc/decisions_py.c),
