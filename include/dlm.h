@@ -75,7 +75,9 @@ typedef struct dlm_state dlm_state;
  * layout of its own for them (what all workgroups read at the same step adjacent in memory): the
  * model then takes up to twice its layer weights (30 GB for an 8B model).  A copy that does not fit
  * is left out; the environment variable DLM_W_STEPS=0, read by this call, leaves them all out
- * (results are bit-identical either way: the same products are added in the same order).
+ * (results are bit-identical either way: the same products are added in the same order).  A bf16 model
+ * whose matrices take up to 320 MiB has them read through the memory-side cache, which keeps them from pass to
+ * pass, a larger one past it; DLM_W_CACHED=1 or =0, read by this call, says which (bit-identical as well).
  * Errors: DLM_EINVAL (null pointer, bad dtype), DLM_ESHAPE (unsupported dimensions), DLM_ENOMEM. */
 int dlm_model_create(const dlm_config* cfg, const dlm_weights* w, void* stream, dlm_model** out);
 void dlm_model_destroy(dlm_model* m);

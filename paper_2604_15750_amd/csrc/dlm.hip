@@ -86,6 +86,7 @@ struct dlm_model {
   // kernel has no such layout for the shape): 0.44 GB per layer of an 8B model, 14 GB of 288 in all
   std::vector<DevBuf> w_steps[4];  // QKV, O, gate/up, down
   int steps_ct[4] = {0, 0, 0, 0};
+  bool w_cached = false;  // the matrices stay in the memory-side cache from pass to pass (WEIGHTS_CACHED_BYTES)
 };
 
 thread_local LaunchStamp g_launch_stamp = {nullptr, nullptr};
@@ -199,6 +200,9 @@ extern "C" int dlm_model_create(const dlm_config* cfg, const dlm_weights* w, voi
   const int qkv = (cfg->n_q_heads + 2 * cfg->n_kv_heads) * cfg->head_dim, qd = cfg->n_q_heads * cfg->head_dim;
   m->wqkv = std::vector<DevBuf>(L); m->wo = std::vector<DevBuf>(L); m->w_gate_up = std::vector<DevBuf>(L);
   m->w_down = std::vector<DevBuf>(L); m->norm1 = std::vector<DevBuf>(L); m->norm2 = std::vector<DevBuf>(L);
+  const size_t layer = (size_t)qkv * d + (size_t)d * qd + 3 * (size_t)d * cfg->d_ffn;
+  m->w_cached = (layer * L + (size_t)cfg->vocab * d) * sizeof(op_t) <= WEIGHTS_CACHED_BYTES;
+  if (const char* env = getenv("DLM_W_CACHED")) m->w_cached = atoi(env) != 0;
   int rc = DLM_OK;
   auto step = [&](int r) { if (rc == DLM_OK) rc = r; return rc == DLM_OK; };
   if (dt == DLM_BF16) step(copy_plain<bf16_t>(m->embed, w->embed, (size_t)cfg->vocab * d, st));
@@ -461,6 +465,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   memset(&base, 0, sizeof base);
   base.part = (float*)s->part.p;
   base.counters = (int*)s->counters.p;
+  base.w_cached = m->w_cached;
   // every layer GEMM of this pass must fit the partial-tile workspace the state was created with
   {
     const int shapes[4][3] = {{qd + 2 * nkv * hd, dm, EPI_QKV}, {dm, qd, EPI_RESID}, {2 * ffn, dm, EPI_SWIGLU}, {dm, ffn, EPI_RESID}};

@@ -9,6 +9,13 @@
 __device__ inline bf16x4 to_bf16x4(f32x4 v) { return bf16x4{(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]}; }
 __device__ inline f16x4 to_f16x4_sat(f32x4 v) { return f16x4{to_f16_sat(v[0]), to_f16_sat(v[1]), to_f16_sat(v[2]), to_f16_sat(v[3])}; }
 
+// a fragment's 16 bytes of this lane; NT: past the memory-side cache
+template <bool NT>
+__device__ __attribute__((always_inline)) inline op8 load_weight(const op8* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
 // ---- exchanges between the lanes of a wavefront, on fragments in the accumulator layout (all 64 lanes together)
 // The halves of two fragments: lo = the lower 32 lanes' values of u and, in the upper 32 lanes, of v; hi = the upper 32 lanes'.  So
 // where a fragment's columns 0 .. 7 meet its columns 8 .. 15 (gate and up, rotary partners), each lane gets one pair.

@@ -100,7 +100,7 @@ struct MacroShape {
 
 // form: bit 0: the weights are packed in interleaved pairs of column tiles, not in single runs (weight_pack_rows - 1); and with ORDER
 // bit 1: two chunks of the squares per column block, the other bits: k-tiles after which a second sum starts (0: one sum)
-// NT: W is read once (a single row block), so most of its copies are non-temporal (see issue)
+// NT: W is read once (a single row block) and is not kept from pass to pass, so most of its copies are non-temporal (see issue)
 template <int WM, int WN, int RW, int CW, int KB, int EPI, bool ORDER, bool NT>
 __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
                                                                                int form, int nblocks, int mblocks, int splits, int kt_per_split, GemmEpi e) {
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   // moves the last one again.  The fragments' addresses at the first k-tile are kept, so that a copy costs one scalar shift and one add
   // (recomputing them from the tile indices each time took 3 .. 5 % of a wide launch).
   // Where W is read by one workgroup only, the rounds that are all W (which comes first then) are non-temporal: they do not enter the memory-side cache, in which
-  // W never stays from pass to pass (a plain read of HBM 6.2 -> 7.1 TB/s; the LM head of the 8B model, 8 rows 180 -> 158 us, 96 rows 196 ->
+  // W does not stay from pass to pass unless the model is small (WEIGHTS_CACHED_BYTES; a plain read of HBM 6.2 -> 7.1 TB/s; the LM head of the 8B model, 8 rows 180 -> 158 us, 96 rows 196 ->
   // 185).  Where row blocks share W it loses what the L2 keeps for the second of them (two readers of a stream 5.1 -> 4.7 TB/s, four 3.6 ->
   // 2.9), and so does a fragment that several wavefronts move; with one such round and nothing else of W, 96 x 128 tiles, it loses as well
   // (head of the 7B model at 96 rows 229 -> 238).
@@ -612,7 +612,7 @@ void launch_macro_epi(const op_t* xt, const op_t* wt, int M, int N, int K, const
       if (p.tile == i && (p.fold || p.ssq_parts > 1)) return launch_tile<WM, WN, RW, CW, KB, EPI, true, false>(xt, wt, M, N, K, p, e, st); \
     }                                                                                                                          \
     if constexpr (macro_non_temporal(RW, CW, WN)) {                                                                            \
-      if (p.tile == i && p.mblocks == 1) return launch_tile<WM, WN, RW, CW, KB, EPI, false, true>(xt, wt, M, N, K, p, e, st);  \
+      if (p.tile == i && p.mblocks == 1 && !e.w_cached) return launch_tile<WM, WN, RW, CW, KB, EPI, false, true>(xt, wt, M, N, K, p, e, st);  \
     }                                                                                                                          \
     if (p.tile == i) return launch_tile<WM, WN, RW, CW, KB, EPI, false, false>(xt, wt, M, N, K, p, e, st);                    \
   }                                                                                                                            \

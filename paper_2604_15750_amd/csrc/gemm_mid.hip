@@ -9,8 +9,8 @@
 // per CT + MT fragments fetched), everything in registers:
 //   * W goes HBM -> registers, three steps at a time (a step is one k-tile, two for the narrowest groups; a wavefront keeps 8 .. 24 KiB
 //     of W in flight, a workgroup 32 .. 96 KiB: what it takes to keep HBM busy with 128 .. 256 workgroups), non-temporally: one workgroup
-//     reads a column group's W, once a pass, and the memory-side cache never holds it until the next (a plain read of HBM 6.2 -> 7.1
-//     TB/s; gate/up of an 8B model at 8 rows, this and the loads' start below, 33.6 -> 31.4 us, at 37 rows 37.4 -> 33.2, QKV 19.0 -> 17.2);
+//     reads a column group's W, once a pass, and the memory-side cache does not hold it until the next unless the model is small
+//     (WEIGHTS_CACHED_BYTES; a plain read of HBM 6.2 -> 7.1 TB/s; gate/up of an 8B model at 8 rows, this and the loads' start below, 33.6 -> 31.4 us, at 37 rows 37.4 -> 33.2, QKV 19.0 -> 17.2);
 //     X goes L2 -> registers as many steps ahead (one for more than four row tiles), issued BEFORE the W loads of
 //     the same step, because the memory counter retires in order and a wait for X must not wait for younger W loads;
 //   * the first loads need nothing from memory (their arguments arrive in registers), and no load in front of the loop is waited for
@@ -56,8 +56,8 @@ struct MidShape {
 };
 
 // grid.x = groups * splits; MT >= ceil(M / 16), and X has MT row tiles (the activation buffers are padded to 16 rows).
-// STEPS: wt is the step-major copy of W.
-template <int MT, int CT, int PR, int EPI, bool STEPS>
+// STEPS: wt is the step-major copy of W.  NT: W is read non-temporally.
+template <int MT, int CT, int PR, int EPI, bool STEPS, bool NT>
 __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N, int K,
                                                        int kt_per_split, int splits, GemmEpi e) {
   typedef MidShape<MT, CT> SH;
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   const int group = STEPS ? blockIdx.x : blockIdx.x / splits, split = STEPS ? 0 : blockIdx.x - group * splits;  // (the copy: no K split)
   const int groups = (N + 16 * CT - 1) / (16 * CT);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int KT = K >> 5, NT = N >> 4;
+  const int KT = K >> 5, NTILES = N >> 4;
   const int nt0 = group * CT;
   const int tb = split * kt_per_split, te = min(KT, tb + kt_per_split);
   const int per = (te - tb + NWV - 1) / NWV;
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   const op8* wptr[CT];
 #pragma unroll
   for (int r = 0; r < CT; ++r) {
-    const int nt = min(nt0 + r, NT - 1);
+    const int nt = min(nt0 + r, NTILES - 1);
     wptr[r] = steps ? wt + ((size_t)(group * NWV + wave) * CT + r) * 64
                     : PR == 2 ? wt + ((size_t)(nt >> 1) * KT * 2 + (nt & 1)) * 64 : wt + (size_t)nt * KT * 64;
   }
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
     for (int i = 0; i < KB; ++i) {
       const int tc = min(t0 + st * KB + i, t1 - 1);
 #pragma unroll
-      for (int r = 0; r < CT; ++r) w[slot][i][r] = __builtin_nontemporal_load(wptr[r] + (size_t)(tc - tsub) * wstep + lane);
+      for (int r = 0; r < CT; ++r) w[slot][i][r] = load_weight<NT>(wptr[r] + (size_t)(tc - tsub) * wstep + lane);
     }
   };
   auto compute = [&](const int ws, const int xs, int st) __attribute__((always_inline)) {
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   // variants of narrow passes, which are short enough for that round trip to show
   EpiAhead ahead = epi_none();
   if constexpr (MT <= 2 && (EPI == EPI_RESID || EPI == EPI_QKV)) {
-    if (splits == 1 && wave < F && nt0 + wave / MT < NT)
+    if (splits == 1 && wave < F && nt0 + wave / MT < NTILES)
       ahead = epi_ahead<EPI>(e, M, N, (wave % MT) * 16 + (lane & 15), (nt0 + wave / MT) * 16, lane >> 4);
   }
   if (any) {
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
     const int r = f / MT, j = f - r * MT;
     const int nt = nt0 + r, m = j * 16 + ml;
     float ss = 0.f;
-    if (nt < NT) ss = finish_frag<EPI>(e, M, N, m, nt * 16, g, v, EPI == EPI_RESID ? 1.f : s_rinv[m], f == wave ? ahead : epi_none());  // uniform in the wavefront
+    if (nt < NTILES) ss = finish_frag<EPI>(e, M, N, m, nt * 16, g, v, EPI == EPI_RESID ? 1.f : s_rinv[m], f == wave ? ahead : epi_none());  // uniform in the wavefront
     if (EPI == EPI_RESID && g == 0) s_ssq[r * MT * 16 + m] = ss;
   };
 #pragma unroll
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
         finish(f, v);
       } else {  // partial tile -> workspace, written through to device scope
         const int r = f / MT, j = f - r * MT;
-        if (nt0 + r < NT && j * 16 < M) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), partial(split), (unsigned)(f * 64 + lane) * 16u, 0, SC1);
+        if (nt0 + r < NTILES && j * 16 < M) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), partial(split), (unsigned)(f * 64 + lane) * 16u, 0, SC1);
       }
     }
   }
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
 #pragma unroll
     for (int i = 0; i < FW; ++i) {
       const int f = wave + NWV * i, r = f / MT, j = f - r * MT;
-      off[i] = (f < F && nt0 + r < NT && j * 16 < M) ? (unsigned)(f * 64 + lane) * 16u : 0u;  // fragments that do not exist re-read element 0
+      off[i] = (f < F && nt0 + r < NTILES && j * 16 < M) ? (unsigned)(f * 64 + lane) * 16u : 0u;  // fragments that do not exist re-read element 0
       v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     for (int s = 0; s < splits; s += 2) {  // two splits per trip to memory
@@ -320,23 +320,32 @@ MidPlan mid_plan(int M, int N, int K) {
   return best;
 }
 
-template <int MT, int CT, int PR, int EPI, bool STEPS>
+template <int MT, int CT, int PR, int EPI, bool STEPS, bool NT>
 void launch_kernel(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
   typedef MidShape<MT, CT> SH;
   static bool configured = false;  // raise the dynamic LDS limit of this instantiation once
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_mid_kernel<MT, CT, PR, EPI, STEPS>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
+    (void)hipFuncSetAttribute((const void*)gemm_mid_kernel<MT, CT, PR, EPI, STEPS, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, SH::LDS_BYTES);
     configured = true;
   }
-  DLM_LAUNCH((gemm_mid_kernel<MT, CT, PR, EPI, STEPS>), p.groups * p.splits, TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
+  DLM_LAUNCH((gemm_mid_kernel<MT, CT, PR, EPI, STEPS, NT>), p.groups * p.splits, TPB, SH::LDS_BYTES, st, (const op8*)xt, (const op8*)wt, M, N, K,
              p.kps, p.splits, e);
+}
+template <int MT, int CT, int PR, int EPI, bool NT>
+void launch_layout(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
+  if constexpr (MT <= MID_STEPS_MAX_MT) {
+    if (e.w_steps) return launch_kernel<MT, CT, PR, EPI, true, NT>(xt, e.w_steps, M, N, K, p, e, st);
+  }
+  launch_kernel<MT, CT, PR, EPI, false, NT>(xt, wt, M, N, K, p, e, st);
 }
 template <int MT, int CT, int PR, int EPI>
 void launch_one(const op_t* xt, const op_t* wt, int M, int N, int K, const MidPlan& p, const GemmEpi& e, hipStream_t st) {
-  if constexpr (MT <= MID_STEPS_MAX_MT) {
-    if (e.w_steps) return launch_kernel<MT, CT, PR, EPI, true>(xt, e.w_steps, M, N, K, p, e, st);
+  // (a layer's matrix, not a plain product's, which is not read again; beyond four row tiles W is the smaller part: a pass of 96 rows
+  // through 4 layers of 1024 x 3584 takes 201 us with every W non-temporal, 195 with none)
+  if constexpr (EPI != EPI_SUM && MT <= 4) {
+    if (e.w_cached) return launch_layout<MT, CT, PR, EPI, false>(xt, wt, M, N, K, p, e, st);
   }
-  launch_kernel<MT, CT, PR, EPI, false>(xt, wt, M, N, K, p, e, st);
+  launch_layout<MT, CT, PR, EPI, true>(xt, wt, M, N, K, p, e, st);
 }
 
 template <int MT, int EPI>

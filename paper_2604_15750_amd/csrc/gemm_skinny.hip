@@ -9,7 +9,7 @@
 // load bandwidth as W itself for the narrow matrices, so lanes whose row does not exist fetch no line of
 // their own (they re-read a row that exists): a fragment's 128-byte lines hold 8 rows each, and a block
 // of 8 rows (the minimum block length) reads half of them.  W is read non-temporally: once a pass, by one workgroup, and the memory-side
-// cache never holds it until the next pass (a plain read of HBM 6.2 -> 7.1 TB/s); with both first batches in flight before anything else is
+// cache does not hold it until the next pass unless the model is small (WEIGHTS_CACHED_BYTES; a plain read of HBM 6.2 -> 7.1 TB/s); with both first batches in flight before anything else is
 // read, O and down of an 8B model at 8 rows 12.8 -> 12.0 us on average, gate/up of a 7B one at 16 rows 46.8 -> 43.1.
 #include "gemm_epilogue.h"
 
@@ -17,9 +17,9 @@ namespace {
 
 // grid.x = N / (16 R) workgroups of NWV wavefronts; wavefront w multiplies k-tiles [w*per, (w+1)*per) of the
 // workgroup's R column tiles against all MT row tiles, D k-tiles per batch, two batches of registers.
-// STEPS: wt is the step-major copy of W.
+// STEPS: wt is the step-major copy of W.  NT: W is read non-temporally.
 // TWO: registers for two workgroups on a compute unit.
-template <int MT, int R, int NWV, int D, int EPI, bool STEPS = false, bool TWO = false>
+template <int MT, int R, int NWV, int D, int EPI, bool NT, bool STEPS = false, bool TWO = false>
 __global__ __launch_bounds__(NWV * 64, TWO ? NWV / 2 : 1) void gemm_skinny_kernel(const op8* __restrict__ xt, const op8* __restrict__ wt, int M, int N,
                                                                int K, GemmEpi e) {
   __shared__ f32x4 red[NWV][R * MT][64];
@@ -55,7 +55,7 @@ __global__ __launch_bounds__(NWV * 64, TWO ? NWV / 2 : 1) void gemm_skinny_kerne
     for (int i = 0; i < D; ++i) {
       const int t = min(tb + i, t_end - 1);
 #pragma unroll
-      for (int r = 0; r < R; ++r) wreg[buf][i][r] = __builtin_nontemporal_load(wbase + (size_t)(t - tsub) * wstride + r * 64 + lane);
+      for (int r = 0; r < R; ++r) wreg[buf][i][r] = load_weight<NT>(wbase + (size_t)(t - tsub) * wstride + r * 64 + lane);
 #pragma unroll
       for (int j = 0; j < MT; ++j) xreg[buf][i][j] = (xt + ((size_t)j * KT + t) * 64)[j == MT - 1 ? xlane_last : lane];
     }
@@ -133,24 +133,32 @@ __global__ __launch_bounds__(NWV * 64, TWO ? NWV / 2 : 1) void gemm_skinny_kerne
 // the step-major copy reads best with batches of four (measured: deeper batches add queueing, not bandwidth), of two with two row
 // tiles, where a wavefront has few k-tiles and those past its last are read again.  Interleaved pairs
 // of column tiles (wide matrices) come here with one row tile only: from 17 rows on the mid or the macro kernel has them.
-template <int MT, int EPI>
-void launch_skinny(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, const GemmEpi& e, hipStream_t st) {
+template <int MT, int EPI, bool NT>
+void launch_layout(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, const GemmEpi& e, hipStream_t st) {
   if (pr == 1 && e.w_steps) {
-    DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 ? 2 : 4), EPI, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
+    DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 ? 2 : 4), EPI, NT, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
   } else if (pr == 1) {
     // More column tiles than compute units: two workgroups a unit, with batches that leave them the registers, instead of a second round of few
     // (QKV of a 7B model, 288 tiles: 24 rows 16.9 -> 13.7 us, 32 rows 18.7 -> 15.7, 48 rows 22.4 -> 19.2, 64 rows 26.3 -> 22.4).
     if constexpr (MT > 1) {
       if (N / 16 > 256) {
-        DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 || (MT == 3 && EPI == EPI_QKV) ? 2 : 1), EPI, false, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
+        DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 || (MT == 3 && EPI == EPI_QKV) ? 2 : 1), EPI, NT, false, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
         return;
       }
     }
-    DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT <= 2 ? 8 : 4), EPI>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
+    DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT <= 2 ? 8 : 4), EPI, NT>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
   } else if constexpr (MT == 1) {
-    if (e.w_steps) DLM_LAUNCH((gemm_skinny_kernel<MT, 2, 4, 4, EPI, true>), N / 32, 256, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
-    else DLM_LAUNCH((gemm_skinny_kernel<MT, 2, 4, 4, EPI>), N / 32, 256, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
+    if (e.w_steps) DLM_LAUNCH((gemm_skinny_kernel<MT, 2, 4, 4, EPI, NT, true>), N / 32, 256, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
+    else DLM_LAUNCH((gemm_skinny_kernel<MT, 2, 4, 4, EPI, NT>), N / 32, 256, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
   }
+}
+
+template <int MT, int EPI>
+void launch_skinny(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, const GemmEpi& e, hipStream_t st) {
+  if constexpr (EPI != EPI_SUM) {  // (of a layer's matrix: a plain product's is not read again)
+    if (e.w_cached) return launch_layout<MT, EPI, false>(xt, wt, pr, M, N, K, e, st);
+  }
+  launch_layout<MT, EPI, true>(xt, wt, pr, M, N, K, e, st);
 }
 
 template <int EPI>

@@ -468,14 +468,26 @@ def test_wide_spans_behind_prefixes_of_any_length(device, hd, commits, spans):
 
 def _one_pass_matches(cfg, M, device, seed, stats=False):
     """One pass of M rows of one sequence without a prefix: every row's logits against the oracle's, and (stats) the statistics
-    against the oracle's of the logits as written."""
+    against the oracle's of the logits as written.  The models are small enough for their weights to be read through the memory-side
+    cache; a large one's are read past it, with the same bits."""
     W = _weights(cfg, seed, device)
-    model = api.Model(cfg, W)
-    state = api.State(model, 1, M, M, 8)
-    out = api.StepOutputs(M, cfg["vocab"], model.torch_dtype, device)
     tokens = torch.randint(0, cfg["vocab"] - 1, (M,), generator=torch.Generator().manual_seed(seed), dtype=torch.int32)
-    api.dlm_step(state, tokens.to(device), out, [0, M], [0], [0], [0])
-    torch.cuda.synchronize()
+
+    def one_pass(cached):
+        with pytest.MonkeyPatch.context() as mp:
+            mp.setenv("DLM_W_CACHED", str(cached))
+            model = api.Model(cfg, W)
+        state = api.State(model, 1, M, M, 8)
+        out = api.StepOutputs(M, cfg["vocab"], model.torch_dtype, device)
+        api.dlm_step(state, tokens.to(device), out, [0, M], [0], [0], [0])
+        torch.cuda.synchronize()
+        state.close()
+        model.close()
+        return out
+
+    out, past = one_pass(1), one_pass(0)
+    for key in ("logits", "lse", "entropy", "conf", "argmax"):
+        assert torch.equal(getattr(out, key), getattr(past, key)), key
     z = o_fwd.widen(inputs.tensor_to_numpy(out.logits))
     ref = o_fwd.forward_span(cfg, inputs.weights_to_numpy(W), o_fwd.KVCache(cfg), tokens.numpy(), 0, 0)
     scale = np.maximum(np.abs(ref).max(-1, keepdims=True), SIGMA_LOGIT)
@@ -485,8 +497,6 @@ def _one_pass_matches(cfg, M, device, seed, stats=False):
         for key in ("max_logit", "lse", "entropy", "conf"):
             assert (np.abs(getattr(out, key).cpu().numpy() - st[key]) <= 1e-5 * np.maximum(1.0, np.abs(st[key]))).all(), key
         assert (out.argmax.cpu().numpy() == st["argmax"]).all()
-    state.close()
-    model.close()
 
 
 # (epilogue, tile, rows, model dimensions): the layer's epilogues on the wavefront shapes with an odd number of column tiles, whose last
