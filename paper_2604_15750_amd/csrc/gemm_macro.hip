@@ -70,8 +70,9 @@ MacroPlan macro_plan(int M, int N, int K, int kind) {
     for (const MacroTile& t : g_tiles) {
       ++c;
       if (kind == EPI_STATS && 16 * t.rw * t.wm > GEMM_STATS_MAX_ROWS) continue;  // (not instantiated)
-      if (macro_product_only(t.wm, t.wn, t.cw) && kind != EPI_DIRECT && kind != EPI_STATS && kind != EPI_SUM) continue;
       const int at = t.rw * t.wm, bt = t.cw * t.wn, mb = (mt + at - 1) / at, nb = (nt + bt - 1) / bt, tiles = mb * nb;
+      // (never faster where row blocks share W, and not instantiated for the layer's epilogues)
+      if (macro_product_only(t.wm, t.wn, t.cw) && (mb > 1 || !(kind == EPI_DIRECT || kind == EPI_STATS || kind == EPI_SUM))) continue;
       const int parts = order.fixed && kind == EPI_RESID && bt == 2 * order.bt ? 2 : 1;  // (two chunks of a block of 16 column tiles: bt % 4 == 0)
       const bool keeps = may_split && macro_can_keep_order(t.wm, t.wn, t.kb);
       if (order.fixed && kind == EPI_RESID && (bt != order.bt * parts || (parts == 2 && !(keeps && bt % 4 == 0)))) continue;

@@ -29,9 +29,10 @@
 
 // {WM, WN, RW, CW, KB, ns1, ns4}: tile of 16 RW WM rows x 16 CW WN columns; nanoseconds per k-tile on a chip full of such
 // workgroups when each streams a W of its own (one row block) and when four or more row blocks share it (operands of random
-// values; fitted to 3500 launches of the layer and head matrices of an 8B and a 7B grouped-query model at 24 .. 2822 rows).
+// values; fitted to 3500 launches of the layer and head matrices of an 8B and a 7B grouped-query model at 24 .. 2822 rows; but the first
+// of 64 x 320 and 128 x 320, which serve single row blocks only, to the head of macro_product_only, and their second stands for nothing).
 #define MACRO_TILES(X)                                                                                            \
-  X(2, 2, 1, 8, 2, 683, 399) X(1, 5, 2, 4, 2, 822, 487) X(2, 5, 2, 4, 2, 823, 1000) X(4, 5, 2, 4, 1, 834, 1000) \
+  X(2, 2, 1, 8, 2, 683, 399) X(1, 5, 2, 4, 2, 822, 487) X(2, 5, 2, 4, 2, 823, 823) X(4, 5, 2, 4, 1, 834, 834)   \
   X(2, 1, 2, 4, 2, 174, 130) X(1, 3, 4, 2, 2, 262, 195) X(1, 5, 4, 2, 2, 429, 236) X(2, 4, 2, 4, 2, 696, 330)     \
   X(3, 2, 2, 4, 2, 348, 244) X(3, 4, 2, 4, 2, 706, 395)                                                           \
   X(2, 2, 4, 2, 2, 252, 193) X(2, 3, 4, 2, 2, 301, 232) X(4, 2, 2, 4, 2, 361, 278)                                \
@@ -44,7 +45,7 @@
 
 // 64 and 128 x 320, for the plain product only: a vocabulary whose 160-column blocks are a little under four rounds and whose 256-column
 // ones a little over two takes two of these (head of a 7B model, 152064 columns, in the pass: 64 rows 200 -> 187 us, 96 rows 229 -> 189).  Never
-// faster where row blocks share W (the second figure keeps them out).
+// faster where row blocks share W: the planner leaves them out there.
 constexpr bool macro_product_only(int wm, int wn, int cw) { return wm > 1 && wn * cw == 20; }
 
 struct MacroTile {

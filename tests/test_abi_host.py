@@ -217,6 +217,19 @@ def test_paired_column_tiles_leave_the_skinny_kernel_at_17_rows():
                     assert p["kernel"] != "skinny" or p["cols"] == 16, (M, N, K, epi)
 
 
+@pytest.mark.parametrize("epi", ["direct", "sum", "qkv", "swiglu", "resid"])
+def test_widest_tiles_serve_single_row_blocks(epi):
+    """64 and 128 x 320: plain products whose rows are one block of such a tile, whatever the planner's estimates of the others."""
+    seen = 0
+    for N, K in ((152064, 3584), (66400, 416), (150336, 4096), (37888, 3584), (8192, 4096)):
+        for M in range(1, 700, 3):
+            p = api.plan_gemm(M, N, K, epi)
+            if p["kernel"] == "macro" and p["cols"] == 320 and p["rows"] > 32:
+                assert epi in ("direct", "sum") and M <= p["rows"] and p["workgroups"] == -(-N // 320), (M, N, K, p)
+                seen += 1
+    assert seen or epi not in ("direct", "sum")
+
+
 def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_there_for():
     """A retuned planner must not leave a variant without a test."""
     import test_gpu_kernels as k
