@@ -13,12 +13,17 @@ BOUNDARY = C.CFUNCTYPE(C.c_int, VP, VP, VP, VP, VP, C.c_int, VP, VP, VP, VP, VP)
 SELECT = C.CFUNCTYPE(C.c_int, VP, C.c_int, C.c_int, VP, VP, VP, VP, VP, VP, VP, C.c_int, C.c_int, VP, C.c_int, VP, VP, VP, VP)
 
 
+class Calls:
+    """Calling it runs a function through both ways, the extension first, and gives the recorded calls of each (or the exception's type);
+    `taken` then says whether the extension took the call itself, and `status` is what the recorder returns."""
+
+
 @pytest.fixture
 def calls(monkeypatch):
-    """Runs a function through both ways, the extension first; gives the recorded calls of each."""
     ext = api._decisions()
     assert ext is not None, "the extension has not been built"
-    seen = []
+    seen, self = [], Calls()
+    self.status = 0
 
     def ints(p, n):
         return None if not p else tuple((I32 * n).from_address(p))
@@ -26,12 +31,12 @@ def calls(monkeypatch):
     def boundary(I, H, ws, wl, cold, n, p, L, S, m, st):
         q = C.cast(p, C.POINTER(api.dlm_boundary_params))[0]
         seen.append((I, H, ints(ws, n), ints(wl, n), ints(cold, n), n, q.lam, q.l_min, q.smooth_radius, q.norm_mode, q.rule, L, S, m, st))
-        return 0
+        return self.status
 
     def select(z, V, dt, lse, cf, am, tok, rs, ts, bl, n, mask, p, ap, sel, ns, m, st):
         q = C.cast(p, C.POINTER(api.dlm_select_params))[0]
         seen.append((z, V, dt, lse, cf, am, tok, ints(rs, n), ints(ts, n), ints(bl, n), n, mask, q.tau_low, q.tau_high, q.gamma, q.mode, ap, sel, ns, m, st))
-        return 0
+        return self.status
 
     cb, cs, L = BOUNDARY(boundary), SELECT(select), api.lib()
     real = [C.cast(f, VP).value for f in (L.block_boundary, L.select_parallel)]
@@ -39,11 +44,24 @@ def calls(monkeypatch):
     class Recorder:
         block_boundary, select_parallel, dlm_last_error = cb, cs, L.dlm_last_error
 
+    class Spy:
+        """The extension; a call that it takes has reached the library when it returns, one that it declines has not."""
+        @staticmethod
+        def ask(f, args):
+            before = len(seen)
+            rc = f(*args)
+            assert rc in (None, self.status) and len(seen) - before == (rc is not None)
+            self.taken = rc is not None
+            return rc
+
+        boundary = staticmethod(lambda *a: Spy.ask(ext.boundary, a))
+        select = staticmethod(lambda *a: Spy.ask(ext.select, a))
+
     def run(f):
         out = []
         for through_ext in (True, False):
             seen.clear()
-            monkeypatch.setattr(api, "_decisions", (lambda: ext) if through_ext else (lambda: None))
+            monkeypatch.setattr(api, "_decisions", (lambda: Spy) if through_ext else (lambda: None))
             try:
                 f()
                 out.append(list(seen))
@@ -51,16 +69,30 @@ def calls(monkeypatch):
                 out.append(type(e))
         return out
 
+    Calls.__call__ = lambda self, f: run(f)
+
     monkeypatch.setattr(api, "lib", lambda: Recorder)
     monkeypatch.setattr(api, "_stream", lambda: 0x1230)
     ext.bind(C.cast(cb, VP).value, C.cast(cs, VP).value, torch.float32, torch.bfloat16)
-    yield run
+    yield self
     ext.bind(*real, torch.float32, torch.bfloat16)
 
 
 f = torch.zeros(64)
 i = torch.zeros(64, dtype=torch.int32)
 ARRAYS = [[0, 8], (0, 8), [True, 8], np.array([0, 8], dtype=np.int32), [np.int64(0), 8], torch.tensor([0, 8]), [0.0, 8.9], [0, 2**31], [], ["a", 1], None, list(range(33))]
+
+
+def plain(v, n=None):
+    """Whether a host array (n None: the first, else one beside a first of n entries) is one that the extension takes."""
+    return type(v) in (list, tuple) and (len(v) <= 32 if n is None else len(v) >= n) and all(number(x) for x in v[:n])
+
+
+def number(x):
+    """... a whole number or a real one of a parameter struct."""
+    if isinstance(x, int):
+        return -2**31 <= x < 2**31
+    return type(x) is float and (abs(x) < 3.4e38 or x - x != 0)
 
 
 @pytest.mark.parametrize("arr", range(len(ARRAYS)))
@@ -70,6 +102,8 @@ def test_block_boundary_forms(calls, arr, lam, l_min):
         for S in (None, f):
             a, b = calls(lambda: api.block_boundary(f, f, ARRAYS[arr], [8] * 40, i, lam, l_min, 1, 0, 1, cold=cold, S_out=S))
             assert a == b
+            assert calls.taken == (plain(ARRAYS[arr]) and not any(type(x) is float for x in ARRAYS[arr]) and type(lam) is float and number(lam) and
+                                   isinstance(l_min, int) and number(l_min))
 
 
 @pytest.mark.parametrize("arr", range(len(ARRAYS)))
@@ -80,6 +114,8 @@ def test_select_parallel_forms(calls, arr, dtype):
         for apply, mask in ((True, 15), (0, np.int32(15)), (2, 2**33), ("x", 15)):
             a, b = calls(lambda: api.select_parallel(z, f, f, i, i, ARRAYS[arr], [0, 8] * 17, [8, 8] * 17, mask, tau, 0.9, -16.0, 0, i, i, apply, margin_out=None))
             assert a == b
+            assert calls.taken == (plain(ARRAYS[arr]) and not any(type(x) is float for x in ARRAYS[arr]) and dtype != torch.float16 and
+                                   type(tau) is float and number(tau) and isinstance(apply, int) and isinstance(mask, int) and number(mask))
     for bad in (None, 3, "x"):
         a, b = calls(lambda: api.select_parallel(bad, f, f, i, i, [0], [0], [8], 15, 0.5, 0.9, -16.0, 0, i, i))
         assert a == b
@@ -122,3 +158,15 @@ def test_short_host_arrays_of_a_step_are_refused(monkeypatch, short):
         with pytest.raises(ValueError, match="entries"):
             step()
     assert len(seen) == (short is None)
+
+
+def test_a_refused_call_raises_either_way(calls):
+    boundary = lambda: api.block_boundary(f, f, [0, 8], [8, 8], i, 1.2, 8)  # noqa: E731
+    z = torch.zeros(8, 16)
+    select = lambda: api.select_parallel(z, f, f, i, i, [0], [0], [8], 15, 0.5, 0.9, -16.0, 0, i, i)  # noqa: E731
+    for call in (boundary, select):
+        calls.status = 0
+        a, b = calls(call)
+        assert a == b and len(a) == 1 and calls.taken
+        calls.status = -2
+        assert calls(call) == [api.DlmError, api.DlmError] and calls.taken
