@@ -138,8 +138,11 @@ void launch_layout(const op_t* xt, const op_t* wt, int pr, int M, int N, int K, 
   if (pr == 1 && e.w_steps) {
     DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 ? 2 : 4), EPI, NT, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)e.w_steps, M, N, K, e);
   } else if (pr == 1) {
-    // More column tiles than compute units: two workgroups a unit, with batches that leave them the registers, instead of a second round of few
-    // (QKV of a 7B model, 288 tiles: 24 rows 16.9 -> 13.7 us, 32 rows 18.7 -> 15.7, 48 rows 22.4 -> 19.2, 64 rows 26.3 -> 22.4).
+    // 257 to 384 column tiles (and more where there is no step-major copy): two workgroups a unit, with batches that leave them the registers,
+    // instead of a second round of few (QKV of a 7B model, 288 tiles: 24 rows 16.9 -> 13.7 us, 32 rows 18.7 -> 15.7, 48 rows 22.4 -> 19.2, 64
+    // rows 26.3 -> 22.4; O of 272 tiles, K = 4352, 20 / 64 rows 18.6 -> 16.2 / 26.8 -> 24.5; gate/up of 320, K = 6144, 22.7 -> 21.8 / 37.2 -> 34.7).
+    // From 385 tiles on, nearly two full rounds, the copy's workgroups are as fast or faster (two a unit / the copy: O of 448 tiles, K =
+    // 7168, 20 rows 28.0 / 26.5, 64 rows 41.2 / 40.3; QKV of 448, K = 5120, 20.4 / 19.7, 29.7 / 30.1).
     if constexpr (MT > 1) {
       if (N / 16 > 256) {
         DLM_LAUNCH((gemm_skinny_kernel<MT, 1, 8, (MT == 2 || (MT == 3 && EPI == EPI_QKV) ? 2 : 1), EPI, NT, false, true>), N / 16, 512, 0, st, (const op8*)xt, (const op8*)wt, M, N, K, e);
