@@ -56,14 +56,19 @@ def test_gemm_bf16(device, M, N, K):
 # One shape for every tile the macro GEMM's planner has for more than 32 rows, each with a ragged last row block, a ragged last
 # column block, an odd number of k-tiles (13: more than the pipeline has stages) and rows that are no multiple of 16; and K splits
 # of three and four ways, whose workgroups hand their partial tiles to the last arriver, run twice (the tickets reset themselves).
-# Each with the tile and the split that it is there for.  (The 32-row tiles serve the LM head: test_statistics_of_every_head_tile.)
+# Each with the tile and the split that it is there for.  (The statistics epilogue's tiles: test_statistics_of_every_head_tile.)
 MACRO_TILE_SHAPES = [
     ((209, 96, 416), (64, 64, 1)), ((97, 8320, 416), (64, 96, 1)), ((17, 32864, 416), (64, 160, 1)), ((259, 10976, 416), (64, 256, 1)),
     ((130, 12224, 416), (96, 128, 1)), ((259, 16608, 416), (96, 256, 1)), ((70, 12704, 416), (128, 64, 1)), ((129, 8704, 416), (128, 96, 1)),
     ((97, 24768, 416), (128, 128, 1)), ((68, 33088, 416), (128, 160, 1)), ((17, 40992, 416), (128, 192, 1)), ((199, 24672, 416), (128, 256, 1)),
     ((129, 24928, 416), (160, 128, 1)), ((291, 16448, 416), (160, 192, 1)), ((133, 16448, 416), (192, 96, 1)), ((164, 24896, 416), (192, 160, 1)),
     ((161, 41024, 416), (192, 192, 1)), ((387, 16640, 416), (256, 192, 1)), ((257, 24608, 416), (256, 256, 1)),
-    ((97, 66400, 416), (128, 320, 1)), ((300, 160, 4128), (64, 64, 3)), ((264, 96, 4128), (64, 64, 4)), ((290, 4064, 8224), (96, 128, 2))]
+    ((97, 66400, 416), (128, 320, 1)),
+    # ... in a single row block, where most copies of W are non-temporal
+    ((19, 49216, 416), (32, 256, 1)), ((19, 65632, 2592), (32, 320, 1)), ((51, 49184, 416), (64, 256, 1)), ((51, 65632, 2592), (64, 320, 1)),
+    ((83, 49184, 416), (96, 256, 1)), ((115, 49184, 416), (128, 256, 1)), ((147, 40992, 416), (160, 192, 1)), ((243, 32800, 416), (256, 192, 1)),
+    ((243, 49184, 416), (256, 256, 1)),
+    ((300, 160, 4128), (64, 64, 3)), ((264, 96, 4128), (64, 64, 4)), ((290, 4064, 8224), (96, 128, 2))]
 # ... and the mid kernel's: (rows, columns of a group, split); both sides of every row count at which choose_kernel leaves it
 MID_SHAPES = [
     ((17, 16480, 416), (32, 96, 1)), ((17, 24768, 416), (32, 128, 1)), ((64, 24608, 512), (64, 128, 1)), ((48, 24544, 512), (48, 96, 1)),

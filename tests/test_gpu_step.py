@@ -511,7 +511,7 @@ EPILOGUE_TILES = [
     ("swiglu", (64, 160), 17, (1, 256, 2, 1, 128, 16576, 256)), ("swiglu", (128, 96), 134, (1, 256, 2, 1, 128, 4288, 256)),
     ("swiglu", (128, 160), 71, (1, 256, 2, 1, 128, 16576, 256)), ("swiglu", (128, 192), 197, (1, 256, 2, 1, 128, 10432, 256)),
     ("swiglu", (160, 192), 306, (1, 256, 2, 1, 128, 8320, 256)), ("swiglu", (192, 96), 134, (1, 256, 2, 1, 128, 8320, 256)),
-    ("swiglu", (192, 160), 161, (1, 256, 2, 1, 128, 12352, 256)),
+    ("swiglu", (192, 160), 161, (1, 256, 2, 1, 128, 12352, 256)), ("swiglu", (256, 192), 197, (1, 256, 2, 1, 128, 16448, 256)),
     ("resid", (64, 64), 209, (1, 256, 2, 1, 128, 64, 256)), ("resid", (64, 96), 260, (1, 3328, 2, 1, 128, 64, 256)),
     ("resid", (64, 160), 260, (1, 5632, 2, 1, 128, 64, 256)), ("resid", (128, 96), 398, (1, 4352, 2, 1, 128, 64, 256))]
 
@@ -528,7 +528,7 @@ def test_epilogues_of_odd_wavefront_shapes(device, epi, tile, M, dims):
     _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 19)
 
 
-# Gate/up of the mid kernel, whose rows' sums of squares are fetched in one run at 5 to 8 rows: the edges, two widths of its column groups
+# Gate/up of the mid kernel at one row tile, whose rows' sums of squares every wavefront fetches for its own rows: two widths of its column groups
 @pytest.mark.parametrize("M", [1, 4, 5, 8, 9, 16])
 @pytest.mark.parametrize("d,ffn", [(256, 2112), (256, 6144)])
 def test_gate_up_of_few_rows(device, M, d, ffn):
@@ -600,7 +600,6 @@ def test_statistics_from_the_lm_head_epilogue(device, L):
     model.close()
 
 
-# (vocabulary, rows, tile): every tile the LM head's statistics epilogue has, with a ragged last column block where the tile allows one
 # A narrow matrix of more column tiles than compute units (QKV: 384 of them) shares its units between two of the skinny kernel's
 # workgroups: every number of row tiles, ragged, and rows' scales of one chunk and of more than the kernel keeps (down of 2304 columns)
 @pytest.mark.parametrize("M", [17, 33, 50, 64])
@@ -611,6 +610,16 @@ def test_skinny_two_workgroups_a_unit(device, M, dims):
     _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 31 + M)
 
 
+# ... and so do a narrow gate/up and the residual products of a wide model (O and down)
+@pytest.mark.parametrize("M", [17, 33, 50, 64])
+@pytest.mark.parametrize("dims,epi,N,K,workgroups", [((1, 512, 2, 1, 128, 2560, 256), "swiglu", 5120, 512, 320), ((1, 4352, 2, 1, 128, 64, 256), "resid", 4352, 256, 272)])
+def test_skinny_two_workgroups_a_unit_behind_other_epilogues(device, M, dims, epi, N, K, workgroups):
+    p = api.plan_gemm(M, N, K, epi)
+    assert (p["kernel"], p["workgroups"]) == ("skinny", workgroups)
+    _one_pass_matches(inputs.model_config(*dims, "bf16"), M, device, 37 + M)
+
+
+# (vocabulary, rows, tile): every tile the LM head's statistics epilogue has, with a ragged last column block where the tile allows one
 HEAD_TILES = [(64, 1, (64, 64)), (16416, 37, (64, 96)), (24704, 17, (64, 160)), (41696, 24, (32, 256)), (41696, 33, (64, 256)), (67552, 8, (32, 320)),
               (67552, 45, (64, 320))]
 
