@@ -1,12 +1,14 @@
 """The two decisions called through the extension and through ctypes: the same C call for every form of arguments (a recorder in
 place of the library's entry points; nothing is launched)."""
 import ctypes as C
+import os
+import sysconfig
 
 import numpy as np
 import pytest
 import torch
 
-from paper_2604_15750_amd import api
+from paper_2604_15750_amd import api, build
 
 I32, F32, VP = C.c_int32, C.c_float, C.c_void_p
 BOUNDARY = C.CFUNCTYPE(C.c_int, VP, VP, VP, VP, VP, C.c_int, VP, VP, VP, VP, VP)
@@ -170,3 +172,13 @@ def test_a_refused_call_raises_either_way(calls):
         assert a == b and len(a) == 1 and calls.taken
         calls.status = -2
         assert calls(call) == [api.DlmError, api.DlmError] and calls.taken
+
+
+def test_the_extension_is_the_interpreters_own_and_the_library_builds_without_it(monkeypatch, tmp_path, capsys):
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert suffix != ".so" and os.path.basename(api._decisions().__file__) == "_decisions" + suffix
+    monkeypatch.setattr(build, "OUT_PY", str(tmp_path / ("_decisions" + suffix)))
+    (tmp_path / "_decisions.so").touch()  # of an earlier build
+    assert build.build_extension() == build.OUT_PY and os.listdir(tmp_path) == ["_decisions" + suffix]
+    monkeypatch.setattr(build.shutil, "which", lambda name: None)
+    assert build.build_extension() is None and os.listdir(tmp_path) == [] and "ctypes" in capsys.readouterr().err
