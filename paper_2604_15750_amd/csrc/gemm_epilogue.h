@@ -74,8 +74,7 @@ __device__ __attribute__((always_inline)) inline float sum_row4(float v) {
 // 1/rms of rows [m_lo, m_lo + rows) from the producer's partial sums of squares into s_rinv, by the whole workgroup of NT
 // threads: sixteen lanes per row, each adding every sixteenth chunk in ascending order, then a fixed butterfly
 // (deterministic).  A lane's sixteen loads of a block of 256 chunks are issued together and waited for once: one trip to
-// memory per block instead of one per chunk.  STRAIGHT: chunks past the end re-read the last one instead of being skipped by a path
-// per load.
+// memory per block instead of one per chunk.
 template <int NT>
 __device__ inline void block_rinv(const RowScale& rs, int m_lo, int rows, float* s_rinv) {
   const int sub = threadIdx.x & 15;
@@ -133,9 +132,14 @@ struct RinvBatch {
   template <int CTRL>
   static __device__ inline float rotate_add(float a) { return a + __uint_as_float(dpp<CTRL>(__float_as_uint(a))); }
   __device__ __attribute__((always_inline)) inline void publish(const RowScale& rs, int rows, float* s_rinv) const {
-    float ss[RPT];
-    add(rs, ss);
-    finish(rs, rows, ss, s_rinv);
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      const int row = (threadIdx.x >> 4) + r * (NT / 16);
+      float ss = 0.f;
+#pragma unroll
+      for (int k = 0; k < CH; ++k) ss += (int)(threadIdx.x & 15) + 16 * k < rs.nch ? v[r][k] : 0.f;
+      finish(rs, row, rows, ss, s_rinv);
+    }
   }
   // ... for rows of any number of chunks (a model of d_model > 4096 has more than 256 from a skinny product, more than 64 from a mid one):
   // those beyond the batch are read here, four of every row in a trip, and added behind the batch's.  d_model 5120, 64 rows, gate/up behind
@@ -145,7 +149,12 @@ struct RinvBatch {
     constexpr int TAIL = 4;
     const int sub = threadIdx.x & 15;
     float ss[RPT];
-    add(rs, ss);
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+      ss[r] = 0.f;
+#pragma unroll
+      for (int k = 0; k < CH; ++k) ss[r] += sub + 16 * k < rs.nch ? v[r][k] : 0.f;
+    }
     if (rs.ssq)
       for (int c0 = 16 * CH; c0 < rs.nch; c0 += 16 * TAIL) {
         float t[RPT][TAIL];
@@ -160,26 +169,15 @@ struct RinvBatch {
 #pragma unroll
           for (int k = 0; k < TAIL; ++k) ss[r] += c0 + sub + 16 * k < rs.nch ? t[r][k] : 0.f;
       }
-    finish(rs, rows, ss, s_rinv);
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) finish(rs, (threadIdx.x >> 4) + r * (NT / 16), rows, ss[r], s_rinv);
   }
 
  private:
-  __device__ __attribute__((always_inline)) inline void add(const RowScale& rs, float (&ss)[RPT]) const {
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-      ss[r] = 0.f;
-#pragma unroll
-      for (int k = 0; k < CH; ++k) ss[r] += (int)(threadIdx.x & 15) + 16 * k < rs.nch ? v[r][k] : 0.f;
-    }
-  }
-  static __device__ __attribute__((always_inline)) inline void finish(const RowScale& rs, int rows, const float (&ss)[RPT], float* s_rinv) {
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-      const int row = (threadIdx.x >> 4) + r * (NT / 16);
-      // row_ror:8, 4, 2, 1
-      const float s = rotate_add<0x121>(rotate_add<0x122>(rotate_add<0x124>(rotate_add<0x128>(ss[r]))));
-      if ((threadIdx.x & 15) == 0 && row < rows) s_rinv[row] = rs.ssq ? rsqrtf(s * rs.inv_d + rs.eps) : 1.f;
-    }
+  static __device__ __attribute__((always_inline)) inline void finish(const RowScale& rs, int row, int rows, float ss, float* s_rinv) {
+    // row_ror:8, 4, 2, 1
+    ss = rotate_add<0x121>(rotate_add<0x122>(rotate_add<0x124>(rotate_add<0x128>(ss))));
+    if ((threadIdx.x & 15) == 0 && row < rows) s_rinv[row] = rs.ssq ? rsqrtf(ss * rs.inv_d + rs.eps) : 1.f;
   }
 };
 
