@@ -64,7 +64,11 @@ constexpr int MACRO_SPLIT_FRAGS = 16;
 // kernel keeps its loop and its registers (QKV, 96 x 128: 95 against 124, 128 x 256: 229 against 250)
 constexpr bool macro_can_keep_order(int wm, int wn, int kb) { return kb == 2 && wm * wn >= 6 && wm * wn <= MACRO_SPLIT_FRAGS; }
 
-// tiles that also come with non-temporal copies of W, for launches of one row block (see issue)
+// Tiles that also come with non-temporal copies of W, for launches of one row block (see issue): those with more than one whole round of W.
+// With exactly one (96 x 128, 128 x 128, 160 x 128) it depends on the launch, and they are left plain.  Plain / non-temporal, K = 4096: in one
+// round of workgroups gate/up of 28672 columns, 80 rows 47.5 / 43.4 us, 112 rows 48.8 / 44.8, 144 rows 55.9 / 52.8, down from 14336, split, 144 rows
+// 42.6 / 32.3; in two the head of
+// 51200 columns, 144 rows 105.8 / 100.4; in three that of 98304, 70 rows 150.2 / 148.9, 96 rows 149.0 / 154.6 (152064, K = 3584: 229 / 238).
 constexpr bool macro_non_temporal(int rw, int cw, int wn) { return cw * wn > rw * cw; }
 
 // gemm_macro_<epilogue>.hip: the launches of one epilogue's instantiations
@@ -135,8 +139,7 @@ __global__ __launch_bounds__(RW * CW * 64, RW * CW / 4) void gemm_macro_kernel(c
   // Where W is read by one workgroup only, the rounds that are all W (which comes first then) are non-temporal: they do not enter the memory-side cache, in which
   // W does not stay from pass to pass unless the model is small (WEIGHTS_CACHED_BYTES; a plain read of HBM 6.2 -> 7.1 TB/s; the LM head of the 8B model, 8 rows 180 -> 158 us, 96 rows 196 ->
   // 185).  Where row blocks share W it loses what the L2 keeps for the second of them (two readers of a stream 5.1 -> 4.7 TB/s, four 3.6 ->
-  // 2.9), and so does a fragment that several wavefronts move; with one such round and nothing else of W, 96 x 128 tiles, it loses as well
-  // (head of the 7B model at 96 rows 229 -> 238).
+  // 2.9), and so does a fragment that several wavefronts move.
   constexpr bool W_FIRST = macro_non_temporal(RW, CW, WN);
   constexpr int FIRST_OP = W_FIRST ? BF : AT;
   static_assert(W_FIRST || !NT, "whole rounds of W come first");

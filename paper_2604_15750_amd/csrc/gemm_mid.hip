@@ -13,8 +13,10 @@
 //     (WEIGHTS_CACHED_BYTES; a plain read of HBM 6.2 -> 7.1 TB/s; gate/up of an 8B model at 8 rows, this and the loads' start below, 33.6 -> 31.4 us, at 37 rows 37.4 -> 33.2, QKV 19.0 -> 17.2);
 //     X goes L2 -> registers as many steps ahead (one for more than four row tiles), issued BEFORE the W loads of
 //     the same step, because the memory counter retires in order and a wait for X must not wait for younger W loads;
-//   * the first loads need nothing from memory (their arguments arrive in registers), and no load in front of the loop is waited for
-//     before the products are: the rows' 1/rms is finished behind it;
+//   * the first loads need nothing from memory (their arguments arrive in registers), and what the rows' 1/rms needs is fetched behind them
+//     and finished behind the loop (with three and four row tiles its 48 and 64 loads and the ring's are more than the memory counter's 63: the
+//     wait for the first step then takes part of the second step in as well.  With batches that fit, half as large, the chunks left for
+//     the end cost more: gate/up of an 8B model at 37 rows 32.3 -> 32.5 us, at 64 rows 34.0 -> 34.2);
 //   * no barrier, no LDS inside the loop: a wavefront never waits for another.  (X through
 //     direct-to-LDS loads would save a third of the registers, but the compiler then no longer counts
 //     the register loads beside them and waits for every load in flight once per trip.)
@@ -63,7 +65,7 @@ __global__ __launch_bounds__(TPB) void gemm_mid_kernel(const op8* __restrict__ x
   typedef MidShape<MT, CT> SH;
   constexpr int F = SH::F, FW = SH::FW, FR = SH::FR, ROUNDS = SH::ROUNDS;
   constexpr int KB = SH::KB, WD = SH::WD, XD = SH::XD, TRIP = SH::TRIP;
-  static_assert(KB * ((XD - 1) * MT + (WD - 1) * CT) < 64, "the loads in flight must fit the memory counter");
+  static_assert(KB * ((XD - 1) * MT + (WD - 1) * CT) < 64, "the loop's loads in flight must fit the memory counter");
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int s_last;
   float* s_rinv = (float*)(lds + SH::BODY);  // [MT * 16]
