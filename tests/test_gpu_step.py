@@ -499,6 +499,25 @@ def _one_pass_matches(cfg, M, device, seed, stats=False):
         assert (out.argmax.cpu().numpy() == st["argmax"]).all()
 
 
+@pytest.mark.parametrize("M", [5, 40])
+def test_f32_rows_of_more_chunks_than_are_fetched_ahead(device, M):
+    """The fp32 GEMM keeps 64 chunks of a row's squares; d_model 2304 leaves 72 (one per 32 columns) for gate/up, QKV and the head."""
+    cfg = inputs.model_config(2, 2304, 2, 2, 64, 256, 256, "f32")
+    W = _weights(cfg, 23 + M, device)
+    tokens = torch.randint(0, cfg["vocab"] - 1, (M,), generator=torch.Generator().manual_seed(M), dtype=torch.int32)
+    model = api.Model(cfg, W)
+    state = api.State(model, 1, M, M, 8)
+    out = api.StepOutputs(M, cfg["vocab"], model.torch_dtype, device)
+    api.dlm_step(state, tokens.to(device), out, [0, M], [0], [0], [0])
+    torch.cuda.synchronize()
+    ref = o_fwd.forward_span(cfg, inputs.weights_to_numpy(W), o_fwd.KVCache(cfg), tokens.numpy(), 0, 0)
+    # 2304 roundings of 2^-24 of partial sums as large as the result, through the seven products of two layers and the head's
+    bound = 8 * 2304 * 2.0 ** -24
+    assert (np.abs(out.logits.cpu().numpy() - ref) <= bound * np.maximum(np.abs(ref).max(-1, keepdims=True), SIGMA_LOGIT)).all()
+    state.close()
+    model.close()
+
+
 # (epilogue, tile, rows, model dimensions): the layer's epilogues on the wavefront shapes with an odd number of column tiles, whose last
 # one has no partner to pair with, and on the narrowest one; rows and columns ragged
 EPILOGUE_TILES = [
