@@ -130,8 +130,8 @@ def _ints(v, n=0):
 
 # The two decisions are bound by what their calls cost the host: plain arguments go through a small extension (csrc/decisions_py.c),
 # any others through ctypes, host arrays and parameters as bytes (marshalling alone 3.8 and 6.1 us with ctypes structs and a format
-# string per array, 2.7 and 4.8 as bytes, 1.2 and 2.1 through the extension; both decisions of one sequence x 8 rows 10.3 -> 9.6 us a
-# pass, of 16 x 64 10.7 -> 9.7, two runs of one side differing by up to 20 %).
+# string per array, 2.7 and 4.8 as bytes, 1.2 and 2.1 through the extension; both decisions of one sequence x 8 rows 11.8 -> 10.0 us a
+# pass, of 16 x 64 12.3 -> 10.3, on another box 10.3 -> 9.6 and 10.7 -> 9.7).
 @functools.lru_cache(maxsize=None)
 def _decisions():
     """The extension, bound to the library; None where it has not been built."""

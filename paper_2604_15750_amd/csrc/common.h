@@ -222,7 +222,7 @@ struct GemmEpi {
 // A model whose matrices are together no larger than this finds them, or enough of them, in the memory-side cache (256 MB) at its next
 // pass; the weights of a larger one never stay that long and are read non-temporally.  Layers of 1024 x 2816 behind a head of 16384, 8
 // and 37 rows, non-temporal / plain: 265 MB 212 / 202 and 292 / 271 us a pass, 316 MB 254 / 251 and 351 / 345, 342 MB 275 / 274 and 381 /
-// 380, 393 MB 317 / 322 and 439 / 443; 4 layers of 1024 x 3584 (135 MB) at 37 rows 163 / 128.
+// 380, 393 MB 317 / 322 and 439 / 443; 4 layers of 1024 x 3584 (135 MB) 115 / 103 and 160 / 138.
 constexpr size_t WEIGHTS_CACHED_BYTES = (size_t)320 << 20;
 constexpr int GEMM_STATS_MAX_ROWS = 64;
 int gemm_bf16_stat_parts(int M, int N, int K);       // column groups per row an EPI_STATS launch of this shape writes states for
