@@ -123,6 +123,11 @@ struct StatsMeta {  // which rows are compared with / retained as p^prev; offset
   int32_t kl_first[DLM_MAX_SEQS], kl_count[DLM_MAX_SEQS], save_first[DLM_MAX_SEQS], save_count[DLM_MAX_SEQS];
   int64_t prev_off[DLM_MAX_SEQS], save_off[DLM_MAX_SEQS];
 };
+inline int compared_rows(const StatsMeta& sm) {  // (entries beyond the pass's sequences are zero)
+  int n = 0;
+  for (int c : sm.kl_count) n += c;
+  return n;
+}
 struct AttnMeta {
   int32_t n_seqs;
   int32_t row_off[DLM_MAX_SEQS + 1];
@@ -332,7 +337,7 @@ constexpr size_t STATS_STATE_BYTES = 32;  // one online-softmax state (stats_par
 // (stats_part.h), merged in a fixed order.
 void launch_stats_merge(const void* parts, int rows, int nparts, int vocab, const StatsRows& sr, const StatsOut& o, hipStream_t st);
 template <typename T>
-void launch_vocab_stats(const T* logits, int rows, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st);
+void launch_vocab_stats(const T* logits, int rows, int compared, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st);
 
 void launch_block_boundary(const float* I, const float* H, const BoundaryMeta& meta, int n_seqs, dlm_boundary_params p, int32_t* L_out,
                            float* S_out, float* margin_out, hipStream_t st);

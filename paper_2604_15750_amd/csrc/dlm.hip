@@ -443,7 +443,7 @@ int run_step_f32(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, cons
     ProfScope ps(pf, st, PC_STATS);
     StatsRows sr{t.prev_row, t.save_row, s->prev_logits.p, s->prev_logits.p, (const float*)s->prev_lse.p, (float*)s->prev_lse.p};
     StatsOut so{d->max_logit, d->lse, d->entropy, d->kl, d->conf, d->argmax};
-    launch_vocab_stats<T>((const T*)d->logits, rows, c.vocab, c.mask_id, sr, so, s->stats_ws.p, st);
+    launch_vocab_stats<T>((const T*)d->logits, rows, compared_rows(sm), c.vocab, c.mask_id, sr, so, s->stats_ws.p, st);
   }
   return DLM_OK;
 }
@@ -544,7 +544,7 @@ int run_step_bf16(dlm_state* s, const dlm_step_desc* d, const SeqMeta& meta, con
   {
     ProfScope ps(pf, st, PC_STATS);
     if (fused) launch_stats_merge(s->stats_ws.p, rows, gemm_bf16_stat_parts(rows, c.vocab, dm), c.vocab, sr, so, st);
-    else launch_vocab_stats<T>((const T*)d->logits, rows, c.vocab, c.mask_id, sr, so, s->stats_ws.p, st);
+    else launch_vocab_stats<T>((const T*)d->logits, rows, compared_rows(sm), c.vocab, c.mask_id, sr, so, s->stats_ws.p, st);
   }
   return DLM_OK;
 }
@@ -692,8 +692,8 @@ extern "C" int dlm_vocab_stats(const void* logits, const void* prev, const float
   StatsRows sr{nullptr, nullptr, prev, nullptr, prev ? prev_lse : nullptr, nullptr};  // prev without a row table: row r pairs with row r
   StatsOut so{max_logit, lse, entropy, kl, conf, argmax};
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == DLM_BF16) launch_vocab_stats<bf16_t>((const bf16_t*)logits, rows, vocab, mask_id, sr, so, workspace, st);
-  else launch_vocab_stats<float>((const float*)logits, rows, vocab, mask_id, sr, so, workspace, st);
+  if (dtype == DLM_BF16) launch_vocab_stats<bf16_t>((const bf16_t*)logits, rows, prev ? rows : 0, vocab, mask_id, sr, so, workspace, st);
+  else launch_vocab_stats<float>((const float*)logits, rows, prev ? rows : 0, vocab, mask_id, sr, so, workspace, st);
   return DLM_OK;
 }
 
@@ -712,8 +712,8 @@ extern "C" int dlm_vocab_stats_static(const void* logits, const void* prev, cons
   StatsRows sr{nullptr, nullptr, prev, nullptr, prev ? prev_lse : nullptr, nullptr};
   StatsOut so{max_logit, lse, entropy, kl, conf, argmax};
   hipStream_t st = (hipStream_t)stream;
-  if (dtype == DLM_BF16) launch_vocab_stats<bf16_t>((const bf16_t*)logits, rows, vocab, mask_id, sr, so, ws, st);
-  else launch_vocab_stats<float>((const float*)logits, rows, vocab, mask_id, sr, so, ws, st);
+  if (dtype == DLM_BF16) launch_vocab_stats<bf16_t>((const bf16_t*)logits, rows, prev ? rows : 0, vocab, mask_id, sr, so, ws, st);
+  else launch_vocab_stats<float>((const float*)logits, rows, prev ? rows : 0, vocab, mask_id, sr, so, ws, st);
   return DLM_OK;
 }
 

@@ -121,8 +121,9 @@ __device__ inline void finalize(const Part& p, int row, bool has_prev, float pre
 // One wavefront's share of elements [lo, hi) of a row (the workgroup walks them together: lane l of the workgroup takes the
 // l-th vector of every stride).  Whole trips of U vectors (16 bytes each) per lane are loaded together and absorbed one after
 // the other without a bounds or mask test; the trip that holds the mask token and the ragged last one take the path with
-// per-element validity.  Loop bounds are uniform in the workgroup: the absorb steps exchange values between lanes.
-template <typename T, int TPB, bool VECTOR, bool KL, bool PREV_SUMS>
+// per-element validity.  AHEAD: a trip's loads go out before the trip in front of it is absorbed (loads_ahead).  Loop bounds are uniform
+// in the workgroup: the absorb steps exchange values between lanes.
+template <typename T, int TPB, bool VECTOR, bool AHEAD, bool KL, bool PREV_SUMS>
 __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const T* __restrict__ p_row, T* __restrict__ s_row, int lo,
                                     int hi, int mask_id) {
   constexpr int N = Vec<T>::N;
@@ -153,7 +154,7 @@ __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const
     for (int t = 0; t * TRIP < hi - lo;) {
       const int end = mask_trip >= t && mask_trip < nfull ? mask_trip : nfull;  // whole trips without the mask token
       V zv[U], pv[U];
-      if constexpr (TPB > 256) {
+      if constexpr (AHEAD) {
         if (t < end) {
           V zw[U], pw[U];
           fetch(zv, pv, t);
@@ -217,7 +218,7 @@ __device__ inline void stream_chunk(Run& run, const T* __restrict__ z_row, const
 // Workgroups of 256 threads of the vector path on a compute unit, held (stats_plan) where the registers would let one more in
 template <typename T> constexpr int HELD = sizeof(T) == 2 ? 5 : 6;
 
-template <typename T, int TPB, bool VECTOR, int PER_UNIT>
+template <typename T, int TPB, bool VECTOR, int PER_UNIT, bool AHEAD>
 __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(1, TPB == 256 ? PER_UNIT : 8))) void vocab_stats_kernel(const T* __restrict__ logits, int vocab, int mask_id, int chunk,
                                                           int nchunks, StatsRows sr, StatsOut o, Part* __restrict__ parts) {
   __shared__ Part sh[TPB / 64];
@@ -232,9 +233,9 @@ __global__ __launch_bounds__(TPB) __attribute__((amdgpu_waves_per_eu(1, TPB == 2
   const int lo = c * chunk, hi = min(vocab, lo + chunk);
 
   Run run = run_init();
-  if (!kl) stream_chunk<T, TPB, VECTOR, false, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
-  else if (!prev_sums) stream_chunk<T, TPB, VECTOR, true, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
-  else stream_chunk<T, TPB, VECTOR, true, true>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  if (!kl) stream_chunk<T, TPB, VECTOR, AHEAD, false, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  else if (!prev_sums) stream_chunk<T, TPB, VECTOR, AHEAD, true, false>(run, z_row, p_row, s_row, lo, hi, mask_id);
+  else stream_chunk<T, TPB, VECTOR, AHEAD, true, true>(run, z_row, p_row, s_row, lo, hi, mask_id);
   const Part p = run_finish(run);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = p;
   __syncthreads();
@@ -278,10 +279,10 @@ __global__ __launch_bounds__(64) void vocab_stats_merge_kernel(const Part* __res
 constexpr int MAX_CHUNKS = 32;
 constexpr int ROW_MIN = 136, ROW_MAX = 256;  // rows that can get a workgroup of 1024 threads each (stats_plan)
 
-template <typename T, int TPB, bool VECTOR, int PER_UNIT = 8>
+template <typename T, int TPB, bool VECTOR, int PER_UNIT = 8, bool AHEAD = false>
 void launch_items(const T* logits, int rows, int vocab, int mask_id, const StatsPlan& p, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
   // (the hardware dispatcher balances better than a resident grid walking the items)
-  vocab_stats_kernel<T, TPB, VECTOR, PER_UNIT><<<rows * p.chunks, TPB, 0, st>>>(logits, vocab, mask_id, p.chunk, p.chunks, sr, o, (Part*)workspace);
+  vocab_stats_kernel<T, TPB, VECTOR, PER_UNIT, AHEAD><<<rows * p.chunks, TPB, 0, st>>>(logits, vocab, mask_id, p.chunk, p.chunks, sr, o, (Part*)workspace);
   if (p.chunks > 1) vocab_stats_merge_kernel<<<rows, 64, 0, st>>>((const Part*)workspace, rows, p.chunks, vocab, sr, o);
 }
 
@@ -336,14 +337,32 @@ StatsPlan stats_plan(int rows, int vocab, int elem_size) {
   return p;
 }
 
+// Whether a whole row's workgroup has the next trip's loads in flight while it absorbs one: where the wait for a trip shows, that is where
+// the rows read, those of z and of z', are few; with more of them the reads are bound by bandwidth and more in flight only queue.
+// us a call, waiting for each trip -> a trip ahead:
+//   bf16, nothing compared, 126464 tokens: 136 rows 16.6 -> 15.7, 200: 17.0 -> 16.0, 256: 17.4 -> 17.2; 152064: 17.9 -> 16.5, 18.2 -> 16.9, 18.6 -> 17.9
+//   bf16, all compared, 126464: 136 rows 20.0 -> 19.5, 152: 19.8 -> 19.9, 176: 20.2 -> 21.2, 208: 21.6 -> 22.5, 256: 24.8 -> 25.6; their
+//     log-sum-exp recomputed, more arithmetic per byte: 136 rows 25.9 -> 24.8, 192: 26.0 -> 26.0, 224: 26.3 -> 26.8, 256: 27.1 -> 28.0
+//   bf16, some compared, in a pass of a small model: 152 rows, 64 of them, 93.9 -> 93.3, 176, 64: 97.6 -> 96.9, 192, 128: 100.3 -> 100.8, 224,
+//     64: 81.4 -> 82.2, 256, 64: 82.9 -> 85.0; of a 7B one 152, 64: 28.0 -> 24.3 the launch
+//   fp32, nothing compared, 126464: 136 rows 16.8 -> 15.9, 192: 19.1 -> 18.9, 224: 20.9 -> 21.2, 256: 23.3 -> 24.4; any compared (136 .. 256
+//     rows, 32 to all of them) loses 1 to 9 %: all of 152 26.0 -> 28.1, of 256 41.1 -> 41.3.
+// The same additions in the same order, and so the same values, either way.
 template <typename T>
-void launch_vocab_stats(const T* logits, int rows, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
+bool loads_ahead(int rows, int compared, bool lse_given) {
+  if (sizeof(T) == 4) return compared == 0 && rows <= 200;
+  return compared == 0 || (rows <= 192 && rows + compared <= (lse_given ? 304 : 384));
+}
+
+template <typename T>
+void launch_vocab_stats(const T* logits, int rows, int compared, int vocab, int mask_id, const StatsRows& sr, const StatsOut& o, void* workspace, hipStream_t st) {
   const StatsPlan p = stats_plan(rows, vocab, sizeof(T));
-  if (p.threads == 1024) launch_items<T, 1024, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  if (p.threads == 1024 && loads_ahead<T>(rows, compared, sr.prev_lse != nullptr)) launch_items<T, 1024, true, 8, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
+  else if (p.threads == 1024) launch_items<T, 1024, true>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
   else if (p.vector && p.per_unit > HELD<T>) launch_items<T, 256, true, HELD<T> + 1>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
   else if (p.vector) launch_items<T, 256, true, HELD<T>>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
   else launch_items<T, 256, false>(logits, rows, vocab, mask_id, p, sr, o, workspace, st);
 }
 
-template void launch_vocab_stats<float>(const float*, int, int, int, const StatsRows&, const StatsOut&, void*, hipStream_t);
-template void launch_vocab_stats<bf16_t>(const bf16_t*, int, int, int, const StatsRows&, const StatsOut&, void*, hipStream_t);
+template void launch_vocab_stats<float>(const float*, int, int, int, int, const StatsRows&, const StatsOut&, void*, hipStream_t);
+template void launch_vocab_stats<bf16_t>(const bf16_t*, int, int, int, int, const StatsRows&, const StatsOut&, void*, hipStream_t);

@@ -331,6 +331,29 @@ def test_order_of_the_streamed_sums(device, dt, rows, V):
     assert (_np(got["kl"]) == want).all(), np.abs(_np(got["kl"]) - want).max()
 
 
+# Whole rows with the next trip's loads in flight and without: bf16 from 153 rows on (193 where the previous rows' log-sum-exp is
+# recomputed) and fp32 with any previous row, or from 201 rows on, wait for each trip.  Whole trips and ragged ends, one and an even and an odd number of them
+@pytest.mark.parametrize("dt,few,rows", [("bf16", 152, 153), ("bf16", 136, 256), ("bf16", 192, 193), ("f32", 200, 201), ("f32", 136, 256)])
+@pytest.mark.parametrize("V", [16384, 24584, 50000, 65536])
+def test_whole_rows_a_trip_ahead_or_not(device, dt, few, rows, V):
+    """A row's values are the same bits by either kernel, compared or not, wherever the mask token lies; and a sample against 64 bits."""
+    tdt = torch.bfloat16 if dt == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(rows + V)
+    z = (torch.randn(rows, V, generator=g, device=device) * 4).to(tdt)
+    zp = (z.float() + 0.5 * torch.randn(rows, V, generator=g, device=device)).to(tdt)
+    at = [0, few // 2, few - 1]
+    for mask_id in (0, V // 2, V - 1):
+        lse_prev = api.dlm_vocab_stats(zp, mask_id)["lse"]
+        for prev, lse in ((None, None), (zp, lse_prev), (zp, None)):
+            head = lambda t: None if t is None else t[:few].contiguous()  # noqa: E731
+            part, got = api.dlm_vocab_stats(z[:few], mask_id, head(prev), prev_lse=head(lse)), api.dlm_vocab_stats(z, mask_id, prev, prev_lse=lse)
+            torch.cuda.synchronize()
+            for k, v in part.items():
+                assert torch.equal(got[k][:few], v), (mask_id, k)
+            z64, zp64 = o_fwd.widen(_np(z[at])), None if prev is None else o_fwd.widen(_np(zp[at]))
+            _check_stats({k: v[at] for k, v in got.items()}, o_stats.vocab_stats(z64, mask_id, zp64), z64, zp64, mask_id)
+
+
 @pytest.mark.parametrize("dt,rows,few", [("bf16", 360, 345), ("bf16", 500, 384), ("f32", 383, 308)])
 @pytest.mark.parametrize("own_lse", [True, False])
 def test_vocab_stats_of_many_rows_at_a_real_vocabulary(device, dt, rows, few, own_lse):
